@@ -7,25 +7,29 @@
 //   dQ_i = sum_j g_ij k_j      dK_j = sum_i g_ij q_i          dV_j = sum_i p_ij G_i   (+ the fill's share)
 // The weights are recomputed from Q and K (the forward keeps no statistics):
 //   bwd_stats_kernel   partial (max, sum, weighted sum of c) per kept query and key split
-//   bwd_dq_kernel      combines them into ln sum exp and D, then dQ (per key split)
-//   bwd_dkv_kernel     key-stationary: dK, dV, the fill's gradient, zero rows
+//   bwd_main_kernel    combines them, then dK, dV, the fill's gradient, zero rows, and dQ (per key split)
 //   bwd_dq_reduce_kernel  adds the key splits of dQ in split order
 // All five contractions run on the matrix cores (v_mfma_f64_16x16x4f64 on exactly widened inputs):
 //   lane (c, g) = (lane % 16, lane / 16)
 //   A[i][k]: i = c, k = g      B[k][j]: k = g, j = c      D[i][j]: i = 4r + g, j = c  (r = 0..3)
-// A wave takes 16 keys against a tile of 16 kept queries.  The query-stationary kernels compute the scores
-// transposed (keys on the rows), so that a lane's four values belong to ONE query (its statistics are
-// per-lane scalars) and are, unchanged, the B operand of the product that contracts over keys (dQ).  The
-// key-stationary kernel computes them upright (queries on the rows), so that the same holds for the
-// products that contract over queries (dK, dV).  Operands come straight from global memory: for the score
-// products a lane reads 16 contiguous elements of its row (step t of lane group g stands for element
-// 16 g + t in both operands: the contraction order is free), for the others 4 contiguous elements 4c ..
-// 4c + 3, component dt feeding accumulator dt, whose row m then stands for element 4 m + dt.
 // Both tensor types are computed in float64: where attention is sharply peaked (the queries
 // the selection prefers) p_ij is almost 1 for one key and c_ij - D_i is a difference of nearly
 // equal numbers, of which float32 arithmetic leaves only noise (measured on bfloat16 tensors:
 // errors of 4 times the gradient's own size).  Every sum has a fixed order, so results do not
 // depend on scheduling.
+//
+// What bounds it: the matrix pipe.  A float64 MFMA takes 65 cycles of its SIMD, and the SIMD issues no vector
+// instruction meanwhile (micro-benchmark: the times of both add up, whatever waves they come from), so a vector
+// instruction costs its own 3 to 5 cycles on top.  The kernels therefore
+//   * form the scores s and c twice, not three times: one kernel computes dQ with dK and dV, so a tile of 16
+//     queries x 16 keys costs 32 (statistics) + 80 MFMAs; recomputing them once more for dQ alone made it 144;
+//   * widen every operand once: a wave keeps the 16 key rows it owns as float64 in registers and finds the
+//     group's query rows as float64 in LDS, where the work-group has put them once;
+//   * run two work-groups of 4 waves (one per SIMD) on a CU, so that one fills the matrix pipe while the other
+//     stages rows, waits at a barrier or stores, and cut the key axis so that their number fills whole rounds of
+//     the CUs.
+// Measured (whole call): B=8 H=8 L=2048 bfloat16, 39 kept queries 212 -> 139 us (statistics 40, gradients 96 us, of
+// which 21 and 57 us are MFMAs); B=16 H=4 L=512 float32, 256 kept queries 225 -> 167 us.
 #include <type_traits>
 
 #include "psa_device.h"
@@ -33,67 +37,91 @@
 
 namespace psa {
 
-constexpr int kBwdThreads = 256;
-constexpr int kBwdKeys = 64;         // keys per block: 16 per wave
-constexpr int kBwdQ = 16;            // kept queries per tile
+constexpr int kBwdThreads = 256;     // 4 waves, one per SIMD; two work-groups share a CU
 constexpr int kBwdWaves = kBwdThreads / 64;
-constexpr int kBwdStaged = 64;        // kept queries staged in LDS at a time by the key-stationary kernel
-constexpr int kBwdStage = kD + 4;     // floats between their rows
-constexpr int kBwdChunk = 2048;      // rows per pass of the fill's column sums
+constexpr int kBwdKeys = 64;         // keys per block of the statistics kernel: 16 per wave
+constexpr int kBwdQ = 16;            // kept queries per tile
+// LDS row strides, chosen so that every access pattern below spreads evenly over the 64 banks
+constexpr int kBwdQRow = kD + 2;             // doubles between staged query rows
+constexpr int kBwdKRow = kD + 4;             // floats between staged key rows
+constexpr int kBwdStatGroup = 64;    // kept queries staged in LDS at a time by the statistics kernel (4 tiles) ...
+constexpr int kBwdStatTiles = kBwdStatGroup / kBwdQ;
+constexpr int kBwdStatsLds = 2 * kBwdStatGroup * kBwdQRow * 8;                   // 67584
+constexpr int kBwdGroup = 32;        // ... and by the gradient kernel (2 tiles)
+constexpr int kBwdTiles = kBwdGroup / kBwdQ;
+constexpr int kBwdChunk = 2048;      // rows per bit mask of the fill's column sums
+constexpr int kBwdMaxSplit = 64;     // key splits (their partial results are added up by one thread each)
+constexpr int kBwdKeepStats = 768;   // most kept queries whose statistics the gradient kernel keeps in LDS (two work-groups per CU)
 typedef double bwd_x4 __attribute__((ext_vector_type(4)));
+typedef double bwd_x2 __attribute__((ext_vector_type(2)));
 
-template <typename T> __device__ __forceinline__ float load_elem(const T* p);
-template <> __device__ __forceinline__ float load_elem<float>(const float* p) { return *p; }
-template <> __device__ __forceinline__ float load_elem<bf16_t>(const bf16_t* p) { return bf16_to_f32(p->x); }
-
-// 16 or 4 contiguous elements as float, and a 4-element store
-template <typename T> struct BwdMem;
-template <> struct BwdMem<float> {
-    static __device__ __forceinline__ void row16(const float* p, float (&v)[16]) {
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const float4 x = reinterpret_cast<const float4*>(p)[k];
-            v[4 * k] = x.x; v[4 * k + 1] = x.y; v[4 * k + 2] = x.z; v[4 * k + 3] = x.w;
-        }
-    }
-    static __device__ __forceinline__ void row4(const float* p, float (&v)[4]) {
-        const float4 x = *reinterpret_cast<const float4*>(p);
-        v[0] = x.x; v[1] = x.y; v[2] = x.z; v[3] = x.w;
-    }
-    static __device__ __forceinline__ void store4(float* p, const float (&v)[4]) {
-        *reinterpret_cast<float4*>(p) = make_float4(v[0], v[1], v[2], v[3]);
-    }
-};
-template <> struct BwdMem<bf16_t> {
-    static __device__ __forceinline__ void row16(const bf16_t* p, float (&v)[16]) {
-#pragma unroll
-        for (int k = 0; k < 2; ++k) {
-            const uint4 x = reinterpret_cast<const uint4*>(p)[k];
-            v[8 * k] = bf16_lo(x.x); v[8 * k + 1] = bf16_hi(x.x); v[8 * k + 2] = bf16_lo(x.y); v[8 * k + 3] = bf16_hi(x.y);
-            v[8 * k + 4] = bf16_lo(x.z); v[8 * k + 5] = bf16_hi(x.z); v[8 * k + 6] = bf16_lo(x.w); v[8 * k + 7] = bf16_hi(x.w);
-        }
-    }
-    static __device__ __forceinline__ void row4(const bf16_t* p, float (&v)[4]) {
-        const uint2 x = *reinterpret_cast<const uint2*>(p);
-        v[0] = bf16_lo(x.x); v[1] = bf16_hi(x.x); v[2] = bf16_lo(x.y); v[3] = bf16_hi(x.y);
-    }
-    static __device__ __forceinline__ void store4(bf16_t* p, const float (&v)[4]) {
-        *reinterpret_cast<uint2*>(p) = make_uint2(pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3]));
-    }
+// How the 4 waves of the gradient kernel's work-group share its keys and the two tiles of a group: KS waves of 16
+// keys each; with KS = 2 two waves have the same keys and one query tile each.
+template <int KS> struct BwdShare {
+    static constexpr int kSlots = kBwdWaves / KS;                        // 1, 2
+    static constexpr int kKeys = 16 * KS;                                // keys per block: 64, 32
+    static constexpr int kPerSlot = kBwdTiles / kSlots;                  // tiles a wave takes of a group: 2, 1
+    static constexpr int kGRow = kKeys + 2;                              // doubles between the rows (queries) of a g tile
+    static constexpr int kFixed = 2 * kBwdGroup * kBwdQRow * 8 + kBwdGroup * kGRow * 8 + kKeys * kBwdKRow * 4;   // 68096, 51200
+    static constexpr int kLds = kFixed + kBwdKeepStats * 16;             // the most: u_pad statistics of 16 bytes
 };
 
-// e^x in float64 (2^(x log2 e) by the degree-7 series of the forward: 5e-9 relative); e^(-inf) = 0
-__device__ __forceinline__ double bwd_exp(double x) { return exp2_f64(x * 1.4426950408889634074); }
+// N contiguous elements (N = 4, 8 or 16) as they lie in memory, widened where they are used (so that a request
+// stays a request until then), and a 4-element store
+template <typename T, int N> struct BwdRow;
+template <int N> struct BwdRow<float, N> {
+    float4 x[N / 4];
+    __device__ __forceinline__ void load(const float* p) {
+#pragma unroll
+        for (int k = 0; k < N / 4; ++k) x[k] = reinterpret_cast<const float4*>(p)[k];
+    }
+    __device__ __forceinline__ float at(int e) const {
+        const float4 v = x[e >> 2];
+        return (e & 3) == 0 ? v.x : (e & 3) == 1 ? v.y : (e & 3) == 2 ? v.z : v.w;
+    }
+};
+template <int N> struct BwdRow<bf16_t, N> {
+    uint32_t x[N / 2];
+    __device__ __forceinline__ void load(const bf16_t* p) {
+        if constexpr (N == 4) {
+            const uint2 v = *reinterpret_cast<const uint2*>(p);
+            x[0] = v.x; x[1] = v.y;
+        } else {
+#pragma unroll
+            for (int k = 0; k < N / 8; ++k) {
+                const uint4 v = reinterpret_cast<const uint4*>(p)[k];
+                x[4 * k] = v.x; x[4 * k + 1] = v.y; x[4 * k + 2] = v.z; x[4 * k + 3] = v.w;
+            }
+        }
+    }
+    __device__ __forceinline__ float at(int e) const { return (e & 1) ? bf16_hi(x[e >> 1]) : bf16_lo(x[e >> 1]); }
+};
+__device__ __forceinline__ void bwd_store4(float* p, const float (&v)[4]) {
+    *reinterpret_cast<float4*>(p) = make_float4(v[0], v[1], v[2], v[3]);
+}
+__device__ __forceinline__ void bwd_store4(bf16_t* p, const float (&v)[4]) {
+    *reinterpret_cast<uint2*>(p) = make_uint2(cvt_pk_bf16(v[0], v[1]), cvt_pk_bf16(v[2], v[3]));
+}
+
+// 16 bytes of a row: the values, or zeros
+__device__ __forceinline__ void bwd_store16(float* p, const float (&v)[4], bool keep) {
+    *reinterpret_cast<float4*>(p) = keep ? make_float4(v[0], v[1], v[2], v[3]) : make_float4(0.f, 0.f, 0.f, 0.f);
+}
+__device__ __forceinline__ void bwd_store16(bf16_t* p, const float (&v)[8], bool keep) {
+    const uint4 x = make_uint4(cvt_pk_bf16(v[0], v[1]), cvt_pk_bf16(v[2], v[3]), cvt_pk_bf16(v[4], v[5]), cvt_pk_bf16(v[6], v[7]));
+    *reinterpret_cast<uint4*>(p) = keep ? x : make_uint4(0u, 0u, 0u, 0u);
+}
+
+constexpr double kBwdScaleLog2e = 0.125 * 1.4426950408889634074;     // scores to base-2 exponents
 
 struct BwdParams {
     const void* Q; const void* K; const void* V; const void* G;
     const int* lengths; const int* sel; const int* u;
     void* dQ; void* dK; void* dV;
-    void* stats_part;      // [BH][QT][S][16][3]  (max, sum, weighted c) per kept query and key split
-    void* stats;           // [BH][QT * 16][2]    ln sum exp, D
-    void* gsum_part;       // [BH][S][64]         column sums of G over the valid rows outside I_sparse, per key split
-    void* dq_part;         // [BH][QT][S][16][64] (S > 1)
-    int H, L, u_stride, QT, S, blocks_per_split, fill;
+    double* stats_part;    // [BH][S1][u_pad][3]  (max, sum, weighted c) per kept query and key split, base 2
+    double* gsum_part;     // [BH][S1][64]        column sums of G over the valid rows outside I_sparse, per key split
+    double* dq_part;       // [BH][S2][u_pad][64], or nullptr: dQ rows are written directly
+    int H, L, u_stride, u_pad, n_group, S1, blocks1, S2, blocks2, fill;
 };
 
 __device__ __forceinline__ int kept_count(const BwdParams& P, int b, int n)
@@ -110,30 +138,106 @@ __device__ __forceinline__ int kept_row(const BwdParams& P, int head, int t, int
     return (i < 0 || i >= n) ? -1 : i;
 }
 
-// the two score products of 16 rows `a` against 16 rows `b` (16 contiguous elements per lane each):
-// s = sum_e a1[e] b1[e], c = sum_e a2[e] b2[e], two independent MFMA chains
-__device__ __forceinline__ void score_products(const float (&a1)[16], const double (&b1)[16], const float (&a2)[16],
-                                               const double (&b2)[16], bwd_x4& s, bwd_x4& c)
+// Kept queries q0 .. q0 + ROWS - 1 of the head: their rows of Q and of G as float64 in LDS (zeros for an absent
+// entry), 8 threads per row.  `find` looks the rows up in the list, `request` asks for them, `put` writes them to
+// LDS (the caller's barrier makes them visible); a caller may have other work between the three.
+template <typename T, int ROWS>
+struct QueryStage {
+    static constexpr int kPasses = ROWS * 8 / kBwdThreads;
+    int qi[kPasses];                          // list entries as they lie in memory, rows (or -1) from `request` on
+    BwdRow<T, 8> a[kPasses], b[kPasses];
+    static __device__ __forceinline__ int row_of(int k) { return k * (kBwdThreads / 8) + ((int)threadIdx.x >> 3); }
+    __device__ __forceinline__ void find(const BwdParams& P, int head, int q0) {
+#pragma unroll
+        for (int k = 0; k < kPasses; ++k) {
+            const int t = q0 + row_of(k);
+            qi[k] = P.sel[(size_t)head * P.u_stride + (t < P.u_stride ? t : P.u_stride - 1)];
+        }
+    }
+    __device__ __forceinline__ void request(const T* Qh, const T* Gh, int q0, int n, int ub) {
+        const int part = threadIdx.x & 7;
+#pragma unroll
+        for (int k = 0; k < kPasses; ++k) {
+            if (q0 + row_of(k) >= ub || qi[k] < 0 || qi[k] >= n) qi[k] = -1;
+            a[k].load(Qh + (size_t)(qi[k] >= 0 ? qi[k] : 0) * kD + 8 * part);
+            b[k].load(Gh + (size_t)(qi[k] >= 0 ? qi[k] : 0) * kD + 8 * part);
+        }
+    }
+    __device__ __forceinline__ void put(double* sQ, double* sG) const {
+        const int part = threadIdx.x & 7;
+#pragma unroll
+        for (int k = 0; k < kPasses; ++k) {
+            bwd_x2* dq = reinterpret_cast<bwd_x2*>(sQ + row_of(k) * kBwdQRow + 8 * part);
+            bwd_x2* dg = reinterpret_cast<bwd_x2*>(sG + row_of(k) * kBwdQRow + 8 * part);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                dq[e] = qi[k] >= 0 ? bwd_x2{(double)a[k].at(2 * e), (double)a[k].at(2 * e + 1)} : bwd_x2{0.0, 0.0};
+                dg[e] = qi[k] >= 0 ? bwd_x2{(double)b[k].at(2 * e), (double)b[k].at(2 * e + 1)} : bwd_x2{0.0, 0.0};
+            }
+        }
+    }
+};
+
+// Widens a wave's key rows into registers, once: the compiler would rather repeat the conversion at every use.
+template <typename T>
+__device__ __forceinline__ void widen16(const BwdRow<T, 16>& x, double (&d)[16])
+{
+#pragma unroll
+    for (int t = 0; t < 16; ++t) { d[t] = (double)x.at(t); asm volatile("" : "+v"(d[t])); }
+}
+
+// The two score products of a tile's 16 staged queries against the wave's 16 keys, two independent MFMA chains.
+// Lane group g takes elements 16 g .. 16 g + 15 of its row on both sides (the contraction order is free).
+// QUERY_ROWS: queries on the rows of the result (lane: queries 4r + g against key c), else keys on the rows.
+// The staged operands of 4 elements are read while the products of the 4 before them run.
+template <bool QUERY_ROWS>
+__device__ __forceinline__ void score_products(const double* sQ, const double* sG, int tile, int c, int g,
+                                               const double (&kd)[16], const double (&vd)[16], bwd_x4& s, bwd_x4& cc)
 {
     s = bwd_x4{0.0, 0.0, 0.0, 0.0};
-    c = bwd_x4{0.0, 0.0, 0.0, 0.0};
+    cc = bwd_x4{0.0, 0.0, 0.0, 0.0};
+    const bwd_x2* qr = reinterpret_cast<const bwd_x2*>(sQ + (16 * tile + c) * kBwdQRow + 16 * g);
+    const bwd_x2* gr = reinterpret_cast<const bwd_x2*>(sG + (16 * tile + c) * kBwdQRow + 16 * g);
+    bwd_x2 q2[2][2], g2[2][2];
+    q2[0][0] = qr[0]; q2[0][1] = qr[1]; g2[0][0] = gr[0]; g2[0][1] = gr[1];
 #pragma unroll
-    for (int t = 0; t < 16; ++t) {
-        s = __builtin_amdgcn_mfma_f64_16x16x4f64((double)a1[t], b1[t], s, 0, 0, 0);
-        c = __builtin_amdgcn_mfma_f64_16x16x4f64((double)a2[t], b2[t], c, 0, 0, 0);
+    for (int st = 0; st < 4; ++st) {
+        const int cur = st & 1;
+        if (st < 3) {
+            q2[cur ^ 1][0] = qr[2 * st + 2]; q2[cur ^ 1][1] = qr[2 * st + 3];
+            g2[cur ^ 1][0] = gr[2 * st + 2]; g2[cur ^ 1][1] = gr[2 * st + 3];
+            __builtin_amdgcn_sched_barrier(0);
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const double qv = q2[cur][e >> 1][e & 1], gv = g2[cur][e >> 1][e & 1];
+            if (QUERY_ROWS) {
+                s = __builtin_amdgcn_mfma_f64_16x16x4f64(qv, kd[4 * st + e], s, 0, 0, 0);
+                cc = __builtin_amdgcn_mfma_f64_16x16x4f64(gv, vd[4 * st + e], cc, 0, 0, 0);
+            } else {
+                s = __builtin_amdgcn_mfma_f64_16x16x4f64(kd[4 * st + e], qv, s, 0, 0, 0);
+                cc = __builtin_amdgcn_mfma_f64_16x16x4f64(vd[4 * st + e], gv, cc, 0, 0, 0);
+            }
+        }
     }
 }
 
-// ---- partial softmax statistics per kept query and key split; column sums of G over the rows the fill serves
+__device__ __forceinline__ int opaque(int x) { asm volatile("" : "+v"(x)); return x; }
+
+// a maximum over no key: far below any score, and finite, so that differences of such values stay numbers
+constexpr double kBwdNoMax = -1e300;
+
+// ---- partial softmax statistics per kept query and key split; column sums of G over the rows the mean fill serves.
+// grid (key splits, groups of 64 kept queries, heads)
 template <typename T>
-__global__ __launch_bounds__(kBwdThreads)
+__global__ __launch_bounds__(kBwdThreads, 2)
 void bwd_stats_kernel(const BwdParams P)
 {
-    using M = BwdMem<T>;
-    __shared__ double s_part[kBwdWaves][kBwdQ][3];
-    __shared__ double s_gs[4 * kBwdWaves][kD];
+    extern __shared__ __attribute__((aligned(16))) double bwd_smem[];
     __shared__ unsigned s_bits[kBwdChunk / 32];
-    const int split = blockIdx.x, qt = blockIdx.y, head = blockIdx.z;
+    double* sQ = bwd_smem;
+    double* sG = bwd_smem + kBwdStatGroup * kBwdQRow;
+    const int split = blockIdx.x, group = blockIdx.y, head = blockIdx.z;
     const int b = head / P.H, L = P.L;
     const int n = valid_len(P.lengths, b, L);
     const int ub = kept_count(P, b, n);
@@ -142,38 +246,102 @@ void bwd_stats_kernel(const BwdParams P)
     const T* Kh = static_cast<const T*>(P.K) + (size_t)head * L * kD;
     const T* Vh = static_cast<const T*>(P.V) + (size_t)head * L * kD;
     const T* Gh = static_cast<const T*>(P.G) + (size_t)head * L * kD;
-    const int k_first = split * P.blocks_per_split * kBwdKeys;
-    int k_end = k_first + P.blocks_per_split * kBwdKeys;
+    const int k_first = split * P.blocks1 * kBwdKeys;
+    int k_end = k_first + P.blocks1 * kBwdKeys;
     k_end = k_end < n ? k_end : n;
+    const bool sums = group == 0 && P.fill == PSA_FILL_MEAN;         // work-group-uniform: this one sums G
+    const int q0 = group * kBwdStatGroup;
+    int n_t = (ub - q0 + kBwdQ - 1) / kBwdQ;                         // tiles of kept queries: 0 .. 4
+    n_t = n_t < 0 ? 0 : (n_t < kBwdStatTiles ? n_t : kBwdStatTiles);
+    if (n_t == 0 && !sums) return;
 
-    // the fill's rows: valid rows of this key range that are not kept (query tile 0 only).  The range is walked
-    // in chunks of 2048 rows whose kept rows are marked in a bit mask; a wave then reads 4 rows per load
-    // instruction (16 bytes per lane), 8 of them in flight, and adds the rows that are not marked.
-    if (qt == 0) {
-        double* gs = static_cast<double*>(P.gsum_part) + ((size_t)head * P.S + split) * kD;
-        double tot[4] = {0.0, 0.0, 0.0, 0.0};                        // columns 4c .. 4c + 3 over rows 4 it + g
-        for (int c0 = k_first; c0 < k_end; c0 += kBwdChunk) {
-            const int c1 = c0 + kBwdChunk < k_end ? c0 + kBwdChunk : k_end;
+    // the wave's 16 key rows (lane: 16 elements of row c) and, for the column sums, the same 16 rows of G (lane:
+    // elements 4c .. 4c + 3 of rows 4 i + g); the next block's are requested before the current one is worked on
+    // (on a clamped row: harmless past the end)
+    BwdRow<T, 16> kn, vn;
+    BwdRow<T, 4> gn[4];
+    auto request = [&](int j0) {
+        if (n_t > 0) {
+            const int row = j0 + c < n ? j0 + c : n - 1;
+            kn.load(Kh + (size_t)row * kD + 16 * g);
+            vn.load(Vh + (size_t)row * kD + 16 * g);
+        }
+        if (sums) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int row = j0 + 4 * i + g < n ? j0 + 4 * i + g : n - 1;
+                gn[i].load(Gh + (size_t)row * kD + 4 * c);
+            }
+        }
+    };
+    if (k_first < k_end) request(k_first + 16 * wave);               // (n > 0)
+    if (n_t > 0) {
+        QueryStage<T, kBwdStatGroup> qs;
+        qs.find(P, head, q0);
+        qs.request(Qh, Gh, q0, n, ub);
+        qs.put(sQ, sG);
+    }
+    __syncthreads();
+
+    // this lane: query c of every tile, keys 4r + g of the wave's 16
+    double m[kBwdStatTiles], l[kBwdStatTiles], dacc[kBwdStatTiles], tot[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int tt = 0; tt < kBwdStatTiles; ++tt) { m[tt] = kBwdNoMax; l[tt] = 0.0; dacc[tt] = 0.0; }
+#pragma unroll 1
+    for (int blk0 = k_first; blk0 < k_end; blk0 += kBwdKeys) {       // work-group-uniform
+        const int j0 = blk0 + 16 * wave;
+        if (sums && (blk0 - k_first) % kBwdChunk == 0) {
+            // mark the kept rows of the next 2048: they take no part in the column sums
             __syncthreads();
             if (tid < kBwdChunk / 32) s_bits[tid] = 0u;
             __syncthreads();
             for (int t = tid; t < ub; t += kBwdThreads) {
-                const int i = P.sel[(size_t)head * P.u_stride + t];
-                if (i >= c0 && i < c1) atomicOr(&s_bits[(i - c0) >> 5], 1u << ((i - c0) & 31));
+                const int i = P.sel[(size_t)head * P.u_stride + t] - blk0;
+                if (i >= 0 && i < kBwdChunk) atomicOr(&s_bits[i >> 5], 1u << (i & 31));
             }
             __syncthreads();
-            const int n_it = (c1 - c0 + 3) >> 2;
-#pragma unroll 8
-            for (int it = wave; it < n_it; it += kBwdWaves) {        // (rows in a fixed order per lane)
-                const int rr = 4 * it + g, jr = c0 + rr;
-                float x[4];
-                M::row4(Gh + (size_t)(jr < c1 ? jr : c1 - 1) * kD + 4 * c, x);
-                const bool use = jr < c1 && !((s_bits[rr >> 5] >> (rr & 31)) & 1u);
+        }
+        if (j0 >= k_end) continue;                                   // wave-uniform
+        double kd[16], vd[16];
+        if (n_t > 0) { widen16(kn, kd); widen16(vn, vd); }
+        if (sums) {
 #pragma unroll
-                for (int e = 0; e < 4; ++e) tot[e] += use ? (double)x[e] : 0.0;
+            for (int i = 0; i < 4; ++i) {
+                const int rr = (j0 - k_first) % kBwdChunk + 4 * i + g;
+                const bool use = j0 + 4 * i + g < k_end && !((s_bits[rr >> 5] >> (rr & 31)) & 1u);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) tot[e] += (double)(use ? gn[i].at(e) : 0.f);
             }
         }
-        __syncthreads();
+        if (j0 + kBwdKeys < k_end) request(j0 + kBwdKeys);
+#pragma unroll
+        for (int tt = 0; tt < kBwdStatTiles; ++tt) {
+            if (tt < n_t) {                                          // work-group-uniform
+                bwd_x4 s, cc;
+                score_products<false>(sQ, sG, tt, c, g, kd, vd, s, cc);
+                double sc[4];
+#pragma unroll
+                for (int r = 0; r < 4; ++r) sc[r] = s[r] * kBwdScaleLog2e;
+                if (j0 + 16 > k_end) {                               // wave-uniform: the last keys
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) sc[r] = j0 + 4 * r + g < k_end ? sc[r] : -INFINITY;
+                }
+                const double mn = fmax(fmax(fmax(sc[0], sc[1]), fmax(sc[2], sc[3])), m[tt]);
+                const double a = exp2_f64(m[tt] - mn);               // (0 for the first key)
+                double w[4];
+#pragma unroll
+                for (int r = 0; r < 4; ++r) w[r] = exp2_f64(sc[r] - mn);
+                l[tt] = fma(l[tt], a, (w[0] + w[1]) + (w[2] + w[3]));
+                dacc[tt] *= a;
+#pragma unroll
+                for (int r = 0; r < 4; ++r) dacc[tt] = fma(w[r], cc[r], dacc[tt]);
+                m[tt] = mn;
+            }
+        }
+    }
+    __syncthreads();                                                 // the query rows have been read
+    if (sums) {
+        double (*s_gs)[kD] = reinterpret_cast<double (*)[kD]>(bwd_smem + kBwdWaves * kBwdStatGroup * 3);     // [4 * waves][64], behind s_part
 #pragma unroll
         for (int e = 0; e < 4; ++e) s_gs[wave * 4 + g][4 * c + e] = tot[e];
         __syncthreads();
@@ -181,409 +349,499 @@ void bwd_stats_kernel(const BwdParams P)
             double t = 0.0;
 #pragma unroll
             for (int k = 0; k < 4 * kBwdWaves; ++k) t += s_gs[k][tid];   // fixed order
-            gs[tid] = t;
+            P.gsum_part[((size_t)head * P.S1 + split) * kD + tid] = t;
         }
     }
-    if (qt * kBwdQ >= ub) return;                                    // no kept query in this tile (work-group-uniform)
-
-    // B operands: the kept query of column c and its upstream gradient (zeros for an absent entry)
-    const int qi = kept_row(P, head, qt * kBwdQ + c, n, ub);
-    double qd[16], gd[16];
-    {
-        float qf[16], gf[16];
-        M::row16(Qh + (size_t)(qi >= 0 ? qi : 0) * kD + 16 * g, qf);
-        M::row16(Gh + (size_t)(qi >= 0 ? qi : 0) * kD + 16 * g, gf);
+    if (n_t == 0) return;
+    // fold the four lane groups (the same query, different keys), then the waves, in fixed order
+    double (*s_part)[kBwdStatGroup][3] = reinterpret_cast<double (*)[kBwdStatGroup][3]>(bwd_smem);    // [wave][query][m, l, d]
 #pragma unroll
-        for (int t = 0; t < 16; ++t) { qd[t] = qi >= 0 ? (double)qf[t] : 0.0; gd[t] = qi >= 0 ? (double)gf[t] : 0.0; }
-    }
-    // this lane: query c, keys 4r + g of the wave's sub-blocks (wave w takes sub-blocks w, w + 4, ... of 16 keys)
-    double m = -INFINITY, l = 0.0, dacc = 0.0;
-    // the next sub-block's rows are requested before the current one is worked on (on a clamped row, so the
-    // request past the end is harmless; n > 0: the head has kept queries)
-    float kn[16], vn[16];
-    {
-        const int row = k_first + 16 * wave + c < n ? k_first + 16 * wave + c : n - 1;
-        M::row16(Kh + (size_t)row * kD + 16 * g, kn);
-        M::row16(Vh + (size_t)row * kD + 16 * g, vn);
-    }
-    for (int j0 = k_first + 16 * wave; j0 < k_end; j0 += kBwdKeys) {
-        float kf[16], vf[16];
-#pragma unroll
-        for (int t = 0; t < 16; ++t) { kf[t] = kn[t]; vf[t] = vn[t]; }
-        {
-            const int row = j0 + kBwdKeys + c < n ? j0 + kBwdKeys + c : n - 1;
-            M::row16(Kh + (size_t)row * kD + 16 * g, kn);
-            M::row16(Vh + (size_t)row * kD + 16 * g, vn);
-        }
-        bwd_x4 s, cc;
-        score_products(kf, qd, vf, gd, s, cc);
-        double sc[4], mn = m;
-        bool ok[4];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            ok[r] = j0 + 4 * r + g < k_end;
-            sc[r] = s[r] * 0.125;
-            if (ok[r] && sc[r] > mn) mn = sc[r];
-        }
-        if (mn > -INFINITY) {
-            const double a = m == -INFINITY ? 0.0 : bwd_exp(m - mn);
-            l *= a; dacc *= a;
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const double w = ok[r] ? bwd_exp(sc[r] - mn) : 0.0;
-                l += w; dacc += w * cc[r];
-            }
-            m = mn;
-        }
-    }
-    // fold the four lane groups (the same query, different keys), then the four waves, in fixed order
-    {
-        double mw = m;
-        { const double o = __shfl_xor(mw, 16, 64); mw = o > mw ? o : mw; }
-        { const double o = __shfl_xor(mw, 32, 64); mw = o > mw ? o : mw; }
-        const double a = m == -INFINITY ? 0.0 : bwd_exp(m - mw);
-        l *= a; dacc *= a;
-        l += __shfl_xor(l, 16, 64); dacc += __shfl_xor(dacc, 16, 64);
-        l += __shfl_xor(l, 32, 64); dacc += __shfl_xor(dacc, 32, 64);
-        if (g == 0) { s_part[wave][c][0] = mw; s_part[wave][c][1] = l; s_part[wave][c][2] = dacc; }
+    for (int tt = 0; tt < kBwdStatTiles; ++tt) {
+        double mw = fmax(m[tt], __shfl_xor(m[tt], 16, 64));
+        mw = fmax(mw, __shfl_xor(mw, 32, 64));
+        const double a = exp2_f64(m[tt] - mw);
+        double lw = l[tt] * a, dw = dacc[tt] * a;
+        lw += __shfl_xor(lw, 16, 64); dw += __shfl_xor(dw, 16, 64);
+        lw += __shfl_xor(lw, 32, 64); dw += __shfl_xor(dw, 32, 64);
+        if (g == 0) { s_part[wave][16 * tt + c][0] = mw; s_part[wave][16 * tt + c][1] = lw; s_part[wave][16 * tt + c][2] = dw; }
     }
     __syncthreads();
-    if (tid < kBwdQ) {
-        double mx = -INFINITY;
+    if (tid < n_t * kBwdQ) {                                         // (at most 64)
+        double mx = kBwdNoMax;
 #pragma unroll
-        for (int w = 0; w < kBwdWaves; ++w) mx = s_part[w][tid][0] > mx ? s_part[w][tid][0] : mx;
+        for (int w = 0; w < kBwdWaves; ++w) mx = fmax(mx, s_part[w][tid][0]);
         double lt = 0.0, dt = 0.0;
 #pragma unroll
         for (int w = 0; w < kBwdWaves; ++w) {
-            const double a = s_part[w][tid][0] == -INFINITY ? 0.0 : bwd_exp(s_part[w][tid][0] - mx);
-            lt += a * s_part[w][tid][1]; dt += a * s_part[w][tid][2];
+            const double a = exp2_f64(s_part[w][tid][0] - mx);
+            lt = fma(a, s_part[w][tid][1], lt); dt = fma(a, s_part[w][tid][2], dt);
         }
-        double* sp = static_cast<double*>(P.stats_part) + ((((size_t)head * P.QT + qt) * P.S + split) * kBwdQ + tid) * 3;
+        double* sp = P.stats_part + (((size_t)head * P.S1 + split) * P.u_pad + q0 + tid) * 3;
         sp[0] = mx; sp[1] = lt; sp[2] = dt;
     }
 }
 
-// combine the key splits' statistics of the tile's 16 kept queries: ln sum exp and D (threads 0 .. 15)
-__device__ __forceinline__ void combine_stats(double* lse, double* D, const BwdParams& P, int head, int qt)
+// the key splits' statistics of kept query t together: log2 of the sum of exponentials, and D
+__device__ __forceinline__ void combine_stats(const BwdParams& P, int head, int t, double& lse, double& D)
 {
-    if (threadIdx.x < kBwdQ) {
-        const double* sp = static_cast<const double*>(P.stats_part) + (((size_t)head * P.QT + qt) * P.S * kBwdQ + threadIdx.x) * 3;
-        double mx = -INFINITY;
-        for (int s = 0; s < P.S; ++s) { const double v = sp[(size_t)s * kBwdQ * 3]; mx = v > mx ? v : mx; }
-        double lt = 0, dt = 0;
-        for (int s = 0; s < P.S; ++s) {
-            const double ms = sp[(size_t)s * kBwdQ * 3];
-            const double a = ms == -INFINITY ? 0.0 : exp(ms - mx);
-            lt += a * sp[(size_t)s * kBwdQ * 3 + 1];
-            dt += a * sp[(size_t)s * kBwdQ * 3 + 2];
+    const double* sp = P.stats_part + ((size_t)head * P.S1 * P.u_pad + t) * 3;
+    const size_t step = (size_t)P.u_pad * 3;
+    double mx = kBwdNoMax, lt = 0.0, dt = 0.0;
+    for (int s0 = 0; s0 < P.S1; s0 += 4) {                           // split order, 4 in flight
+        double ms[4], ls[4], ds[4], mn = mx;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const double* q = sp + (size_t)(s0 + k < P.S1 ? s0 + k : P.S1 - 1) * step;
+            ms[k] = q[0]; ls[k] = q[1]; ds[k] = q[2];
         }
-        lse[threadIdx.x] = lt > 0 ? mx + log(lt) : 0.0;
-        D[threadIdx.x] = lt > 0 ? dt / lt : 0.0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) mn = fmax(mn, ms[k]);
+        const double a0 = exp2_f64(mx - mn);
+        lt *= a0; dt *= a0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const double a = s0 + k < P.S1 ? exp2_f64(ms[k] - mn) : 0.0;
+            lt = fma(a, ls[k], lt); dt = fma(a, ds[k], dt);
+        }
+        mx = mn;
     }
+    lse = mx + log2(lt);                                             // (lt > 0: a kept query has at least one valid key)
+    D = dt / lt;
 }
 
-// ---- dQ of the tile's kept queries over this key split
-template <typename T>
-__global__ __launch_bounds__(kBwdThreads)
-void bwd_dq_kernel(const BwdParams P)
+// ---- dK and dV of blocks of 16 KS keys over all kept queries of the head, and dQ over those keys.
+// Wave w takes keys 16 (w % KS) .. + 15 of the block and, of the two query tiles of a group, both (KS = 4) or tile
+// w / 2 (KS = 2).  Scores are formed upright (queries on the rows), so that a lane's four p and g values are,
+// unchanged, the B operand of the products that contract over queries (dK, dV).  For dQ, which contracts over keys,
+// the waves put their g values into LDS; wave w then takes elements 16 w .. + 15 of both tiles over all keys of the
+// block, so that nothing has to be added up across waves.
+// grid (key splits, heads), blocks2 key blocks per work-group, which adds to the dQ it wrote for the block before.
+// MANY: more than kBwdKeepStats kept queries: the statistics of a group are put together anew for every block.
+template <typename T, int KS, bool MANY>
+__global__ __launch_bounds__(kBwdThreads, 2)
+void bwd_main_kernel(const BwdParams P)
 {
-    using M = BwdMem<T>;
-    __shared__ double s_lse[kBwdQ], s_D[kBwdQ];
-    __shared__ double s_acc[kBwdWaves][16][64];                      // the waves' accumulators, register by register
-    const int split = blockIdx.x, qt = blockIdx.y, head = blockIdx.z;
+    using SH = BwdShare<KS>;
+    constexpr int GR = SH::kGRow;
+    extern __shared__ __attribute__((aligned(16))) double bwd_smem[];
+    __shared__ double s_gm[kD];
+    __shared__ unsigned s_bits[kBwdChunk / 32];                      // the kept ones among 2048 rows
+    double* sQ = bwd_smem;
+    double* sG = sQ + kBwdGroup * kBwdQRow;
+    double* sg = sG + kBwdGroup * kBwdQRow;                          // [2 tiles][16 queries][GR]
+    float* sK = reinterpret_cast<float*>(sg + kBwdGroup * GR);       // [keys][kBwdKRow]
+    bwd_x2* s_stat = reinterpret_cast<bwd_x2*>(sK + SH::kKeys * kBwdKRow);       // [queries] (log2 sum exp, -D/8)
+    const int split = blockIdx.x, head = blockIdx.y;
     const int b = head / P.H, L = P.L;
     const int n = valid_len(P.lengths, b, L);
     const int ub = kept_count(P, b, n);
-    if (qt * kBwdQ >= ub) return;                                    // work-group-uniform
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, c = lane & 15, g = lane >> 4;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int ks = wave % KS, slot = wave / KS;
     const T* Qh = static_cast<const T*>(P.Q) + (size_t)head * L * kD;
     const T* Kh = static_cast<const T*>(P.K) + (size_t)head * L * kD;
     const T* Vh = static_cast<const T*>(P.V) + (size_t)head * L * kD;
     const T* Gh = static_cast<const T*>(P.G) + (size_t)head * L * kD;
-    const int k_first = split * P.blocks_per_split * kBwdKeys;
-    int k_end = k_first + P.blocks_per_split * kBwdKeys;
-    k_end = k_end < n ? k_end : n;
 
-    combine_stats(s_lse, s_D, P, head, qt);
-    __syncthreads();
-    if (split == 0 && tid < kBwdQ) {                                 // for the key-stationary kernel
-        double* st = static_cast<double*>(P.stats) + ((size_t)head * P.QT * kBwdQ + qt * kBwdQ + tid) * 2;
-        st[0] = s_lse[tid]; st[1] = s_D[tid];
-    }
-    const int qi = kept_row(P, head, qt * kBwdQ + c, n, ub);
-    double qd[16], gd[16];
-    {
-        float qf[16], gf[16];
-        M::row16(Qh + (size_t)(qi >= 0 ? qi : 0) * kD + 16 * g, qf);
-        M::row16(Gh + (size_t)(qi >= 0 ? qi : 0) * kD + 16 * g, gf);
-#pragma unroll
-        for (int t = 0; t < 16; ++t) { qd[t] = qi >= 0 ? (double)qf[t] : 0.0; gd[t] = qi >= 0 ? (double)gf[t] : 0.0; }
-    }
-    const double lse_c = s_lse[c], D_c = s_D[c];
-    // dQ^T of this wave's keys: acc[dt][r] is element 4 (4r + g) + dt of query c
-    bwd_x4 acc[4];
-#pragma unroll
-    for (int dt = 0; dt < 4; ++dt) acc[dt] = bwd_x4{0.0, 0.0, 0.0, 0.0};
-    // operands of a sub-block: the lane's key row for the score products (16 contiguous elements), and for the
-    // second product's A the keys 4r + g, elements 4c .. 4c + 3; the next sub-block's are requested before
-    // the current one is worked on (clamped rows: the request past the end is harmless)
-    float kn[16], vn[16], k4n[4][4];
-    auto request = [&](int j0) {
-        const int row = j0 + c < n ? j0 + c : n - 1;
-        M::row16(Kh + (size_t)row * kD + 16 * g, kn);
-        M::row16(Vh + (size_t)row * kD + 16 * g, vn);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int key = j0 + 4 * r + g;
-            M::row4(Kh + (size_t)(key < n ? key : n - 1) * kD + 4 * c, k4n[r]);
-        }
+    // the key rows of a block: requested ahead (clamped: harmless if none is valid)
+    const int r_first = split * P.blocks2 * SH::kKeys;
+    BwdRow<T, 16> kn, vn;
+    auto request = [&](int r0) {
+        const int lo = opaque(lane), j = r0 + 16 * ks + (lo & 15), row = j < n ? j : (n > 0 ? n - 1 : 0);
+        kn.load(Kh + (size_t)row * kD + 16 * (lo >> 4));
+        vn.load(Vh + (size_t)row * kD + 16 * (lo >> 4));
     };
-    request(k_first + 16 * wave);
-    for (int j0 = k_first + 16 * wave; j0 < k_end; j0 += kBwdKeys) {
-        float kf[16], vf[16], k4[4][4];
-#pragma unroll
-        for (int t = 0; t < 16; ++t) { kf[t] = kn[t]; vf[t] = vn[t]; }
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-#pragma unroll
-            for (int dt = 0; dt < 4; ++dt) k4[r][dt] = k4n[r][dt];
-        request(j0 + kBwdKeys);
-        bwd_x4 s, cc;
-        score_products(kf, qd, vf, gd, s, cc);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const bool ok = j0 + 4 * r + g < k_end && qi >= 0;
-            const double p = ok ? bwd_exp(s[r] * 0.125 - lse_c) : 0.0;
-            const double gv = 0.125 * p * (cc[r] - D_c);             // g_ij of query c and key 4r + g
-#pragma unroll
-            for (int dt = 0; dt < 4; ++dt)
-                acc[dt] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)k4[r][dt], gv, acc[dt], 0, 0, 0);
+    auto stat_of = [&](int t) -> bwd_x2 {
+        // an absent entry of the list: no weight on any key
+        double lse = INFINITY, D = 0.0;
+        if (kept_row(P, head, t, n, ub) >= 0) combine_stats(P, head, t, lse, D);
+        return bwd_x2{lse, -0.125 * D};
+    };
+    if (r_first < n) {
+        // the mean fill's share of dV: every valid v_j receives 1/n of each filled row's gradient
+        if (tid < kD) {
+            double t = 0.0;
+            if (P.fill == PSA_FILL_MEAN) {
+                const double* gs = P.gsum_part + (size_t)head * P.S1 * kD + tid;
+#pragma unroll 8
+                for (int s = 0; s < P.S1; ++s) t += gs[(size_t)s * kD];      // split order
+            }
+            s_gm[tid] = t / (double)n;
+        }
+        if (!MANY) for (int t = tid; t < P.u_pad; t += kBwdThreads) s_stat[t] = stat_of(t);
+        request(r_first);
+    }
+
+    if (r_first >= n && P.dq_part) {                                 // no valid key here: zeros
+        for (int t = tid >> 4; t < ub; t += kBwdThreads / 16) {
+            bwd_x2* dp = reinterpret_cast<bwd_x2*>(P.dq_part + (((size_t)head * P.S2 + split) * P.u_pad + t) * kD + 4 * (tid & 15));
+            dp[0] = dp[1] = bwd_x2{0.0, 0.0};
         }
     }
-    // the four waves' shares in wave order: thread (wave w, lane) adds up row r = w of every accumulator, which
-    // gives it the four consecutive elements 16 w + 4 g .. + 3 of query c
-#pragma unroll
-    for (int dt = 0; dt < 4; ++dt)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) s_acc[wave][4 * dt + r][lane] = acc[dt][r];
-    __syncthreads();
-    double tot[4];
-#pragma unroll
-    for (int dt = 0; dt < 4; ++dt) {
-        double t = 0.0;
-#pragma unroll
-        for (int w = 0; w < kBwdWaves; ++w) t += s_acc[w][4 * dt + wave][lane];
-        tot[dt] = t;
-    }
-    const int e0 = 16 * wave + 4 * g;
-    if (P.S == 1) {
-        if (qi >= 0) {
-            const float v[4] = {(float)tot[0], (float)tot[1], (float)tot[2], (float)tot[3]};
-            M::store4(static_cast<T*>(P.dQ) + ((size_t)head * L + qi) * kD + e0, v);
+    QueryStage<T, kBwdGroup> qs;
+    if (r_first < n) { qs.find(P, head, 0); qs.request(Qh, Gh, 0, n, ub); qs.put(sQ, sG); }
+
+    // (Barriers order LDS only: the stores of a block and the loads of the next need not be waited for.  Positions
+    // within a tile are derived anew from an opaque lane number where they are used: hoisted out of the loops they
+    // would cost registers, and a spilled register is worse than its few instructions, since reading it back waits
+    // for the stores before it.)
+#pragma unroll 1
+    for (int blk = 0; blk < P.blocks2; ++blk) {
+        const int r0 = r_first + blk * SH::kKeys;
+        if (r0 >= L) break;                                          // work-group-uniform
+        if ((blk * SH::kKeys) % kBwdChunk == 0) {
+            // mark the kept rows among the next 2048
+            if (tid < kBwdChunk / 32) s_bits[tid] = 0u;
+            lds_barrier();
+            for (int t = tid; t < ub; t += kBwdThreads) {
+                const int i = P.sel[(size_t)head * P.u_stride + t] - r0;
+                if (i >= 0 && i < kBwdChunk && r0 + i < n) atomicOr(&s_bits[i >> 5], 1u << (i & 31));
+            }
         }
-    } else {
-        double* dp = static_cast<double*>(P.dq_part) + ((((size_t)head * P.QT + qt) * P.S + split) * kBwdQ + c) * kD + e0;
+        // dK^T, dV^T of this wave's 16 keys: acc[dt][r] is element 4 (4r + g) + dt of key c
+        bwd_x4 dk[4], dv[4];
 #pragma unroll
-        for (int dt = 0; dt < 4; ++dt) dp[dt] = tot[dt];
+        for (int dt = 0; dt < 4; ++dt) { dk[dt] = bwd_x4{0.0, 0.0, 0.0, 0.0}; dv[dt] = bwd_x4{0.0, 0.0, 0.0, 0.0}; }
+        if (r0 < n && ub > 0) {                                      // work-group-uniform
+            const bool wave_live = r0 + 16 * ks < n;                 // wave-uniform: some key of the wave is valid
+            const bool more = blk + 1 < P.blocks2 && r0 + SH::kKeys < n;     // another block with a valid key follows
+            // B operands of the score products: this lane's key row.  A row beyond n stands for the last valid one:
+            // what comes of it is not stored, and for dQ the staged row is zero.
+            double kd[16], vd[16];
+            if (slot == 0) {                                         // the block's keys as float for the dQ product
+                const int lo = opaque(lane), c = lo & 15, g = lo >> 4;
+                float4* kr = reinterpret_cast<float4*>(sK + (16 * ks + c) * kBwdKRow + 16 * g);
+                const bool ok = r0 + 16 * ks + c < n;
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    kr[k] = ok ? make_float4(kn.at(4 * k), kn.at(4 * k + 1), kn.at(4 * k + 2), kn.at(4 * k + 3)) : make_float4(0.f, 0.f, 0.f, 0.f);
+            }
+            widen16(kn, kd);
+            widen16(vn, vd);
+
+            bwd_x2 old[kBwdTiles][2];                                // what this very lane wrote of dQ for the block before
+            int q_next = 0;
+            bool stage_next = false;
+            // this wave's share of dQ, elements 16 wave .. + 15 of both tiles of group q0 (the A operand's rows are taken
+            // in such an order that a lane's four values are elements e_own .. e_own + 3 of query c); two MFMA chains,
+            // 16 keys at a time, the next 16 keys' operands read while these products run
+            auto finish_group = [&](int q0) {
+                const int lo = opaque(lane), c = lo & 15, g = lo >> 4;
+                const double* gr = sg + c * GR + g;
+                const float* kr = sK + g * kBwdKRow + 16 * wave + 4 * (c & 3) + (c >> 2);
+                bwd_x4 dq[kBwdTiles];
+#pragma unroll
+                for (int i = 0; i < kBwdTiles; ++i) dq[i] = bwd_x4{0.0, 0.0, 0.0, 0.0};
+                auto product = [&](auto tiles) {
+                    constexpr int NT = decltype(tiles)::value;
+                    float ka[2][4];
+                    double gb[2][NT][4];
+                    auto fetch = [&](int kq) {
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) {
+                            ka[kq & 1][r] = kr[(16 * kq + 4 * r) * kBwdKRow];
+#pragma unroll
+                            for (int i = 0; i < NT; ++i) gb[kq & 1][i][r] = gr[16 * i * GR + 16 * kq + 4 * r];
+                        }
+                    };
+                    fetch(0);
+#pragma unroll
+                    for (int kq = 0; kq < KS; ++kq) {                // keys in order
+                        if (kq + 1 < KS) fetch(kq + 1);
+                        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) {
+                            const double kv = (double)ka[kq & 1][r];
+#pragma unroll
+                            for (int i = 0; i < NT; ++i) dq[i] = __builtin_amdgcn_mfma_f64_16x16x4f64(kv, gb[kq & 1][i][r], dq[i], 0, 0, 0);
+                        }
+                    }
+                };
+                if (q0 + 16 < ub) product(std::integral_constant<int, 2>{});
+                else              product(std::integral_constant<int, 1>{});
+                if (stage_next) qs.put(sQ, sG);                      // (their readers are behind the barrier before this)
+                const int e_own = 16 * wave + 4 * g;
+#pragma unroll
+                for (int i = 0; i < kBwdTiles; ++i) {
+                    const int t = q0 + 16 * i;
+                    if (t >= ub) break;                              // work-group-uniform
+                    if (P.dq_part == nullptr) {                      // the only block of the head
+                        const int qi = kept_row(P, head, t + c, n, ub);
+                        const float v[4] = {(float)dq[i][0], (float)dq[i][1], (float)dq[i][2], (float)dq[i][3]};
+                        if (qi >= 0) bwd_store4(static_cast<T*>(P.dQ) + ((size_t)head * L + qi) * kD + e_own, v);
+                    } else {
+                        if (blk > 0) dq[i] += bwd_x4{old[i][0][0], old[i][0][1], old[i][1][0], old[i][1][1]};
+                        bwd_x2* dp = reinterpret_cast<bwd_x2*>(P.dq_part + (((size_t)head * P.S2 + split) * P.u_pad + t + c) * kD + e_own);
+                        dp[0] = bwd_x2{dq[i][0], dq[i][1]};
+                        dp[1] = bwd_x2{dq[i][2], dq[i][3]};
+                    }
+                }
+            };
+            int q0 = 0;
+#pragma unroll 1
+            for (;; q0 += kBwdGroup) {                               // work-group-uniform
+                // the list entries of what comes after this group: the next group, or the first for the next block
+                q_next = q0 + kBwdGroup < ub ? q0 + kBwdGroup : 0;
+                stage_next = ub > kBwdGroup && (q_next > 0 || more); // work-group-uniform
+                if (stage_next) qs.find(P, head, q_next);
+                const bwd_x2* stat = s_stat + (MANY ? 0 : q0);
+                if (MANY && tid < kBwdGroup) s_stat[tid] = stat_of(q0 + tid);
+                lds_barrier();
+                {
+                    const int lo = opaque(lane), c = lo & 15, g = lo >> 4;
+#pragma unroll 1
+                    for (int i = 0; i < SH::kPerSlot; ++i) {         // query tiles in order
+                        const int tt = slot + i;
+                        if (q0 + 16 * tt >= ub) break;               // wave-uniform
+                        double* g_out = sg + (16 * tt + g) * GR + 16 * ks + c;
+                        if (!wave_live) {                            // (these keys take no part in dQ)
+#pragma unroll
+                            for (int r = 0; r < 4; ++r) g_out[4 * r * GR] = 0.0;
+                            continue;
+                        }
+                        bwd_x4 s, cc;
+                        score_products<true>(sQ, sG, tt, c, g, kd, vd, s, cc);       // [r]: staged query 16 tt + 4r + g against key c
+                        // A operands of the products that contract over the queries: elements 4c .. 4c + 3 of row
+                        // 16 tt + 4r + g, the next row's read while this one's products run
+                        const double* qr = sQ + (16 * tt + g) * kBwdQRow + 4 * c;
+                        const double* gr = sG + (16 * tt + g) * kBwdQRow + 4 * c;
+                        bwd_x2 qa[2][2], ga[2][2];
+                        auto fetch = [&](int r) {
+                            const bwd_x2* x = reinterpret_cast<const bwd_x2*>(qr + 4 * r * kBwdQRow);
+                            const bwd_x2* y = reinterpret_cast<const bwd_x2*>(gr + 4 * r * kBwdQRow);
+                            qa[r & 1][0] = x[0]; qa[r & 1][1] = x[1]; ga[r & 1][0] = y[0]; ga[r & 1][1] = y[1];
+                        };
+                        fetch(0);
+                        double p[4], gv[4];
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) {
+                            const bwd_x2 sd = stat[16 * tt + 4 * r + g];
+                            p[r] = exp2_f64(fma(s[r], kBwdScaleLog2e, -sd[0]));
+                            gv[r] = fma(cc[r], 0.125, sd[1]);
+                        }
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) { gv[r] *= p[r]; g_out[4 * r * GR] = gv[r]; }
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) {
+                            if (r < 3) { fetch(r + 1); __builtin_amdgcn_sched_barrier(0); }
+#pragma unroll
+                            for (int dt = 0; dt < 4; ++dt) {
+                                dk[dt] = __builtin_amdgcn_mfma_f64_16x16x4f64(qa[r & 1][dt >> 1][dt & 1], gv[r], dk[dt], 0, 0, 0);
+                                dv[dt] = __builtin_amdgcn_mfma_f64_16x16x4f64(ga[r & 1][dt >> 1][dt & 1], p[r], dv[dt], 0, 0, 0);
+                            }
+                        }
+                    }
+                }
+                // under this group's dQ travel: what was written of it for the block before, and the rows of what
+                // comes next
+                if (blk > 0) {
+                    const int lo = opaque(lane), e_own = 16 * wave + 4 * (lo >> 4);
+#pragma unroll
+                    for (int i = 0; i < kBwdTiles; ++i) {
+                        const int t = (q0 + 16 * i < ub ? q0 + 16 * i : q0) + (lo & 15);
+                        const bwd_x2* dp = reinterpret_cast<const bwd_x2*>(P.dq_part + (((size_t)head * P.S2 + split) * P.u_pad + t) * kD + e_own);
+                        old[i][0] = dp[0]; old[i][1] = dp[1];
+                    }
+                }
+                if (stage_next) qs.request(Qh, Gh, q_next, n, ub);
+                if (q0 + kBwdGroup >= ub) break;
+                lds_barrier();
+                finish_group(q0);
+            }
+            // the last group: the next block's key rows travel too, now that the registers of this one's are free
+            if (more) request(r0 + SH::kKeys);
+            lds_barrier();
+            finish_group(q0);
+        }
+        lds_barrier();                                               // s_bits; every wave is done with this block's LDS
+        if constexpr (SH::kSlots == 2) {
+            // the two slots' shares of dK and dV together, through the g tiles' LDS
+            const int lo = opaque(lane);
+            double* at = sg + (size_t)ks * 8 * 64 + lo;
+#pragma unroll
+            for (int part = 0; part < 4; ++part) {
+                bwd_x4 (&x)[4] = part < 2 ? dk : dv;
+                if (part > 0) lds_barrier();
+                if (slot == 1) {
+#pragma unroll
+                    for (int d2 = 0; d2 < 2; ++d2)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) at[(4 * d2 + r) * 64] = x[2 * (part & 1) + d2][r];
+                }
+                lds_barrier();
+                if (slot == 0) {
+#pragma unroll
+                    for (int d2 = 0; d2 < 2; ++d2)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) x[2 * (part & 1) + d2][r] += at[(4 * d2 + r) * 64];
+                }
+            }
+        }
+        // Rows of dK and dV (and the rows of dQ outside I_sparse, which no gradient reaches).  A lane holds 4-element
+        // pieces of one row; they go through the g tiles' LDS, 16 rows of 64 floats per wave (pieces of 16 bytes
+        // swapped by row, for the banks), so that a store instruction writes whole rows, 16 bytes per lane.
+        if (slot == 0) {
+            constexpr int EPV = 16 / sizeof(T), LPR = kD / EPV, RPI = 64 / LPR;      // elements per lane, lanes per row, rows per instruction
+            const int lo = opaque(lane), c = lo & 15, g = lo >> 4;
+            float* stage = reinterpret_cast<float*>(sg) + (size_t)ks * 16 * kD;
+            const int row_l = lo / LPR, e_l = (lo % LPR) * EPV;
+            const int j0 = r0 + 16 * ks, bit0 = (j0 - r_first) % kBwdChunk;          // (a multiple of 16)
+            const unsigned bits = (s_bits[bit0 >> 5] >> (bit0 & 31)) & 0xFFFFu;      // kept rows among these 16 (none at or beyond n)
+            // the value fill hands v_j the gradient of its own row
+            const bool use_own = P.fill != PSA_FILL_MEAN && j0 + c < n && !((bits >> c) & 1u);
+            BwdRow<T, 4> own[4];
+            if (use_own) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r) own[r].load(Gh + (size_t)(j0 + c) * kD + 16 * r + 4 * g);
+            }
+            auto piece = [&](int row, int p4) -> float4* { return reinterpret_cast<float4*>(stage + row * kD + 4 * (p4 ^ row)); };
+#pragma unroll
+            for (int half = 0; half < 2; ++half) {
+                const bwd_x4 (&x)[4] = half == 0 ? dk : dv;
+                wave_lds_sync();                                     // the first tensor has been read
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {                        // elements 4 (4r + g) .. + 3 of key c
+                    double v[4];
+#pragma unroll
+                    for (int dt = 0; dt < 4; ++dt) {
+                        v[dt] = x[dt][r];
+                        if (half == 1 && P.fill == PSA_FILL_MEAN) v[dt] += s_gm[16 * r + 4 * g + dt];
+                        if (half == 1 && use_own) v[dt] += (double)own[r].at(dt);
+                    }
+                    *piece(c, 4 * r + g) = make_float4((float)v[0], (float)v[1], (float)v[2], (float)v[3]);
+                }
+                wave_lds_sync();
+                T* base = static_cast<T*>(half == 0 ? P.dK : P.dV) + ((size_t)head * L + j0) * kD + e_l;
+                T* base_q = static_cast<T*>(P.dQ) + ((size_t)head * L + j0) * kD + e_l;
+#pragma unroll
+                for (int it = 0; it < 16 / RPI; ++it) {
+                    const int row = it * RPI + row_l;
+                    const bool valid = j0 + row < n;
+                    float v[EPV];
+#pragma unroll
+                    for (int q = 0; q < EPV / 4; ++q) {
+                        const float4 f = *piece(row, e_l / 4 + q);
+                        v[4 * q] = f.x; v[4 * q + 1] = f.y; v[4 * q + 2] = f.z; v[4 * q + 3] = f.w;
+                    }
+                    if (j0 + row < L) {
+                        bwd_store16(base + (size_t)row * kD, v, valid);
+                        if (half == 0 && !((bits >> row) & 1u)) bwd_store16(base_q + (size_t)row * kD, v, false);
+                    }
+                }
+            }
+        }
+        lds_barrier();                                               // the next block's LDS
     }
 }
 
+// adds the key splits of dQ in split order; 16 threads per kept query, 4 elements each
 template <typename T>
-__global__ __launch_bounds__(kBwdThreads)
+__global__ __launch_bounds__(256)
 void bwd_dq_reduce_kernel(const BwdParams P)
 {
-    using M = BwdMem<T>;
-    const int qt = blockIdx.x, head = blockIdx.y;
-    const int b = head / P.H;
-    const int n = valid_len(P.lengths, b, P.L);
-    const int ub = kept_count(P, b, n);
-    if (qt * kBwdQ >= ub) return;
-    const int tid = threadIdx.x, i = tid >> 4, e0 = 4 * (tid & 15);
-    const int qi = kept_row(P, head, qt * kBwdQ + i, n, ub);
+    const int head = blockIdx.y;
+    const int n = valid_len(P.lengths, head / P.H, P.L);
+    const int ub = kept_count(P, head / P.H, n);
+    const int t = blockIdx.x * 16 + (threadIdx.x >> 4), e0 = 4 * (threadIdx.x & 15);
+    const int qi = kept_row(P, head, t, n, ub);
     if (qi < 0) return;
-    const double* dp = static_cast<const double*>(P.dq_part) + (((size_t)head * P.QT + qt) * P.S * kBwdQ + i) * kD + e0;
-    double acc[4] = {0, 0, 0, 0};
-    for (int s = 0; s < P.S; ++s)                                    // split order
-#pragma unroll
-        for (int e = 0; e < 4; ++e) acc[e] += dp[(size_t)s * kBwdQ * kD + e];
+    const double* dp = P.dq_part + ((size_t)head * P.S2 * P.u_pad + t) * kD + e0;
+    const size_t step = (size_t)P.u_pad * kD;
+    double acc[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll 4
+    for (int s = 0; s < P.S2; ++s) {
+        const bwd_x2 x = *reinterpret_cast<const bwd_x2*>(dp + s * step), y = *reinterpret_cast<const bwd_x2*>(dp + s * step + 2);
+        acc[0] += x[0]; acc[1] += x[1]; acc[2] += y[0]; acc[3] += y[1];
+    }
     const float v[4] = {(float)acc[0], (float)acc[1], (float)acc[2], (float)acc[3]};
-    M::store4(static_cast<T*>(P.dQ) + ((size_t)head * P.L + qi) * kD + e0, v);
-}
-
-// ---- key-stationary: one work-group per block of 64 keys (16 per wave) walks all kept queries of the head
-template <typename T>
-__global__ __launch_bounds__(kBwdThreads)
-void bwd_dkv_kernel(const BwdParams P)
-{
-    using M = BwdMem<T>;
-    __shared__ unsigned char s_flag[kBwdKeys];
-    __shared__ double s_gm[kD];
-    __shared__ __attribute__((aligned(16))) float s_q[kBwdStaged][kBwdStage], s_g[kBwdStaged][kBwdStage];
-    __shared__ double s_lse[kBwdStaged], s_D[kBwdStaged];
-    __shared__ int s_qrow[kBwdStaged];
-    const int blk = blockIdx.x, head = blockIdx.y;
-    const int b = head / P.H, L = P.L;
-    const int n = valid_len(P.lengths, b, L);
-    const int ub = kept_count(P, b, n);
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, c = lane & 15, g = lane >> 4;
-    const int r0 = blk * kBwdKeys;
-    const T* Qh = static_cast<const T*>(P.Q) + (size_t)head * L * kD;
-    const T* Kh = static_cast<const T*>(P.K) + (size_t)head * L * kD;
-    const T* Vh = static_cast<const T*>(P.V) + (size_t)head * L * kD;
-    const T* Gh = static_cast<const T*>(P.G) + (size_t)head * L * kD;
-    const int j = r0 + 16 * wave + c;                                // this lane's key (the column of its accumulators)
-
-    // which rows of this block are kept queries; the fill's share of dV under the mean fill: every valid v_j
-    // receives 1/n of each filled row's gradient
-    if (tid < kBwdKeys) s_flag[tid] = 0;
-    if (tid < kD) {
-        double t = 0;
-        if (P.fill == PSA_FILL_MEAN) {
-            const double* gs = static_cast<const double*>(P.gsum_part) + (size_t)head * P.S * kD + tid;
-            for (int s = 0; s < P.S; ++s) t += gs[(size_t)s * kD]; // split order
-        }
-        s_gm[tid] = n > 0 ? t / (double)n : 0.0;
-    }
-    __syncthreads();
-    for (int t = tid; t < ub; t += kBwdThreads) {
-        const int i = P.sel[(size_t)head * P.u_stride + t];
-        if (i >= r0 && i < r0 + kBwdKeys && i < n) s_flag[i - r0] = 1;
-    }
-    __syncthreads();
-
-    // dK^T, dV^T of this wave's 16 keys: acc[dt][r] is element 4 (4r + g) + dt of key j
-    bwd_x4 dk[4], dv[4];
-#pragma unroll
-    for (int dt = 0; dt < 4; ++dt) { dk[dt] = bwd_x4{0.0, 0.0, 0.0, 0.0}; dv[dt] = bwd_x4{0.0, 0.0, 0.0, 0.0}; }
-    const bool wave_live = r0 + 16 * wave < n;                       // wave-uniform: some key of the wave is valid
-    // B operands of the score products: this lane's key row
-    double kd[16], vd[16];
-    if (r0 < n) {                                                    // (work-group-uniform; n > 0 inside)
-        const int row = j < n ? j : n - 1;
-        float kf[16], vf[16];
-        M::row16(Kh + (size_t)row * kD + 16 * g, kf);
-        M::row16(Vh + (size_t)row * kD + 16 * g, vf);
-#pragma unroll
-        for (int t = 0; t < 16; ++t) { kd[t] = (double)kf[t]; vd[t] = (double)vf[t]; }
-        // The kept queries are the same for all four waves: their rows of Q and G (as float) and their
-        // statistics are staged in LDS 64 at a time, so the loop over query tiles touches no global memory.
-        // Rows are kBwdStage floats apart: 16-byte reads of 8 consecutive rows then fall on all 32 banks.
-        for (int q0 = 0; q0 < ub; q0 += kBwdStaged) {                // work-group-uniform
-            __syncthreads();                                         // the previous 64 have been used
-            {
-                const int row_s = tid >> 2, part = tid & 3;          // 64 rows, 4 threads each
-                const int qs = kept_row(P, head, q0 + row_s, n, ub);
-                float a[16], bq[16];
-                M::row16(Qh + (size_t)(qs >= 0 ? qs : 0) * kD + 16 * part, a);
-                M::row16(Gh + (size_t)(qs >= 0 ? qs : 0) * kD + 16 * part, bq);
-#pragma unroll
-                for (int t = 0; t < 16; ++t) {
-                    s_q[row_s][16 * part + t] = qs >= 0 ? a[t] : 0.f;
-                    s_g[row_s][16 * part + t] = qs >= 0 ? bq[t] : 0.f;
-                }
-                if (part == 0) {
-                    s_qrow[row_s] = qs;
-                    // (statistics exist for the tiles that hold a kept query)
-                    const bool has = q0 + row_s < ((ub + kBwdQ - 1) / kBwdQ) * kBwdQ;
-                    const double* st = static_cast<const double*>(P.stats) + ((size_t)head * P.QT * kBwdQ + (has ? q0 + row_s : 0)) * 2;
-                    s_lse[row_s] = has ? st[0] : 0.0;
-                    s_D[row_s] = has ? st[1] : 0.0;
-                }
-            }
-            __syncthreads();
-            if (!wave_live) continue;
-            int n_t = (ub - q0 + kBwdQ - 1) / kBwdQ;
-            n_t = n_t < kBwdStaged / kBwdQ ? n_t : kBwdStaged / kBwdQ;
-            for (int tt = 0; tt < n_t; ++tt) {                       // query tiles in order
-                // A operands of the score products: staged query 16 tt + c
-                float qf[16], gf[16];
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    const float4 x = *reinterpret_cast<const float4*>(&s_q[16 * tt + c][16 * g + 4 * k]);
-                    const float4 y = *reinterpret_cast<const float4*>(&s_g[16 * tt + c][16 * g + 4 * k]);
-                    qf[4 * k] = x.x; qf[4 * k + 1] = x.y; qf[4 * k + 2] = x.z; qf[4 * k + 3] = x.w;
-                    gf[4 * k] = y.x; gf[4 * k + 1] = y.y; gf[4 * k + 2] = y.z; gf[4 * k + 3] = y.w;
-                }
-                bwd_x4 s, cc;
-                score_products(qf, kd, gf, vd, s, cc);               // s[r], cc[r]: staged query 16 tt + 4r + g against key j
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int qq = 16 * tt + 4 * r + g;
-                    const bool ok = j < n && s_qrow[qq] >= 0;
-                    const double p = ok ? bwd_exp(s[r] * 0.125 - s_lse[qq]) : 0.0;
-                    const double gv = 0.125 * p * (cc[r] - s_D[qq]);
-                    // A operands of the products that contract over the queries: elements 4c .. 4c + 3 of row qq
-                    const float4 q4 = *reinterpret_cast<const float4*>(&s_q[qq][4 * c]);
-                    const float4 g4 = *reinterpret_cast<const float4*>(&s_g[qq][4 * c]);
-                    dk[0] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)q4.x, gv, dk[0], 0, 0, 0);
-                    dv[0] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)g4.x, p, dv[0], 0, 0, 0);
-                    dk[1] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)q4.y, gv, dk[1], 0, 0, 0);
-                    dv[1] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)g4.y, p, dv[1], 0, 0, 0);
-                    dk[2] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)q4.z, gv, dk[2], 0, 0, 0);
-                    dv[2] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)g4.z, p, dv[2], 0, 0, 0);
-                    dk[3] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)q4.w, gv, dk[3], 0, 0, 0);
-                    dv[3] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)g4.w, p, dv[3], 0, 0, 0);
-                }
-            }
-        }
-    }
-    // rows of dK, dV (and the rows of dQ outside I_sparse, which no gradient reaches): 16 bytes at a time
-    if (j < L) {
-        const bool valid = j < n, kept = valid && s_flag[16 * wave + c];
-        T* dkr = static_cast<T*>(P.dK) + ((size_t)head * L + j) * kD;
-        T* dvr = static_cast<T*>(P.dV) + ((size_t)head * L + j) * kD;
-        T* dqr = static_cast<T*>(P.dQ) + ((size_t)head * L + j) * kD;
-        const float zero[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int e0 = 16 * r + 4 * g;
-            float own[4] = {0.f, 0.f, 0.f, 0.f};                     // the value fill hands v_j the gradient of its own row
-            if (P.fill != PSA_FILL_MEAN && valid && !kept) M::row4(Gh + (size_t)j * kD + e0, own);
-            float ok_[4], ov[4];
-#pragma unroll
-            for (int dt = 0; dt < 4; ++dt) {
-                double v = dv[dt][r];
-                if (P.fill == PSA_FILL_MEAN) v += s_gm[e0 + dt]; else v += (double)own[dt];
-                ok_[dt] = valid ? (float)dk[dt][r] : 0.f;
-                ov[dt] = valid ? (float)v : 0.f;
-            }
-            M::store4(dkr + e0, ok_);
-            M::store4(dvr + e0, ov);
-            if (!kept) M::store4(dqr + e0, zero);
-        }
-    }
+    bwd_store4(static_cast<T*>(P.dQ) + ((size_t)head * P.L + qi) * kD + e0, v);
 }
 
 template <typename T>
-static hipError_t launch_bwd_t(const BwdParams& P, int BH, hipStream_t stream)
+static hipError_t raise_bwd_limits()
 {
-    const dim3 qgrid(P.S, P.QT, BH);
-    hipLaunchKernelGGL(bwd_stats_kernel<T>, qgrid, dim3(kBwdThreads), 0, stream, P);
-    hipLaunchKernelGGL(bwd_dq_kernel<T>, qgrid, dim3(kBwdThreads), 0, stream, P);
-    hipLaunchKernelGGL(bwd_dkv_kernel<T>, dim3((P.L + kBwdKeys - 1) / kBwdKeys, BH), dim3(kBwdThreads), 0, stream, P);
-    if (P.S > 1) hipLaunchKernelGGL(bwd_dq_reduce_kernel<T>, dim3(P.QT, BH), dim3(kBwdThreads), 0, stream, P);
+    static std::atomic<uint64_t> raised[4];            // per instantiation: devices already served
+    const void* fn[4] = {(const void*)bwd_stats_kernel<T>, (const void*)bwd_main_kernel<T, 4, false>,
+                         (const void*)bwd_main_kernel<T, 2, false>, (const void*)bwd_main_kernel<T, 4, true>};
+    const int lds[4] = {kBwdStatsLds, BwdShare<4>::kLds, BwdShare<2>::kLds, BwdShare<4>::kLds};
+    for (int k = 0; k < 4; ++k) { const hipError_t e = ensure_lds_limit(fn[k], lds[k], raised[k]); if (e != hipSuccess) return e; }
+    return hipSuccess;
+}
+hipError_t init_backward()
+{
+    const hipError_t e = raise_bwd_limits<float>();
+    return e != hipSuccess ? e : raise_bwd_limits<bf16_t>();
+}
+
+template <typename T>
+static hipError_t launch_bwd_t(const BwdParams& P, int BH, int ks, hipStream_t stream)
+{
+    const hipError_t e = raise_bwd_limits<T>();
+    if (e != hipSuccess) return e;
+    const dim3 grid(P.S2, BH), block(kBwdThreads);
+    hipLaunchKernelGGL(bwd_stats_kernel<T>, dim3(P.S1, P.n_group, BH), block, kBwdStatsLds, stream, P);
+    if (P.u_pad > kBwdKeepStats)
+        hipLaunchKernelGGL((bwd_main_kernel<T, 4, true>), grid, block, BwdShare<4>::kFixed + kBwdGroup * 16, stream, P);
+    else if (ks == 4)
+        hipLaunchKernelGGL((bwd_main_kernel<T, 4, false>), grid, block, BwdShare<4>::kFixed + P.u_pad * 16, stream, P);
+    else
+        hipLaunchKernelGGL((bwd_main_kernel<T, 2, false>), grid, block, BwdShare<2>::kFixed + P.u_pad * 16, stream, P);
+    if (P.dq_part) hipLaunchKernelGGL(bwd_dq_reduce_kernel<T>, dim3(P.u_pad / kBwdQ, BH), dim3(256), 0, stream, P);
     return hipGetLastError();
 }
 
-// Plan of the backward: query tiles, key splits and the carving of its workspace (host arithmetic).
+// Key blocks per work-group for `rows` (head, query group) pairs of `n_blocks` blocks: the number that takes the
+// least time when work-groups run two per CU in rounds of 512 (a CU with one work-group takes 0.6 of the time of
+// one with two), each paying `fixed` (staging, first loads; in units of a block's work) beside its blocks.  At most
+// 64 splits.
+static int blocks_per_split(int64_t rows, int n_blocks, double fixed, double* cost_out)
+{
+    int best = n_blocks;
+    double best_cost = 1e300;
+    for (int r = 1; r <= 8; ++r) {                              // half rounds of the CUs aimed at
+        int64_t S = 256 * r / rows;
+        S = S < 1 ? 1 : (S > kBwdMaxSplit ? kBwdMaxSplit : (S > n_blocks ? n_blocks : S));
+        const int per = (int)((n_blocks + S - 1) / S);
+        const int64_t wgs = rows * ((n_blocks + per - 1) / per), half = (wgs + 255) / 256;
+        const double cost = ((double)(half / 2) + (half & 1 ? 0.6 : 0.0)) * (per + fixed);
+        if (cost < best_cost) { best_cost = cost; best = per; }
+    }
+    *cost_out = best_cost;
+    return best;
+}
+
+// Plan of the backward: query groups, key splits and the carving of its workspace (host arithmetic).
 BwdPlan make_bwd_plan(const psa_shape_t& s, int u_stride)
 {
     BwdPlan p;
-    const int BH = s.B * s.H;
-    const size_t ce = sizeof(double);                           // the arithmetic type of every intermediate
-    p.QT = (u_stride + kBwdQ - 1) / kBwdQ;
+    const int64_t BH = (int64_t)s.B * s.H;
+    p.n_group = (u_stride + kBwdStatGroup - 1) / kBwdStatGroup;
+    p.u_pad = (u_stride + kBwdQ - 1) / kBwdQ * kBwdQ;
+    const int tiles = p.u_pad / kBwdQ;
+    double cost;
     const int n_blocks = (s.L_K + kBwdKeys - 1) / kBwdKeys;
-    int S = (int)((512 + (int64_t)BH * p.QT - 1) / ((int64_t)BH * p.QT));
-    S = S < 1 ? 1 : (S > 64 ? 64 : S);
-    S = S > n_blocks ? n_blocks : S;
-    p.blocks_per_split = (n_blocks + S - 1) / S;
-    p.S = (n_blocks + p.blocks_per_split - 1) / p.blocks_per_split;
+    p.blocks1 = blocks_per_split(BH * p.n_group, n_blocks, 4.0 / (tiles < 4 ? tiles : 4), &cost);
+    p.S1 = (n_blocks + p.blocks1 - 1) / p.blocks1;
+    // The gradient kernel: blocks of 64 keys, or of 32 with the waves sharing out the query tiles as well where
+    // there are too few heads and keys to give every CU work of the larger kind.  In units of one query tile on 4
+    // waves (80 MFMAs, 2.2 us); beside its tiles a work-group pays about two such units, and the smaller blocks a
+    // little more for adding up the slots' shares and for more splits of dQ.
+    double best = 1e300;
+    for (int ks = 4; ks >= (p.u_pad > kBwdKeepStats ? 4 : 2); ks >>= 1) {
+        const int slots = kBwdWaves / ks, nb = (s.L_K + 16 * ks - 1) / (16 * ks);
+        const double per_block = (double)((tiles + slots - 1) / slots) + (slots > 1 ? 0.5 : 0.0);
+        const int per = blocks_per_split(BH, nb, 2.0 / per_block, &cost);
+        if (cost * per_block < best * 0.95) {
+            best = cost * per_block;
+            p.ks = ks; p.blocks2 = per; p.S2 = (nb + per - 1) / per;
+        }
+    }
+    // dQ goes straight to memory where one block holds all keys of a head
+    p.parts = p.S2 > 1 || p.blocks2 > 1;
     auto al = [](size_t x) { return (x + 255) & ~(size_t)255; };
     size_t off = 0;
-    p.off_stats_part = off; off += al((size_t)BH * p.QT * p.S * kBwdQ * 3 * ce);
-    p.off_stats = off;      off += al((size_t)BH * p.QT * kBwdQ * 2 * ce);
-    p.off_gsum = off;       off += al((size_t)BH * p.S * kD * ce);
-    p.off_dq_part = off;    off += p.S > 1 ? al((size_t)BH * p.QT * p.S * kBwdQ * kD * ce) : 0;
+    p.off_stats_part = off; off += al((size_t)BH * p.S1 * p.u_pad * 3 * sizeof(double));
+    p.off_gsum = off;       off += al((size_t)BH * p.S1 * kD * sizeof(double));
+    p.off_dq_part = off;    off += p.parts ? al((size_t)BH * p.S2 * p.u_pad * kD * sizeof(double)) : 0;
     p.total = off;
     return p;
 }
@@ -596,12 +854,14 @@ hipError_t launch_backward(const psa_shape_t& s, const BwdPlan& bp, const void* 
     BwdParams P;
     P.Q = Q; P.K = K; P.V = V; P.G = G; P.lengths = lengths; P.sel = sel; P.u = u;
     P.dQ = dQ; P.dK = dK; P.dV = dV;
-    P.stats_part = w + bp.off_stats_part; P.stats = w + bp.off_stats; P.gsum_part = w + bp.off_gsum;
-    P.dq_part = w + bp.off_dq_part;
-    P.H = s.H; P.L = s.L_K; P.u_stride = u_stride; P.QT = bp.QT; P.S = bp.S; P.blocks_per_split = bp.blocks_per_split;
+    P.stats_part = reinterpret_cast<double*>(w + bp.off_stats_part);
+    P.gsum_part = reinterpret_cast<double*>(w + bp.off_gsum);
+    P.dq_part = bp.parts ? reinterpret_cast<double*>(w + bp.off_dq_part) : nullptr;
+    P.H = s.H; P.L = s.L_K; P.u_stride = u_stride; P.u_pad = bp.u_pad; P.n_group = bp.n_group;
+    P.S1 = bp.S1; P.blocks1 = bp.blocks1; P.S2 = bp.S2; P.blocks2 = bp.blocks2;
     P.fill = fill;
     const int BH = s.B * s.H;
-    return s.dtype == PSA_F32 ? launch_bwd_t<float>(P, BH, stream) : launch_bwd_t<bf16_t>(P, BH, stream);
+    return s.dtype == PSA_F32 ? launch_bwd_t<float>(P, BH, bp.ks, stream) : launch_bwd_t<bf16_t>(P, BH, bp.ks, stream);
 }
 
 }  // namespace psa

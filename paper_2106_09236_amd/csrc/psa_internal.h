@@ -116,6 +116,7 @@ Scratch carve(const Plan& p, void* workspace);
 // functions do the same on their first use.
 hipError_t init_measure();
 hipError_t init_attend();
+hipError_t init_backward();
 
 hipError_t launch_measure(const Plan& p, const Args& a, const Scratch& w);
 hipError_t launch_select(const Plan& p, const Args& a, const Scratch& w);
@@ -124,11 +125,12 @@ hipError_t launch_attend(const Plan& p, const Args& a, const Scratch& w);
 hipError_t launch_vsum(const Plan& p, const Args& a, const Scratch& w);             // V column sums alone
 hipError_t launch_prep_indices(const Plan& p, const Args& a, const Scratch& w);     // mean of V, caller's index sets
 
-// Gradients of stages a3 and a4 for a fixed index set (psa_backward.hip): query tiles of 16 kept
-// queries, S key splits of `blocks_per_split` blocks of 64 keys, and the carving of the workspace.
+// Gradients of stages a3 and a4 for a fixed index set (psa_backward.hip): groups of 64 kept queries, key
+// splits of blocks1 blocks of 64 keys (statistics) and blocks2 blocks of 16 ks keys (gradients), and the carving
+// of the workspace (parts: dQ goes through partial sums).
 struct BwdPlan {
-    int QT, S, blocks_per_split;
-    size_t off_stats_part, off_stats, off_gsum, off_dq_part, total;
+    int n_group, u_pad, S1, blocks1, S2, blocks2, ks, parts;
+    size_t off_stats_part, off_gsum, off_dq_part, total;
 };
 BwdPlan make_bwd_plan(const psa_shape_t& s, int u_stride);
 hipError_t launch_backward(const psa_shape_t& s, const BwdPlan& bp, const void* Q, const void* K, const void* V,
