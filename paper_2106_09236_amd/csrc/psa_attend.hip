@@ -33,11 +33,8 @@ constexpr int kF32SmemBytes = kF32Waves * kStateDoubles * 64 * 8;     // 73728: 
 //   [ m[NQ] | l[NQ] as float64 | O / l as float32: per column tile ct a block of 1024 = [16 registers][64 lanes] ]
 // element e of query q: block q / 16, register 4 (e % 4) + e / 16, lane ((e / 4) % 4) * 16 + q % 16
 // (F32Tile::reg_of, grp_of), i.e. exactly the accumulator layout, so record stores are fully coalesced.
-// ALLFULL: the host knows that every key tile of every head is wholly valid (no lengths, L a multiple of
-// 32): the loads then need no clamps and the step no masks (a run-time test per tile with both forms of
-// the step in one kernel measured slower: 20.1 -> 26.8 us).
 // The work of one work-group (key split `split`, query group `qgroup` of `head`); `smem`: kF32SmemBytes of LDS.
-template <int NCG, bool ALLFULL, typename CS>      // NCG: column tiles of 16 selected queries per query group, 1 or 2
+template <int NCG, typename CS>      // NCG: column tiles of 16 selected queries per query group, 1 or 2
 __device__ __forceinline__ void attend_f32_body(const AttendParams& P, int split, int qgroup, int head, double* smem, CS& cs)
 {
     const float* Q = static_cast<const float*>(P.Q);
@@ -67,18 +64,15 @@ __device__ __forceinline__ void attend_f32_body(const AttendParams& P, int split
     F32Tile tile;
     tile.init();
     const int j_first = (split * rounds * KT + kt) * kTile;
-    // A wave whose first tile lies past the end (more waves than key tiles: short heads) does no tile
-    // step, but its first loads are issued before that is looked at; the masked loads clamp every row,
-    // the unmasked ones must be pointed at rows that exist (rows 0 .. 31: L is a multiple of 32 here).
-    const int j_ld = (ALLFULL && j_first >= n) ? 0 : j_first;
+    const __amdgpu_buffer_rsrc_t kr = head_rows<256>(Kh, n), vr = head_rows<256>(Vh, n);
     int u;
-    const int* selp = attend_prologue<512>(P, head, n, wg_in_head, cs, u,
-                                           [&]() { F32Tile::load_k_into<ALLFULL>(tile.kreg, Kh, j_ld, n, c, g); });
+    const SelList selp = attend_prologue<512>(P, head, n, wg_in_head, cs, u,
+                                              [&]() { F32Tile::load_k_into(tile.kreg, kr, j_first, c, g); });
     PSA_TS(1);
     const int qrank = qgroup * NQ + ct * 16 + c;
     const int qi = qrank < u ? selp[qrank] : -1;
-    tile.load_q(Qh, qi, qi >= 0 && qi < n, g);
-    tile.load_v<ALLFULL>(Vh, j_ld, n, c, g);                  // behind K and Q in the queue, needed last
+    tile.load_q(head_rows<256>(Qh, n), qi, g);
+    tile.load_v(vr, j_first, c, g);                           // behind K and Q in the queue, needed last
 
     // ---- stage a4 for this work-group's share of the rows: the stores go out now
     // and complete under the matrix work below
@@ -97,9 +91,9 @@ __device__ __forceinline__ void attend_f32_body(const AttendParams& P, int split
 #pragma unroll
                 for (int v = 0; v < 4; ++v) tile.kreg[sb][v] = knext[sb][v];
         }
-        if (rd + 1 < rounds) F32Tile::load_k_into(knext, Kh, j0 + KT * kTile, n, c, g);     // (may lie past the end: clamped)
-        if (rd == 0) tile.step<true, ALLFULL>(Vh, j0, n, c, g);
-        else         tile.step<false, ALLFULL>(Vh, j0, n, c, g);
+        if (rd + 1 < rounds) F32Tile::load_k_into(knext, kr, j0 + KT * kTile, c, g);        // (zeros past the end)
+        if (rd == 0) tile.step<true>(vr, j0, n, c, g);
+        else         tile.step<false>(vr, j0, n, c, g);
     }
     PSA_TS(3);
     const float m_run = tile.m_run;
@@ -178,13 +172,13 @@ __device__ __forceinline__ void attend_f32_body(const AttendParams& P, int split
     PSA_TS(8);
 }
 
-template <int NCG, bool ALLFULL>
+template <int NCG>
 __global__ __launch_bounds__(512)
 void attend_f32_kernel(const AttendParams P)
 {
     __shared__ CommonScratch<512> cs;
     extern __shared__ __attribute__((aligned(16))) double smem[];
-    attend_f32_body<NCG, ALLFULL>(P, blockIdx.x, blockIdx.y, blockIdx.z, smem, cs);
+    attend_f32_body<NCG>(P, blockIdx.x, blockIdx.y, blockIdx.z, smem, cs);
 }
 
 // =============================================================================
@@ -305,7 +299,7 @@ __device__ __forceinline__ void attend_bf16_body(const AttendParams& P, int spli
     uint4 kn[4], vn[4];
     PSA_TS(0);
     int u;
-    const int* selp = attend_prologue<512>(P, head, n, wg_in_head, cs, u, [&]() {
+    const SelList selp = attend_prologue<512>(P, head, n, wg_in_head, cs, u, [&]() {
         Bf16Tile<NQT>::load_k_operand(kn, Kh, tile0 * kTile, n, c, h);
         Bf16Tile<NQT>::load_v_rows(vn, Vh, tile0 * kTile, n, lane);
     });
@@ -588,7 +582,7 @@ void merge_kernel(const AttendParams P)
 // the second half of the key tiles for the same queries and hand their state (m, l, O) to the first
 // four through LDS, lane for lane: a two-way merge inside the work-group, once per kernel.
 template <int KSPLIT>
-__global__ __launch_bounds__(256 * KSPLIT)
+__global__ __launch_bounds__(256 * KSPLIT, 2)
 void attend_rows_f32_kernel(const AttendParams P)
 {
     constexpr int NT = 256 * KSPLIT;
@@ -613,14 +607,15 @@ void attend_rows_f32_kernel(const AttendParams P)
 
     F32Tile tile;
     tile.init();
+    const __amdgpu_buffer_rsrc_t kr = head_rows<256>(Kh, n), vr = head_rows<256>(Vh, n);
     float4 knext[2][4];
     int u;
-    const int* selp = attend_prologue<NT>(P, head, n, qblock, cs, u,
-                                          [&]() { F32Tile::load_k_into(knext, Kh, j_begin, n, c, g); });
+    const SelList selp = attend_prologue<NT>(P, head, n, qblock, cs, u,
+                                          [&]() { F32Tile::load_k_into(knext, kr, j_begin, c, g); });
     const int rank = qblock * 64 + wq * 16 + c;
     int qi = rank < u ? selp[rank] : -1;
     if (qi >= n) qi = -1;
-    tile.load_q(Qh, qi, qi >= 0, g);
+    tile.load_q(head_rows<256>(Qh, n), qi, g);
     fill_rows<float, NT>(P, oh, Vh, selp, u, n, qblock, cs);
     const bool live = qblock * 64 + wq * 16 < u;          // wave-uniform: some rank of this wave is in use
     if (KSPLIT == 1 && !live) return;
@@ -630,11 +625,8 @@ void attend_rows_f32_kernel(const AttendParams P)
             for (int sb = 0; sb < 2; ++sb)
 #pragma unroll
                 for (int v = 0; v < 4; ++v) tile.kreg[sb][v] = knext[sb][v];
-            // tiles that lie wholly inside the valid rows (all but the last one or two) need no masks
-            if (j0 + 2 * kTile <= n) F32Tile::load_k_into<true>(knext, Kh, j0 + kTile, n, c, g);
-            else                     F32Tile::load_k_into<false>(knext, Kh, j0 + kTile, n, c, g);
-            if (j0 + kTile <= n) tile.step<false, true>(Vh, j0, n, c, g);
-            else                 tile.step<false, false>(Vh, j0, n, c, g);
+            F32Tile::load_k_into(knext, kr, j0 + kTile, c, g);
+            tile.step(vr, j0, n, c, g);
         }
     }
     if constexpr (KSPLIT == 2) {
@@ -717,7 +709,7 @@ void attend_rows_bf16_kernel(const AttendParams P)
     };
     uint4 xk, xv;
     int u;
-    const int* selp = attend_prologue<NT>(P, head, n, qblock, cs, u, [&]() { fetch(j_begin, xk, xv); });
+    const SelList selp = attend_prologue<NT>(P, head, n, qblock, cs, u, [&]() { fetch(j_begin, xk, xv); });
     Bf16Tile<1> tile;
     tile.init();
     const int rank = qblock * 128 + wq * 32 + c;
@@ -782,17 +774,16 @@ void attend_rows_bf16_kernel(const AttendParams P)
 
 // The four attend kernels that use more than the default 64 KB of dynamic LDS, and the
 // devices on which each has had its limit raised.
-static std::atomic<uint64_t> g_attend_raised[6];
+static std::atomic<uint64_t> g_attend_raised[4];
 static hipError_t raise_attend_limit(int k)
 {
-    const void* fn[6] = {(const void*)attend_f32_kernel<1, false>, (const void*)attend_f32_kernel<2, false>,
-                         (const void*)attend_f32_kernel<1, true>, (const void*)attend_f32_kernel<2, true>,
+    const void* fn[4] = {(const void*)attend_f32_kernel<1>, (const void*)attend_f32_kernel<2>,
                          (const void*)attend_bf16_kernel<1>, (const void*)attend_bf16_kernel<2>};
-    return ensure_lds_limit(fn[k], k < 4 ? kF32SmemBytes : kB16SmemBytes, g_attend_raised[k]);
+    return ensure_lds_limit(fn[k], k < 2 ? kF32SmemBytes : kB16SmemBytes, g_attend_raised[k]);
 }
 hipError_t init_attend()
 {
-    for (int k = 0; k < 6; ++k) { const hipError_t e = raise_attend_limit(k); if (e != hipSuccess) return e; }
+    for (int k = 0; k < 4; ++k) { const hipError_t e = raise_attend_limit(k); if (e != hipSuccess) return e; }
     return hipSuccess;
 }
 
@@ -818,17 +809,14 @@ hipError_t launch_attend(const Plan& p, const Args& a, const Scratch& w)
     dim3 grid(p.n_split, p.n_qgroup, p.BH);
     if (p.dtype == PSA_F32) {
         // 72 KB of dynamic LDS: above the 64 KB default
-        const bool all_full = a.lengths == nullptr && p.L % kTile == 0;      // every key tile of every head is wholly valid
-        const int which = (p.nq_group == 16 ? 0 : 1) + (all_full ? 2 : 0);
+        const int which = p.nq_group == 16 ? 0 : 1;
         const hipError_t e = raise_attend_limit(which);
         if (e != hipSuccess) return e;
-        if (which == 0)      hipLaunchKernelGGL((attend_f32_kernel<1, false>), grid, dim3(512), kF32SmemBytes, a.stream, P);
-        else if (which == 1) hipLaunchKernelGGL((attend_f32_kernel<2, false>), grid, dim3(512), kF32SmemBytes, a.stream, P);
-        else if (which == 2) hipLaunchKernelGGL((attend_f32_kernel<1, true>), grid, dim3(512), kF32SmemBytes, a.stream, P);
-        else                 hipLaunchKernelGGL((attend_f32_kernel<2, true>), grid, dim3(512), kF32SmemBytes, a.stream, P);
+        if (which == 0) hipLaunchKernelGGL(attend_f32_kernel<1>, grid, dim3(512), kF32SmemBytes, a.stream, P);
+        else            hipLaunchKernelGGL(attend_f32_kernel<2>, grid, dim3(512), kF32SmemBytes, a.stream, P);
     } else {
         const int which = p.nq_group == 32 ? 0 : 1;
-        const hipError_t e = raise_attend_limit(4 + which);
+        const hipError_t e = raise_attend_limit(2 + which);
         if (e != hipSuccess) return e;
         if (which == 0) hipLaunchKernelGGL(attend_bf16_kernel<1>, grid, dim3(512), kB16SmemBytes, a.stream, P);
         else            hipLaunchKernelGGL(attend_bf16_kernel<2>, grid, dim3(512), kB16SmemBytes, a.stream, P);

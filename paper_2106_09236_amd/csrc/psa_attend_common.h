@@ -48,6 +48,15 @@ struct CommonScratch {
     int last;
 };
 
+// A head's list of selected queries: in LDS, or in global memory where it does not fit.  Two pointers of their own
+// address spaces: one pointer that may be either kind makes every read a flat access, which waits for all global
+// loads in flight (the tiles requested ahead) before it returns.
+struct SelList {
+    const __attribute__((address_space(3))) int* lds;
+    const __attribute__((address_space(1))) int* global;           // nullptr: the list is in LDS
+    __device__ __forceinline__ int operator[](int t) const { return global ? global[t] : lds[t]; }
+};
+
 // ---- prologue: I_sparse and the mean of the valid V rows.
 // Two ways, by the shape of the problem (decided on the host):
 //  * candidate lists (short heads measured by the LDS kernel): the measure stage
@@ -60,14 +69,14 @@ struct CommonScratch {
 // `issue_tile` is called once the prologue's own loads are in flight: the caller
 // requests its first K tile there, so that the tile streams in behind them while
 // the selection runs (barriers inside are LDS-only and do not wait for it).
-// Returns the pointer to the head's selected indices (LDS or global) and u.
+// Returns the head's selected indices and u.
 template <int NT, typename CS, typename F>
-__device__ __forceinline__ const int* attend_prologue(const AttendParams& P, int head, int n, int wg_in_head,
+__device__ __forceinline__ SelList attend_prologue(const AttendParams& P, int head, int n, int wg_in_head,
                                                       CS& cs, int& u, F&& issue_tile)
 {
     const int tid = threadIdx.x;
     const int b = head / P.H;
-    const int* selp;
+    SelList selp{(const __attribute__((address_space(3))) int*)cs.sel, nullptr};
     // The last wave sums the per-chunk float64 column sums of V (fixed order).  The
     // first 8 chunks are requested BEFORE the K tile (loads complete in issue order,
     // so anything requested after the tile would wait for all of it).
@@ -117,7 +126,6 @@ __device__ __forceinline__ const int* attend_prologue(const AttendParams& P, int
             for (int t = tid; t < P.u_max; t += NT) P.sel[(size_t)head * P.u_max + t] = cs.sel[t];
             if (tid == 0 && head % P.H == 0) P.ucount[b] = u;
         }
-        selp = cs.sel;
     } else if (P.fused_select) {                 // implies candidate lists (cand_len > 0)
         {
             constexpr int CPT = (CS::kCand + NT - 1) / NT;         // candidates per thread
@@ -239,7 +247,6 @@ __device__ __forceinline__ const int* attend_prologue(const AttendParams& P, int
             for (int t = tid; t < P.u_max; t += NT) P.sel[(size_t)head * P.u_max + t] = cs.sel[t];
             if (tid == 0 && head % P.H == 0) P.ucount[b] = u;
         }
-        selp = cs.sel;
     } else {
         // I_sparse, u and the mean come from the select kernel; the index list is
         // copied to LDS when it fits, so that later reads do not go to memory again
@@ -248,11 +255,11 @@ __device__ __forceinline__ const int* attend_prologue(const AttendParams& P, int
         u = P.ucount[b];
         const float mv = P.mu[(size_t)head * kD + (tid & (kD - 1))];
         issue_tile();
-        selp = gsel;
         if (P.u_max <= CS::kSel) {
             if (tid < P.u_max) cs.sel[tid] = s0v;
             for (int t = tid + NT; t < P.u_max; t += NT) cs.sel[t] = gsel[t];
-            selp = cs.sel;
+        } else {
+            selp.global = (const __attribute__((address_space(1))) int*)gsel;
         }
         if (tid < kD) cs.mean[tid] = mv;
         for (int t = tid; t < 512; t += NT) cs.flag[t] = 0;         // for fill_rows (see above)
@@ -282,7 +289,7 @@ template <> struct OutTraits<bf16_t> {
 // the plain average of the values) or, with VALUE_FILL, its own row of V (Eq. 12
 // as printed); a row at or beyond the length receives zeros.
 template <typename T, int NT, bool VALUE_FILL, typename CS>
-__device__ __forceinline__ void fill_rows_impl(T* out_head, const T* V_head, const int* selp, int u, int n, int L,
+__device__ __forceinline__ void fill_rows_impl(T* out_head, const T* V_head, const SelList& selp, int u, int n, int L,
                                                int r0, int rows, CS& cs)
 {
     using OT = OutTraits<T>;
@@ -327,7 +334,7 @@ __device__ __forceinline__ void fill_rows_impl(T* out_head, const T* V_head, con
     }
 }
 template <typename T, int NT, typename CS>
-__device__ __forceinline__ void fill_rows(const AttendParams& P, T* out_head, const T* V_head, const int* selp,
+__device__ __forceinline__ void fill_rows(const AttendParams& P, T* out_head, const T* V_head, const SelList& selp,
                                           int u, int n, int wg_in_head, CS& cs)
 {
     if (P.fill == PSA_FILL_VALUE)
@@ -358,7 +365,7 @@ __device__ __forceinline__ double rec_exp2(double x) { return exp2_f64(x); }
 // of [16 registers][64 lanes] per 16 queries) instead of [query][64], as float32 values O / l behind
 // the float64 m and l.
 template <typename T, typename R, bool ACC_LAYOUT, int NT, typename CS>
-__device__ __forceinline__ void ticket_and_merge(const AttendParams& P, int head, int n, int u, const int* selp,
+__device__ __forceinline__ void ticket_and_merge(const AttendParams& P, int head, int n, int u, const SelList& selp,
                                                  int nq, CS& cs)
 {
     using OT = OutTraits<T>;

@@ -25,18 +25,19 @@ void exact_measure_f32_kernel(const float* __restrict__ Q, const float* __restri
     const float* Kh = K + (size_t)head * L * kD;
 
     F32Tile tile;
-    tile.load_q(Qh, q, q < n, g);
+    const __amdgpu_buffer_rsrc_t kr = head_rows<256>(Kh, n);
+    tile.load_q(head_rows<256>(Qh, n), q, g);
     // this lane's keys only (4r + g of every 16): running maximum and sum of 2^(t - max)
     // in base 2, and the plain sum of the scores; the four lanes of a query are combined at the end
     double m = -INFINITY, l = 0.0, ssum = 0.0;
     float4 knext[2][4];
-    F32Tile::load_k_into(knext, Kh, 0, n, c, g);
+    F32Tile::load_k_into(knext, kr, 0, c, g);
     for (int j0 = 0; j0 < n; j0 += kTile) {
 #pragma unroll
         for (int sb = 0; sb < 2; ++sb)
 #pragma unroll
             for (int v = 0; v < 4; ++v) tile.kreg[sb][v] = knext[sb][v];
-        F32Tile::load_k_into(knext, Kh, j0 + kTile, n, c, g);          // clamped: in flight during the step
+        F32Tile::load_k_into(knext, kr, j0 + kTile, c, g);             // zeros past the end: in flight during the step
         doublex4 s[2];
         tile.scores(s);
         double t[2][4], tmax = -INFINITY;

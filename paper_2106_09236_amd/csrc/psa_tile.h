@@ -18,6 +18,16 @@ namespace psa {
 
 typedef double doublex4 __attribute__((ext_vector_type(4)));
 
+// A head's valid rows (of RB bytes each) as a raw buffer: a load at or beyond n rows reads zeros.
+template <int RB>
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t head_rows(const void* base, int n) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, n * RB, 0x00020000);
+}
+template <typename V>
+__device__ __forceinline__ V buffer_load16(__amdgpu_buffer_rsrc_t r, int ofs) {
+    return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b128(r, ofs, 0, 0));
+}
+
 // row every clamped load falls back to: the last valid one, or row 0 of an empty item
 __device__ __forceinline__ int last_row(int n) { return n > 0 ? n - 1 : 0; }
 
@@ -59,52 +69,30 @@ struct F32Tile {
 #pragma unroll
         for (int dt = 0; dt < 4; ++dt) oacc[dt] = doublex4{0.0, 0.0, 0.0, 0.0};
     }
-    // query row `qrow` (nullptr-safe through `ok`): lanes c of the tile pass their own row
-    __device__ __forceinline__ void load_q(const float* Qh, int qi, bool ok, int g) {
-        const float* src = Qh + (size_t)(ok ? qi : 0) * kD + 4 * g;
+    // Rows come through a buffer descriptor over the head's valid rows (head_rows), which reads zeros beyond them:
+    // no clamp, no select and, above all, no branch around a load (the compiler made one of every guarded load
+    // and waited for each before the next).  An absent query (qi < 0) is a row beyond the end as well.
+    __device__ __forceinline__ void load_q(__amdgpu_buffer_rsrc_t q, int qi, int g) {
+        const int ofs = qi >= 0 ? qi * 256 + 16 * g : -16;
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-            float4 x = *reinterpret_cast<const float4*>(src + 16 * v);
-            if (!ok) x = make_float4(0.f, 0.f, 0.f, 0.f);
+            const float4 x = buffer_load16<float4>(q, ofs + (qi >= 0 ? 64 * v : 0));
             qreg[4 * v + 0] = (double)x.x; qreg[4 * v + 1] = (double)x.y;
             qreg[4 * v + 2] = (double)x.z; qreg[4 * v + 3] = (double)x.w;
         }
     }
-    // Loads are unconditional on a clamped row (a guarded load would cost a branch
-    // and a wait each); rows at or beyond n are zeroed afterwards.  FULL (the caller
-    // knows, wave-uniformly, that all 32 rows of the tile are valid) drops the clamps,
-    // the zeroing and, in the step, the masks: about a sixth of the step's vector
-    // instructions.  Used by the rows kernel (7 % faster); in the key-split kernel and the
-    // dense baseline the second copy of the step measured slower (20.1 -> 26.8 us, 98.6 ->
-    // 104.4 us), so they keep the masked form alone.
-    template <bool FULL = false>
-    static __device__ __forceinline__ void load_k_into(float4 (&dst)[2][4], const float* Kh, int j0, int n, int c, int g) {
-#pragma unroll
-        for (int sb = 0; sb < 2; ++sb) {
-            const int j = j0 + 16 * sb + c;
-            const bool ok = FULL || j < n;
-            const float* row = Kh + (size_t)(ok ? j : last_row(n)) * kD + 4 * g;
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                float4 x = *reinterpret_cast<const float4*>(row + 16 * v);
-                if (!ok) x = make_float4(0.f, 0.f, 0.f, 0.f);
-                dst[sb][v] = x;
-            }
-        }
-    }
-    __device__ __forceinline__ void load_k(const float* Kh, int j0, int n, int c, int g) { load_k_into(kreg, Kh, j0, n, c, g); }
-    template <bool FULL = false>
-    __device__ __forceinline__ void load_v(const float* Vh, int j0, int n, int c, int g) {
+    static __device__ __forceinline__ void load_k_into(float4 (&dst)[2][4], __amdgpu_buffer_rsrc_t k, int j0, int c, int g) {
 #pragma unroll
         for (int sb = 0; sb < 2; ++sb)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int j = j0 + 16 * sb + 4 * r + g;
-                const bool ok = FULL || j < n;
-                float4 x = *reinterpret_cast<const float4*>(Vh + (size_t)(ok ? j : last_row(n)) * kD + 4 * c);
-                if (!ok) x = make_float4(0.f, 0.f, 0.f, 0.f);
-                vreg[sb][r] = x;
-            }
+            for (int v = 0; v < 4; ++v) dst[sb][v] = buffer_load16<float4>(k, (j0 + 16 * sb + c) * 256 + 16 * g + 64 * v);
+    }
+    __device__ __forceinline__ void load_k(__amdgpu_buffer_rsrc_t k, int j0, int c, int g) { load_k_into(kreg, k, j0, c, g); }
+    __device__ __forceinline__ void load_v(__amdgpu_buffer_rsrc_t v, int j0, int c, int g) {
+#pragma unroll
+        for (int sb = 0; sb < 2; ++sb)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) vreg[sb][r] = buffer_load16<float4>(v, (j0 + 16 * sb + 4 * r + g) * 256 + 16 * c);
     }
     // First product for both 16-key sub-tiles of the K tile in kreg (two independent
     // MFMA chains): s[sb][r] = q . k of key j0 + 16sb + 4r + g, unscaled.
@@ -126,25 +114,30 @@ struct F32Tile {
     // tile.  With V_PRELOADED the caller has already requested the V tile;
     // otherwise it is requested here, once the first product has been issued, so
     // that it arrives under the MFMAs and the softmax.
-    template <bool V_PRELOADED = false, bool FULL = false>
-    __device__ __forceinline__ void step(const float* Vh, int j0, int n, int c, int g) {
+    template <bool V_PRELOADED = false>
+    __device__ __forceinline__ void step(__amdgpu_buffer_rsrc_t vrows, int j0, int n, int c, int g) {
         doublex4 s[2];
         scores(s);
-        if (!V_PRELOADED) load_v<FULL>(Vh, j0, n, c, g);
+        if (!V_PRELOADED) load_v(vrows, j0, c, g);
         // online softmax in base 2 over the 32 keys.  The subtracted constant only
         // has to be the same for every key of a query, so the running max is kept
         // in float32 while the exponent itself is formed in float64.
         double t[2][4];
-        bool ok[2][4];
         float tmax = -INFINITY;
 #pragma unroll
         for (int sb = 0; sb < 2; ++sb)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                ok[sb][r] = FULL || (j0 + 16 * sb + 4 * r + g) < n;
-                t[sb][r] = s[sb][r] * kScaleLog2eD;
-                if (ok[sb][r]) tmax = fmaxf(tmax, (float)t[sb][r]);
-            }
+            for (int r = 0; r < 4; ++r) t[sb][r] = s[sb][r] * kScaleLog2eD;
+        if (j0 + kTile > n) {                                 // wave-uniform: the last keys (2^-inf = 0)
+#pragma unroll
+            for (int sb = 0; sb < 2; ++sb)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) t[sb][r] = (j0 + 16 * sb + 4 * r + g) < n ? t[sb][r] : -INFINITY;
+        }
+#pragma unroll
+        for (int sb = 0; sb < 2; ++sb)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) tmax = fmaxf(tmax, (float)t[sb][r]);
         tmax = fmaxf(tmax, __shfl_xor(tmax, 16, 64));
         tmax = fmaxf(tmax, __shfl_xor(tmax, 32, 64));
         const float m_new = fmaxf(m_run, tmax);               // finite: key j0 is valid
@@ -154,7 +147,7 @@ struct F32Tile {
         for (int sb = 0; sb < 2; ++sb)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                p[sb][r] = ok[sb][r] ? exp2_f64(t[sb][r] - (double)m_new) : 0.0;
+                p[sb][r] = exp2_f64(t[sb][r] - (double)m_new);
                 lsum += p[sb][r];
             }
         l_run = l_run * alpha + lsum;
