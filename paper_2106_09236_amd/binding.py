@@ -1,7 +1,10 @@
-"""Thin ctypes binding over libprobsparse.so (the C ABI in include/probsparse.h).
+"""Thin binding over libprobsparse.so (the C ABI in include/probsparse.h).
 
 Argument marshalling only: every step of the forward runs in the library's HIP
-kernels.  PyTorch is used for device memory and streams.  There is no CPU
+kernels.  PyTorch is used for device memory and streams.  The hot entry points
+go through the extension module _native (csrc/python), which does the same
+marshalling in native code and hands back what it cannot take (None); the ctypes
+functions below it serve everything else and report every error.  There is no CPU
 fallback: if the library has not been built, loading raises.
 """
 from __future__ import annotations
@@ -14,6 +17,7 @@ import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libprobsparse.so")
+NATIVE_PATH = os.path.join(_HERE, "_native.so")
 
 PSA_F32, PSA_BF16 = 0, 1
 STAGE_MEASURE, STAGE_SELECT, STAGE_ATTEND, STAGE_ALL = 1, 2, 4, 7
@@ -53,11 +57,12 @@ class ProbSparseError(RuntimeError):
 
 
 _lib = None
+_native = None          # the extension module, loaded with the library
 
 
 def load() -> ctypes.CDLL:
     """Load the library (once).  Raises FileNotFoundError if it was never built."""
-    global _lib
+    global _lib, _native
     if _lib is not None:
         return _lib
     if not os.path.exists(LIB_PATH):
@@ -123,8 +128,18 @@ def load() -> ctypes.CDLL:
     lib.probsparse_init.argtypes = []
     lib.probsparse_describe_plan.restype = ctypes.c_int
     lib.probsparse_describe_plan.argtypes = [shp, optp, ctypes.c_int32, ctypes.c_char_p, ctypes.c_size_t]
-    _lib = lib
+    if not os.path.exists(NATIVE_PATH):
+        raise FileNotFoundError(f"{NATIVE_PATH} is missing: build it with `python -m paper_2106_09236_amd.build`")
+    from . import _native as native
+    _lib, _native = lib, native
     return lib
+
+
+def _fast():
+    """The extension module."""
+    if _native is None:
+        load()
+    return _native
 
 
 def strerror(code: int) -> str:
@@ -185,6 +200,9 @@ def alloc_workspace(shape: PsaShape, c: float, device="cuda") -> torch.Tensor:
 
 def probsparse_attn_fwd(Q, K, V, lengths, sample_idx, c: float, out=None, workspace=None):
     """out = prob-sparse self-attention of (Q, K, V); see include/probsparse.h."""
+    done = (_native or _fast()).attn_fwd(Q, K, V, lengths, sample_idx, c, out, workspace)
+    if done is not None:
+        return done
     _require_dev(Q, K, V, lengths, sample_idx, out, workspace)
     shape = _shape_of(Q, sample_idx)
     if out is None:
@@ -239,6 +257,10 @@ def probsparse_attn_fwd_opt(Q, K, V, lengths, sample_idx, u_rule: int, factor: f
     """The forward with the rule for u (U_LOG: ceil(factor ln n), U_RATIO: ceil(factor n))
     and the fill (FILL_MEAN, FILL_VALUE) selectable.  Returns (out, M, sel, u) with
     taps, else out."""
+    if not taps:
+        done = (_native or _fast()).attn_fwd_opt(Q, K, V, lengths, sample_idx, u_rule, factor, fill, out, workspace)
+        if done is not None:
+            return done
     _require_dev(Q, K, V, lengths, sample_idx, out, workspace)
     shape = _shape_of(Q, sample_idx)
     opt = PsaOptions(u_rule, fill, factor)
@@ -265,6 +287,9 @@ def probsparse_attn_fwd_opt(Q, K, V, lengths, sample_idx, u_rule: int, factor: f
 
 def probsparse_attn_fwd_with_indices(Q, K, V, lengths, sel, u, fill: int = FILL_MEAN, out=None, workspace=None):
     """Steps a3 + a4 for given index sets: sel [B, H, u_stride] int32, u [B] int32."""
+    done = (_native or _fast()).attn_fwd_with_indices(Q, K, V, lengths, sel, u, fill, out, workspace)
+    if done is not None:
+        return done
     _require_dev(Q, K, V, lengths, sel, u, out, workspace)
     shape = _shape_of(Q, None)
     u_stride = sel.shape[-1]
@@ -284,6 +309,9 @@ def probsparse_attn_fwd_with_indices(Q, K, V, lengths, sel, u, fill: int = FILL_
 
 def probsparse_attn_bwd(Q, K, V, lengths, sel, u, dOut, fill: int = FILL_MEAN, workspace=None):
     """Gradients (dQ, dK, dV) of steps a3 + a4 for the index sets sel [B, H, u_stride], u [B]."""
+    done = (_native or _fast()).attn_bwd(Q, K, V, lengths, sel, u, dOut, fill, workspace)
+    if done is not None:
+        return done
     _require_dev(Q, K, V, lengths, sel, u, dOut, workspace)
     shape = _shape_of(Q, None)
     u_stride = sel.shape[-1]
@@ -346,6 +374,9 @@ def probsparse_out_project(A, weights: PsaMhsaWeights):
 def probsparse_mhsa_fwd(X, weights: PsaMhsaWeights, lengths, sample_idx, u_rule: int, factor: float, fill: int,
                         Y=None, workspace=None):
     """The whole module: projections, prob-sparse attention per head, output matrix."""
+    done = (_native or _fast()).mhsa_fwd(X, weights, lengths, sample_idx, u_rule, factor, fill, Y, workspace)
+    if done is not None:
+        return done
     _require_dev(X, lengths, sample_idx, Y, workspace)
     shape = _mhsa_shape(X, sample_idx.shape[-1])
     opt = PsaOptions(u_rule, fill, factor)
