@@ -114,16 +114,27 @@ bool make_plan(const psa_shape_t* s, URule urule, int u_stride, Plan* p)
 
     const size_t row_bytes = p->dtype == PSA_F32 ? 256 : 128;
     p->measure_lds = !p->given_indices && (size_t)p->L * row_bytes <= (size_t)kLdsMaxBytes;
-    const int mq = p->measure_lds ? kLdsQueries : kMeasureQueries;
+    // LDS measure kernel.  bfloat16 heads whose K fits 64 KB: two work-groups per CU (one copies its K while the
+    // other gathers).  A chunk is 128 queries; where that leaves CUs idle, 64 or 32: the gather is bound by the LDS
+    // rate of a CU and by the instruction stream of a wave (B=1 H=4 L=128 float32: 8.6 us at 128, 4.7 at 32).
+    // At most 8 chunks (lists) per head, and at most 64 KB of K for the smallest work-groups, 16 pieces per thread.
+    const size_t k_bytes = (size_t)p->L * row_bytes;
+    const bool two_per_cu = p->measure_lds && p->dtype == PSA_BF16 && k_bytes <= (size_t)kLdsMaxBytes / 2;
+    const int slots = two_per_cu ? 512 : 256;
+    p->measure_queries = p->measure_lds ? kLdsQueries : kMeasureQueries;
+    if (p->measure_lds) {
+        if (two_per_cu) p->measure_lds = 2;
+        for (int q = kLdsQueries / 2; q >= 32; q >>= 1) {
+            const int chunks = (p->L + q - 1) / q;
+            if (chunks > 8 || (int64_t)p->BH * chunks > slots || (q == 32 && k_bytes > (size_t)64 * 1024)) break;
+            p->measure_queries = q;
+        }
+    }
+    const int mq = p->measure_queries;
     p->n_chunk = (p->L + mq - 1) / mq;
-    // LDS measure kernel (one work-group per CU): once the heads alone would fill the
-    // 256 CUs, a work-group takes several chunks of its head and loads the head's K once
+    // once the heads alone would fill the CUs, a work-group takes several chunks of its head and loads the head's K once
     p->chunks_per_wg = 1;
     if (p->measure_lds) {
-        // bfloat16 heads whose K fits 64 KB: two work-groups per CU (one copies its K while the other gathers)
-        const bool two_per_cu = p->dtype == PSA_BF16 && (size_t)p->L * row_bytes <= (size_t)kLdsMaxBytes / 2;
-        if (two_per_cu) p->measure_lds = 2;
-        const int slots = two_per_cu ? 512 : 256;
         while (p->chunks_per_wg < p->n_chunk &&
                (int64_t)p->BH * ((p->n_chunk + p->chunks_per_wg - 1) / p->chunks_per_wg) > slots) ++p->chunks_per_wg;
     }
@@ -137,7 +148,7 @@ bool make_plan(const psa_shape_t* s, URule urule, int u_stride, Plan* p)
     // sorted per-chunk candidate lists: only with the LDS measure kernel (few chunks per head)
     p->cand_len = 0;
     if (p->measure_lds) {
-        const int len = p->u_max < kLdsQueries ? p->u_max : kLdsQueries;
+        const int len = p->u_max < mq ? p->u_max : mq;
         if (p->n_chunk * len <= kMaxCandidates) p->cand_len = len;
     }
     p->n_lists = p->n_chunk;

@@ -780,18 +780,20 @@ __device__ __forceinline__ int quad_bcast(int x) {
 // query in a 16-wave work-group, with the index passed by an LDS lane shuffle,
 // measured 4..9 % slower.)
 // -----------------------------------------------------------------------------
-constexpr int kQuadThreads = 512;
-constexpr int kQuadQueriesPerWave = 16;
-static_assert(kLdsQueries == (kQuadThreads / 64) * kQuadQueriesPerWave, "one query per 4 lanes, 8 waves");
+// NQ: queries per chunk (the plan's measure_queries).  128: one per 4 lanes, 8 waves.  64 or 32, where the heads are
+// few and short, leaves a SIMD with one wave, and a wave's own instruction stream is what takes the time: then a query
+// has EIGHT lanes, two quads that take the sample rounds in turn and hand each other the scores, which are still added
+// in the order of the samples; and the rows are requested one round before they are multiplied.
+// KCOPY: 16-byte pieces of K per thread.  128 queries and 8 pieces (64 KB): two work-groups fit a CU; for bfloat16
+// rows the registers are capped to let them (4 waves per SIMD), so that one work-group copies its K while the other
+// gathers.
+// B=1 H=4 L=128 float32: 8.6 us with one work-group of 128 queries per head, 4.7 with four of 32.
+template <int NQ> constexpr int kQuadLanes = NQ < kLdsQueries ? 8 : 4;          // lanes per query
+template <int NQ> constexpr int kQuadThreads = NQ * kQuadLanes<NQ>;
 
-
-// KCOPY: 16-byte pieces of K per thread = LDS bytes / 8 KB: 16 (a head of up to 128 KB) or 8 (up
-// to 64 KB).  With 64 KB two work-groups fit a CU; for bfloat16 rows the registers are capped to
-// let them (4 waves per SIMD), so that one work-group copies its K while
-// the other gathers.
-// The work of one work-group: chunks [chunk0, chunk0 + chunks_per_wg) of `head`.  sK: KCOPY * 8 KB of LDS for
-// the head's K; s_red, s_key: the work-group's reduction scratch.
-template <typename T, int KCOPY>
+// The work of one work-group: chunks [chunk0, chunk0 + chunks_per_wg) of `head`.  sK: LDS for the head's K;
+// s_red, s_key: the work-group's reduction scratch.
+template <typename T, int KCOPY, int NQ>
 __device__ __forceinline__ void measure_quad_body(const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V,
                                                   const int* __restrict__ lengths, const int* __restrict__ idx,
                                                   float* __restrict__ M, double* __restrict__ vpart,
@@ -803,7 +805,9 @@ __device__ __forceinline__ void measure_quad_body(const T* __restrict__ Q, const
     using RT = RowTraits<T>;
     using Vec = typename std::conditional<sizeof(T) == 4, float4, uint4>::type;
     constexpr int NP = RT::kRowBytes / 64;               // 16-byte pieces per lane and row: 4 (f32) or 2 (bf16)
-    static_assert(KCOPY * 16 * kQuadThreads <= kLdsMaxBytes, "at most 128 KB of K");
+    constexpr int kThreads = kQuadThreads<NQ>;
+    constexpr int LPQ = kQuadLanes<NQ>, HALVES = LPQ / 4;
+    static_assert(KCOPY * 16 * kThreads <= kLdsMaxBytes, "at most 128 KB of K");
     auto put_v = [](double* p, double v) { *p = v; };
     auto put_c = [](uint2* p, unsigned key, unsigned q) { *p = make_uint2(key, q); };
 
@@ -815,18 +819,20 @@ __device__ __forceinline__ void measure_quad_body(const T* __restrict__ Q, const
     const int lane = tid & 63, wave = tid >> 6;
     const int s = lane & 3;
     const int qrot = (lane >> 2) & (RT::kRowBytes / 64 - 1);           // the quad's rotation of the piece order
-    const int ql = wave * kQuadQueriesPerWave + (lane >> 2);            // query within a chunk
+    const int half = HALVES == 2 ? (lane >> 2) & 1 : 0;                 // which of a query's quads
+    const bool first = (lane & (LPQ - 1)) == 0;                         // the query's first lane
+    const int ql = tid / LPQ;                                           // query within a chunk
     // s_key: (order key, ~query) of a chunk's measures: one 64-bit compare ranks
 
     // chunks that are padding as a whole (all of them, once one is: chunks ascend)
-    const int first_pad = (n + kLdsQueries - 1) / kLdsQueries;          // first chunk with no valid query
+    const int first_pad = (n + NQ - 1) / NQ;          // first chunk with no valid query
     for (int chunk = (chunk0 > first_pad ? chunk0 : first_pad); chunk < chunk_end; ++chunk) {
-        const int i = chunk * kLdsQueries + ql;
-        if (i < L && s == 0) M[(size_t)head * L + i] = 0.f;
+        const int i = chunk * NQ + ql;
+        if (i < L && first) M[(size_t)head * L + i] = 0.f;
         if (tid < kD) put_v(vpart + ((size_t)head * chunks_per_head + chunk) * kD + tid, 0.0);
         if (cand) {
             uint2* co = cand + ((size_t)head * chunks_per_head + chunk) * cand_len;
-            for (int t = tid; t < cand_len; t += kQuadThreads) put_c(co + t, 0u, 0xFFFFFFFFu);
+            for (int t = tid; t < cand_len; t += kThreads) put_c(co + t, 0u, 0xFFFFFFFFu);
         }
     }
     chunk_end = chunk_end < first_pad ? chunk_end : first_pad;
@@ -842,27 +848,27 @@ __device__ __forceinline__ void measure_quad_body(const T* __restrict__ Q, const
     // clamped addresses, before anything uses them: a load inside a branch (or
     // sunk into one by the compiler) costs a full round trip of its own.
     //   q pieces and first sample indices of this lane's query (lane s of a quad
-    //   holds samples 4k + s), this chunk's V rows for the column sums;
-    // before the first chunk also K[0 .. n) of the head (16 bytes per thread, 16 in
-    // flight; rows >= n are never read).  The loads of the next chunk are issued
-    // before the current one is worked on.
-    constexpr int VLPR = RT::kRowBytes / 16, VEPL = kD / VLPR, VRPP = kQuadThreads / VLPR, VN = kLdsQueries / VRPP;
-    constexpr int KPRE = 10;                              // sample rounds fetched up front (U <= 40)
-    const int n_r = (U + 3) >> 2;
+    //   holds samples 4 r + s of the quad's rounds r), this chunk's V rows for the column sums;
+    // before the first chunk also K[0 .. n) of the head (16 bytes per thread and piece; rows >= n are never read).
+    // The loads of the next chunk are issued before the current one is worked on.
+    constexpr int VLPR = RT::kRowBytes / 16, VEPL = kD / VLPR, VRPP = kThreads / VLPR, VN = NQ / VRPP;
+    constexpr int KPRE = 10 / HALVES;                     // sample rounds per quad fetched up front (U <= 40)
+    const int n_r = (U + 4 * HALVES - 1) / (4 * HALVES);  // rounds per quad
+    auto sample_of = [&](int k) { return 4 * (HALVES * k + half) + s; };
     const int vsub = tid % VLPR, vrow = tid / VLPR;
     struct ChunkLoads { Vec q[NP]; int jraw[KPRE]; Vec vbuf[VN]; };
     auto issue = [&](int chunk, ChunkLoads& c) {
-        const int i = chunk * kLdsQueries + ql;
+        const int i = chunk * NQ + ql;
         const int ic = i < n ? i : 0;                     // n > 0 here
 #pragma unroll
         for (int v = 0; v < NP; ++v)
             c.q[v] = *reinterpret_cast<const Vec*>(Qb + (size_t)ic * RT::kRowBytes + piece_ofs(v));
         const int* irow = idx + ((size_t)head * L + (i < L ? i : 0)) * U;
 #pragma unroll
-        for (int k = 0; k < KPRE; ++k) { const int t = 4 * k + s; c.jraw[k] = irow[t < U ? t : U - 1]; }
+        for (int k = 0; k < KPRE; ++k) { const int t = sample_of(k); c.jraw[k] = irow[t < U ? t : U - 1]; }
 #pragma unroll
         for (int k = 0; k < VN; ++k) {
-            const int j = chunk * kLdsQueries + vrow + k * VRPP;
+            const int j = chunk * NQ + vrow + k * VRPP;
             c.vbuf[k] = reinterpret_cast<const Vec*>(Vh + (size_t)(j < n ? j : n - 1) * kD)[vsub];
         }
     };
@@ -875,17 +881,17 @@ __device__ __forceinline__ void measure_quad_body(const T* __restrict__ Q, const
         uint4 buf[KCOPY];
 #pragma unroll
         for (int k = 0; k < KCOPY; ++k) {
-            const int ci = k * kQuadThreads + tid;
+            const int ci = k * kThreads + tid;
             buf[k] = reinterpret_cast<const uint4*>(Kb)[ci < n_chunks16 ? ci : n_chunks16 - 1];
         }
         PSA_TS(1);
-        // ---- K -> LDS (the LDS area spans KCOPY * 8 KB, so the store needs no guard)
+        // ---- K -> LDS (the LDS area spans KCOPY pieces of every thread, so the store needs no guard)
 #pragma unroll
-        for (int k = 0; k < KCOPY; ++k) reinterpret_cast<uint4*>(sK)[k * kQuadThreads + tid] = buf[k];
+        for (int k = 0; k < KCOPY; ++k) reinterpret_cast<uint4*>(sK)[k * kThreads + tid] = buf[k];
     }
 
     for (int chunk = chunk0; chunk < chunk_end; ++chunk) {
-        const int i = chunk * kLdsQueries + ql;
+        const int i = chunk * NQ + ql;
         const bool in_tensor = i < L;
         const bool active = i < n;
         const int* irow = idx + ((size_t)head * L + (in_tensor ? i : 0)) * U;
@@ -898,7 +904,7 @@ __device__ __forceinline__ void measure_quad_body(const T* __restrict__ Q, const
             for (int e = 0; e < VEPL; ++e) acc[e] = 0.0;
 #pragma unroll
             for (int k = 0; k < VN; ++k) {
-                const bool vok = chunk * kLdsQueries + vrow + k * VRPP < n;
+                const bool vok = chunk * NQ + vrow + k * VRPP < n;
                 if constexpr (sizeof(T) == 4) {
                     const float4 v = cur.vbuf[k];
                     acc[0] += vok ? (double)v.x : 0.0; acc[1] += vok ? (double)v.y : 0.0;
@@ -934,7 +940,7 @@ __device__ __forceinline__ void measure_quad_body(const T* __restrict__ Q, const
         if (tid < kD) {
             double t = 0.0;
 #pragma unroll
-            for (int w = 0; w < kQuadThreads / 64; ++w) t += s_red[w][tid];           // fixed order
+            for (int w = 0; w < kThreads / 64; ++w) t += s_red[w][tid];           // fixed order
             put_v(vpart + ((size_t)head * chunks_per_head + chunk) * kD + tid, t);
         }
 
@@ -956,66 +962,96 @@ __device__ __forceinline__ void measure_quad_body(const T* __restrict__ Q, const
             }
             return d;
         };
-        // one round of 4 samples: jv is sample 4k + s of this lane's query, -1 if none
-        auto gather_round = [&](int jv) {
-            const int j[4] = {quad_bcast<0>(jv), quad_bcast<1>(jv), quad_bcast<2>(jv), quad_bcast<3>(jv)};
-            if (__ballot((unsigned)jv >= (unsigned)n) == 0ull) {
+        // One round of 4 samples per quad; jv: this lane's sample, -1 if none.  CLAMP: jv may lie outside [0, n).
+        struct Round { int jv; Vec kr[4][NP]; };
+        auto request = [&](int jv, Round& r, auto clamp) {
+            r.jv = jv;
+            const int jc = !clamp.value || (unsigned)jv < (unsigned)n ? jv : 0;
+            const int j[4] = {quad_bcast<0>(jc), quad_bcast<1>(jc), quad_bcast<2>(jc), quad_bcast<3>(jc)};
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+#pragma unroll
+                for (int v = 0; v < NP; ++v)
+                    r.kr[t][v] = *reinterpret_cast<const Vec*>(sK + (uint32_t)j[t] * RT::kRowBytes + piece_ofs(v));
+        };
+        // the quad's four scores of a round.  With two quads per query their rounds follow one another: the first quad
+        // adds its own four and then the other's (what the second quad's sums hold is not used)
+        auto reduce = [&](const Round& r, bool whole) {
+            float d[4];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) d[t] = row_dot(r.kr[t]);
+            // sums over the quad, one exchange stage at a time for all rows; the 1/sqrt(64) is
+            // applied once at the end (exact: a power of 2)
+#pragma unroll
+            for (int t = 0; t < 4; ++t) d[t] += dpp_mov<0xB1>(d[t]);
+#pragma unroll
+            for (int t = 0; t < 4; ++t) d[t] += dpp_mov<0x4E>(d[t]);
+            float e[4];
+            if constexpr (HALVES == 2)
+#pragma unroll
+                for (int t = 0; t < 4; ++t) e[t] = dpp_mov<0x141>(d[t]);                 // the other quad's
+            if (whole) {
                 // every sample of this round is usable in every query of the wave
-                Vec kr[4][NP];
-#pragma unroll
-                for (int t = 0; t < 4; ++t)
-#pragma unroll
-                    for (int v = 0; v < NP; ++v)
-                        kr[t][v] = *reinterpret_cast<const Vec*>(sK + (uint32_t)j[t] * RT::kRowBytes + piece_ofs(v));
-                float d[4];
-#pragma unroll
-                for (int t = 0; t < 4; ++t) d[t] = row_dot(kr[t]);
-                // sums over the quad, one exchange stage at a time for all rows; the 1/sqrt(64) is
-                // applied once at the end (exact: a power of 2)
-#pragma unroll
-                for (int t = 0; t < 4; ++t) d[t] += dpp_mov<0xB1>(d[t]);
-#pragma unroll
-                for (int t = 0; t < 4; ++t) d[t] += dpp_mov<0x4E>(d[t]);
 #pragma unroll
                 for (int t = 0; t < 4; ++t) { mx = fmaxf(mx, d[t]); sm += d[t]; }
-                cnt += 4;
+                if constexpr (HALVES == 2)
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) { mx = fmaxf(mx, e[t]); sm += e[t]; }
+                cnt += LPQ;
             } else {
                 // padded queries, the tail of U, or indices outside [0, n): drop those samples
-#pragma unroll
-                for (int t = 0; t < 4; ++t) {
-                    const bool ok = (unsigned)j[t] < (unsigned)n;
-                    Vec kr[NP];
-#pragma unroll
-                    for (int v = 0; v < NP; ++v)
-                        kr[v] = *reinterpret_cast<const Vec*>(sK + (uint32_t)(ok ? j[t] : 0) * RT::kRowBytes + piece_ofs(v));
-                    const float sc = quad_sum(row_dot(kr));
+                const int raw[4] = {quad_bcast<0>(r.jv), quad_bcast<1>(r.jv), quad_bcast<2>(r.jv), quad_bcast<3>(r.jv)};
+                auto take = [&](int j, float sc) {
+                    const bool ok = (unsigned)j < (unsigned)n;
                     mx = ok ? fmaxf(mx, sc) : mx;
                     sm += ok ? sc : 0.f;
                     cnt += ok ? 1 : 0;
-                }
+                };
+#pragma unroll
+                for (int t = 0; t < 4; ++t) take(raw[t], d[t]);
+                if constexpr (HALVES == 2)
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) take(__builtin_amdgcn_update_dpp(0, raw[t], 0x141, 0xF, 0xF, false), e[t]);
             }
         };
-        // Rounds whose indices came with the chunk's other loads (no global load in this loop: the
+        auto all_usable = [&](int jv) { return __ballot((unsigned)jv >= (unsigned)n) == 0ull; };      // wave-uniform
+        auto gather_round = [&](int jv) {
+            Round r;
+            if (all_usable(jv)) { request(jv, r, std::false_type{}); reduce(r, true); }
+            else                { request(jv, r, std::true_type{});  reduce(r, false); }
+        };
+        // Rounds whose indices came with the chunk's other loads (no global load here: the
         // wait for it would also wait for the next chunk's loads, which are in flight on purpose).
         const int n_pre = n_r < KPRE ? n_r : KPRE;
-#pragma unroll 1
-        for (int k = 0; k < n_pre; ++k) {
-            int raw = jraw[KPRE - 1];
+        auto sample = [&](int k, int raw) { return active && sample_of(k) < U ? raw : -1; };
+        if constexpr (HALVES == 2) {
+            Round r[2];
+            request(sample(0, jraw[0]), r[0], std::true_type{});
 #pragma unroll
-            for (int kk = 0; kk < KPRE - 1; ++kk) raw = (k == kk) ? jraw[kk] : raw;
-            gather_round((active && 4 * k + s < U) ? raw : -1);
+            for (int k = 0; k < KPRE; ++k)
+                if (k < n_pre) {                          // wave-uniform
+                    if (k + 1 < KPRE) request(sample(k + 1, jraw[k + 1 < KPRE ? k + 1 : 0]), r[(k + 1) & 1], std::true_type{});
+                    reduce(r[k & 1], all_usable(r[k & 1].jv));
+                }
+        } else {
+#pragma unroll 1
+            for (int k = 0; k < n_pre; ++k) {
+                int raw = jraw[KPRE - 1];
+#pragma unroll
+                for (int kk = 0; kk < KPRE - 1; ++kk) raw = (k == kk) ? jraw[kk] : raw;
+                gather_round(sample(k, raw));
+            }
         }
         // only for U > 40: the remaining rounds, their indices fetched here
 #pragma unroll 1
         for (int k = KPRE; k < n_r; ++k) {
-            const int t = 4 * k + s;
-            const int raw = irow[t < U ? t : U - 1];
-            gather_round((active && t < U) ? raw : -1);
+            const int t = sample_of(k);
+            gather_round(sample(k, irow[t < U ? t : U - 1]));
         }
         PSA_TS(4);
         float m = 0.f;
         if (active && cnt > 0) m = (mx - sm / (float)cnt) * 0.125f;         // 1/sqrt(64), exact
-        if (in_tensor && s == 0) M[(size_t)head * L + i] = m;
+        if (in_tensor && first) M[(size_t)head * L + i] = m;
 
         // ---- local ranking for stage a2.  Any query among the head's u largest is
         // among its own chunk's u largest, so each chunk hands on only its first
@@ -1026,7 +1062,7 @@ __device__ __forceinline__ void measure_quad_body(const T* __restrict__ Q, const
             float f = m + 0.0f;                                         // -0 -> +0
             const unsigned ub = __float_as_uint(f);
             const unsigned key = active ? ((ub & 0x80000000u) ? ~ub : (ub | 0x80000000u)) : 0u;   // 0 = not a candidate
-            if (s == 0) s_key[ql] = ((unsigned long long)key << 32) | (unsigned)~ql;      // equal keys: the lower query is larger
+            if (first) s_key[ql] = ((unsigned long long)key << 32) | (unsigned)~ql;      // equal keys: the lower query is larger
         }
         PSA_TS(5);
         lds_barrier();                       // also: every wave is done with s_red before the next chunk writes it
@@ -1036,14 +1072,15 @@ __device__ __forceinline__ void measure_quad_body(const T* __restrict__ Q, const
             const unsigned mine = (unsigned)(mine64 >> 32);
             int beat = 0;                                               // chunk-mates that come before this query
 #pragma unroll
-            for (int t = 0; t < kLdsQueries / 4; ++t)
-                beat += s_key[4 * t + s] > mine64 ? 1 : 0;              // (adjacent words for the quad's lanes: no bank conflict)
+            for (int t = 0; t < NQ / LPQ; ++t)
+                beat += s_key[LPQ * t + (lane & (LPQ - 1))] > mine64 ? 1 : 0;           // (adjacent words: no bank conflict)
             beat += __builtin_amdgcn_update_dpp(0, beat, 0xB1, 0xF, 0xF, false);     // sum over the quad
             beat += __builtin_amdgcn_update_dpp(0, beat, 0x4E, 0xF, 0xF, false);
-            if (s == 0 && mine != 0u && beat < cand_len) put_c(cand_out + beat, mine, (unsigned)i);
+            if constexpr (HALVES == 2) beat += __builtin_amdgcn_update_dpp(0, beat, 0x141, 0xF, 0xF, false);
+            if (first && mine != 0u && beat < cand_len) put_c(cand_out + beat, mine, (unsigned)i);
             // slots beyond the chunk's valid queries are marked empty
-            const int n_here = n - chunk * kLdsQueries < kLdsQueries ? n - chunk * kLdsQueries : kLdsQueries;
-            for (int t = n_here + tid; t < cand_len; t += kQuadThreads) put_c(cand_out + t, 0u, 0xFFFFFFFFu);
+            const int n_here = n - chunk * NQ < NQ ? n - chunk * NQ : NQ;
+            for (int t = n_here + tid; t < cand_len; t += kThreads) put_c(cand_out + t, 0u, 0xFFFFFFFFu);
         }
         cur = nxt;
         // the ranking reads s_key; the next chunk writes it only after its own first barrier
@@ -1051,9 +1088,8 @@ __device__ __forceinline__ void measure_quad_body(const T* __restrict__ Q, const
     PSA_TS(7);
 }
 
-// KCOPY: 16-byte pieces of K per thread = LDS bytes / 8 KB (see measure_quad_body).
-template <typename T, int KCOPY>
-__global__ __launch_bounds__(kQuadThreads, (KCOPY == 8 && sizeof(T) == 2) ? 4 : 2)
+template <typename T, int KCOPY, int NQ>
+__global__ __launch_bounds__(kQuadThreads<NQ>, (NQ == kLdsQueries && KCOPY == 8 && sizeof(T) == 2) ? 4 : 2)
 void measure_quad_kernel(const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V,
                          const int* __restrict__ lengths, const int* __restrict__ idx,
                          float* __restrict__ M, double* __restrict__ vpart, int* __restrict__ ticket,
@@ -1061,8 +1097,8 @@ void measure_quad_kernel(const T* __restrict__ Q, const T* __restrict__ K, const
                          int H, int L, int U, int chunks_per_head, int chunks_per_wg, int n_heads)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char sK[];    // [n][row bytes]
-    __shared__ double s_red[kQuadThreads / 64][kD];
-    __shared__ unsigned long long s_key[kLdsQueries];
+    __shared__ double s_red[kQuadThreads<NQ> / 64][kD];
+    __shared__ unsigned long long s_key[NQ];
     // A work-group takes chunks_per_wg consecutive chunks of one head (the head's K
     // goes to LDS once for all of them); all work-groups of a head sit on one XCD.
     const int groups_per_head = (chunks_per_head + chunks_per_wg - 1) / chunks_per_wg;
@@ -1071,16 +1107,17 @@ void measure_quad_kernel(const T* __restrict__ Q, const T* __restrict__ K, const
     const int chunk0 = (slot % groups_per_head) * chunks_per_wg;
     if (head >= n_heads) return;
     if (chunk0 == 0 && threadIdx.x == 0) ticket[head] = 0;        // the attend stage counts work-groups per head
-    measure_quad_body<T, KCOPY>(Q, K, V, lengths, idx, M, vpart, cand, cand_len, H, L, U, chunks_per_head,
+    measure_quad_body<T, KCOPY, NQ>(Q, K, V, lengths, idx, M, vpart, cand, cand_len, H, L, U, chunks_per_head,
                                        chunks_per_wg, head, chunk0, sK, s_red, s_key);
 }
 
-// The LDS measure kernel with 128 KB of K is above the default 64 KB of dynamic LDS.
+// Heads of more than 64 KB need the limit of dynamic LDS raised.
 template <typename T>
 static hipError_t raise_measure_limit()
 {
-    static std::atomic<uint64_t> raised;               // per instantiation: devices already served
-    return ensure_lds_limit((const void*)measure_quad_kernel<T, 16>, kLdsMaxBytes, raised);
+    static std::atomic<uint64_t> raised[2];            // per instantiation: devices already served
+    const hipError_t e = ensure_lds_limit((const void*)measure_quad_kernel<T, 16, 128>, kLdsMaxBytes, raised[0]);
+    return e != hipSuccess ? e : ensure_lds_limit((const void*)measure_quad_kernel<T, 16, 64>, kLdsMaxBytes, raised[1]);
 }
 
 
@@ -1105,21 +1142,27 @@ static hipError_t launch_measure_t(const Plan& p, const Args& a, const Scratch& 
 {
     const int head_rounds = (p.BH + 7) / 8;
     if (p.measure_lds) {
-        const int chunks = p.n_chunk;                      // ceil(L / 128)
+        const int chunks = p.n_chunk;                      // ceil(L / queries per chunk)
         const int groups = (chunks + p.chunks_per_wg - 1) / p.chunks_per_wg;
-        dim3 grid((unsigned)(head_rounds * groups * 8)), block(kQuadThreads);
+        const dim3 grid((unsigned)(head_rounds * groups * 8));
         uint2* cand = p.cand_len > 0 ? w.cand : nullptr;
-        if (p.measure_lds == 2) {                         // K of a head within 64 KB: two work-groups per CU
-            hipLaunchKernelGGL((measure_quad_kernel<T, 8>), grid, block, kLdsMaxBytes / 2, a.stream,
-                               (const T*)a.Q, (const T*)a.K, (const T*)a.V, a.lengths, a.idx, w.M, w.vpart, w.ticket,
-                               cand, p.cand_len, p.H, p.L, p.U, chunks, p.chunks_per_wg, p.BH);
-            return hipGetLastError();
-        }
         const hipError_t e = raise_measure_limit<T>();
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL((measure_quad_kernel<T, 16>), grid, block, kLdsMaxBytes, a.stream,
-                           (const T*)a.Q, (const T*)a.K, (const T*)a.V, a.lengths, a.idx, w.M, w.vpart, w.ticket,
-                           cand, p.cand_len, p.H, p.L, p.U, chunks, p.chunks_per_wg, p.BH);
+#define PSA_QUAD(KCOPY, NQ)                                                                                            \
+        hipLaunchKernelGGL((measure_quad_kernel<T, KCOPY, NQ>), grid, dim3(kQuadThreads<NQ>), KCOPY * 16 * kQuadThreads<NQ>, \
+                           a.stream, (const T*)a.Q, (const T*)a.K, (const T*)a.V, a.lengths, a.idx, w.M, w.vpart, w.ticket, \
+                           cand, p.cand_len, p.H, p.L, p.U, chunks, p.chunks_per_wg, p.BH)
+        // 8 or 16 pieces of K per thread, whichever cover the head
+        const int threads = p.measure_queries * (p.measure_queries < kLdsQueries ? 8 : 4);
+        const bool half = p.L * RowTraits<T>::kRowBytes <= 8 * 16 * threads;
+        if (p.measure_queries == 32) {
+            if (half) PSA_QUAD(8, 32); else PSA_QUAD(16, 32);
+        } else if (p.measure_queries == 64) {
+            if (half) PSA_QUAD(8, 64); else PSA_QUAD(16, 64);
+        } else {
+            if (half) PSA_QUAD(8, 128); else PSA_QUAD(16, 128);
+        }
+#undef PSA_QUAD
         return hipGetLastError();
     }
     const int chunks = p.n_chunk;                          // ceil(L / 64)
