@@ -37,6 +37,43 @@ static bool good_rule(URule r)
     return (r.rule == PSA_U_LOG || r.rule == PSA_U_RATIO) && r.factor > 0.0 && isfinite(r.factor);
 }
 
+// float32 tensors: queries per group and key splits of the key-split attend kernel, by the time of its rounds of
+// work-groups (one per CU).  In microseconds, fitted to sweeps of both over 15 shapes: 5.5 to start a work-group and
+// pick the selection, 2.3 for each tile step of a SIMD (64 float64 MFMAs), and for a split the hand-over of records:
+// 3 and 1.5 for each trip of the last work-group's merge (32 queries x 4 splits), or the merge kernel.  A last round
+// of work-groups that is not full counts half: heads are often shorter than L.
+// Against groups of 32 and 512 work-groups for every shape: B=24 H=4 L=750 ragged 87 -> 75 us, B=16 H=4 L=1000
+// 83 -> 63, B=64 H=4 L=200 52 -> 36, B=1 H=4 L=333 26.0 -> 23.8 us.
+static void split_f32(Plan* p, int n_tiles)
+{
+    float best = INFINITY;
+    for (int ncg = 2; ncg >= 1; --ncg) {                      // (of equals the larger groups: they read K and V less often)
+        const int nq = 16 * ncg, tiles_wg = 8 / ncg;
+        const int n_qgroup = (p->u_max + nq - 1) / nq;
+        const int64_t per_split = (int64_t)p->BH * n_qgroup;
+        int max_split = (n_tiles + tiles_wg - 1) / tiles_wg;
+        if (max_split > kMaxSplit) max_split = kMaxSplit;
+        // 1 .. 8 splits, or as many as give each CU a work-group
+        const int fill = per_split < 256 ? (int)(256 / per_split) : 1;
+        for (int k = 1; k <= kTicketMaxSplit + 1; ++k) {
+            int split = k <= kTicketMaxSplit ? k : fill;
+            if (split > max_split) split = max_split;
+            const int rounds = (n_tiles + split * tiles_wg - 1) / (split * tiles_wg);
+            split = (n_tiles + rounds * tiles_wg - 1) / (rounds * tiles_wg);
+            const int tiles = n_tiles < rounds * tiles_wg ? n_tiles : rounds * tiles_wg;
+            const int steps = (tiles * ncg + 3) / 4;
+            const float fills = (float)(per_split * split) / 256.f;
+            const float cost = (fills <= 1.f ? 1.f : 0.5f * (fills + ceilf(fills))) * (5.5f + 2.3f * (float)steps) +
+                (split == 1 ? 0.f : split > kTicketMaxSplit ? 6.f : 3.f + 1.5f * (float)((p->u_max + 31) / 32 * ((split + 3) / 4)));
+            if (cost < best) {
+                best = cost;
+                p->nq_group = nq; p->n_qgroup = n_qgroup; p->n_split = split; p->tiles_per_wave = rounds;
+            }
+            if (k >= max_split) break;
+        }
+    }
+}
+
 bool make_plan(const psa_shape_t* s, URule urule, int u_stride, Plan* p)
 {
     if (check_shape(s) != PSA_OK) return false;
@@ -46,32 +83,28 @@ bool make_plan(const psa_shape_t* s, URule urule, int u_stride, Plan* p)
     p->B = s->B; p->H = s->H; p->L = s->L_K; p->U = s->U; p->dtype = s->dtype;
     p->BH = s->B * s->H;
     p->u_max = p->given_indices ? u_stride : u_max_of(urule, p->L);
-    // float32 tensors run on 16-wide float64 MFMA tiles (<= 2 per work-group),
-    // bfloat16 tensors on 32-wide tiles (<= 2 per work-group)
-    // (with very few heads, two groups of 16 queries give twice the work-groups)
-    if (p->dtype == PSA_F32) p->nq_group = (p->u_max > 16 && (int64_t)p->BH * ((p->L + 127) / 128) >= 64) ? 32 : 16;
-    else                     p->nq_group = p->u_max > 32 ? 64 : 32;
-    p->n_qgroup = (p->u_max + p->nq_group - 1) / p->nq_group;
-
-    // key splits: enough work-groups to cover the 256 CUs twice (float32) or once
-    // (bfloat16, whose work-groups take a CU each).  One round of an attend
-    // work-group walks `tiles_wg` tiles of 32 keys: 8 (one per wave) for bfloat16;
-    // 8 or 4 for float32 (8 waves over 1 or 2 column tiles).
-    const int tiles_wg = p->dtype == PSA_F32 ? (p->nq_group == 16 ? 8 : 4) : 8;
+    // A work-group covers the selected queries in groups of 16 or 32 (float32: float64 MFMA tiles of 16) or 32 or
+    // 64 (bfloat16: tiles of 32) and walks its keys in rounds of `tiles_wg` tiles of 32.
     const int n_tiles = (p->L + kTile - 1) / kTile;
-    const int max_split = (n_tiles + tiles_wg - 1) / tiles_wg;
-    const int wg_goal = p->dtype == PSA_F32 ? 512 : 256;     // bfloat16: one 8-wave work-group per CU
-    int target = (wg_goal + p->BH * p->n_qgroup - 1) / (p->BH * p->n_qgroup);
-    if (target < 1) target = 1;
-    int n_split = target < max_split ? target : max_split;
-    if (n_split > kMaxSplit) n_split = kMaxSplit;
-    p->tiles_per_wave = (n_tiles + n_split * tiles_wg - 1) / (n_split * tiles_wg);      // rounds
-    p->n_split = (n_tiles + p->tiles_per_wave * tiles_wg - 1) / (p->tiles_per_wave * tiles_wg);
+    if (p->dtype == PSA_F32) {
+        split_f32(p, n_tiles);
+    } else {
+        // key splits: enough work-groups to cover the 256 CUs once (a work-group takes a CU)
+        p->nq_group = p->u_max > 32 ? 64 : 32;
+        p->n_qgroup = (p->u_max + p->nq_group - 1) / p->nq_group;
+        const int max_split = (n_tiles + 7) / 8;
+        int target = (256 + p->BH * p->n_qgroup - 1) / (p->BH * p->n_qgroup);
+        if (target < 1) target = 1;
+        int n_split = target < max_split ? target : max_split;
+        if (n_split > kMaxSplit) n_split = kMaxSplit;
+        p->tiles_per_wave = (n_tiles + n_split * 8 - 1) / (n_split * 8);      // rounds
+        p->n_split = (n_tiles + p->tiles_per_wave * 8 - 1) / (p->tiles_per_wave * 8);
+    }
     // bfloat16: any split brings the hand-over of records to the head's last work-group (or, beyond 8 splits, the
     // merge kernel) while a round of tiles takes about 2 us, so heads are cut only where that saves at least three
     // rounds (B=16 H=8 L=1024: 20.1 us whole against 20.5 us in two splits that save two rounds)
     if (p->dtype == PSA_BF16 && p->n_split > 1) {
-        const int rounds_whole = (n_tiles + tiles_wg - 1) / tiles_wg;
+        const int rounds_whole = (n_tiles + 7) / 8;
         if (rounds_whole - p->tiles_per_wave < 3) { p->n_split = 1; p->tiles_per_wave = rounds_whole; }
     }
 
