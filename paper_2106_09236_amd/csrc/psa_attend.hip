@@ -33,10 +33,15 @@ constexpr int kF32SmemBytes = kF32Waves * kStateDoubles * 64 * 8;     // 73728: 
 //   [ m[NQ] | l[NQ] as float64 | O / l as float32: per column tile ct a block of 1024 = [16 registers][64 lanes] ]
 // element e of query q: block q / 16, register 4 (e % 4) + e / 16, lane ((e / 4) % 4) * 16 + q % 16
 // (F32Tile::reg_of, grp_of), i.e. exactly the accumulator layout, so record stores are fully coalesced.
-// The work of one work-group (key split `split`, query group `qgroup` of `head`); `smem`: kF32SmemBytes of LDS.
+// The work of one work-group; `smem`: kF32SmemBytes of LDS.
 template <int NCG, typename CS>      // NCG: column tiles of 16 selected queries per query group, 1 or 2
-__device__ __forceinline__ void attend_f32_body(const AttendParams& P, int split, int qgroup, int head, double* smem, CS& cs)
+__device__ __forceinline__ void attend_f32_body(const AttendParams& P, double* smem, CS& cs)
 {
+    // (a division only where both cuts are in use)
+    const HeadBlock hb = head_block(P);
+    const int head = hb.head, wg_in_head = hb.wg;
+    const int qgroup = P.n_qgroup == 1 ? 0 : P.n_split == 1 ? wg_in_head : wg_in_head / P.n_split;
+    const int split = wg_in_head - qgroup * P.n_split;
     const float* Q = static_cast<const float*>(P.Q);
     const float* K = static_cast<const float*>(P.K);
     const float* V = static_cast<const float*>(P.V);
@@ -51,7 +56,6 @@ __device__ __forceinline__ void attend_f32_body(const AttendParams& P, int split
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int c = lane & 15, g = lane >> 4;
     const int ct = wave % NCG, kt = wave / NCG;
-    const int wg_in_head = qgroup * n_split + split;
 
     const float* Qh = Q + (size_t)head * L * kD;
     const float* Kh = K + (size_t)head * L * kD;
@@ -178,7 +182,7 @@ void attend_f32_kernel(const AttendParams P)
 {
     __shared__ CommonScratch<512> cs;
     extern __shared__ __attribute__((aligned(16))) double smem[];
-    attend_f32_body<NCG>(P, blockIdx.x, blockIdx.y, blockIdx.z, smem, cs);
+    attend_f32_body<NCG>(P, smem, cs);
 }
 
 // =============================================================================
@@ -269,9 +273,13 @@ __device__ __forceinline__ void store_quad_b16(bf16_t* out_head, int i, int quad
 // The work of one work-group; `smem_b16`: kB16SmemBytes of LDS, or with ALIAS (the wave states reuse the V tiles'
 // area behind a barrier) kB16MergeBytes.
 template <int NQT, bool ALIAS, typename CS>     // NQT: column tiles of 32 selected queries per work-group
-__device__ __forceinline__ void attend_bf16_body(const AttendParams& P, int split, int qgroup, int head,
-                                                 unsigned char* smem_b16, CS& cs)
+__device__ __forceinline__ void attend_bf16_body(const AttendParams& P, unsigned char* smem_b16, CS& cs)
 {
+    // (a division only where both cuts are in use)
+    const HeadBlock hb = head_block(P);
+    const int head = hb.head, wg_in_head = hb.wg;
+    const int qgroup = P.n_qgroup == 1 ? 0 : P.n_split == 1 ? wg_in_head : wg_in_head / P.n_split;
+    const int split = wg_in_head - qgroup * P.n_split;
     const bf16_t* Q = static_cast<const bf16_t*>(P.Q);
     const bf16_t* K = static_cast<const bf16_t*>(P.K);
     const bf16_t* V = static_cast<const bf16_t*>(P.V);
@@ -282,7 +290,6 @@ __device__ __forceinline__ void attend_bf16_body(const AttendParams& P, int spli
     const int n = valid_len(P.lengths, b, L);
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int c = lane & 31, h = lane >> 5;
-    const int wg_in_head = qgroup * n_split + split;
 
     const bf16_t* Qh = Q + (size_t)head * L * kD;
     const bf16_t* Kh = K + (size_t)head * L * kD;
@@ -434,7 +441,7 @@ void attend_bf16_kernel(const AttendParams P)
 {
     __shared__ CommonScratch<512> cs;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_b16[];
-    attend_bf16_body<NQT, false>(P, blockIdx.x, blockIdx.y, blockIdx.z, smem_b16, cs);
+    attend_bf16_body<NQT, false>(P, smem_b16, cs);
 }
 
 // Merge kernel for bfloat16 records: work-group (quad, query tile, head), four
@@ -588,7 +595,8 @@ void attend_rows_f32_kernel(const AttendParams P)
     constexpr int NT = 256 * KSPLIT;
     __shared__ CommonScratch<NT> cs;
     __shared__ double s_state[KSPLIT == 2 ? 4 * 18 * 64 : 1];       // [query tile][m, l, O^T 16][lane]
-    const int qblock = blockIdx.x, head = blockIdx.y;
+    const HeadBlock hb = head_block(P);
+    const int qblock = hb.wg, head = hb.head;
     const int H = P.H, L = P.L;
     const int n = valid_len(P.lengths, head / H, L);
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -676,7 +684,8 @@ void attend_rows_bf16_kernel(const AttendParams P)
     __shared__ CommonScratch<NT> cs;
     __shared__ __attribute__((aligned(16))) uint16_t sKV[KSPLIT][2][2][kTile * kB16Stride];   // [key half][buffer][K|V]
     static_assert(sizeof(sKV) >= 4 * 34 * 64 * sizeof(float), "the state hand-over reuses the tile buffers");
-    const int qblock = blockIdx.x, head = blockIdx.y;
+    const HeadBlock hb = head_block(P);
+    const int qblock = hb.wg, head = hb.head;
     const int H = P.H, L = P.L;
     const int n = valid_len(P.lengths, head / H, L);
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -799,14 +808,15 @@ hipError_t launch_attend(const Plan& p, const Args& a, const Scratch& w)
     P.fused_select = p.fused_select; P.rows_per_wg = p.rows_per_wg; P.urule = a.urule; P.fill = a.fill;
     P.cand = w.cand; P.cand_len = p.cand_len; P.separate_merge = p.separate_merge; P.nq = p.nq_group;
     P.given_sel = p.given_inline ? a.given_sel : nullptr; P.given_u = a.given_u;
+    P.head_shift = p.BH % 8 == 0 && (p.n_qgroup > 1 || p.dtype == PSA_F32) ? 3 : 0;
     if (p.rows_mode) {
-        const dim3 rgrid(p.n_qgroup, p.BH);
+        const dim3 rgrid = attend_grid(p.n_qgroup, p.BH, P.head_shift);
         if (p.dtype == PSA_F32 && p.rows_mode == 2) hipLaunchKernelGGL(attend_rows_f32_kernel<2>, rgrid, dim3(512), 0, a.stream, P);
         else if (p.dtype == PSA_F32) hipLaunchKernelGGL(attend_rows_f32_kernel<1>, rgrid, dim3(256), 0, a.stream, P);
         else                    hipLaunchKernelGGL(attend_rows_bf16_kernel, rgrid, dim3(512), 0, a.stream, P);
         return hipGetLastError();
     }
-    dim3 grid(p.n_split, p.n_qgroup, p.BH);
+    const dim3 grid = attend_grid(p.n_wg_head, p.BH, P.head_shift);
     if (p.dtype == PSA_F32) {
         // 72 KB of dynamic LDS: above the 64 KB default
         const int which = p.nq_group == 16 ? 0 : 1;

@@ -31,7 +31,21 @@ struct AttendParams {
     int nq;                  // selected queries per query group (= per record)
     int fill;                // psa_fill_t: what the unselected valid rows receive
     URule urule;
+    int head_shift;          // 3: heads are dealt to the 8 XCDs (attend_grid), else 0
 };
+
+// The grid of the attend kernels: work-groups go to the 8 XCDs (each with an L2 of its own) in turn by their linear
+// id, so with the heads in eights on the fastest axis all work-groups of a head share one L2 for its K, V and lists,
+// the one that holds them from the measure stage.  Only for whole eights: 4 heads would keep to half of the chip
+// (B=1 H=4 L=4096 float32: 50 -> 62 us); and not for bfloat16 heads in one query group, whose work-groups share no row
+// (B=8 H=8 L=2048: 55.8 us as they come, 56.4 in eights).  B=8 H=8 L=2048 bfloat16, half of the queries kept: 116.7 ->
+// 111.9 us; B=4 H=8 L=568 float32: 41.1 -> 39.2 us, B=16 H=4 L=512: 30.6 -> 29.9 us.
+struct HeadBlock { int head, wg; };
+__device__ __forceinline__ HeadBlock head_block(const AttendParams& P)
+{
+    return {(int)((blockIdx.y << P.head_shift) + (blockIdx.x & ((1u << P.head_shift) - 1u))), (int)(blockIdx.x >> P.head_shift)};
+}
+inline dim3 attend_grid(int wgs, int BH, int head_shift) { return dim3((unsigned)wgs << head_shift, (unsigned)BH >> head_shift); }
 
 // NSEL: longest index list kept in LDS; NCAND: most candidates (lists * list length) the prologue merges.
 // The single-launch kernel for short heads uses a small instance (64 / 256) so that two of its
