@@ -326,24 +326,25 @@ __device__ __forceinline__ void attend_bf16_body(const AttendParams& P, unsigned
     PSA_TS(2);
 
     uint16_t* sV = reinterpret_cast<uint16_t*>(smem_b16) + wave * kTile * kB16Stride;
+    // (every tile but the item's last is whole)
     for (int ti = 0; ti < nt - 1; ++ti) {
         const int j0 = (tile0 + ti) * kTile;
         uint4 kc[4];
 #pragma unroll
         for (int kk = 0; kk < 4; ++kk) kc[kk] = kn[kk];
         wave_lds_sync();                                      // previous tile's reads are done
-        Bf16Tile<NQT>::stage_v_rows(vn, sV, j0, n, lane);
+        Bf16Tile<NQT>::template stage_v_rows<false>(vn, sV, j0, n, lane);
         Bf16Tile<NQT>::load_k_operand(kn, Kh, j0 + kTile, n, c, h);        // next tile, in flight during the step
         Bf16Tile<NQT>::load_v_rows(vn, Vh, j0 + kTile, n, lane);
         wave_lds_sync();
-        tile.step_ops(kc, sV, j0, n, c, h);
+        tile.template step_ops<false>(kc, sV, j0, n, c, h);
     }
     if (nt > 0) {
         const int j0 = (tile0 + nt - 1) * kTile;
         wave_lds_sync();
-        Bf16Tile<NQT>::stage_v_rows(vn, sV, j0, n, lane);
+        Bf16Tile<NQT>::template stage_v_rows<true>(vn, sV, j0, n, lane);
         wave_lds_sync();
-        tile.step_ops(kn, sV, j0, n, c, h);
+        tile.template step_ops<true>(kn, sV, j0, n, c, h);
     }
     PSA_TS(3);
 
@@ -696,21 +697,20 @@ void attend_rows_bf16_kernel(const AttendParams P)
     const bf16_t* Vh = static_cast<const bf16_t*>(P.V) + (size_t)head * L * kD;
     bf16_t* oh = static_cast<bf16_t*>(P.out) + (size_t)head * L * kD;
 
-    // this half's keys: tiles [0, half) or [half, all); every wave makes `half` rounds (the barriers are the work-group's)
+    // this half's keys: tiles [0, first) or [first, all); every wave makes `half` rounds (the barriers are the
+    // work-group's).  The second half is the longer one, so that a tile with keys beyond n is the last of all rounds.
     const int n_tiles = (n + kTile - 1) / kTile;
-    const int half = KSPLIT == 2 ? (n_tiles + 1) / 2 : n_tiles;
-    const int j_begin = kh * half * kTile;
-    const int j_end = (kh == KSPLIT - 1) ? n : (half * kTile < n ? half * kTile : n);
+    const int first = n_tiles / 2, half = n_tiles - first;
+    const int j_begin = kh * first * kTile;
+    const int j_end = kh == 1 ? n : first * kTile;
 
-    // thread t of a half stages 16 bytes of row t / 8 of the half's tile
+    // thread t of a half stages 16 bytes of row t / 8 of the half's tile (zeros at or beyond n)
     const int srow = (tid & 255) >> 3, scol = tid & 7;
+    const __amdgpu_buffer_rsrc_t kr = head_rows<128>(Kh, n), vr = head_rows<128>(Vh, n);
     auto fetch = [&](int j0, uint4& xk, uint4& xv) {
-        const int j = j0 + srow;
-        const bool ok = j < n;
-        const size_t ro = (size_t)(ok ? j : last_row(n)) * kD;
-        xk = reinterpret_cast<const uint4*>(Kh + ro)[scol];
-        xv = reinterpret_cast<const uint4*>(Vh + ro)[scol];
-        if (!ok) { xk = make_uint4(0u, 0u, 0u, 0u); xv = xk; }
+        const int ofs = (j0 + srow) * 128 + scol * 16;
+        xk = buffer_load16<uint4>(kr, ofs);
+        xv = buffer_load16<uint4>(vr, ofs);
     };
     auto put = [&](int buf, const uint4& xk, const uint4& xv) {
         *reinterpret_cast<uint4*>(&sKV[kh][buf][0][srow * kB16Stride + scol * 8]) = xk;
@@ -728,22 +728,20 @@ void attend_rows_bf16_kernel(const AttendParams P)
     fill_rows<bf16_t, NT>(P, oh, Vh, selp, u, n, qblock, cs);
     if (qblock * 128 >= u) return;                        // work-group-uniform: no rank of this block is in use
     put(0, xk, xv);
+    // the halves differ by at most one tile: all rounds but the last need no test and no masks (a branch around the
+    // step costs 8 % of the loop)
+    int j0 = j_begin;
     __syncthreads();
     int buf = 0;
-    {
-        // the halves differ by at most one tile: all rounds but the last need no test (a branch around the
-        // step costs 8 % of the loop)
-        int j0 = j_begin;
-        for (int i = 0; i + 1 < half; ++i, j0 += kTile) {
-            fetch(j0 + kTile, xk, xv);                       // next tile, in flight during the step
-            tile.step(sKV[kh][buf][0], sKV[kh][buf][1], j0, n, c, h);
-            put(buf ^ 1, xk, xv);
-            __syncthreads();
-            buf ^= 1;
-        }
-        if (j0 < j_end) tile.step(sKV[kh][buf][0], sKV[kh][buf][1], j0, n, c, h);     // (wave-uniform)
-        __syncthreads();                                     // the buffers are reused below
+    for (int i = 0; i + 1 < half; ++i, j0 += kTile) {
+        fetch(j0 + kTile, xk, xv);                           // next tile, in flight during the step
+        tile.step<false>(sKV[kh][buf][0], sKV[kh][buf][1], j0, n, c, h);
+        put(buf ^ 1, xk, xv);
+        __syncthreads();
+        buf ^= 1;
     }
+    if (j0 < j_end) tile.step<true>(sKV[kh][buf][0], sKV[kh][buf][1], j0, n, c, h);     // (wave-uniform)
+    __syncthreads();                                         // the buffers are reused below
     {
         // every wave is past its last tile: the tile buffers carry the second half's state to the first
         float* ex = reinterpret_cast<float*>(&sKV[0][0][0][0]) + (size_t)wq * 34 * 64 + lane;
@@ -757,7 +755,7 @@ void attend_rows_bf16_kernel(const AttendParams P)
         lds_barrier();
         if (kh == 1) return;
         const float m_b = ex[0];
-        const float m_new = fmaxf(tile.m_run[0], m_b);      // finite whenever n > 0: the first half holds key 0
+        const float m_new = fmaxf(tile.m_run[0], m_b);      // finite whenever n > 0: the second half holds a key
         const float wa = tile.m_run[0] == -INFINITY ? 0.f : fast_exp2(tile.m_run[0] - m_new);
         const float wb = m_b == -INFINITY ? 0.f : fast_exp2(m_b - m_new);
         tile.l_run[0] = tile.l_run[0] * wa + ex[64] * wb;

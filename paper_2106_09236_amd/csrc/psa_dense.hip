@@ -94,13 +94,15 @@ void dense_bf16_kernel(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ 
     put(0, xk, xv);
     __syncthreads();
     int buf = 0;
-    for (int j0 = 0; j0 < n; j0 += kTile) {
+    int j0 = 0;
+    for (; j0 + kTile < n; j0 += kTile) {                    // whole tiles; the last one masks its keys
         fetch(j0 + kTile, xk, xv);                           // next tile, in flight during the step
-        tile.step(sKV[buf][0], sKV[buf][1], j0, n, c, h);
+        tile.step<false>(sKV[buf][0], sKV[buf][1], j0, n, c, h);
         put(buf ^ 1, xk, xv);
         __syncthreads();
         buf ^= 1;
     }
+    if (n > 0) tile.step<true>(sKV[buf][0], sKV[buf][1], j0, n, c, h);
     const float l_tot = tile.l_run[0] + swap_half(tile.l_run[0]);
     if (q < L) {
         const float inv = (q < n && l_tot > 0.f) ? 1.f / l_tot : 0.f;

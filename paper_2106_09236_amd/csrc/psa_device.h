@@ -81,6 +81,17 @@ __device__ __forceinline__ void lds_barrier() {
 // Exchange with the lane 32 away (the other half of the wave).
 __device__ __forceinline__ float swap_half(float x) { return __shfl_xor(x, 32, 64); }
 
+// Maximum over the lanes 32 apart, and over those 16 apart, in every lane: the swap instructions exchange half-waves
+// (rows of 16) between two registers, here two copies of x, without the trip through the LDS unit a shuffle makes.
+__device__ __forceinline__ float max_xor32(float x) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+__device__ __forceinline__ float max_xor16(float x) {
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+
 // 2^x in float64 for x <= ~0 (anything below -1000, -inf included, gives 0; NaN stays NaN):
 // x = n + f with |f| <= 1/2 by adding and taking away 1.5 * 2^52, 2^f by the polynomial of degree 6 with
 // constant term 1 whose largest relative error on [-1/2, 1/2] is least (2.0e-9; 2^0 is exactly 1; the softmax weights need 1e-6, see

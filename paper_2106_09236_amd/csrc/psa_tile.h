@@ -33,6 +33,7 @@ __device__ __forceinline__ int last_row(int n) { return n > 0 ? n - 1 : 0; }
 
 constexpr float  kScaleLog2e  = 0.125f * 1.4426950408889634f;   // (1/sqrt(64)) * log2(e)
 constexpr double kScaleLog2eD = 0.125 * 1.4426950408889634074;
+constexpr float  kLagLog2 = 8.f;      // how far (as a power of 2) a weight may exceed 1 before the running constant follows
 
 // 2^x on the transcendental unit; -inf -> 0, no denormal handling needed here
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
@@ -138,8 +139,7 @@ struct F32Tile {
         for (int sb = 0; sb < 2; ++sb)
 #pragma unroll
             for (int r = 0; r < 4; ++r) tmax = fmaxf(tmax, (float)t[sb][r]);
-        tmax = fmaxf(tmax, __shfl_xor(tmax, 16, 64));
-        tmax = fmaxf(tmax, __shfl_xor(tmax, 32, 64));
+        tmax = max_xor32(max_xor16(tmax));
         const float m_new = fmaxf(m_run, tmax);               // finite: key j0 is valid
         const double alpha = exp2_f64((double)m_run - (double)m_new);
         double p[2][4], lsum = 0.0;
@@ -224,22 +224,24 @@ struct Bf16Tile {
     }
     // ... and into the wave's LDS tile, rows at or beyond n as zeros (P is 0 there, but
     // 0 times a NaN in the padding would still poison the sum).
+    template <bool MASK>
     static __device__ __forceinline__ void stage_v_rows(const uint4 (&vr)[4], uint16_t* sV, int j0, int n, int lane) {
 #pragma unroll
         for (int it = 0; it < 4; ++it) {
             const int row = it * 8 + (lane >> 3);
-            const uint4 x = (j0 + row < n) ? vr[it] : make_uint4(0u, 0u, 0u, 0u);
+            const uint4 x = (!MASK || j0 + row < n) ? vr[it] : make_uint4(0u, 0u, 0u, 0u);
             *reinterpret_cast<uint4*>(sV + row * kB16Stride + (lane & 7) * 8) = x;
         }
     }
 
     // One step over the staged keys j0 .. j0+31 (key j0 valid; rows at or beyond n
-    // are zero in LDS), K from LDS as well.
+    // are zero in LDS), K from LDS as well.  Without MASK every key must be valid.
+    template <bool MASK = true>
     __device__ __forceinline__ void step(const uint16_t* sK, const uint16_t* sV, int j0, int n, int c, int h) {
         uint4 ka[4];
 #pragma unroll
         for (int kk = 0; kk < 4; ++kk) ka[kk] = *reinterpret_cast<const uint4*>(sK + c * kB16Stride + 32 * h + 8 * kk);
-        step_ops(ka, sV, j0, n, c, h);
+        step_ops<MASK>(ka, sV, j0, n, c, h);
     }
 
     // First product of one K tile with query tile qt: s[r] = q . k of key
@@ -254,42 +256,56 @@ struct Bf16Tile {
         return s;
     }
 
+    // A operand of the second product, shared by all query tiles: for step st and element e the key is
+    // 16st + 8(e/4) + 4h + e%4 (the row order of the S^T accumulator registers 8st..8st+7), column 32dt + c.
+    // V lies row-major in LDS; the transposing LDS read (ds_read_b64_tr_b16) hands a lane of each
+    // group of 16 lanes one column of a 4 x 16 block: source lane s of the group points at row
+    // s / 4 of the block, columns 4 (s % 4) .. + 3, and lane i receives column i of the four rows.
+    // Two such reads (keys 16st + 4h .. + 3 and 16st + 8 + 4h .. + 3) make the operand's 8 elements.
+    static __device__ __forceinline__ void load_v_operand(uint4 (&vop)[2][2], const uint16_t* sV, int c, int h) {
+        typedef short shortx4 __attribute__((ext_vector_type(4)));
+        const int s16 = c & 15;
+        const uint16_t* src = sV + (4 * h + (s16 >> 2)) * kB16Stride + (c & 16) + 4 * (s16 & 3);
+#pragma unroll
+        for (int st = 0; st < 2; ++st)
+#pragma unroll
+            for (int dt = 0; dt < 2; ++dt) {
+                const uint16_t* p0 = src + (16 * st) * kB16Stride + dt * 32;
+                const shortx4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+                    (shortx4 __attribute__((address_space(3)))*)(p0));
+                const shortx4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+                    (shortx4 __attribute__((address_space(3)))*)(p0 + 8 * kB16Stride));
+                const uint2 l2 = __builtin_bit_cast(uint2, lo), h2 = __builtin_bit_cast(uint2, hi);
+                vop[st][dt] = make_uint4(l2.x, l2.y, h2.x, h2.y);
+            }
+    }
+
     // The step proper: ka = A operand of the first product (this lane's K row,
     // elements 32h + 8kk .. +8), V tile in LDS.
+    // With many tiles per wave this is bound by issue: 12 MFMAs (8 quad-cycles each) and some 120 vector instructions
+    // a query tile take their times one after the other (counters, and the same time with 2 or 4 waves on a SIMD or
+    // with the products of the next tile set between the instructions of the softmax).  So it spends few:
+    //   * the constant m_run subtracted in online softmax (in base 2 on the raw scores: the scale is positive, commutes
+    //     with the maximum and folds into the exponent's multiply-add) is a maximum seen before, not the newest one.
+    //     Weights up to 2^kLagLog2 are as exact as weights up to 1, so it follows only where the scores have grown by
+    //     more than that; with 32 queries to a wave some maximum moves, and 32 accumulators are scaled, in most
+    //     tiles otherwise;
+    //   * P = P_hi + P_lo, both bf16 (16 significant bits survive), the low terms by one v_dot2_f32_bf16 each: p - hi as
+    //     the pair times (-1, 0) or (0, -1), exact, where a shift and a difference took two instructions;
+    //   * masks exist in the copy for the last tile only (a run-time test became 48 unconditional instructions).
+    // B=8 H=8 L=2048, 1024 queries kept: whole call 110.9 -> 105.0 us, of it 58 us in this loop.
+    template <bool MASK>
     __device__ __forceinline__ void step_ops(const uint4 (&ka)[4], const uint16_t* sV, int j0, int n, int c, int h) {
-        // A operand of the second product, shared by all query tiles: for step st
-        // and element e the key is 16st + 8(e/4) + 4h + e%4 (the row order of the
-        // S^T accumulator registers 8st..8st+7), column 32dt + c
-        // V lies row-major in LDS; the transposing LDS read (ds_read_b64_tr_b16) hands a lane of each
-        // group of 16 lanes one column of a 4 x 16 block: source lane s of the group points at row
-        // s / 4 of the block, columns 4 (s % 4) .. + 3, and lane i receives column i of the four rows.
-        // Two such reads (keys 16st + 4h .. + 3 and 16st + 8 + 4h .. + 3) make the operand's 8 elements.
-        typedef short shortx4 __attribute__((ext_vector_type(4)));
         uint4 vop[2][2];
-        {
-            const int s16 = c & 15;
-            const uint16_t* src = sV + (4 * h + (s16 >> 2)) * kB16Stride + (c & 16) + 4 * (s16 & 3);
-#pragma unroll
-            for (int st = 0; st < 2; ++st)
-#pragma unroll
-                for (int dt = 0; dt < 2; ++dt) {
-                    const uint16_t* p0 = src + (16 * st) * kB16Stride + dt * 32;
-                    const shortx4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-                        (shortx4 __attribute__((address_space(3)))*)(p0));
-                    const shortx4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-                        (shortx4 __attribute__((address_space(3)))*)(p0 + 8 * kB16Stride));
-                    const uint2 l2 = __builtin_bit_cast(uint2, lo), h2 = __builtin_bit_cast(uint2, hi);
-                    vop[st][dt] = make_uint4(l2.x, l2.y, h2.x, h2.y);
-                }
-        }
-        const bool full = j0 + kTile <= n;                        // wave-uniform: no key of the tile is masked
+        load_v_operand(vop, sV, c, h);
+        // in scalar registers: as a literal the compiler encodes (-1, 0) as the inline constant -1.0, which the
+        // instruction reads as another pair
+        uint32_t minus_lo = 0x0000BF80u, minus_hi = 0xBF800000u;
+        asm("" : "+s"(minus_lo), "+s"(minus_hi));
 #pragma unroll
         for (int qt = 0; qt < NQT; ++qt) {
             floatx16 s = scores(ka, qt);
-            // online softmax in base 2 on the raw scores (the scale is positive, so it
-            // commutes with the maximum and folds into the exponent's multiply-add);
-            // keys at or beyond n are masked out
-            if (!full) {
+            if (MASK) {
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
                     const int j = j0 + 8 * (r >> 2) + 4 * h + (r & 3);
@@ -299,21 +315,21 @@ struct Bf16Tile {
             float tmax = s[0];
 #pragma unroll
             for (int r = 1; r < 16; ++r) tmax = fmaxf(tmax, s[r]);
-            tmax = fmaxf(tmax, swap_half(tmax));
-            const float m_new = fmaxf(m_run[qt], tmax * kScaleLog2e);   // finite: key j0 is valid
+            const float tm = max_xor32(tmax) * kScaleLog2e;       // finite: key j0 is valid
+            const float m_new = tm > m_run[qt] + kLagLog2 ? tm : m_run[qt];
             const float alpha = fast_exp2(m_run[qt] - m_new);
             float lsum = 0.f;
 #pragma unroll
             for (int r = 0; r < 16; ++r) { s[r] = fast_exp2(fmaf(s[r], kScaleLog2e, -m_new)); lsum += s[r]; }
             l_run[qt] = l_run[qt] * alpha + lsum;
-            if (__builtin_amdgcn_ballot_w64(m_new > m_run[qt]) != 0) {  // wave-uniform: some maximum moved
+            // (wave-uniform; nothing else in the branch: with more in it the compiler copies the accumulators)
+            if (__builtin_expect_with_probability(__builtin_amdgcn_ballot_w64(m_new > m_run[qt]) != 0, 1, 0.5)) {
 #pragma unroll
                 for (int dt = 0; dt < 2; ++dt)
 #pragma unroll
                     for (int r = 0; r < 16; ++r) oacc[qt][dt][r] *= alpha;
             }
             m_run[qt] = m_new;
-            // P = P_hi + P_lo, both bf16: 16 significant bits survive
 #pragma unroll
             for (int st = 0; st < 2; ++st) {
                 uint32_t ph[4], pl[4];
@@ -321,7 +337,9 @@ struct Bf16Tile {
                 for (int e2 = 0; e2 < 4; ++e2) {
                     const float p0 = s[8 * st + 2 * e2], p1 = s[8 * st + 2 * e2 + 1];
                     ph[e2] = cvt_pk_bf16(p0, p1);
-                    pl[e2] = cvt_pk_bf16(p0 - bf16_lo(ph[e2]), p1 - bf16_hi(ph[e2]));
+                    const bf16x2 hi = __builtin_bit_cast(bf16x2, ph[e2]);
+                    pl[e2] = cvt_pk_bf16(__builtin_amdgcn_fdot2_f32_bf16(hi, __builtin_bit_cast(bf16x2, minus_lo), p0, false),
+                                         __builtin_amdgcn_fdot2_f32_bf16(hi, __builtin_bit_cast(bf16x2, minus_hi), p1, false));
                 }
                 const bf16x8 bh = __builtin_bit_cast(bf16x8, make_uint4(ph[0], ph[1], ph[2], ph[3]));
                 const bf16x8 bl = __builtin_bit_cast(bf16x8, make_uint4(pl[0], pl[1], pl[2], pl[3]));

@@ -43,3 +43,27 @@ def test_float32_cuts(B, H, L, nq, splits, rounds):
 def test_cuts_against_oracle(dtype, B, H, L, c):
     cfg = W.small_config("cuts", B, H, L, 12, c, dtype, "mixture", B > 1, max(1, L // 3), L)
     check_against_oracle(W.make_workload(cfg, seed=900 + L), label=f"B{B} H{H} L{L} c{c} {dtype}")
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("B,H,L", [(8, 4, 1041), (2, 4, 333), (8, 4, 1088)])       # rows kernel (odd, whole tiles), key split
+@pytest.mark.parametrize("growth", [0.0, 0.13, 0.26, 1.5, -0.5])                    # of the scores, powers of 2 per key
+def test_running_maximum_that_lags(B, H, L, growth):
+    """Scores that rise along the keys: not at all, by 4 and 8 powers of 2 per tile of 32 keys (the maximum follows in
+    some tiles only), in every tile, and never.  bfloat16 results are rounded once: 2^-8 of the row's norm."""
+    import torch
+    from paper_2106_09236_amd import binding as psa
+    g = torch.Generator().manual_seed(L)
+    Q, K, V = (0.3 * torch.randn((B, H, L, 64), generator=g) for _ in range(3))
+    Q[..., 0] = 8.0
+    # q . k = 8 k_0 + ...; in powers of 2 that is k_0 log2(e); a period of 256 keys keeps k_0 exact enough in bfloat16
+    K[..., 0] = (torch.arange(L) % 256) * growth / 1.4426950408889634
+    Q, K, V = (t.to(torch.bfloat16) for t in (Q, K, V))
+    sel = torch.stack([torch.randperm(L, generator=g) for _ in range(B * H)]).reshape(B, H, L).to(torch.int32)
+    u = torch.full((B,), L, dtype=torch.int32)
+    out = psa.probsparse_attn_fwd_with_indices(Q.cuda(), K.cuda(), V.cuda(), None, sel.cuda(), u.cuda(), psa.FILL_MEAN).cpu().double()
+    dense = psa.dense_attn_fwd(Q.cuda(), K.cuda(), V.cuda(), None).cpu().double()
+    ref = torch.softmax(Q.double() @ K.double().transpose(-1, -2).contiguous() / 8.0, dim=-1) @ V.double()
+    for name, got in (("kept", out), ("dense", dense)):
+        err = ((got - ref).norm(dim=-1) / ref.norm(dim=-1)).max().item()
+        assert err <= 2.0 ** -8, (name, growth, err)
