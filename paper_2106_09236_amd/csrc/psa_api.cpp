@@ -74,31 +74,66 @@ static void split_f32(Plan* p, int n_tiles)
     }
 }
 
-bool make_plan(const psa_shape_t* s, URule urule, int u_stride, Plan* p)
+// Streaming measure kernel with `cpw` chunks per work-group: length of the sorted list each work-group hands on, or 0
+// where a select kernel follows.  Lists only where the attend prologue can merge them (up to 8 per head; no select
+// launch: 8.3 us at B=8 H=8 L=2048), the ranking at the end of a work-group is short (all pairs of up to 256 queries,
+// a microsecond), and the candidates are few: every attend work-group of the head merges them (with half of 2048
+// queries kept 134 us with lists against 123 us with the select kernel).
+static int stream_list_len(const Plan& p, int cpw)
 {
-    if (check_shape(s) != PSA_OK) return false;
+    const int groups = (p.n_chunk + cpw - 1) / cpw, span = cpw * kMeasureQueries;
+    const int len = p.u_max < span ? p.u_max : span;
+    return p.U <= kPipeMaxSamples && groups <= 8 && span <= kListMax && (int64_t)groups * len <= 512 ? len : 0;
+}
+
+// Streaming measure kernel, float32: consecutive chunks of a head that one of its persistent work-groups takes, by the
+// most chunks that a CU ends up with (half a chunk more to start a work-group, and where a select kernel follows).
+// A float32 work-group (256-byte rows) reaches the rate of the CU's return path alone and only takes turns with a
+// second one: B=16 H=4 L=1000 63.0 us in 512 work-groups of 2 chunks, 59.3 us in 256 of 4.  Of equals the longer one has
+// fewer lists.  With lengths a fifth of the work-groups is taken to be padding, which leaves at once.  Means of six
+// ragged batches, against two work-groups per CU: B=24 H=4 L=750 76.0 -> 63.5 us, B=20 H=4 L=600 49.4 -> 41.5 us, B=12
+// H=8 L=520 47.5 -> 40.3 us.  bfloat16 work-groups share a CU to advantage (B=8 H=8 L=2048 55.8 us in 512, 63.4 in 256).
+static int stream_cut_f32(const Plan& p, bool ragged)
+{
+    float best = INFINITY;
+    int pick = 1;
+    for (int cpw = 1; cpw <= 16 && cpw <= p.n_chunk; ++cpw) {
+        const int64_t wgs = (int64_t)p.BH * ((p.n_chunk + cpw - 1) / cpw);
+        const int64_t busy = ragged ? (4 * wgs + 4) / 5 : wgs;
+        const float cost = (float)((busy + 255) / 256) * ((float)cpw + 0.5f) + (stream_list_len(p, cpw) > 0 ? 0.f : 0.5f);
+        if (cost <= best) { best = cost; pick = cpw; }
+    }
+    return pick;
+}
+
+// How much of a plan is cut anew (see make_plan).
+enum Cuts { kFirstCuts = 0, kShortChunks = 1, kStreamCut = 2, kSplitCut = 3 };
+
+static void build_plan(const psa_shape_t* s, URule urule, int u_stride, bool ragged, Cuts cuts, Plan* p)
+{
     p->given_indices = u_stride > 0;
-    if (!p->given_indices && !good_rule(urule)) return false;
-    if (u_stride < 0 || u_stride > s->L_K) return false;
     p->B = s->B; p->H = s->H; p->L = s->L_K; p->U = s->U; p->dtype = s->dtype;
     p->BH = s->B * s->H;
     p->u_max = p->given_indices ? u_stride : u_max_of(urule, p->L);
     // A work-group covers the selected queries in groups of 16 or 32 (float32: float64 MFMA tiles of 16) or 32 or
     // 64 (bfloat16: tiles of 32) and walks its keys in rounds of `tiles_wg` tiles of 32.
     const int n_tiles = (p->L + kTile - 1) / kTile;
-    if (p->dtype == PSA_F32) {
+    if (p->dtype == PSA_F32 && cuts >= kSplitCut) {
         split_f32(p, n_tiles);
     } else {
-        // key splits: enough work-groups to cover the 256 CUs once (a work-group takes a CU)
-        p->nq_group = p->u_max > 32 ? 64 : 32;
+        // key splits: enough work-groups to cover the 256 CUs once (bfloat16) or twice
+        if (p->dtype == PSA_F32) p->nq_group = (p->u_max > 16 && (int64_t)p->BH * ((p->L + 127) / 128) >= 64) ? 32 : 16;
+        else                     p->nq_group = p->u_max > 32 ? 64 : 32;
         p->n_qgroup = (p->u_max + p->nq_group - 1) / p->nq_group;
-        const int max_split = (n_tiles + 7) / 8;
-        int target = (256 + p->BH * p->n_qgroup - 1) / (p->BH * p->n_qgroup);
+        const int tiles_wg = p->dtype == PSA_F32 && p->nq_group == 32 ? 4 : 8;
+        const int max_split = (n_tiles + tiles_wg - 1) / tiles_wg;
+        const int wg_goal = p->dtype == PSA_F32 ? 512 : 256;
+        int target = (wg_goal + p->BH * p->n_qgroup - 1) / (p->BH * p->n_qgroup);
         if (target < 1) target = 1;
         int n_split = target < max_split ? target : max_split;
         if (n_split > kMaxSplit) n_split = kMaxSplit;
-        p->tiles_per_wave = (n_tiles + n_split * 8 - 1) / (n_split * 8);      // rounds
-        p->n_split = (n_tiles + p->tiles_per_wave * 8 - 1) / (p->tiles_per_wave * 8);
+        p->tiles_per_wave = (n_tiles + n_split * tiles_wg - 1) / (n_split * tiles_wg);      // rounds
+        p->n_split = (n_tiles + p->tiles_per_wave * tiles_wg - 1) / (p->tiles_per_wave * tiles_wg);
     }
     // bfloat16: any split brings the hand-over of records to the head's last work-group (or, beyond 8 splits, the
     // merge kernel) while a round of tiles takes about 2 us, so heads are cut only where that saves at least three
@@ -157,7 +192,7 @@ bool make_plan(const psa_shape_t* s, URule urule, int u_stride, Plan* p)
     p->measure_queries = p->measure_lds ? kLdsQueries : kMeasureQueries;
     if (p->measure_lds) {
         if (two_per_cu) p->measure_lds = 2;
-        for (int q = kLdsQueries / 2; q >= 32; q >>= 1) {
+        for (int q = kLdsQueries / 2; q >= 32 && cuts >= kShortChunks; q >>= 1) {
             const int chunks = (p->L + q - 1) / q;
             if (chunks > 8 || (int64_t)p->BH * chunks > slots || (q == 32 && k_bytes > (size_t)64 * 1024)) break;
             p->measure_queries = q;
@@ -171,8 +206,9 @@ bool make_plan(const psa_shape_t* s, URule urule, int u_stride, Plan* p)
         while (p->chunks_per_wg < p->n_chunk &&
                (int64_t)p->BH * ((p->n_chunk + p->chunks_per_wg - 1) / p->chunks_per_wg) > slots) ++p->chunks_per_wg;
     }
+    else if (!p->given_indices && p->dtype == PSA_F32 && cuts >= kStreamCut) p->chunks_per_wg = stream_cut_f32(*p, ragged);
     else if (!p->given_indices) {
-        // streaming measure kernel: about two persistent work-groups per CU, each on consecutive chunks of one head
+        // about two persistent work-groups per CU, each on consecutive chunks of one head
         const int64_t chunks_all = (int64_t)p->BH * p->n_chunk;
         int cpw = (int)((chunks_all + 511) / 512);
         cpw = cpw < 1 ? 1 : (cpw > 16 ? 16 : cpw);
@@ -187,17 +223,11 @@ bool make_plan(const psa_shape_t* s, URule urule, int u_stride, Plan* p)
     p->n_lists = p->n_chunk;
     p->stream_lists = 0;
     // Streamed heads: a work-group of the measure kernel ranks the queries of its own chunks and hands on its
-    // best u as one sorted list, exactly as a chunk of the LDS kernel does; where the head's work-groups are
-    // at most 8 (the attend prologue merges up to 8 lists) no select launch is needed (conformer_l: 8.3 us).
-    if (!p->measure_lds && !p->given_indices && p->U <= kPipeMaxSamples) {
-        const int groups = (p->n_chunk + p->chunks_per_wg - 1) / p->chunks_per_wg;
-        const int span = p->chunks_per_wg * kMeasureQueries;
-        const int len = p->u_max < span ? p->u_max : span;
-        // (the ranking at the end of a work-group is all pairs of its queries: up to 256 of them, a microsecond)
-        // (few candidates only: every attend work-group of the head merges them; with hundreds of kept queries per
-        // head the select kernel is the cheaper way: conformer_l at r_sparse = 0.5 134 against 123 us)
-        if (groups <= 8 && span <= kListMax && (int64_t)groups * len <= 512) {
-            p->cand_len = len; p->n_lists = groups; p->stream_lists = 1;
+    // best u as one sorted list, exactly as a chunk of the LDS kernel does (see stream_list_len)
+    if (!p->measure_lds && !p->given_indices) {
+        const int len = stream_list_len(*p, p->chunks_per_wg);
+        if (len > 0) {
+            p->cand_len = len; p->n_lists = (p->n_chunk + p->chunks_per_wg - 1) / p->chunks_per_wg; p->stream_lists = 1;
         }
     }
     p->n_seg = 0;
@@ -239,8 +269,27 @@ bool make_plan(const psa_shape_t* s, URule urule, int u_stride, Plan* p)
     p->off_u = off;      off += align256((size_t)p->B * sizeof(int));
     p->off_ticket = off; off += align256((size_t)p->BH * sizeof(int));
     p->off_cand = off;   off += align256((size_t)p->BH * p->n_lists * p->cand_len * sizeof(uint2));
-    p->off_part = off;   off += p->rows_mode ? 0 : align256((size_t)p->BH * p->n_qgroup * p->n_split * p->part_stride * p->part_elem);
+    const bool records = !p->rows_mode && (p->n_split > 1 || cuts == kFirstCuts);      // a head in one split hands over none
+    p->off_part = off;   off += !records ? 0 : align256((size_t)p->BH * p->n_qgroup * p->n_split * p->part_stride * p->part_elem);
     p->total = off;
+}
+
+// The workspace has the size that the first rules for the cuts gave (two work-groups per CU in every stage, chunks of
+// 128 queries, records for every split): callers keep workspaces by it, and the static scratch admits calls by it.  The
+// present rules are taken as far as what they need fits; short heads in small chunks may need more (at most 512
+// chunks of a few KB).
+bool make_plan(const psa_shape_t* s, URule urule, int u_stride, bool ragged, Plan* p)
+{
+    if (check_shape(s) != PSA_OK) return false;
+    if (u_stride <= 0 && !good_rule(urule)) return false;
+    if (u_stride < 0 || u_stride > s->L_K) return false;
+    build_plan(s, urule, u_stride, ragged, kFirstCuts, p);
+    const size_t size = p->total;
+    for (int cuts = kSplitCut; cuts >= kShortChunks; --cuts) {
+        build_plan(s, urule, u_stride, ragged, (Cuts)cuts, p);
+        if (p->total <= size) break;
+    }
+    if (p->total < size) p->total = size;
     return true;
 }
 
@@ -285,7 +334,7 @@ static int run(const void* Q, const void* K, const void* V, const int32_t* lengt
     if (rc != PSA_OK) return rc;
     if (misaligned(sample_idx, 4)) return PSA_ERR_ALIGN;
     Plan p;
-    if (!make_plan(shape, urule, 0, &p)) return PSA_ERR_SHAPE;
+    if (!make_plan(shape, urule, 0, lengths != nullptr, &p)) return PSA_ERR_SHAPE;
     if (workspace_bytes < p.total) return PSA_ERR_WORKSPACE;
     if (checks_only) return PSA_OK;
 
@@ -333,7 +382,7 @@ static int run_indices(const void* Q, const void* K, const void* V, const int32_
     if (rc != PSA_OK) return rc;
     if (misaligned(sel, 4) || misaligned(u, 4)) return PSA_ERR_ALIGN;
     Plan p;
-    if (!make_plan(shape, URule{PSA_U_LOG, 1.0}, u_stride, &p)) return PSA_ERR_SHAPE;
+    if (!make_plan(shape, URule{PSA_U_LOG, 1.0}, u_stride, lengths != nullptr, &p)) return PSA_ERR_SHAPE;
     if (workspace_bytes < p.total) return PSA_ERR_WORKSPACE;
 
     Args a;
@@ -410,7 +459,7 @@ int probsparse_attn_fwd_static(const void* Q, const void* K, const void* V, cons
     if (rc != PSA_OK) return rc;
     Plan p;
     if (!good_rule(URule{PSA_U_LOG, c})) return PSA_ERR_ARG;
-    if (!make_plan(shape, c, &p)) return PSA_ERR_SHAPE;
+    if (!make_plan(shape, URule{PSA_U_LOG, c}, 0, lengths != nullptr, &p)) return PSA_ERR_SHAPE;
     if (p.total > kStaticScratchBytes) return PSA_ERR_WORKSPACE;
     if (!Q || !K || !V || !sample_idx || !out) return PSA_ERR_NULL;
     void* ws = nullptr;
@@ -478,27 +527,27 @@ int probsparse_mhsa_fwd(const void* X, const psa_mhsa_weights_t* weights, const 
 size_t probsparse_attn_workspace_bytes(const psa_shape_t* shape, double c)
 {
     psa::Plan p;
-    return psa::make_plan(shape, c, &p) ? p.total : 0;
+    return psa::make_plan(shape, psa::URule{PSA_U_LOG, c}, 0, false, &p) ? p.total : 0;
 }
 
 int32_t probsparse_u_max(const psa_shape_t* shape, double c)
 {
     psa::Plan p;
-    return psa::make_plan(shape, c, &p) ? p.u_max : 0;
+    return psa::make_plan(shape, psa::URule{PSA_U_LOG, c}, 0, false, &p) ? p.u_max : 0;
 }
 
 size_t probsparse_attn_workspace_bytes_opt(const psa_shape_t* shape, const psa_options_t* opt)
 {
     psa::Plan p;
     if (!opt || (opt->fill != PSA_FILL_MEAN && opt->fill != PSA_FILL_VALUE)) return 0;
-    return psa::make_plan(shape, psa::URule{opt->u_rule, opt->factor}, 0, &p) ? p.total : 0;
+    return psa::make_plan(shape, psa::URule{opt->u_rule, opt->factor}, 0, false, &p) ? p.total : 0;
 }
 
 int32_t probsparse_u_max_opt(const psa_shape_t* shape, const psa_options_t* opt)
 {
     psa::Plan p;
     if (!opt) return 0;
-    return psa::make_plan(shape, psa::URule{opt->u_rule, opt->factor}, 0, &p) ? p.u_max : 0;
+    return psa::make_plan(shape, psa::URule{opt->u_rule, opt->factor}, 0, false, &p) ? p.u_max : 0;
 }
 
 int probsparse_attn_fwd_opt(const void* Q, const void* K, const void* V, const int32_t* lengths,
@@ -514,7 +563,7 @@ size_t probsparse_attn_with_indices_workspace_bytes(const psa_shape_t* shape, in
 {
     psa::Plan p;
     if (u_stride < 1) return 0;
-    return psa::make_plan(shape, psa::URule{PSA_U_LOG, 1.0}, u_stride, &p) ? p.total : 0;
+    return psa::make_plan(shape, psa::URule{PSA_U_LOG, 1.0}, u_stride, false, &p) ? p.total : 0;
 }
 
 int probsparse_attn_fwd_with_indices(const void* Q, const void* K, const void* V, const int32_t* lengths,
@@ -603,7 +652,7 @@ int probsparse_describe_plan(const psa_shape_t* shape, const psa_options_t* opt,
     const URule urule = opt ? URule{opt->u_rule, opt->factor} : URule{PSA_U_LOG, 1.0};
     if (u_stride < 0) return PSA_ERR_ARG;
     if (u_stride == 0 && !good_rule(urule)) return PSA_ERR_ARG;
-    if (!make_plan(shape, urule, u_stride, &p)) return u_stride > 0 ? PSA_ERR_ARG : PSA_ERR_SHAPE;
+    if (!make_plan(shape, urule, u_stride, false, &p)) return u_stride > 0 ? PSA_ERR_ARG : PSA_ERR_SHAPE;
     const char* measure = p.given_indices ? "none" : p.measure_lds == 2 ? "lds_half" : p.measure_lds == 1 ? "lds" : "stream";
     const char* select = p.given_indices ? (p.given_inline ? "given_inline" : "given_prep")
                        : p.n_seg > 0 ? "segments" : p.fused_select ? "lists" : "kernel";

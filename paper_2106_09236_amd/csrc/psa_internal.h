@@ -109,8 +109,8 @@ inline hipError_t ensure_lds_limit(const void* fn, int bytes, std::atomic<uint64
     return e;
 }
 
-bool make_plan(const psa_shape_t* s, URule urule, int u_stride, Plan* p);
-inline bool make_plan(const psa_shape_t* s, double c, Plan* p) { return make_plan(s, URule{PSA_U_LOG, c}, 0, p); }
+// ragged: the call has lengths (which cut the streaming measure kernel takes; the workspace's layout does not depend on it).
+bool make_plan(const psa_shape_t* s, URule urule, int u_stride, bool ragged, Plan* p);
 Scratch carve(const Plan& p, void* workspace);
 
 // One-time, per-device set-up of the kernels that need it (dynamic LDS limits); the launch

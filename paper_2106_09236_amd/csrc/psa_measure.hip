@@ -391,10 +391,13 @@ void measure_pipe_kernel(const T* __restrict__ Q, const T* __restrict__ K, const
     __shared__ int s_clean[2];                    // per stage: every query of the chunk is valid and every sample index usable
     extern __shared__ __attribute__((aligned(16))) unsigned char s_stage[];    // [2][ idx [64][Us] | q [64][row bytes] ]
 
+    // all work-groups of a head on one XCD; the last groups of all heads come last, so that where a second work-group
+    // shares a CU it is one that is padding in a shorter item
     const int groups_per_head = (chunks_per_head + chunks_per_wg - 1) / chunks_per_wg;
-    const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-    const int head = (slot / groups_per_head) * 8 + xcd;          // all work-groups of a head on one XCD
-    const int chunk0 = (slot % groups_per_head) * chunks_per_wg;
+    const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3, rounds = (n_heads + 7) >> 3;
+    const int group = slot / rounds;
+    const int head = (slot - group * rounds) * 8 + xcd;
+    const int chunk0 = group * chunks_per_wg;
     if (head >= n_heads) return;                  // grid is padded to a multiple of 8 heads (work-group-uniform)
     int chunk_end = chunk0 + chunks_per_wg;
     chunk_end = chunk_end < chunks_per_head ? chunk_end : chunks_per_head;
@@ -416,8 +419,8 @@ void measure_pipe_kernel(const T* __restrict__ Q, const T* __restrict__ K, const
         if (tid < kD) vpart[((size_t)head * chunks_per_head + chunk) * kD + tid] = 0.0;
     }
     chunk_end = chunk_end < first_pad ? chunk_end : first_pad;
-    uint2* cand_out = cand ? cand + ((size_t)head * groups_per_head + slot % groups_per_head) * cand_len : nullptr;
-    double* vlist_out = cand ? vlist + ((size_t)head * groups_per_head + slot % groups_per_head) * kD : nullptr;
+    uint2* cand_out = cand ? cand + ((size_t)head * groups_per_head + group) * cand_len : nullptr;
+    double* vlist_out = cand ? vlist + ((size_t)head * groups_per_head + group) * kD : nullptr;
     if (chunk0 >= chunk_end) {                    // work-group-uniform: nothing valid here, an empty list
         if (cand_out) for (int t = tid; t < cand_len; t += kPipeThreads) cand_out[t] = make_uint2(0u, 0xFFFFFFFFu);
         if (cand_out && tid < kD) vlist_out[tid] = 0.0;

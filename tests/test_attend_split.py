@@ -67,3 +67,30 @@ def test_running_maximum_that_lags(B, H, L, growth):
     for name, got in (("kept", out), ("dense", dense)):
         err = ((got - ref).norm(dim=-1) / ref.norm(dim=-1)).max().item()
         assert err <= 2.0 ** -8, (name, growth, err)
+
+
+@pytest.mark.parametrize("B,H,L,chunks_per_wg", [
+    (16, 4, 1000, 4), (9, 8, 710, 4), (4, 4, 2048, 2), (2, 4, 1024, 1), (1, 4, 16384, 4),
+])
+def test_float32_measure_cuts(B, H, L, chunks_per_wg):
+    assert plan(B, H, L, 35, "f32")["chunks_per_wg"] == str(chunks_per_wg)
+
+
+def test_static_scratch_admits_what_it_did():
+    # near the limit of 16 MiB: shapes whose present cut would need more than the size the workspace has
+    from paper_2106_09236_amd import binding as psa
+    lib = psa.load()
+    limit = lib.probsparse_static_workspace_bytes()
+    assert limit == 16 << 20
+    for B, H, L, U, c, size in [(227, 8, 12, 8, 5.0, 9655296), (137, 1, 7093, 70, 5.0, 16504320), (167, 4, 977, 40, 3.0, 14128128)]:
+        assert int(plan(B, H, L, U, "f32", c=c)["workspace"]) == size <= limit
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("B,H,L,U", [(16, 4, 1000, 35), (9, 8, 710, 33), (24, 4, 750, 34), (20, 4, 600, 12), (5, 4, 2100, 9),
+                                     (3, 3, 577, 64), (33, 8, 560, 7)])
+def test_measure_cuts_against_oracle(B, H, L, U):
+    # ragged and whole batches of streamed float32 heads: one to nine chunks per work-group, heads in eights and not
+    for ragged in (False, True):
+        cfg = W.small_config("cuts", B, H, L, U, 5.0, "f32", "mixture", ragged, max(1, L // 8), L)
+        check_against_oracle(W.make_workload(cfg, seed=700 + L), label=f"B{B} H{H} L{L} ragged={ragged}")
