@@ -7,8 +7,12 @@
 //   dQ_i = sum_j g_ij k_j      dK_j = sum_i g_ij q_i          dV_j = sum_i p_ij G_i   (+ the fill's share)
 // The weights are recomputed from Q and K (the forward keeps no statistics):
 //   bwd_stats_kernel   partial (max, sum, weighted sum of c) per kept query and key split
+// and then one of two forms (make_bwd_plan): fused,
 //   bwd_main_kernel    combines them, then dK, dV, the fill's gradient, zero rows, and dQ (per key split)
 //   bwd_dq_reduce_kernel  adds the key splits of dQ in split order
+// or, where those partial sums of dQ would take too much memory,
+//   bwd_dq_kernel      combines them, then dQ of 16 kept queries over all keys
+//   bwd_main_kernel    (kKeysOnly) dK, dV, the fill's gradient, zero rows
 // All five contractions run on the matrix cores (v_mfma_f64_16x16x4f64 on exactly widened inputs):
 //   lane (c, g) = (lane % 16, lane / 16)
 //   A[i][k]: i = c, k = g      B[k][j]: k = g, j = c      D[i][j]: i = 4r + g, j = c  (r = 0..3)
@@ -51,6 +55,7 @@ constexpr int kBwdGroup = 32;        // ... and by the gradient kernel (2 tiles)
 constexpr int kBwdTiles = kBwdGroup / kBwdQ;
 constexpr int kBwdChunk = 2048;      // rows per bit mask of the fill's column sums
 constexpr int kBwdMaxSplit = 64;     // key splits (their partial results are added up by one thread each)
+constexpr size_t kBwdPartBytes = (size_t)256 << 20;   // partial sums of dQ that a call may always have (see make_bwd_plan)
 constexpr int kBwdKeepStats = 768;   // most kept queries whose statistics the gradient kernel keeps in LDS (two work-groups per CU)
 typedef double bwd_x4 __attribute__((ext_vector_type(4)));
 typedef double bwd_x2 __attribute__((ext_vector_type(2)));
@@ -114,6 +119,12 @@ __device__ __forceinline__ void bwd_store16(bf16_t* p, const float (&v)[8], bool
 
 constexpr double kBwdScaleLog2e = 0.125 * 1.4426950408889634074;     // scores to base-2 exponents
 
+// What bwd_main_kernel does beside dK and dV:
+//   kFused      dQ as well; the statistics of all kept queries (up to kBwdKeepStats) are put together in LDS once
+//   kFusedMany  the same with more kept queries: the statistics of a group are put together anew for every block
+//   kKeysOnly   nothing: bwd_dq_kernel has computed dQ and left the statistics in memory
+enum BwdForm { kFused, kFusedMany, kKeysOnly };
+
 struct BwdParams {
     const void* Q; const void* K; const void* V; const void* G;
     const int* lengths; const int* sel; const int* u;
@@ -121,6 +132,7 @@ struct BwdParams {
     double* stats_part;    // [BH][S1][u_pad][3]  (max, sum, weighted c) per kept query and key split, base 2
     double* gsum_part;     // [BH][S1][64]        column sums of G over the valid rows outside I_sparse, per key split
     double* dq_part;       // [BH][S2][u_pad][64], or nullptr: dQ rows are written directly
+    double* stats;         // [BH][u_pad][2]       (log2 sum exp, -D/8) per kept query, kKeysOnly form; else nullptr
     int H, L, u_stride, u_pad, n_group, S1, blocks1, S2, blocks2, fill;
 };
 
@@ -409,6 +421,112 @@ __device__ __forceinline__ void combine_stats(const BwdParams& P, int head, int 
     D = dt / lt;
 }
 
+// (log2 sum exp, -D/8) of kept query t of the head; an absent entry of the list has no weight on any key
+__device__ __forceinline__ bwd_x2 stat_of(const BwdParams& P, int head, int t, int n, int ub)
+{
+    double lse = INFINITY, D = 0.0;
+    if (kept_row(P, head, t, n, ub) >= 0) combine_stats(P, head, t, lse, D);
+    return bwd_x2{lse, -0.125 * D};
+}
+
+// ---- dQ of a tile of 16 kept queries over all keys of the head, and their statistics for the kKeysOnly form of
+// bwd_main_kernel.  Scores are formed transposed (keys on the rows), so that a lane's four g values belong to query c
+// and are, unchanged, the B operand of the product that contracts over keys.  Wave w takes the 16 keys 16 w .. + 15 of
+// every 64; the waves' shares of dQ are added in wave order at the end, so nothing goes through memory.  The price is
+// the two score products, formed a third time (48 MFMAs for a tile of 16 queries x 16 keys instead of 16).
+// grid (tiles of 16 kept queries, heads)
+template <typename T>
+__global__ __launch_bounds__(kBwdThreads, 2)
+void bwd_dq_kernel(const BwdParams P)
+{
+    __shared__ bwd_x2 s_stat[kBwdQ];
+    __shared__ double s_acc[kBwdWaves][16][64];                      // the waves' accumulators, register by register
+    const int q0 = blockIdx.x * kBwdQ, head = blockIdx.y;
+    const int b = head / P.H, L = P.L;
+    const int n = valid_len(P.lengths, b, L);
+    const int ub = kept_count(P, b, n);
+    if (q0 >= ub) return;                                            // work-group-uniform (n > 0 behind this)
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, c = lane & 15, g = lane >> 4;
+    const T* Qh = static_cast<const T*>(P.Q) + (size_t)head * L * kD;
+    const T* Kh = static_cast<const T*>(P.K) + (size_t)head * L * kD;
+    const T* Vh = static_cast<const T*>(P.V) + (size_t)head * L * kD;
+    const T* Gh = static_cast<const T*>(P.G) + (size_t)head * L * kD;
+
+    // operands of 16 keys: the lane's key row for the score products (16 elements of key c), and for the product that
+    // contracts over keys elements 4c .. 4c + 3 of keys 4r + g; the next keys' are requested before these are worked
+    // on (on a clamped row: harmless past the end)
+    BwdRow<T, 16> kn, vn;
+    BwdRow<T, 4> k4n[4];
+    auto request = [&](int j0) {
+        const int row = j0 + c < n ? j0 + c : n - 1;
+        kn.load(Kh + (size_t)row * kD + 16 * g);
+        vn.load(Vh + (size_t)row * kD + 16 * g);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int key = j0 + 4 * r + g < n ? j0 + 4 * r + g : n - 1;
+            k4n[r].load(Kh + (size_t)key * kD + 4 * c);
+        }
+    };
+    request(16 * wave);
+    const int qi = kept_row(P, head, q0 + c, n, ub);
+    double qd[16], gd[16];                                           // B operands of the score products: query c (zeros for an absent entry)
+    {
+        BwdRow<T, 16> qf, gf;
+        qf.load(Qh + (size_t)(qi >= 0 ? qi : 0) * kD + 16 * g);
+        gf.load(Gh + (size_t)(qi >= 0 ? qi : 0) * kD + 16 * g);
+#pragma unroll
+        for (int t = 0; t < 16; ++t) { qd[t] = qi >= 0 ? (double)qf.at(t) : 0.0; gd[t] = qi >= 0 ? (double)gf.at(t) : 0.0; }
+    }
+    if (tid < kBwdQ) {
+        const bwd_x2 sd = stat_of(P, head, q0 + tid, n, ub);
+        s_stat[tid] = sd;
+        reinterpret_cast<bwd_x2*>(P.stats)[(size_t)head * P.u_pad + q0 + tid] = sd;
+    }
+    __syncthreads();
+    const bwd_x2 sd = s_stat[c];
+    bwd_x4 acc[4];                                                   // dQ^T of this wave's keys: acc[dt][r] is element 4 (4r + g) + dt of query c
+#pragma unroll
+    for (int dt = 0; dt < 4; ++dt) acc[dt] = bwd_x4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll 1
+    for (int j0 = 16 * wave; j0 < n; j0 += 16 * kBwdWaves) {         // wave-uniform
+        BwdRow<T, 16> kf = kn, vf = vn;
+        BwdRow<T, 4> k4[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) k4[r] = k4n[r];
+        if (j0 + 16 * kBwdWaves < n) request(j0 + 16 * kBwdWaves);
+        bwd_x4 s = bwd_x4{0.0, 0.0, 0.0, 0.0}, cc = bwd_x4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int t = 0; t < 16; ++t) {
+            s = __builtin_amdgcn_mfma_f64_16x16x4f64((double)kf.at(t), qd[t], s, 0, 0, 0);
+            cc = __builtin_amdgcn_mfma_f64_16x16x4f64((double)vf.at(t), gd[t], cc, 0, 0, 0);
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const bool ok = j0 + 4 * r + g < n;
+            const double p = ok ? exp2_f64(fma(s[r], kBwdScaleLog2e, -sd[0])) : 0.0;
+            const double gv = ok ? p * fma(cc[r], 0.125, sd[1]) : 0.0;       // g_ij of query c and key 4r + g
+#pragma unroll
+            for (int dt = 0; dt < 4; ++dt) acc[dt] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)k4[r].at(dt), gv, acc[dt], 0, 0, 0);
+        }
+    }
+    // the four waves' shares in wave order: thread (wave w, lane) adds up register r = w of every accumulator, which
+    // gives it the four elements 16 w + 4 g .. + 3 of query c
+#pragma unroll
+    for (int dt = 0; dt < 4; ++dt)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) s_acc[wave][4 * dt + r][lane] = acc[dt][r];
+    __syncthreads();
+    float v[4];
+#pragma unroll
+    for (int dt = 0; dt < 4; ++dt) {
+        double t = 0.0;
+#pragma unroll
+        for (int w = 0; w < kBwdWaves; ++w) t += s_acc[w][4 * dt + wave][lane];
+        v[dt] = (float)t;
+    }
+    if (qi >= 0) bwd_store4(static_cast<T*>(P.dQ) + ((size_t)head * L + qi) * kD + 16 * wave + 4 * g, v);
+}
+
 // ---- dK and dV of blocks of 16 KS keys over all kept queries of the head, and dQ over those keys.
 // Wave w takes keys 16 (w % KS) .. + 15 of the block and, of the two query tiles of a group, both (KS = 4) or tile
 // w / 2 (KS = 2).  Scores are formed upright (queries on the rows), so that a lane's four p and g values are,
@@ -416,8 +534,7 @@ __device__ __forceinline__ void combine_stats(const BwdParams& P, int head, int 
 // the waves put their g values into LDS; wave w then takes elements 16 w .. + 15 of both tiles over all keys of the
 // block, so that nothing has to be added up across waves.
 // grid (key splits, heads), blocks2 key blocks per work-group, which adds to the dQ it wrote for the block before.
-// MANY: more than kBwdKeepStats kept queries: the statistics of a group are put together anew for every block.
-template <typename T, int KS, bool MANY>
+template <typename T, int KS, BwdForm FORM>
 __global__ __launch_bounds__(kBwdThreads, 2)
 void bwd_main_kernel(const BwdParams P)
 {
@@ -450,12 +567,6 @@ void bwd_main_kernel(const BwdParams P)
         kn.load(Kh + (size_t)row * kD + 16 * (lo >> 4));
         vn.load(Vh + (size_t)row * kD + 16 * (lo >> 4));
     };
-    auto stat_of = [&](int t) -> bwd_x2 {
-        // an absent entry of the list: no weight on any key
-        double lse = INFINITY, D = 0.0;
-        if (kept_row(P, head, t, n, ub) >= 0) combine_stats(P, head, t, lse, D);
-        return bwd_x2{lse, -0.125 * D};
-    };
     if (r_first < n) {
         // the mean fill's share of dV: every valid v_j receives 1/n of each filled row's gradient
         if (tid < kD) {
@@ -467,11 +578,11 @@ void bwd_main_kernel(const BwdParams P)
             }
             s_gm[tid] = t / (double)n;
         }
-        if (!MANY) for (int t = tid; t < P.u_pad; t += kBwdThreads) s_stat[t] = stat_of(t);
+        if (FORM == kFused) for (int t = tid; t < P.u_pad; t += kBwdThreads) s_stat[t] = stat_of(P, head, t, n, ub);
         request(r_first);
     }
 
-    if (r_first >= n && P.dq_part) {                                 // no valid key here: zeros
+    if (FORM != kKeysOnly && r_first >= n && P.dq_part) {                                 // no valid key here: zeros
         for (int t = tid >> 4; t < ub; t += kBwdThreads / 16) {
             bwd_x2* dp = reinterpret_cast<bwd_x2*>(P.dq_part + (((size_t)head * P.S2 + split) * P.u_pad + t) * kD + 4 * (tid & 15));
             dp[0] = dp[1] = bwd_x2{0.0, 0.0};
@@ -507,7 +618,7 @@ void bwd_main_kernel(const BwdParams P)
             // B operands of the score products: this lane's key row.  A row beyond n stands for the last valid one:
             // what comes of it is not stored, and for dQ the staged row is zero.
             double kd[16], vd[16];
-            if (slot == 0) {                                         // the block's keys as float for the dQ product
+            if (FORM != kKeysOnly && slot == 0) {                    // the block's keys as float for the dQ product
                 const int lo = opaque(lane), c = lo & 15, g = lo >> 4;
                 float4* kr = reinterpret_cast<float4*>(sK + (16 * ks + c) * kBwdKRow + 16 * g);
                 const bool ok = r0 + 16 * ks + c < n;
@@ -525,6 +636,10 @@ void bwd_main_kernel(const BwdParams P)
             // in such an order that a lane's four values are elements e_own .. e_own + 3 of query c); two MFMA chains,
             // 16 keys at a time, the next 16 keys' operands read while these products run
             auto finish_group = [&](int q0) {
+                if (FORM == kKeysOnly) {
+                    if (stage_next) qs.put(sQ, sG);
+                    return;
+                }
                 const int lo = opaque(lane), c = lo & 15, g = lo >> 4;
                 const double* gr = sg + c * GR + g;
                 const float* kr = sK + g * kBwdKRow + 16 * wave + 4 * (c & 3) + (c >> 2);
@@ -583,8 +698,10 @@ void bwd_main_kernel(const BwdParams P)
                 q_next = q0 + kBwdGroup < ub ? q0 + kBwdGroup : 0;
                 stage_next = ub > kBwdGroup && (q_next > 0 || more); // work-group-uniform
                 if (stage_next) qs.find(P, head, q_next);
-                const bwd_x2* stat = s_stat + (MANY ? 0 : q0);
-                if (MANY && tid < kBwdGroup) s_stat[tid] = stat_of(q0 + tid);
+                const bwd_x2* stat = s_stat + (FORM == kFused ? q0 : 0);
+                if (FORM == kFusedMany && tid < kBwdGroup) s_stat[tid] = stat_of(P, head, q0 + tid, n, ub);
+                if (FORM == kKeysOnly && tid < kBwdGroup && q0 + (tid & ~(kBwdQ - 1)) < ub)      // (bwd_dq_kernel wrote whole tiles)
+                    s_stat[tid] = reinterpret_cast<const bwd_x2*>(P.stats)[(size_t)head * P.u_pad + q0 + tid];
                 lds_barrier();
                 {
                     const int lo = opaque(lane), c = lo & 15, g = lo >> 4;
@@ -594,8 +711,10 @@ void bwd_main_kernel(const BwdParams P)
                         if (q0 + 16 * tt >= ub) break;               // wave-uniform
                         double* g_out = sg + (16 * tt + g) * GR + 16 * ks + c;
                         if (!wave_live) {                            // (these keys take no part in dQ)
+                            if (FORM != kKeysOnly) {
 #pragma unroll
-                            for (int r = 0; r < 4; ++r) g_out[4 * r * GR] = 0.0;
+                                for (int r = 0; r < 4; ++r) g_out[4 * r * GR] = 0.0;
+                            }
                             continue;
                         }
                         bwd_x4 s, cc;
@@ -619,7 +738,10 @@ void bwd_main_kernel(const BwdParams P)
                             gv[r] = fma(cc[r], 0.125, sd[1]);
                         }
 #pragma unroll
-                        for (int r = 0; r < 4; ++r) { gv[r] *= p[r]; g_out[4 * r * GR] = gv[r]; }
+                        for (int r = 0; r < 4; ++r) {
+                            gv[r] *= p[r];
+                            if (FORM != kKeysOnly) g_out[4 * r * GR] = gv[r];
+                        }
 #pragma unroll
                         for (int r = 0; r < 4; ++r) {
                             if (r < 3) { fetch(r + 1); __builtin_amdgcn_sched_barrier(0); }
@@ -633,7 +755,7 @@ void bwd_main_kernel(const BwdParams P)
                 }
                 // under this group's dQ travel: what was written of it for the block before, and the rows of what
                 // comes next
-                if (blk > 0) {
+                if (FORM != kKeysOnly && blk > 0) {
                     const int lo = opaque(lane), e_own = 16 * wave + 4 * (lo >> 4);
 #pragma unroll
                     for (int i = 0; i < kBwdTiles; ++i) {
@@ -759,11 +881,13 @@ void bwd_dq_reduce_kernel(const BwdParams P)
 template <typename T>
 static hipError_t raise_bwd_limits()
 {
-    static std::atomic<uint64_t> raised[4];            // per instantiation: devices already served
-    const void* fn[4] = {(const void*)bwd_stats_kernel<T>, (const void*)bwd_main_kernel<T, 4, false>,
-                         (const void*)bwd_main_kernel<T, 2, false>, (const void*)bwd_main_kernel<T, 4, true>};
-    const int lds[4] = {kBwdStatsLds, BwdShare<4>::kLds, BwdShare<2>::kLds, BwdShare<4>::kLds};
-    for (int k = 0; k < 4; ++k) { const hipError_t e = ensure_lds_limit(fn[k], lds[k], raised[k]); if (e != hipSuccess) return e; }
+    constexpr int N = 6;
+    static std::atomic<uint64_t> raised[N];            // per instantiation: devices already served
+    const void* fn[N] = {(const void*)bwd_stats_kernel<T>, (const void*)bwd_main_kernel<T, 4, kFused>,
+                         (const void*)bwd_main_kernel<T, 2, kFused>, (const void*)bwd_main_kernel<T, 4, kFusedMany>,
+                         (const void*)bwd_main_kernel<T, 4, kKeysOnly>, (const void*)bwd_main_kernel<T, 2, kKeysOnly>};
+    const int lds[N] = {kBwdStatsLds, BwdShare<4>::kLds, BwdShare<2>::kLds, BwdShare<4>::kLds, BwdShare<4>::kLds, BwdShare<2>::kLds};
+    for (int k = 0; k < N; ++k) { const hipError_t e = ensure_lds_limit(fn[k], lds[k], raised[k]); if (e != hipSuccess) return e; }
     return hipSuccess;
 }
 hipError_t init_backward()
@@ -779,30 +903,39 @@ static hipError_t launch_bwd_t(const BwdParams& P, int BH, int ks, hipStream_t s
     if (e != hipSuccess) return e;
     const dim3 grid(P.S2, BH), block(kBwdThreads);
     hipLaunchKernelGGL(bwd_stats_kernel<T>, dim3(P.S1, P.n_group, BH), block, kBwdStatsLds, stream, P);
-    if (P.u_pad > kBwdKeepStats)
-        hipLaunchKernelGGL((bwd_main_kernel<T, 4, true>), grid, block, BwdShare<4>::kFixed + kBwdGroup * 16, stream, P);
+    if (P.stats) {
+        hipLaunchKernelGGL(bwd_dq_kernel<T>, dim3(P.u_pad / kBwdQ, BH), block, 0, stream, P);
+        if (ks == 4) hipLaunchKernelGGL((bwd_main_kernel<T, 4, kKeysOnly>), grid, block, BwdShare<4>::kFixed + kBwdGroup * 16, stream, P);
+        else         hipLaunchKernelGGL((bwd_main_kernel<T, 2, kKeysOnly>), grid, block, BwdShare<2>::kFixed + kBwdGroup * 16, stream, P);
+    } else if (P.u_pad > kBwdKeepStats)
+        hipLaunchKernelGGL((bwd_main_kernel<T, 4, kFusedMany>), grid, block, BwdShare<4>::kFixed + kBwdGroup * 16, stream, P);
     else if (ks == 4)
-        hipLaunchKernelGGL((bwd_main_kernel<T, 4, false>), grid, block, BwdShare<4>::kFixed + P.u_pad * 16, stream, P);
+        hipLaunchKernelGGL((bwd_main_kernel<T, 4, kFused>), grid, block, BwdShare<4>::kFixed + P.u_pad * 16, stream, P);
     else
-        hipLaunchKernelGGL((bwd_main_kernel<T, 2, false>), grid, block, BwdShare<2>::kFixed + P.u_pad * 16, stream, P);
+        hipLaunchKernelGGL((bwd_main_kernel<T, 2, kFused>), grid, block, BwdShare<2>::kFixed + P.u_pad * 16, stream, P);
     if (P.dq_part) hipLaunchKernelGGL(bwd_dq_reduce_kernel<T>, dim3(P.u_pad / kBwdQ, BH), dim3(256), 0, stream, P);
     return hipGetLastError();
 }
 
+// Time of `wgs` equal work-groups, two per CU in rounds of 512, in times of one round (a CU with one work-group takes
+// 0.6 of the time of one with two).
+static double bwd_rounds(int64_t wgs)
+{
+    const int64_t half = (wgs + 255) / 256;
+    return (double)(half / 2) + (half & 1 ? 0.6 : 0.0);
+}
 // Key blocks per work-group for `rows` (head, query group) pairs of `n_blocks` blocks: the number that takes the
-// least time when work-groups run two per CU in rounds of 512 (a CU with one work-group takes 0.6 of the time of
-// one with two), each paying `fixed` (staging, first loads; in units of a block's work) beside its blocks.  At most
-// 64 splits.
-static int blocks_per_split(int64_t rows, int n_blocks, double fixed, double* cost_out)
+// least time, each work-group paying `fixed` (staging, first loads; in units of a block's work) beside its blocks.  At
+// most `max_split` splits.
+static int blocks_per_split(int64_t rows, int n_blocks, int64_t max_split, double fixed, double* cost_out)
 {
     int best = n_blocks;
     double best_cost = 1e300;
     for (int r = 1; r <= 8; ++r) {                              // half rounds of the CUs aimed at
         int64_t S = 256 * r / rows;
-        S = S < 1 ? 1 : (S > kBwdMaxSplit ? kBwdMaxSplit : (S > n_blocks ? n_blocks : S));
+        S = S < 1 ? 1 : (S > max_split ? max_split : (S > n_blocks ? n_blocks : S));
         const int per = (int)((n_blocks + S - 1) / S);
-        const int64_t wgs = rows * ((n_blocks + per - 1) / per), half = (wgs + 255) / 256;
-        const double cost = ((double)(half / 2) + (half & 1 ? 0.6 : 0.0)) * (per + fixed);
+        const double cost = bwd_rounds(rows * ((n_blocks + per - 1) / per)) * (per + fixed);
         if (cost < best_cost) { best_cost = cost; best = per; }
     }
     *cost_out = best_cost;
@@ -819,28 +952,58 @@ BwdPlan make_bwd_plan(const psa_shape_t& s, int u_stride)
     const int tiles = p.u_pad / kBwdQ;
     double cost;
     const int n_blocks = (s.L_K + kBwdKeys - 1) / kBwdKeys;
-    p.blocks1 = blocks_per_split(BH * p.n_group, n_blocks, 4.0 / (tiles < 4 ? tiles : 4), &cost);
+    p.blocks1 = blocks_per_split(BH * p.n_group, n_blocks, kBwdMaxSplit, 4.0 / (tiles < 4 ? tiles : 4), &cost);
     p.S1 = (n_blocks + p.blocks1 - 1) / p.blocks1;
     // The gradient kernel: blocks of 64 keys, or of 32 with the waves sharing out the query tiles as well where
     // there are too few heads and keys to give every CU work of the larger kind.  In units of one query tile on 4
     // waves (80 MFMAs, 2.2 us); beside its tiles a work-group pays about two such units, and the smaller blocks a
     // little more for adding up the slots' shares and for more splits of dQ.
+    // Fused form: the float64 partial sums of dQ, one set per key split, stay within a quarter of the memory that the
+    // call's own seven tensors take, or 256 MiB where that is more (without a bound one sequence of 16384 frames with
+    // half of its queries kept asked for 2.1 GB beside tensors of 17 MB).  They are written for every key block, read
+    // for every one after a work-group's first, and read by the reduce kernel: a unit for 50 MB.
+    const size_t split_bytes = (size_t)BH * p.u_pad * kD * sizeof(double);
+    const size_t tensors = (size_t)BH * s.L_K * kD * (s.dtype == PSA_F32 ? 4 : 2) * 7;       // Q, K, V, dOut, dQ, dK, dV
+    const size_t fit = (tensors / 4 > kBwdPartBytes ? tensors / 4 : kBwdPartBytes) / split_bytes;
+    const int max_split = fit < (size_t)kBwdMaxSplit ? (int)fit : kBwdMaxSplit;
     double best = 1e300;
-    for (int ks = 4; ks >= (p.u_pad > kBwdKeepStats ? 4 : 2); ks >>= 1) {
+    for (int ks = 4; ks >= (p.u_pad > kBwdKeepStats ? 4 : 2) && max_split > 0; ks >>= 1) {
         const int slots = kBwdWaves / ks, nb = (s.L_K + 16 * ks - 1) / (16 * ks);
         const double per_block = (double)((tiles + slots - 1) / slots) + (slots > 1 ? 0.5 : 0.0);
-        const int per = blocks_per_split(BH, nb, 2.0 / per_block, &cost);
+        const int per = blocks_per_split(BH, nb, max_split, 2.0 / per_block, &cost);
         if (cost * per_block < best * 0.95) {
             best = cost * per_block;
             p.ks = ks; p.blocks2 = per; p.S2 = (nb + per - 1) / per;
         }
     }
+    p.keys_only = 0;
+    if (best < 1e300) {
+        const int nb = (s.L_K + 16 * p.ks - 1) / (16 * p.ks);
+        best = best * (p.u_pad > kBwdKeepStats ? 1.09 : 1.0) + (double)split_bytes * (2 * nb) / 50e6;
+    }
+    // The form without partial sums: 0.8 of the products in bwd_main_kernel, one block a work-group, and 0.6 of them in
+    // bwd_dq_kernel (a work-group for each query tile, all keys).  It is taken where it is estimated to be faster: where the
+    // bound on the partial sums leaves too few key splits, or where few heads with many kept queries do not fill the
+    // CUs with blocks of 64 keys.  Measured (whole call), fused against this form: B=16 H=4 L=512, 256 kept 168 | 203
+    // us; B=8 H=8 L=2048, 1024 kept 2381 | 2672; B=4 H=4 L=1600, 800 kept 483 | 551; B=1 H=4 L=2000, 1000 kept 338 | 209;
+    // B=1 H=8 L=4096, 2048 kept 1412 (in the 32 splits that fit) | 1355; L=16384, 8192 kept 76500 (8 splits) | 20970.
+    const double dq = bwd_rounds(BH * tiles) * (0.6 * n_blocks + 1.0) + 1.5;
+    for (int ks = 4; ks >= 2; ks >>= 1) {
+        const int slots = kBwdWaves / ks, nb = (s.L_K + 16 * ks - 1) / (16 * ks);
+        const double per_block = (double)((tiles + slots - 1) / slots) + (slots > 1 ? 0.5 : 0.0);
+        const double c = bwd_rounds(BH * nb) * (0.8 * per_block + 1.0) + dq;
+        if (c < best * (p.keys_only ? 0.95 : 1.0)) {
+            best = c;
+            p.keys_only = 1; p.ks = ks; p.blocks2 = 1; p.S2 = nb;
+        }
+    }
     // dQ goes straight to memory where one block holds all keys of a head
-    p.parts = p.S2 > 1 || p.blocks2 > 1;
+    p.parts = !p.keys_only && (p.S2 > 1 || p.blocks2 > 1);
     auto al = [](size_t x) { return (x + 255) & ~(size_t)255; };
     size_t off = 0;
     p.off_stats_part = off; off += al((size_t)BH * p.S1 * p.u_pad * 3 * sizeof(double));
     p.off_gsum = off;       off += al((size_t)BH * p.S1 * kD * sizeof(double));
+    p.off_stats = off;      off += p.keys_only ? al((size_t)BH * p.u_pad * 2 * sizeof(double)) : 0;
     p.off_dq_part = off;    off += p.parts ? al((size_t)BH * p.S2 * p.u_pad * kD * sizeof(double)) : 0;
     p.total = off;
     return p;
@@ -857,6 +1020,7 @@ hipError_t launch_backward(const psa_shape_t& s, const BwdPlan& bp, const void* 
     P.stats_part = reinterpret_cast<double*>(w + bp.off_stats_part);
     P.gsum_part = reinterpret_cast<double*>(w + bp.off_gsum);
     P.dq_part = bp.parts ? reinterpret_cast<double*>(w + bp.off_dq_part) : nullptr;
+    P.stats = bp.keys_only ? reinterpret_cast<double*>(w + bp.off_stats) : nullptr;
     P.H = s.H; P.L = s.L_K; P.u_stride = u_stride; P.u_pad = bp.u_pad; P.n_group = bp.n_group;
     P.S1 = bp.S1; P.blocks1 = bp.blocks1; P.S2 = bp.S2; P.blocks2 = bp.blocks2;
     P.fill = fill;

@@ -128,10 +128,10 @@ hipError_t launch_prep_indices(const Plan& p, const Args& a, const Scratch& w); 
 
 // Gradients of stages a3 and a4 for a fixed index set (psa_backward.hip): groups of 64 kept queries, key
 // splits of blocks1 blocks of 64 keys (statistics) and blocks2 blocks of 16 ks keys (gradients), and the carving
-// of the workspace (parts: dQ goes through partial sums).
+// of the workspace (parts: dQ goes through partial sums; keys_only: a kernel of its own computes it).
 struct BwdPlan {
-    int n_group, u_pad, S1, blocks1, S2, blocks2, ks, parts;
-    size_t off_stats_part, off_gsum, off_dq_part, total;
+    int n_group, u_pad, S1, blocks1, S2, blocks2, ks, parts, keys_only;
+    size_t off_stats_part, off_gsum, off_stats, off_dq_part, total;
 };
 BwdPlan make_bwd_plan(const psa_shape_t& s, int u_stride);
 hipError_t launch_backward(const psa_shape_t& s, const BwdPlan& bp, const void* Q, const void* K, const void* V,
