@@ -76,40 +76,58 @@ static void split_f32(Plan* p, int n_tiles)
 
 // Streaming measure kernel with `cpw` chunks per work-group: length of the sorted list each work-group hands on, or 0
 // where a select kernel follows.  Lists only where the attend prologue can merge them (up to 8 per head; no select
-// launch: 8.3 us at B=8 H=8 L=2048), the ranking at the end of a work-group is short (all pairs of up to 256 queries,
-// a microsecond), and the candidates are few: every attend work-group of the head merges them (with half of 2048
-// queries kept 134 us with lists against 123 us with the select kernel).
-static int stream_list_len(const Plan& p, int cpw)
+// launch: 8.3 us at B=8 H=8 L=2048), the ranking at the end of a work-group is short (`most` queries at most: kListMax,
+// or kListMaxF32 for float32; a microsecond), and the candidates are few: every attend work-group of the head merges
+// them (with half of 2048 queries kept 134 us with lists against 123 us with the select kernel).
+static int stream_list_len(const Plan& p, int cpw, int most)
 {
     const int groups = (p.n_chunk + cpw - 1) / cpw, span = cpw * kMeasureQueries;
     const int len = p.u_max < span ? p.u_max : span;
-    return p.U <= kPipeMaxSamples && groups <= 8 && span <= kListMax && (int64_t)groups * len <= 512 ? len : 0;
+    return p.U <= kPipeMaxSamples && groups <= 8 && span <= most && (int64_t)groups * len <= 512 ? len : 0;
 }
 
 // Streaming measure kernel, float32: consecutive chunks of a head that one of its persistent work-groups takes, by the
-// most chunks that a CU ends up with (half a chunk more to start a work-group, and where a select kernel follows).
-// A float32 work-group (256-byte rows) reaches the rate of the CU's return path alone and only takes turns with a
-// second one: B=16 H=4 L=1000 63.0 us in 512 work-groups of 2 chunks, 59.3 us in 256 of 4.  Of equals the longer one has
-// fewer lists.  With lengths a fifth of the work-groups is taken to be padding, which leaves at once.  Means of six
-// ragged batches, against two work-groups per CU: B=24 H=4 L=750 76.0 -> 63.5 us, B=20 H=4 L=600 49.4 -> 41.5 us, B=12
-// H=8 L=520 47.5 -> 40.3 us.  bfloat16 work-groups share a CU to advantage (B=8 H=8 L=2048 55.8 us in 512, 63.4 in 256).
-static int stream_cut_f32(const Plan& p, bool ragged)
+// chunks of the busiest CU when every item is full.  A float32 work-group (256-byte rows) reaches the rate of the CU's
+// return path alone and only takes turns with a second one (B=16 H=4 L=1000: 30.2 us in 256 work-groups of 4 chunks, 33.5
+// in 512 of 2).  A head's work-groups all run on one XCD, 32 CUs, the whole ones of all its heads first and the last,
+// shorter ones behind them; those share a CU with one another where enough CUs are left for them, else with a whole one.
+// In chunks: a quarter for each further work-group of a CU, 0.9 for the select kernel where no list fits.  Of cuts within 3 % the
+// finer one: it loses less where items are shorter than L.
+// Lengths are known on the device only, so calls with and without them take the same cut; one that counted on a fifth of
+// padding took 54 us for the measure of a full B=24 H=4 L=750 where two work-groups per CU take 44 and this one 35.
+// Whole call on full batches, two work-groups per CU | this rule: B=24 H=4 L=750 90 | 81 us, B=12 H=8 L=520 54 | 49, B=9 H=4
+// L=1700 87 | 76, B=1 H=2 L=9000 79 | 71, B=36 H=4 L=800 113 | 121 (the most lost in 35 shapes; 4 % gained in the mean).
+// Ragged batches of few items lose up to an eighth against the cut that counted on padding (B=5 H=4 L=3000 70 | 78 us).
+// bfloat16 work-groups share a CU to advantage (B=8 H=8 L=2048 55.8 us in 512, 63.4 in 256).
+static float stream_cost_f32(const Plan& p, int cpw)
 {
-    float best = INFINITY;
-    int pick = 1;
-    for (int cpw = 1; cpw <= 16 && cpw <= p.n_chunk; ++cpw) {
-        const int64_t wgs = (int64_t)p.BH * ((p.n_chunk + cpw - 1) / cpw);
-        const int64_t busy = ragged ? (4 * wgs + 4) / 5 : wgs;
-        const float cost = (float)((busy + 255) / 256) * ((float)cpw + 0.5f) + (stream_list_len(p, cpw) > 0 ? 0.f : 0.5f);
-        if (cost <= best) { best = cost; pick = cpw; }
+    const int heads = (p.BH + 7) / 8, span = cpw * kMeasureQueries;      // heads of an XCD
+    int whole = heads * (p.L / span), part = p.L % span ? heads : 0;     // its work-groups of cpw chunks, and shorter ones
+    const float rest = (float)(p.L % span) / (float)kMeasureQueries;     // chunks of those
+    float longest = (float)cpw;
+    if (whole == 0) { whole = part; part = 0; longest = rest; }
+    const int rounds = (whole + 31) / 32, left = 32 * rounds - whole;    // CUs that have one whole work-group less than others
+    float cost = longest * (float)rounds + 0.25f * (float)(rounds - 1);
+    if (part > left) {
+        if (rounds == 1 && left >= 4 && part <= 2 * left) cost = fmaxf(longest, 2.f * rest + 0.25f);
+        else cost += rest + 0.25f;
     }
-    return pick;
+    return cost + (stream_list_len(p, cpw, kListMaxF32) > 0 ? 0.f : 0.9f);
+}
+static int stream_cut_f32(const Plan& p)
+{
+    const int most = p.n_chunk < 16 ? p.n_chunk : 16;
+    float best = INFINITY;
+    for (int cpw = 1; cpw <= most; ++cpw) best = fminf(best, stream_cost_f32(p, cpw));
+    int cpw = 1;
+    while (cpw < most && stream_cost_f32(p, cpw) > 1.03f * best) ++cpw;
+    return cpw;
 }
 
 // How much of a plan is cut anew (see make_plan).
 enum Cuts { kFirstCuts = 0, kShortChunks = 1, kStreamCut = 2, kSplitCut = 3 };
 
-static void build_plan(const psa_shape_t* s, URule urule, int u_stride, bool ragged, Cuts cuts, Plan* p)
+static void build_plan(const psa_shape_t* s, URule urule, int u_stride, Cuts cuts, Plan* p)
 {
     p->given_indices = u_stride > 0;
     p->B = s->B; p->H = s->H; p->L = s->L_K; p->U = s->U; p->dtype = s->dtype;
@@ -206,7 +224,7 @@ static void build_plan(const psa_shape_t* s, URule urule, int u_stride, bool rag
         while (p->chunks_per_wg < p->n_chunk &&
                (int64_t)p->BH * ((p->n_chunk + p->chunks_per_wg - 1) / p->chunks_per_wg) > slots) ++p->chunks_per_wg;
     }
-    else if (!p->given_indices && p->dtype == PSA_F32 && cuts >= kStreamCut) p->chunks_per_wg = stream_cut_f32(*p, ragged);
+    else if (!p->given_indices && p->dtype == PSA_F32 && cuts >= kStreamCut) p->chunks_per_wg = stream_cut_f32(*p);
     else if (!p->given_indices) {
         // about two persistent work-groups per CU, each on consecutive chunks of one head
         const int64_t chunks_all = (int64_t)p->BH * p->n_chunk;
@@ -225,7 +243,7 @@ static void build_plan(const psa_shape_t* s, URule urule, int u_stride, bool rag
     // Streamed heads: a work-group of the measure kernel ranks the queries of its own chunks and hands on its
     // best u as one sorted list, exactly as a chunk of the LDS kernel does (see stream_list_len)
     if (!p->measure_lds && !p->given_indices) {
-        const int len = stream_list_len(*p, p->chunks_per_wg);
+        const int len = stream_list_len(*p, p->chunks_per_wg, p->dtype == PSA_F32 && cuts >= kStreamCut ? kListMaxF32 : kListMax);
         if (len > 0) {
             p->cand_len = len; p->n_lists = (p->n_chunk + p->chunks_per_wg - 1) / p->chunks_per_wg; p->stream_lists = 1;
         }
@@ -278,15 +296,15 @@ static void build_plan(const psa_shape_t* s, URule urule, int u_stride, bool rag
 // 128 queries, records for every split): callers keep workspaces by it, and the static scratch admits calls by it.  The
 // present rules are taken as far as what they need fits; short heads in small chunks may need more (at most 512
 // chunks of a few KB).
-bool make_plan(const psa_shape_t* s, URule urule, int u_stride, bool ragged, Plan* p)
+bool make_plan(const psa_shape_t* s, URule urule, int u_stride, Plan* p)
 {
     if (check_shape(s) != PSA_OK) return false;
     if (u_stride <= 0 && !good_rule(urule)) return false;
     if (u_stride < 0 || u_stride > s->L_K) return false;
-    build_plan(s, urule, u_stride, ragged, kFirstCuts, p);
+    build_plan(s, urule, u_stride, kFirstCuts, p);
     const size_t size = p->total;
     for (int cuts = kSplitCut; cuts >= kShortChunks; --cuts) {
-        build_plan(s, urule, u_stride, ragged, (Cuts)cuts, p);
+        build_plan(s, urule, u_stride, (Cuts)cuts, p);
         if (p->total <= size) break;
     }
     if (p->total < size) p->total = size;
@@ -334,7 +352,7 @@ static int run(const void* Q, const void* K, const void* V, const int32_t* lengt
     if (rc != PSA_OK) return rc;
     if (misaligned(sample_idx, 4)) return PSA_ERR_ALIGN;
     Plan p;
-    if (!make_plan(shape, urule, 0, lengths != nullptr, &p)) return PSA_ERR_SHAPE;
+    if (!make_plan(shape, urule, 0, &p)) return PSA_ERR_SHAPE;
     if (workspace_bytes < p.total) return PSA_ERR_WORKSPACE;
     if (checks_only) return PSA_OK;
 
@@ -382,7 +400,7 @@ static int run_indices(const void* Q, const void* K, const void* V, const int32_
     if (rc != PSA_OK) return rc;
     if (misaligned(sel, 4) || misaligned(u, 4)) return PSA_ERR_ALIGN;
     Plan p;
-    if (!make_plan(shape, URule{PSA_U_LOG, 1.0}, u_stride, lengths != nullptr, &p)) return PSA_ERR_SHAPE;
+    if (!make_plan(shape, URule{PSA_U_LOG, 1.0}, u_stride, &p)) return PSA_ERR_SHAPE;
     if (workspace_bytes < p.total) return PSA_ERR_WORKSPACE;
 
     Args a;
@@ -459,7 +477,7 @@ int probsparse_attn_fwd_static(const void* Q, const void* K, const void* V, cons
     if (rc != PSA_OK) return rc;
     Plan p;
     if (!good_rule(URule{PSA_U_LOG, c})) return PSA_ERR_ARG;
-    if (!make_plan(shape, URule{PSA_U_LOG, c}, 0, lengths != nullptr, &p)) return PSA_ERR_SHAPE;
+    if (!make_plan(shape, URule{PSA_U_LOG, c}, 0, &p)) return PSA_ERR_SHAPE;
     if (p.total > kStaticScratchBytes) return PSA_ERR_WORKSPACE;
     if (!Q || !K || !V || !sample_idx || !out) return PSA_ERR_NULL;
     void* ws = nullptr;
@@ -527,27 +545,27 @@ int probsparse_mhsa_fwd(const void* X, const psa_mhsa_weights_t* weights, const 
 size_t probsparse_attn_workspace_bytes(const psa_shape_t* shape, double c)
 {
     psa::Plan p;
-    return psa::make_plan(shape, psa::URule{PSA_U_LOG, c}, 0, false, &p) ? p.total : 0;
+    return psa::make_plan(shape, psa::URule{PSA_U_LOG, c}, 0, &p) ? p.total : 0;
 }
 
 int32_t probsparse_u_max(const psa_shape_t* shape, double c)
 {
     psa::Plan p;
-    return psa::make_plan(shape, psa::URule{PSA_U_LOG, c}, 0, false, &p) ? p.u_max : 0;
+    return psa::make_plan(shape, psa::URule{PSA_U_LOG, c}, 0, &p) ? p.u_max : 0;
 }
 
 size_t probsparse_attn_workspace_bytes_opt(const psa_shape_t* shape, const psa_options_t* opt)
 {
     psa::Plan p;
     if (!opt || (opt->fill != PSA_FILL_MEAN && opt->fill != PSA_FILL_VALUE)) return 0;
-    return psa::make_plan(shape, psa::URule{opt->u_rule, opt->factor}, 0, false, &p) ? p.total : 0;
+    return psa::make_plan(shape, psa::URule{opt->u_rule, opt->factor}, 0, &p) ? p.total : 0;
 }
 
 int32_t probsparse_u_max_opt(const psa_shape_t* shape, const psa_options_t* opt)
 {
     psa::Plan p;
     if (!opt) return 0;
-    return psa::make_plan(shape, psa::URule{opt->u_rule, opt->factor}, 0, false, &p) ? p.u_max : 0;
+    return psa::make_plan(shape, psa::URule{opt->u_rule, opt->factor}, 0, &p) ? p.u_max : 0;
 }
 
 int probsparse_attn_fwd_opt(const void* Q, const void* K, const void* V, const int32_t* lengths,
@@ -563,7 +581,7 @@ size_t probsparse_attn_with_indices_workspace_bytes(const psa_shape_t* shape, in
 {
     psa::Plan p;
     if (u_stride < 1) return 0;
-    return psa::make_plan(shape, psa::URule{PSA_U_LOG, 1.0}, u_stride, false, &p) ? p.total : 0;
+    return psa::make_plan(shape, psa::URule{PSA_U_LOG, 1.0}, u_stride, &p) ? p.total : 0;
 }
 
 int probsparse_attn_fwd_with_indices(const void* Q, const void* K, const void* V, const int32_t* lengths,
@@ -652,7 +670,7 @@ int probsparse_describe_plan(const psa_shape_t* shape, const psa_options_t* opt,
     const URule urule = opt ? URule{opt->u_rule, opt->factor} : URule{PSA_U_LOG, 1.0};
     if (u_stride < 0) return PSA_ERR_ARG;
     if (u_stride == 0 && !good_rule(urule)) return PSA_ERR_ARG;
-    if (!make_plan(shape, urule, u_stride, false, &p)) return u_stride > 0 ? PSA_ERR_ARG : PSA_ERR_SHAPE;
+    if (!make_plan(shape, urule, u_stride, &p)) return u_stride > 0 ? PSA_ERR_ARG : PSA_ERR_SHAPE;
     const char* measure = p.given_indices ? "none" : p.measure_lds == 2 ? "lds_half" : p.measure_lds == 1 ? "lds" : "stream";
     const char* select = p.given_indices ? (p.given_inline ? "given_inline" : "given_prep")
                        : p.n_seg > 0 ? "segments" : p.fused_select ? "lists" : "kernel";

@@ -26,7 +26,8 @@ constexpr int kSegMax = 8;                 // segments per head of the segment-s
 constexpr int kSegKeys = 2048;             // most queries of one segment
 constexpr int kSegCandMax = 256;           // longest list a segment hands on
 constexpr int kPipeMaxSamples = 64;        // samples per query up to which the streaming measure kernel stages a chunk's indices in LDS
-constexpr int kListMax = 256;              // most queries a work-group of the streaming measure kernel ranks among themselves
+constexpr int kListMax = 256;              // most queries a work-group of the streaming measure kernel ranks among themselves ...
+constexpr int kListMaxF32 = 320;           // ... for float32 tensors (two lanes for each of them: all 640)
 
 struct bf16_t { uint16_t x; };
 
@@ -109,8 +110,7 @@ inline hipError_t ensure_lds_limit(const void* fn, int bytes, std::atomic<uint64
     return e;
 }
 
-// ragged: the call has lengths (which cut the streaming measure kernel takes; the workspace's layout does not depend on it).
-bool make_plan(const psa_shape_t* s, URule urule, int u_stride, bool ragged, Plan* p);
+bool make_plan(const psa_shape_t* s, URule urule, int u_stride, Plan* p);
 Scratch carve(const Plan& p, void* workspace);
 
 // One-time, per-device set-up of the kernels that need it (dynamic LDS limits); the launch

@@ -386,7 +386,9 @@ void measure_pipe_kernel(const T* __restrict__ Q, const T* __restrict__ K, const
     constexpr int NCH = RT::kRowBytes / 128;      // 16-byte chunks per lane: 8 lanes cover 128 bytes of a row
     constexpr int NQL = kMeasureQueries * RT::kRowBytes / 1024;     // 16-byte loads per loader lane for 64 rows: 8 or 16
     // (order key, ~position) of the measures of this work-group's queries, for its candidate list (cand != nullptr)
-    __shared__ unsigned long long s_rank[kListMax], s_list[kListMax];
+    constexpr int RMAX = sizeof(T) == 4 ? kListMaxF32 : kListMax;   // queries ranked, in lists of one chunk each
+    static_assert(2 * RMAX <= kPipeThreads, "two lanes per query");
+    __shared__ unsigned long long s_rank[RMAX], s_list[RMAX];
     __shared__ double s_vtot[kD];                 // column sums of V over all chunks of this work-group (with the list)
     __shared__ int s_clean[2];                    // per stage: every query of the chunk is valid and every sample index usable
     extern __shared__ __attribute__((aligned(16))) unsigned char s_stage[];    // [2][ idx [64][Us] | q [64][row bytes] ]
@@ -427,7 +429,7 @@ void measure_pipe_kernel(const T* __restrict__ Q, const T* __restrict__ K, const
         return;
     }
     // n > 0 from here on
-    if (cand_out) for (int t = tid; t < kListMax; t += kPipeThreads) s_rank[t] = 0ull;
+    if (cand_out) for (int t = tid; t < RMAX; t += kPipeThreads) s_rank[t] = 0ull;
     if (tid < kD) s_vtot[tid] = 0.0;
 
     const T* Kh = K + (size_t)head * L * kD;
@@ -701,19 +703,19 @@ void measure_pipe_kernel(const T* __restrict__ Q, const T* __restrict__ K, const
     // this work-group's u largest, so it hands on its first cand_len queries in order of decreasing measure
     // (ties: lower index first) as (order key, query index) pairs.  The last barrier of the loop has made
     // every gather wave's keys visible.  Two steps: every chunk of 64 ranks its own keys (two lanes per key,
-    // 32 comparisons each) into a sorted list in LDS; then the up to 4 lists are merged, the position of an
+    // 32 comparisons each) into a sorted list in LDS; then the up to 4 (float32: 5) lists are merged, the position of an
     // entry being its own rank plus, per other list, the number of entries before it (a binary search per
     // list, four lanes per entry).  Ranking all 256 keys against each other took 3 us at the end of every
     // work-group; this takes under one.
     if (cand_out) {
-        const int n_ch = chunk_end - chunk0;                         // chunks in use: 1 .. 4 (kListMax / 64)
+        const int n_ch = chunk_end - chunk0;                         // chunks in use: 1 .. RMAX / 64
         const int n_pos = n_ch * kMeasureQueries;
         int n_here = n - chunk0 * kMeasureQueries;                   // valid queries of this work-group
         n_here = n_here < n_pos ? n_here : n_pos;
         const int keep = cand_len < kMeasureQueries ? cand_len : kMeasureQueries;    // entries a chunk's list can contribute
         {
-            const int h2 = tid & 1, pos = tid >> 1;                  // 512 gather lanes: two per position
-            const bool ok = tid < kPipeGatherWaves * 64 && pos < n_pos;
+            const int h2 = tid & 1, pos = tid >> 1;                  // two lanes per position
+            const bool ok = tid < 2 * RMAX && pos < n_pos;
             const unsigned long long mine = s_rank[ok ? pos : 0];
             const unsigned long long* row = s_rank + (ok ? pos & ~(kMeasureQueries - 1) : 0);
             int beat = 0;
@@ -732,14 +734,15 @@ void measure_pipe_kernel(const T* __restrict__ Q, const T* __restrict__ K, const
             const int lst = ci / keep, rk = ci - lst * keep;
             const bool ok = ci < n_ch * keep;
             const unsigned long long mine = ok ? s_list[lst * kMeasureQueries + rk] : 0ull;
-            int cnt = 0;
-            if (ok && c2 == lst) cnt = rk;
-            else if (ok && c2 < n_ch) {
-                const unsigned long long* other = s_list + c2 * kMeasureQueries;
-                int lo = 0, hi = keep;                               // first entry that does not come before mine
+            auto before = [&](int list) -> int {                     // entries of a list that come before mine
+                if (list == lst) return rk;
+                const unsigned long long* other = s_list + list * kMeasureQueries;
+                int lo = 0, hi = keep;
                 while (lo < hi) { const int mid = (lo + hi) >> 1; if (other[mid] > mine) lo = mid + 1; else hi = mid; }
-                cnt = lo;
-            }
+                return lo;
+            };
+            int cnt = ok && c2 < n_ch ? before(c2) : 0;
+            if (RMAX > 4 * kMeasureQueries && ok && c2 == 0 && n_ch > 4) cnt += before(4);
             cnt += __builtin_amdgcn_update_dpp(0, cnt, 0xB1, 0xF, 0xF, false);               // sum over the quad
             cnt += __builtin_amdgcn_update_dpp(0, cnt, 0x4E, 0xF, 0xF, false);
             if (ok && c2 == 0 && (unsigned)(mine >> 32) != 0u && cnt < cand_len) {

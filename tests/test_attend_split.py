@@ -94,3 +94,45 @@ def test_measure_cuts_against_oracle(B, H, L, U):
     for ragged in (False, True):
         cfg = W.small_config("cuts", B, H, L, U, 5.0, "f32", "mixture", ragged, max(1, L // 8), L)
         check_against_oracle(W.make_workload(cfg, seed=700 + L), label=f"B{B} H{H} L{L} ragged={ragged}")
+
+
+def _busiest_cu(B, H, L, cpw):
+    """Most chunks of 64 queries on one CU, float32 streamed measure, all items full: the work-groups of an eighth of
+    the heads in order over the 32 CUs of an XCD, the next one to the CU with the least, a quarter for each further one."""
+    load = [0.0] * 32
+    for first in range(0, (L + 63) // 64, cpw):
+        for _ in range((B * H + 7) // 8):
+            k = load.index(min(load))
+            load[k] += min(cpw, L / 64 - first) + (0.25 if load[k] else 0.0)
+    return max(load)
+
+
+@pytest.mark.parametrize("B,H,L", [(24, 4, 750), (20, 4, 600), (12, 8, 520), (16, 4, 1000), (9, 4, 1700), (5, 4, 3000), (22, 4, 1100),
+                                   (40, 4, 900), (1, 2, 9000), (7, 4, 2500), (1, 8, 10000)])
+def test_float32_measure_cut_loses_nothing_on_full_batches(B, H, L):
+    # against two work-groups per CU in equal shares; calls with and without lengths take the same cut
+    two = min(16, (B * H * ((L + 63) // 64) + 511) // 512)
+    assert _busiest_cu(B, H, L, int(plan(B, H, L, 35, "f32")["chunks_per_wg"])) <= _busiest_cu(B, H, L, two)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("B,H,L", [(24, 4, 750), (7, 4, 2500), (9, 4, 1700)])
+def test_lists_of_five_chunks(B, H, L):
+    """Ties across the five chunk lists of a work-group, a head whose measures are all equal, work-groups with a part of
+    their chunks or none, and an empty item."""
+    import numpy as np
+    p = plan(B, H, L, 12, "f32")
+    assert (p["measure"], p["select"], p["chunks_per_wg"]) == ("stream", "lists", "5")
+    cfg = W.small_config("five", B, H, L, 12, 5.0, "f32", "peaky", True, 1, L)
+    w = W.make_workload(cfg, seed=41 + L)
+    w.lengths[0], w.lengths[1], w.lengths[2], w.lengths[3] = L, 321, 257, 0
+    for b in range(B):
+        n = int(w.lengths[b])
+        w.sample_idx[b] = np.minimum(w.sample_idx[b], max(0, n - 1))
+    w.Q[0, 0] = 0                                                        # all equal
+    for first in (64, 128, 192, 256):                                    # the chunks of a work-group repeat each other
+        w.Q[:, 1, first:first + 64] = w.Q[:, 1, :64]
+        w.sample_idx[:, 1, first:first + 64] = w.sample_idx[:, 1, :64]
+    for b in range(B):                                                   # (padding stays zero)
+        w.Q[b, :, int(w.lengths[b]):] = 0
+    check_against_oracle(w, label=f"five-{B}-{H}-{L}")
