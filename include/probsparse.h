@@ -278,7 +278,8 @@ int dense_attn_fwd(const void* Q, const void* K, const void* V, const int32_t* l
  * (`measure=lds|lds_half|stream|none`), how I_sparse is found (`select=lists|kernel|
  * segments|given_inline|given_prep`), which attend kernel (`attend=key_split|rows|
  * rows_half_keys`) and how partial results are merged.  For tests and for reading
- * profiles; the words are not a stable interface.  `opt` gives the selection rule
+ * profiles; the words are not a stable interface.  A call with `lengths` launches the
+ * same kernels as one without.  `opt` gives the selection rule
  * (steps a1..a4); with u_stride > 0 the plan is that of
  * probsparse_attn_fwd_with_indices and `opt` may be NULL.  Errors: PSA_ERR_NULL,
  * PSA_ERR_SHAPE / PSA_ERR_DTYPE, PSA_ERR_ARG (bad rule or stride, or `buf` too small). */

@@ -136,3 +136,22 @@ def test_lists_of_five_chunks(B, H, L):
     for b in range(B):                                                   # (padding stays zero)
         w.Q[b, :, int(w.lengths[b]):] = 0
     check_against_oracle(w, label=f"five-{B}-{H}-{L}")
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("lengths", [False, True])
+@pytest.mark.parametrize("B,H,L", [(24, 4, 750), (12, 8, 520), (9, 4, 1700)])
+def test_described_lists_are_what_a_call_with_lengths_makes(B, H, L, lengths):
+    # where the plan says that the measure kernel hands on lists, the measure and attend stages alone are the whole call
+    import torch
+    from paper_2106_09236_amd import binding as psa
+    assert plan(B, H, L, 20, "f32")["select"] == "lists"
+    g = torch.Generator().manual_seed(L)
+    Q, K, V = (torch.randn((B, H, L, 64), generator=g).cuda() for _ in range(3))
+    n = torch.randint(L // 6, L + 1, (B,), generator=g, dtype=torch.int32)
+    idx = (torch.rand((B, H, L, 20), generator=g) * n.view(B, 1, 1, 1)).to(torch.int32).cuda()
+    n = n.cuda() if lengths else None
+    ws = psa.alloc_workspace(psa.make_shape(B, H, L, 20, psa.PSA_F32), 5.0).zero_()
+    out = torch.zeros_like(Q)
+    psa.probsparse_attn_fwd_stages(Q, K, V, n, idx, 5.0, out, ws, psa.STAGE_MEASURE | psa.STAGE_ATTEND)
+    assert torch.equal(out, psa.probsparse_attn_fwd(Q, K, V, n, idx, 5.0))
