@@ -54,6 +54,14 @@ at::Tensor scratch(const at::Tensor& like, size_t bytes)
     return at::empty({(int64_t)bytes}, like.options().dtype(at::kByte));
 }
 PyObject* none() { Py_RETURN_NONE; }
+// Other Python threads run while a call allocates and enqueues: either may wait (for memory, for room in a queue).
+// No Python object is touched inside; the caller holds the arguments.
+struct Unlocked {
+    PyThreadState* const state = PyEval_SaveThread();
+    Unlocked() = default;
+    Unlocked(const Unlocked&) = delete;
+    ~Unlocked() { PyEval_RestoreThread(state); }
+};
 // the caller's output object, or the one made here
 PyObject* result(PyObject* given, at::Tensor&& made)
 {
@@ -71,18 +79,17 @@ PyObject* forward(PyObject* const* a, const psa_options_t& opt, PyObject* out_o,
     psa_shape_t s;
     if (!shape_of(*q.t, idx, &s)) return none();
     at::Tensor made, room;
-    size_t bytes;
-    if (ws.t) bytes = (size_t)ws.t->numel();
-    else {
-        bytes = probsparse_attn_workspace_bytes_opt(&s, &opt);
-        if (bytes == 0) return none();
-        room = scratch(*q.t, bytes);
-        ws.ptr = room.data_ptr();
+    const size_t bytes = ws.t ? (size_t)ws.t->numel() : probsparse_attn_workspace_bytes_opt(&s, &opt);
+    if (bytes == 0) return none();
+    int rc;
+    {
+        const Unlocked unlocked;
+        if (!ws.t) { room = scratch(*q.t, bytes); ws.ptr = room.data_ptr(); }
+        if (!out.t) { made = at::empty_like(*q.t); out.ptr = made.data_ptr(); }
+        rc = probsparse_attn_fwd_opt(q.ptr, k.ptr, v.ptr, static_cast<const int32_t*>(len.ptr),
+                                     static_cast<const int32_t*>(idx.ptr), &opt, out.ptr, &s, ws.ptr, bytes, stream(),
+                                     nullptr, nullptr, nullptr);
     }
-    if (!out.t) { made = at::empty_like(*q.t); out.ptr = made.data_ptr(); }
-    const int rc = probsparse_attn_fwd_opt(q.ptr, k.ptr, v.ptr, static_cast<const int32_t*>(len.ptr),
-                                           static_cast<const int32_t*>(idx.ptr), &opt, out.ptr, &s, ws.ptr, bytes, stream(),
-                                           nullptr, nullptr, nullptr);
     return rc == PSA_OK ? result(out_o, std::move(made)) : none();
 }
 
@@ -124,18 +131,17 @@ PyObject* attn_fwd_with_indices(PyObject*, PyObject* const* a, Py_ssize_t n)
     if (!shape_of(*q.t, Arg{}, &s) || sel.t->dim() < 1) return none();
     const int32_t stride = (int32_t)sel.t->size(-1);
     at::Tensor made, room;
-    size_t bytes;
-    if (ws.t) bytes = (size_t)ws.t->numel();
-    else {
-        bytes = probsparse_attn_with_indices_workspace_bytes(&s, stride);
-        if (bytes == 0) return none();
-        room = scratch(*q.t, bytes);
-        ws.ptr = room.data_ptr();
+    const size_t bytes = ws.t ? (size_t)ws.t->numel() : probsparse_attn_with_indices_workspace_bytes(&s, stride);
+    if (bytes == 0) return none();
+    int rc;
+    {
+        const Unlocked unlocked;
+        if (!ws.t) { room = scratch(*q.t, bytes); ws.ptr = room.data_ptr(); }
+        if (!out.t) { made = at::empty_like(*q.t); out.ptr = made.data_ptr(); }
+        rc = probsparse_attn_fwd_with_indices(q.ptr, k.ptr, v.ptr, static_cast<const int32_t*>(len.ptr),
+                                              static_cast<const int32_t*>(sel.ptr), static_cast<const int32_t*>(u.ptr),
+                                              stride, fill, out.ptr, &s, ws.ptr, bytes, stream());
     }
-    if (!out.t) { made = at::empty_like(*q.t); out.ptr = made.data_ptr(); }
-    const int rc = probsparse_attn_fwd_with_indices(q.ptr, k.ptr, v.ptr, static_cast<const int32_t*>(len.ptr),
-                                                    static_cast<const int32_t*>(sel.ptr), static_cast<const int32_t*>(u.ptr),
-                                                    stride, fill, out.ptr, &s, ws.ptr, bytes, stream());
     return rc == PSA_OK ? result(a[7], std::move(made)) : none();
 }
 
@@ -150,19 +156,18 @@ PyObject* attn_bwd(PyObject*, PyObject* const* a, Py_ssize_t n)
     psa_shape_t s;
     if (!shape_of(*q.t, Arg{}, &s) || sel.t->dim() < 1) return none();
     const int32_t stride = (int32_t)sel.t->size(-1);
-    at::Tensor room;
-    size_t bytes;
-    if (ws.t) bytes = (size_t)ws.t->numel();
-    else {
-        bytes = probsparse_attn_bwd_workspace_bytes(&s, stride);
-        if (bytes == 0) return none();
-        room = scratch(*q.t, bytes);
-        ws.ptr = room.data_ptr();
+    at::Tensor room, dq, dk, dv;
+    const size_t bytes = ws.t ? (size_t)ws.t->numel() : probsparse_attn_bwd_workspace_bytes(&s, stride);
+    if (bytes == 0) return none();
+    int rc;
+    {
+        const Unlocked unlocked;
+        if (!ws.t) { room = scratch(*q.t, bytes); ws.ptr = room.data_ptr(); }
+        dq = at::empty_like(*q.t); dk = at::empty_like(*q.t); dv = at::empty_like(*q.t);
+        rc = probsparse_attn_bwd(q.ptr, k.ptr, v.ptr, static_cast<const int32_t*>(len.ptr),
+                                 static_cast<const int32_t*>(sel.ptr), static_cast<const int32_t*>(u.ptr), stride, fill,
+                                 g.ptr, dq.data_ptr(), dk.data_ptr(), dv.data_ptr(), &s, ws.ptr, bytes, stream());
     }
-    at::Tensor dq = at::empty_like(*q.t), dk = at::empty_like(*q.t), dv = at::empty_like(*q.t);
-    const int rc = probsparse_attn_bwd(q.ptr, k.ptr, v.ptr, static_cast<const int32_t*>(len.ptr),
-                                       static_cast<const int32_t*>(sel.ptr), static_cast<const int32_t*>(u.ptr), stride, fill,
-                                       g.ptr, dq.data_ptr(), dk.data_ptr(), dv.data_ptr(), &s, ws.ptr, bytes, stream());
     if (rc != PSA_OK) return none();
     PyObject* t = PyTuple_New(3);
     if (!t) return nullptr;
@@ -193,17 +198,16 @@ PyObject* mhsa_fwd(PyObject*, PyObject* const* a, Py_ssize_t n)
     PyBuffer_Release(&view);
     if (!whole) return none();
     at::Tensor made, room;
-    size_t bytes;
-    if (ws.t) bytes = (size_t)ws.t->numel();
-    else {
-        bytes = probsparse_mhsa_workspace_bytes(&s, &opt);
-        if (bytes == 0) return none();
-        room = scratch(*x.t, bytes);
-        ws.ptr = room.data_ptr();
+    const size_t bytes = ws.t ? (size_t)ws.t->numel() : probsparse_mhsa_workspace_bytes(&s, &opt);
+    if (bytes == 0) return none();
+    int rc;
+    {
+        const Unlocked unlocked;
+        if (!ws.t) { room = scratch(*x.t, bytes); ws.ptr = room.data_ptr(); }
+        if (!y.t) { made = at::empty_like(*x.t); y.ptr = made.data_ptr(); }
+        rc = probsparse_mhsa_fwd(x.ptr, &w, static_cast<const int32_t*>(len.ptr), static_cast<const int32_t*>(idx.ptr),
+                                 &opt, y.ptr, &s, ws.ptr, bytes, stream());
     }
-    if (!y.t) { made = at::empty_like(*x.t); y.ptr = made.data_ptr(); }
-    const int rc = probsparse_mhsa_fwd(x.ptr, &w, static_cast<const int32_t*>(len.ptr), static_cast<const int32_t*>(idx.ptr),
-                                       &opt, y.ptr, &s, ws.ptr, bytes, stream());
     return rc == PSA_OK ? result(a[7], std::move(made)) : none();
 }
 
