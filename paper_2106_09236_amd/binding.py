@@ -4,13 +4,16 @@ Argument marshalling only: every step of the forward runs in the library's HIP
 kernels.  PyTorch is used for device memory and streams.  The hot entry points
 go through the extension module _native (csrc/python), which does the same
 marshalling in native code and hands back what it cannot take (None); the ctypes
-functions below it serve everything else and report every error.  There is no CPU
-fallback: if the library has not been built, loading raises.
+functions below it serve everything else and report every error.  The module is for
+speed alone (a short call's time in the interpreter): where it has not been built, or was
+built for another torch, every call goes through ctypes.  There is no CPU fallback: if the
+library has not been built, loading raises.
 """
 from __future__ import annotations
 
 import ctypes
 import os
+import warnings
 from typing import Optional
 
 import torch
@@ -56,8 +59,28 @@ class ProbSparseError(RuntimeError):
         self.code = code
 
 
+class _CtypesOnly:
+    """Stands in for the extension module where there is none: leaves every call to the ctypes path."""
+    @staticmethod
+    def attn_fwd(*args):
+        return None
+    attn_fwd_opt = attn_fwd_with_indices = attn_bwd = mhsa_fwd = attn_fwd
+
+
 _lib = None
-_native = None          # the extension module, loaded with the library
+_native = None          # the extension module or _CtypesOnly, loaded with the library
+
+
+def _load_native():
+    if not os.path.exists(NATIVE_PATH):
+        return _CtypesOnly
+    try:
+        from . import _native as module
+    except ImportError as e:
+        warnings.warn(f"{NATIVE_PATH} cannot be loaded ({e}): calls go through ctypes, which takes some microseconds more "
+                      "each; build it again with `python -m paper_2106_09236_amd.build`")
+        return _CtypesOnly
+    return module
 
 
 def load() -> ctypes.CDLL:
@@ -128,15 +151,12 @@ def load() -> ctypes.CDLL:
     lib.probsparse_init.argtypes = []
     lib.probsparse_describe_plan.restype = ctypes.c_int
     lib.probsparse_describe_plan.argtypes = [shp, optp, ctypes.c_int32, ctypes.c_char_p, ctypes.c_size_t]
-    if not os.path.exists(NATIVE_PATH):
-        raise FileNotFoundError(f"{NATIVE_PATH} is missing: build it with `python -m paper_2106_09236_amd.build`")
-    from . import _native as native
-    _lib, _native = lib, native
+    _lib, _native = lib, _load_native()
     return lib
 
 
 def _fast():
-    """The extension module."""
+    """The extension module, or what stands in for it."""
     if _native is None:
         load()
     return _native

@@ -1,4 +1,7 @@
 """The Python entry points of the hot calls in native code (csrc/python)."""
+import os
+import shutil
+import subprocess
 import sys
 import threading
 import time
@@ -64,3 +67,38 @@ def test_other_threads_run_during_calls(name):
         sys.setswitchinterval(interval)
     torch.cuda.synchronize()
     assert len(results) == 500 and during > 0
+
+
+@pytest.mark.parametrize("module", [None, "not a shared object"])
+def test_library_loads_without_the_module(tmp_path, module):
+    # the package with its library only, or with a module that cannot be loaded
+    here = os.path.dirname(psa.LIB_PATH)
+    package = tmp_path / os.path.basename(here)
+    package.mkdir()
+    for name in ("__init__.py", "binding.py", "libprobsparse.so"):
+        shutil.copy(os.path.join(here, name), package)
+    if module is not None:
+        (package / "_native.so").write_text(module)
+    code = ("from paper_2106_09236_amd import binding as psa; s = psa.make_shape(1, 4, 128, 25, psa.PSA_F32); "
+            "assert psa.LIB_PATH.startswith(%r), psa.LIB_PATH; assert psa.u_max(s, 5.0) == 25; "
+            "print(psa.probsparse_describe_plan(s, psa.PsaOptions(psa.U_LOG, psa.FILL_MEAN, 5.0))['measure'], "
+            "psa._fast().attn_bwd(1, 2, 3))" % str(tmp_path))
+    r = subprocess.run([sys.executable, "-c", code], cwd=tmp_path, capture_output=True, text=True)
+    assert r.returncode == 0 and r.stdout.split() == ["lds", "None"], r.stderr
+    assert ("cannot be loaded" in r.stderr) == (module is not None)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("name", ["fwd", "opt", "indices", "mhsa", "bwd"])
+def test_ctypes_path_gives_the_same(name, monkeypatch):
+    call = _calls()[name]
+
+    def outputs():
+        r = call()
+        r = r[0] if name == "mhsa" else r
+        return [t.clone() for t in (r if isinstance(r, tuple) else (r,))]
+    native = outputs()
+    assert psa._native is not psa._CtypesOnly
+    monkeypatch.setattr(psa, "_native", psa._CtypesOnly)
+    for a, b in zip(native, outputs()):
+        assert torch.equal(a, b)
