@@ -3,8 +3,8 @@
 Argument marshalling only: every step of the forward runs in the library's HIP
 kernels.  PyTorch is used for device memory and streams.  The hot entry points
 go through the extension module _native (csrc/python), which does the same
-marshalling in native code and hands back what it cannot take (None); the ctypes
-functions below it serve everything else and report every error.  The module is for
+marshalling in native code and hands back what it cannot take (None) before anything
+is enqueued; the ctypes functions below it serve everything else.  The module is for
 speed alone (a short call's time in the interpreter): where it has not been built, or was
 built for another torch, every call goes through ctypes.  There is no CPU fallback: if the
 library has not been built, loading raises.
@@ -80,6 +80,7 @@ def _load_native():
         warnings.warn(f"{NATIVE_PATH} cannot be loaded ({e}): calls go through ctypes, which takes some microseconds more "
                       "each; build it again with `python -m paper_2106_09236_amd.build`")
         return _CtypesOnly
+    module.on_status(_check)
     return module
 
 

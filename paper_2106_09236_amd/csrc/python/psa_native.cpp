@@ -3,9 +3,10 @@
 // same call through ctypes took 8 us of the interpreter's time on top of the launches (B=1 H=4 L=128, output and
 // scratch given: 13.0 us per call, here 8.7, of which two launches are 5).
 //
-// A function returns None where anything is out of the ordinary (an argument that is no contiguous device tensor, an
-// unknown type, a status other than PSA_OK); nothing has been enqueued then, and the caller's ctypes path takes over,
-// which reports the error.
+// A function returns None where anything is out of the ordinary before the library is called (an argument that is no
+// contiguous device tensor, an unknown type, no memory); nothing has been enqueued then, and the caller's ctypes path takes
+// over, which reports the error.  A status other than PSA_OK is raised from here: a launch that failed may come after
+// stages that have been enqueued, and those are not enqueued again.
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 
@@ -54,6 +55,21 @@ at::Tensor scratch(const at::Tensor& like, size_t bytes)
     return at::empty({(int64_t)bytes}, like.options().dtype(at::kByte));
 }
 PyObject* none() { Py_RETURN_NONE; }
+// what raises the binding's exception for a status (set by the binding)
+PyObject* raise_status = nullptr;
+PyObject* failed(int rc)
+{
+    PyObject* r = raise_status ? PyObject_CallFunction(raise_status, "i", rc) : nullptr;
+    Py_XDECREF(r);
+    if (!PyErr_Occurred()) PyErr_Format(PyExc_RuntimeError, "libprobsparse: status %d", rc);
+    return nullptr;
+}
+PyObject* on_status(PyObject*, PyObject* callable)
+{
+    Py_INCREF(callable);
+    Py_XSETREF(raise_status, callable);
+    Py_RETURN_NONE;
+}
 // Other Python threads run while a call allocates and enqueues: either may wait (for memory, for room in a queue).
 // No Python object is touched inside; the caller holds the arguments.
 struct Unlocked {
@@ -90,7 +106,7 @@ PyObject* forward(PyObject* const* a, const psa_options_t& opt, PyObject* out_o,
                                      static_cast<const int32_t*>(idx.ptr), &opt, out.ptr, &s, ws.ptr, bytes, stream(),
                                      nullptr, nullptr, nullptr);
     }
-    return rc == PSA_OK ? result(out_o, std::move(made)) : none();
+    return rc == PSA_OK ? result(out_o, std::move(made)) : failed(rc);
 }
 
 // attn_fwd(Q, K, V, lengths, sample_idx, c, out, workspace)
@@ -142,7 +158,7 @@ PyObject* attn_fwd_with_indices(PyObject*, PyObject* const* a, Py_ssize_t n)
                                               static_cast<const int32_t*>(sel.ptr), static_cast<const int32_t*>(u.ptr),
                                               stride, fill, out.ptr, &s, ws.ptr, bytes, stream());
     }
-    return rc == PSA_OK ? result(a[7], std::move(made)) : none();
+    return rc == PSA_OK ? result(a[7], std::move(made)) : failed(rc);
 }
 
 // attn_bwd(Q, K, V, lengths, sel, u, dOut, fill, workspace) -> (dQ, dK, dV)
@@ -168,7 +184,7 @@ PyObject* attn_bwd(PyObject*, PyObject* const* a, Py_ssize_t n)
                                  static_cast<const int32_t*>(sel.ptr), static_cast<const int32_t*>(u.ptr), stride, fill,
                                  g.ptr, dq.data_ptr(), dk.data_ptr(), dv.data_ptr(), &s, ws.ptr, bytes, stream());
     }
-    if (rc != PSA_OK) return none();
+    if (rc != PSA_OK) return failed(rc);
     PyObject* t = PyTuple_New(3);
     if (!t) return nullptr;
     PyTuple_SET_ITEM(t, 0, THPVariable_Wrap(std::move(dq)));
@@ -208,7 +224,7 @@ PyObject* mhsa_fwd(PyObject*, PyObject* const* a, Py_ssize_t n)
         rc = probsparse_mhsa_fwd(x.ptr, &w, static_cast<const int32_t*>(len.ptr), static_cast<const int32_t*>(idx.ptr),
                                  &opt, y.ptr, &s, ws.ptr, bytes, stream());
     }
-    return rc == PSA_OK ? result(a[7], std::move(made)) : none();
+    return rc == PSA_OK ? result(a[7], std::move(made)) : failed(rc);
 }
 
 // exceptions of the tensor library (no memory, say) must not cross into the interpreter: the caller's path meets them
@@ -231,6 +247,7 @@ PyMethodDef methods[] = {
     {"attn_fwd_with_indices", entry<attn_fwd_with_indices>(), METH_FASTCALL, nullptr},
     {"attn_bwd", entry<attn_bwd>(), METH_FASTCALL, nullptr},
     {"mhsa_fwd", entry<mhsa_fwd>(), METH_FASTCALL, nullptr},
+    {"on_status", on_status, METH_O, nullptr},
     {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_native", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
 

@@ -102,3 +102,24 @@ def test_ctypes_path_gives_the_same(name, monkeypatch):
     monkeypatch.setattr(psa, "_native", psa._CtypesOnly)
     for a, b in zip(native, outputs()):
         assert torch.equal(a, b)
+
+
+@pytest.mark.gpu
+def test_a_status_is_raised_without_a_second_attempt(monkeypatch):
+    # a workspace that is too small is refused on the host; the ctypes path, which would call the library again, is not entered
+    Q, K, V, idx = _inputs(1, 4, 128, 8)
+    small = torch.empty(256, dtype=torch.uint8, device="cuda")
+    sel, u = torch.zeros((1, 4, 1), dtype=torch.int32, device="cuda"), torch.ones(1, dtype=torch.int32, device="cuda")
+    X = torch.zeros((1, 128, 256), device="cuda")
+    eye = torch.eye(256, device="cuda")
+    weights = psa.make_weights(eye, eye, eye, eye)
+    entered = []
+    monkeypatch.setattr(psa, "_require_dev", lambda *ts: entered.append(ts))
+    for call in (lambda: psa.probsparse_attn_fwd(Q, K, V, None, idx, 5.0, workspace=small),
+                 lambda: psa.probsparse_attn_fwd_opt(Q, K, V, None, idx, psa.U_RATIO, 0.5, psa.FILL_MEAN, workspace=small, taps=False),
+                 lambda: psa.probsparse_attn_fwd_with_indices(Q, K, V, None, sel, u, workspace=small),
+                 lambda: psa.probsparse_attn_bwd(Q, K, V, None, sel, u, Q, workspace=small),
+                 lambda: psa.probsparse_mhsa_fwd(X, weights, None, idx, psa.U_LOG, 5.0, psa.FILL_MEAN, workspace=small)):
+        with pytest.raises(psa.ProbSparseError) as e:
+            call()
+        assert e.value.code == -5 and not entered          # PSA_ERR_WORKSPACE
