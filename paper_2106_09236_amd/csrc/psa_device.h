@@ -98,6 +98,9 @@ __device__ __forceinline__ float max_xor16(float x) {
 // the parity bound), scaled by adding n to the exponent field.  Vector instructions do not overlap with
 // float64 matrix instructions on a SIMD, so every instruction here counts: a Taylor series of degree 7 (7.0e-9) with
 // rint, a separate factor ln 2 and ldexp took 90 cycles per value, this one about 60.
+// ABOVE: x may be anything; from 1024 on the exponent is set to that of infinity, which gives infinity or NaN where the
+// exponent field would wrap to a finite value (two instructions more).
+template <bool ABOVE = false>
 __device__ __forceinline__ double exp2_f64(double x) {
     const double t = x + 6755399441055744.0;                 // the low word of t now holds n
     const double f = x - (t - 6755399441055744.0);
@@ -107,7 +110,9 @@ __device__ __forceinline__ double exp2_f64(double x) {
     p = fma(f, p, 0.24022647913627504);
     p = fma(f, p, 0.6931472028550949);
     p = fma(f, p, 1.0);
-    const double y = __hiloint2double(__double2hiint(p) + (__double2loint(t) << 20), __double2loint(p));
+    int hi = __double2hiint(p) + (__double2loint(t) << 20);
+    if (ABOVE) hi = x >= 1024.0 ? 0x7FF00000 : hi;
+    const double y = __hiloint2double(hi, __double2loint(p));
     return x < -1000.0 ? 0.0 : y;
 }
 

@@ -122,7 +122,8 @@ struct F32Tile {
         if (!V_PRELOADED) load_v(vrows, j0, c, g);
         // online softmax in base 2 over the 32 keys.  The subtracted constant only
         // has to be the same for every key of a query, so the running max is kept
-        // in float32 while the exponent itself is formed in float64.
+        // in float32 while the exponent itself is formed in float64.  Scores beyond
+        // 2^34 may exceed the rounded max by 1024 and more: infinite weights, NaN.
         double t[2][4];
         float tmax = -INFINITY;
 #pragma unroll
@@ -147,7 +148,7 @@ struct F32Tile {
         for (int sb = 0; sb < 2; ++sb)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                p[sb][r] = exp2_f64(t[sb][r] - (double)m_new);
+                p[sb][r] = exp2_f64<true>(t[sb][r] - (double)m_new);
                 lsum += p[sb][r];
             }
         l_run = l_run * alpha + lsum;

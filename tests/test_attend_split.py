@@ -155,3 +155,29 @@ def test_described_lists_are_what_a_call_with_lengths_makes(B, H, L, lengths):
     out = torch.zeros_like(Q)
     psa.probsparse_attn_fwd_stages(Q, K, V, n, idx, 5.0, out, ws, psa.STAGE_MEASURE | psa.STAGE_ATTEND)
     assert torch.equal(out, psa.probsparse_attn_fwd(Q, K, V, n, idx, 5.0))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("B,H,L,u", [(1, 2, 64, 2), (16, 8, 512, 512)])      # key split; a wave owns its queries
+def test_scores_beyond_the_rounded_maximum(B, H, L, u):
+    """float32: at 2^35 the running maximum, rounded to float32, lies 1030 (as a power of 2) below the largest score.  Weights
+    overflow: the result is NaN or right, never that of the key whose score is 20 lower."""
+    import torch
+    from paper_2106_09236_amd import binding as psa
+    log2e_scale = 0.125 * 1.4426950408889634
+    s = (2.0 ** 35 + 5 * 4096 + 1030) / log2e_scale              # raw score of the best key
+    Q, K, V = (torch.zeros((B, H, L, 64)) for _ in range(3))
+    Q[..., 0], Q[..., 1] = 2.0 ** 17, 1.0
+    high = torch.tensor(s / 2 ** 17).float()
+    K[:, :, :2, 0] = high
+    K[:, :, 0, 1] = s - float(high) * 2 ** 17
+    K[:, :, 1, 1] = K[:, :, 0, 1] - 20 / log2e_scale
+    V[:, :, 0], V[:, :, 1] = 1.0, -1.0
+    t = ((Q[0, 0, :1].double() @ K[0, 0].double().T) * log2e_scale)[0]
+    assert 1025 < float(t[0] - t[0].float().double()) < 1035 and 19 < float(t[0] - t[1]) < 21
+    sel = torch.arange(u, dtype=torch.int32).expand(B, H, u).contiguous()
+    args = Q.cuda(), K.cuda(), V.cuda(), None
+    out = psa.probsparse_attn_fwd_with_indices(*args, sel.cuda(), torch.full((B,), u, dtype=torch.int32).cuda())[:, :, :u].cpu()
+    dense = psa.dense_attn_fwd(*args).cpu()
+    for got in (out, dense):
+        assert bool((got.isnan() | ((got - 1).abs() < 1e-5)).all()), got.flatten()[:4]
