@@ -34,8 +34,8 @@ constexpr int kF32SmemBytes = kF32Waves * kStateDoubles * 64 * 8;     // 73728: 
 // element e of query q: block q / 16, register 4 (e % 4) + e / 16, lane ((e / 4) % 4) * 16 + q % 16
 // (F32Tile::reg_of, grp_of), i.e. exactly the accumulator layout, so record stores are fully coalesced.
 // The work of one work-group; `smem`: kF32SmemBytes of LDS.
-template <int NCG, typename CS>      // NCG: column tiles of 16 selected queries per query group, 1 or 2
-__device__ __forceinline__ void attend_f32_body(const AttendParams& P, double* smem, CS& cs)
+template <int NCG>      // NCG: column tiles of 16 selected queries per query group, 1 or 2
+__device__ __forceinline__ void attend_f32_body(const AttendParams& P, double* smem, CommonScratch& cs)
 {
     // (a division only where both cuts are in use)
     const HeadBlock hb = head_block(P);
@@ -180,7 +180,7 @@ template <int NCG>
 __global__ __launch_bounds__(512)
 void attend_f32_kernel(const AttendParams P)
 {
-    __shared__ CommonScratch<512> cs;
+    __shared__ CommonScratch cs;
     extern __shared__ __attribute__((aligned(16))) double smem[];
     attend_f32_body<NCG>(P, smem, cs);
 }
@@ -270,10 +270,9 @@ __device__ __forceinline__ void store_quad_b16(bf16_t* out_head, int i, int quad
     *reinterpret_cast<uint2*>(out_head + (size_t)i * kD + 8 * quad + 4 * h) = pk;
 }
 
-// The work of one work-group; `smem_b16`: kB16SmemBytes of LDS, or with ALIAS (the wave states reuse the V tiles'
-// area behind a barrier) kB16MergeBytes.
-template <int NQT, bool ALIAS, typename CS>     // NQT: column tiles of 32 selected queries per work-group
-__device__ __forceinline__ void attend_bf16_body(const AttendParams& P, unsigned char* smem_b16, CS& cs)
+// The work of one work-group; `smem_b16`: kB16SmemBytes of LDS.
+template <int NQT>     // NQT: column tiles of 32 selected queries per work-group
+__device__ __forceinline__ void attend_bf16_body(const AttendParams& P, unsigned char* smem_b16, CommonScratch& cs)
 {
     // (a division only where both cuts are in use)
     const HeadBlock hb = head_block(P);
@@ -352,8 +351,7 @@ __device__ __forceinline__ void attend_bf16_body(const AttendParams& P, unsigned
     // publishes its state in register layout, then wave w merges accumulator quad
     // w (registers 4(w % 4) .. +3 of column half w / 4) of all eight states, in
     // wave order, and stores it into the record.
-    if (ALIAS) lds_barrier();                                  // every wave is done with its V tile
-    float4* sState = reinterpret_cast<float4*>(smem_b16 + (ALIAS ? 0 : kB16StageBytes));   // [wave][kB16StateVec][64]
+    float4* sState = reinterpret_cast<float4*>(smem_b16 + kB16StageBytes);   // [wave][kB16StateVec][64]
     float* rec = part + (((size_t)head * n_qgroup + qgroup) * n_split + split) * part_stride;
 #pragma unroll
     for (int qt = 0; qt < NQT; ++qt) {
@@ -440,9 +438,9 @@ template <int NQT>
 __global__ __launch_bounds__(512)
 void attend_bf16_kernel(const AttendParams P)
 {
-    __shared__ CommonScratch<512> cs;
+    __shared__ CommonScratch cs;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_b16[];
-    attend_bf16_body<NQT, false>(P, smem_b16, cs);
+    attend_bf16_body<NQT>(P, smem_b16, cs);
 }
 
 // Merge kernel for bfloat16 records: work-group (quad, query tile, head), four
@@ -594,7 +592,7 @@ __global__ __launch_bounds__(256 * KSPLIT, 2)
 void attend_rows_f32_kernel(const AttendParams P)
 {
     constexpr int NT = 256 * KSPLIT;
-    __shared__ CommonScratch<NT> cs;
+    __shared__ CommonScratch cs;
     __shared__ double s_state[KSPLIT == 2 ? 4 * 18 * 64 : 1];       // [query tile][m, l, O^T 16][lane]
     const HeadBlock hb = head_block(P);
     const int qblock = hb.wg, head = hb.head;
@@ -682,7 +680,7 @@ void attend_rows_bf16_kernel(const AttendParams P)
 {
     constexpr int KSPLIT = 2;
     constexpr int NT = 256 * KSPLIT;
-    __shared__ CommonScratch<NT> cs;
+    __shared__ CommonScratch cs;
     __shared__ __attribute__((aligned(16))) uint16_t sKV[KSPLIT][2][2][kTile * kB16Stride];   // [key half][buffer][K|V]
     static_assert(sizeof(sKV) >= 4 * 34 * 64 * sizeof(float), "the state hand-over reuses the tile buffers");
     const HeadBlock hb = head_block(P);

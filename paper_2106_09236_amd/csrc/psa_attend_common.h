@@ -47,16 +47,11 @@ __device__ __forceinline__ HeadBlock head_block(const AttendParams& P)
 }
 inline dim3 attend_grid(int wgs, int BH, int head_shift) { return dim3((unsigned)wgs << head_shift, (unsigned)BH >> head_shift); }
 
-// NSEL: longest index list kept in LDS; NCAND: most candidates (lists * list length) the prologue merges.
-// The single-launch kernel for short heads uses a small instance (64 / 256) so that two of its
-// work-groups fit a CU.
-template <int NT, int NSEL = kSelLdsMax, int NCAND = kMaxCandidates>
 struct CommonScratch {
-    static constexpr int kSel = NSEL, kCand = NCAND;
     float mean[kD];
-    int sel[NSEL];                   // I_sparse of the head
-    unsigned ckey[NCAND];            // candidate lists of the head: order keys ...
-    int cidx[NCAND];                 // ... and query indices (-1 = empty slot)
+    int sel[kSelLdsMax];             // I_sparse of the head
+    unsigned ckey[kMaxCandidates];   // candidate lists of the head: order keys ...
+    int cidx[kMaxCandidates];        // ... and query indices (-1 = empty slot)
     unsigned char flag[512];
     int plen[8];                     // per list: how many of its first entries can be among the u best
     int last;
@@ -84,9 +79,9 @@ struct SelList {
 // requests its first K tile there, so that the tile streams in behind them while
 // the selection runs (barriers inside are LDS-only and do not wait for it).
 // Returns the head's selected indices and u.
-template <int NT, typename CS, typename F>
+template <int NT, typename F>
 __device__ __forceinline__ SelList attend_prologue(const AttendParams& P, int head, int n, int wg_in_head,
-                                                      CS& cs, int& u, F&& issue_tile)
+                                                      CommonScratch& cs, int& u, F&& issue_tile)
 {
     const int tid = threadIdx.x;
     const int b = head / P.H;
@@ -117,7 +112,7 @@ __device__ __forceinline__ SelList attend_prologue(const AttendParams& P, int he
         // caller-given index sets (Sec. 4.4): entries beyond u_b or outside the item's frames become -1
         // and are skipped; the mean of V comes from the column sums, as below
         const int* gsel = P.given_sel + (size_t)head * P.u_max;
-        constexpr int SPT = (CS::kSel + NT - 1) / NT;              // entries per thread (u_max <= CS::kSel here)
+        constexpr int SPT = (kSelLdsMax + NT - 1) / NT;              // entries per thread (u_max <= kSelLdsMax here)
         int sv[SPT];
 #pragma unroll
         for (int k = 0; k < SPT; ++k) { const int t = k * NT + tid; sv[k] = gsel[t < P.u_max ? t : P.u_max - 1]; }
@@ -142,7 +137,7 @@ __device__ __forceinline__ SelList attend_prologue(const AttendParams& P, int he
         }
     } else if (P.fused_select) {                 // implies candidate lists (cand_len > 0)
         {
-            constexpr int CPT = (CS::kCand + NT - 1) / NT;         // candidates per thread
+            constexpr int CPT = (kMaxCandidates + NT - 1) / NT;         // candidates per thread
             const int total = P.n_chunk * P.cand_len;
             const uint2* ch = P.cand + (size_t)head * total;
             uint2 ce[CPT];
@@ -269,7 +264,7 @@ __device__ __forceinline__ SelList attend_prologue(const AttendParams& P, int he
         u = P.ucount[b];
         const float mv = P.mu[(size_t)head * kD + (tid & (kD - 1))];
         issue_tile();
-        if (P.u_max <= CS::kSel) {
+        if (P.u_max <= kSelLdsMax) {
             if (tid < P.u_max) cs.sel[tid] = s0v;
             for (int t = tid + NT; t < P.u_max; t += NT) cs.sel[t] = gsel[t];
         } else {
@@ -302,9 +297,9 @@ template <> struct OutTraits<bf16_t> {
 // selected receives the mean of the valid V rows (Sec. 3.1: uniform scores give
 // the plain average of the values) or, with VALUE_FILL, its own row of V (Eq. 12
 // as printed); a row at or beyond the length receives zeros.
-template <typename T, int NT, bool VALUE_FILL, typename CS>
+template <typename T, int NT, bool VALUE_FILL>
 __device__ __forceinline__ void fill_rows_impl(T* out_head, const T* V_head, const SelList& selp, int u, int n, int L,
-                                               int r0, int rows, CS& cs)
+                                               int r0, int rows, CommonScratch& cs)
 {
     using OT = OutTraits<T>;
     constexpr int LPR = OT::LPR, EPL = OT::EPL, RPP = NT / LPR;
@@ -347,9 +342,9 @@ __device__ __forceinline__ void fill_rows_impl(T* out_head, const T* V_head, con
         }
     }
 }
-template <typename T, int NT, typename CS>
+template <typename T, int NT>
 __device__ __forceinline__ void fill_rows(const AttendParams& P, T* out_head, const T* V_head, const SelList& selp,
-                                          int u, int n, int wg_in_head, CS& cs)
+                                          int u, int n, int wg_in_head, CommonScratch& cs)
 {
     if (P.fill == PSA_FILL_VALUE)
         fill_rows_impl<T, NT, true>(out_head, V_head, selp, u, n, P.L, wg_in_head * P.rows_per_wg, P.rows_per_wg, cs);
@@ -378,9 +373,9 @@ __device__ __forceinline__ double rec_exp2(double x) { return exp2_f64(x); }
 // R: record element type.  ACC_LAYOUT (float32 tensors): O stored in accumulator layout (blocks
 // of [16 registers][64 lanes] per 16 queries) instead of [query][64], as float32 values O / l behind
 // the float64 m and l.
-template <typename T, typename R, bool ACC_LAYOUT, int NT, typename CS>
+template <typename T, typename R, bool ACC_LAYOUT, int NT>
 __device__ __forceinline__ void ticket_and_merge(const AttendParams& P, int head, int n, int u, const SelList& selp,
-                                                 int nq, CS& cs)
+                                                 int nq, CommonScratch& cs)
 {
     using OT = OutTraits<T>;
     constexpr int LPR = OT::LPR, EPL = OT::EPL, RPP = NT / LPR;

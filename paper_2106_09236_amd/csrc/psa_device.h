@@ -15,7 +15,7 @@ typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 
 // ---- DPP: data-parallel-primitive lane permutations inside a row of 16 lanes
 // quad_perm [1,0,3,2] = 0xB1, quad_perm [2,3,0,1] = 0x4E,
-// row_half_mirror = 0x141 (lane i <-> 7-i in each 8), row_mirror = 0x140 (i <-> 15-i).
+// row_half_mirror = 0x141 (lane i <-> 7-i in each 8).
 template <int CTRL>
 __device__ __forceinline__ float dpp_mov(float x) {
     return __builtin_bit_cast(float,
@@ -29,17 +29,10 @@ __device__ __forceinline__ float group_sum8(float x) {
     x += dpp_mov<0x141>(x);
     return x;
 }
-// Sum over aligned groups of 16 lanes.
-__device__ __forceinline__ float group_sum16(float x) {
-    x = group_sum8(x);
-    x += dpp_mov<0x140>(x);
-    return x;
-}
 
 // ---- bf16 <-> f32
 __device__ __forceinline__ float bf16_lo(uint32_t pair) { return __uint_as_float(pair << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t pair) { return __uint_as_float(pair & 0xFFFF0000u); }
-__device__ __forceinline__ float bf16_to_f32(uint16_t b) { return __uint_as_float((uint32_t)b << 16); }
 // round-to-nearest-even; NaN stays NaN
 __device__ __forceinline__ uint16_t f32_to_bf16(float f) {
     uint32_t u = __float_as_uint(f);

@@ -758,11 +758,6 @@ void measure_pipe_kernel(const T* __restrict__ Q, const T* __restrict__ K, const
     PSA_TS(4);
 }
 
-__device__ __forceinline__ float quad_sum(float x) {
-    x += dpp_mov<0xB1>(x);
-    x += dpp_mov<0x4E>(x);
-    return x;
-}
 template <int T4>                                          // value of lane T4 of the quad, in all four lanes
 __device__ __forceinline__ int quad_bcast(int x) {
     return __builtin_amdgcn_update_dpp(0, x, T4 * 0x55, 0xF, 0xF, false);

@@ -88,7 +88,6 @@ struct F32Tile {
 #pragma unroll
             for (int v = 0; v < 4; ++v) dst[sb][v] = buffer_load16<float4>(k, (j0 + 16 * sb + c) * 256 + 16 * g + 64 * v);
     }
-    __device__ __forceinline__ void load_k(__amdgpu_buffer_rsrc_t k, int j0, int c, int g) { load_k_into(kreg, k, j0, c, g); }
     __device__ __forceinline__ void load_v(__amdgpu_buffer_rsrc_t v, int j0, int c, int g) {
 #pragma unroll
         for (int sb = 0; sb < 2; ++sb)
