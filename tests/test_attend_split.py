@@ -116,14 +116,14 @@ def test_float32_measure_cut_loses_nothing_on_full_batches(B, H, L):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("B,H,L", [(24, 4, 750), (7, 4, 2500), (9, 4, 1700)])
-def test_lists_of_five_chunks(B, H, L):
+@pytest.mark.parametrize("B,H,L,c", [(24, 4, 750, 5.0), (7, 4, 2500, 5.0), (9, 4, 1700, 5.0), (24, 4, 750, 15.0)])   # (the last: longer than a chunk)
+def test_lists_of_five_chunks(B, H, L, c):
     """Ties across the five chunk lists of a work-group, a head whose measures are all equal, work-groups with a part of
     their chunks or none, and an empty item."""
     import numpy as np
-    p = plan(B, H, L, 12, "f32")
+    p = plan(B, H, L, 12, "f32", c=c)
     assert (p["measure"], p["select"], p["chunks_per_wg"]) == ("stream", "lists", "5")
-    cfg = W.small_config("five", B, H, L, 12, 5.0, "f32", "peaky", True, 1, L)
+    cfg = W.small_config("five", B, H, L, 12, c, "f32", "peaky", True, 1, L)
     w = W.make_workload(cfg, seed=41 + L)
     w.lengths[0], w.lengths[1], w.lengths[2], w.lengths[3] = L, 321, 257, 0
     for b in range(B):
