@@ -84,7 +84,7 @@ __device__ __forceinline__ void attend_f32_body(const AttendParams& P, double* s
 
     PSA_TS(2);
     // the K tile of the next round is requested before the current round's products
-    // (clamped addresses past the end: harmless), so only the first round waits for K
+    // (zeros past the end), so only the first round waits for K
     float4 knext[2][4];
     for (int rd = 0; rd < rounds; ++rd) {
         const int j0 = ((split * rounds + rd) * KT + kt) * kTile;

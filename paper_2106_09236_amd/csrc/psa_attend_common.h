@@ -39,7 +39,7 @@ struct AttendParams {
 // the one that holds them from the measure stage.  Only for whole eights: 4 heads would keep to half of the chip
 // (B=1 H=4 L=4096 float32: 50 -> 62 us); and not for bfloat16 heads in one query group, whose work-groups share no row
 // (B=8 H=8 L=2048: 55.8 us as they come, 56.4 in eights).  B=8 H=8 L=2048 bfloat16, half of the queries kept: 116.7 ->
-// 111.9 us; B=4 H=8 L=568 float32: 41.1 -> 39.2 us, B=16 H=4 L=512: 30.6 -> 29.9 us.
+// 111.9 us; B=4 H=8 L=568 float32: 41.1 -> 39.2 us, B=16 H=4 L=512 within the noise (30.35, 30.2 us).
 struct HeadBlock { int head, wg; };
 __device__ __forceinline__ HeadBlock head_block(const AttendParams& P)
 {

@@ -47,7 +47,7 @@ struct Plan {
     int measure_lds;      // 1: a head's K fits in LDS for the measure stage; 2: in half of it (two work-groups per CU)
     int measure_queries;  // queries per measure chunk: 128, 64 or 32 (LDS kernel), 64 (streaming)
     int n_chunk;          // measure chunks (= V column-sum chunks) per head
-    int chunks_per_wg;    // LDS measure kernel: consecutive chunks of a head one work-group takes
+    int chunks_per_wg;    // consecutive chunks of a head one work-group takes (LDS kernel, and streaming up to kPipeMaxSamples)
     int fused_select;     // 1: top-u selection runs inside the attend work-groups
     int cand_len;         // > 0: sorted candidate lists of this length are handed to the attend stage
     int n_seg;            // > 0: long heads, the lists come from the segment-select kernel, n_seg per head
@@ -62,7 +62,7 @@ struct Plan {
     int given_indices;    // 1: I_sparse comes from the caller (no measure, no selection)
     int given_inline;     // 1: the attend work-groups check the caller's sets and form the mean of V themselves (no prep kernel)
     int rows_mode;        // 1: many selected queries: a wave owns its queries and walks all keys (no key split);
-                          // 2: the same with the keys cut in two inside the work-group (float32)
+                          // 2: the same with the keys cut in two inside the work-group
     // workspace carving (byte offsets, each 256-aligned)
     size_t off_M, off_vpart, off_vseg, off_mu, off_sel, off_u, off_ticket, off_cand, off_part, total;
     size_t part_stride;   // elements per (head, qgroup, split) partial record: nq_group * (2 + 64) floats, or nq_group * (2 + 32) doubles
@@ -93,7 +93,6 @@ struct Args {
     hipStream_t stream;
 };
 
-// u_stride > 0: plan for caller-given index sets of that row stride (urule is ignored).
 // Kernels that use more than the default 64 KB of dynamic LDS need the limit raised
 // once per device.  `done` is the kernel's own bit mask of devices already served
 // (devices beyond 63 are simply served on every call); two threads racing on the
@@ -110,6 +109,7 @@ inline hipError_t ensure_lds_limit(const void* fn, int bytes, std::atomic<uint64
     return e;
 }
 
+// u_stride > 0: plan for caller-given index sets of that row stride (urule is ignored).
 bool make_plan(const psa_shape_t* s, URule urule, int u_stride, Plan* p);
 Scratch carve(const Plan& p, void* workspace);
 
