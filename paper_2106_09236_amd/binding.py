@@ -76,11 +76,11 @@ def _load_native():
         return _CtypesOnly
     try:
         from . import _native as module
-    except ImportError as e:
+        module.on_status(_check)
+    except (ImportError, AttributeError) as e:
         warnings.warn(f"{NATIVE_PATH} cannot be loaded ({e}): calls go through ctypes, which takes some microseconds more "
                       "each; build it again with `python -m paper_2106_09236_amd.build`")
         return _CtypesOnly
-    module.on_status(_check)
     return module
 
 
