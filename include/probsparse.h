@@ -213,8 +213,8 @@ int probsparse_attn_fwd_with_indices(const void* Q, const void* K, const void* V
  * arithmetic is float64 for both tensor types (the difference G_i.v_j - sum_j' p_ij' G_i.v_j'
  * cancels almost completely for sharply peaked rows).  shape->U is ignored.
  * Workspace: partial sums of dQ, at most a quarter of the memory that Q, K, V, dOut, dQ, dK and dV
- * take together or 256 MiB, whichever is more, and the statistics of the kept queries (up to
- * 40 bytes for each, or 4 MB). */
+ * take together or 256 MiB, whichever is more, and statistics (up to 40 bytes for each kept
+ * query and 512 for each head, or 5 MB where that is more). */
 size_t probsparse_attn_bwd_workspace_bytes(const psa_shape_t* shape, int32_t u_stride);
 int probsparse_attn_bwd(const void* Q, const void* K, const void* V, const int32_t* lengths,
                         const int32_t* sel, const int32_t* u, int32_t u_stride, int32_t fill,
