@@ -16,11 +16,8 @@
 // All five contractions run on the matrix cores (v_mfma_f64_16x16x4f64 on exactly widened inputs):
 //   lane (c, g) = (lane % 16, lane / 16)
 //   A[i][k]: i = c, k = g      B[k][j]: k = g, j = c      D[i][j]: i = 4r + g, j = c  (r = 0..3)
-// Both tensor types are computed in float64: where attention is sharply peaked (the queries
-// the selection prefers) p_ij is almost 1 for one key and c_ij - D_i is a difference of nearly
-// equal numbers, of which float32 arithmetic leaves only noise (measured on bfloat16 tensors:
-// errors of 4 times the gradient's own size).  Every sum has a fixed order, so results do not
-// depend on scheduling.
+// These are the kernels of float32 tensors, whose gradients are computed in float64 (bfloat16 tensors: psa_backward_bf16.hip,
+// and the plan below bounds the scratch of both).  Every sum has a fixed order, so results do not depend on scheduling.
 //
 // What bounds it: the matrix pipe.  A float64 MFMA takes 65 cycles of its SIMD, and the SIMD issues no vector
 // instruction meanwhile (micro-benchmark: the times of both add up, whatever waves they come from), so a vector
@@ -32,12 +29,10 @@
 //   * run two work-groups of 4 waves (one per SIMD) on a CU, so that one fills the matrix pipe while the other
 //     stages rows, waits at a barrier or stores, and cut the key axis so that their number fills whole rounds of
 //     the CUs.
-// Measured (whole call): B=8 H=8 L=2048 bfloat16, 39 kept queries 212 -> 139 us (statistics 40, gradients 96 us, of
-// which 21 and 57 us are MFMAs); B=16 H=4 L=512 float32, 256 kept queries 225 -> 167 us.
+// Measured (whole call): B=16 H=4 L=512, 256 kept queries 225 -> 167 us.
 #include <type_traits>
 
-#include "psa_device.h"
-#include "psa_internal.h"
+#include "psa_backward_common.h"
 
 namespace psa {
 
@@ -85,36 +80,13 @@ template <int N> struct BwdRow<float, N> {
         return (e & 3) == 0 ? v.x : (e & 3) == 1 ? v.y : (e & 3) == 2 ? v.z : v.w;
     }
 };
-template <int N> struct BwdRow<bf16_t, N> {
-    uint32_t x[N / 2];
-    __device__ __forceinline__ void load(const bf16_t* p) {
-        if constexpr (N == 4) {
-            const uint2 v = *reinterpret_cast<const uint2*>(p);
-            x[0] = v.x; x[1] = v.y;
-        } else {
-#pragma unroll
-            for (int k = 0; k < N / 8; ++k) {
-                const uint4 v = reinterpret_cast<const uint4*>(p)[k];
-                x[4 * k] = v.x; x[4 * k + 1] = v.y; x[4 * k + 2] = v.z; x[4 * k + 3] = v.w;
-            }
-        }
-    }
-    __device__ __forceinline__ float at(int e) const { return (e & 1) ? bf16_hi(x[e >> 1]) : bf16_lo(x[e >> 1]); }
-};
 __device__ __forceinline__ void bwd_store4(float* p, const float (&v)[4]) {
     *reinterpret_cast<float4*>(p) = make_float4(v[0], v[1], v[2], v[3]);
-}
-__device__ __forceinline__ void bwd_store4(bf16_t* p, const float (&v)[4]) {
-    *reinterpret_cast<uint2*>(p) = make_uint2(cvt_pk_bf16(v[0], v[1]), cvt_pk_bf16(v[2], v[3]));
 }
 
 // 16 bytes of a row: the values, or zeros
 __device__ __forceinline__ void bwd_store16(float* p, const float (&v)[4], bool keep) {
     *reinterpret_cast<float4*>(p) = keep ? make_float4(v[0], v[1], v[2], v[3]) : make_float4(0.f, 0.f, 0.f, 0.f);
-}
-__device__ __forceinline__ void bwd_store16(bf16_t* p, const float (&v)[8], bool keep) {
-    const uint4 x = make_uint4(cvt_pk_bf16(v[0], v[1]), cvt_pk_bf16(v[2], v[3]), cvt_pk_bf16(v[4], v[5]), cvt_pk_bf16(v[6], v[7]));
-    *reinterpret_cast<uint4*>(p) = keep ? x : make_uint4(0u, 0u, 0u, 0u);
 }
 
 constexpr double kBwdScaleLog2e = 0.125 * 1.4426950408889634074;     // scores to base-2 exponents
@@ -135,20 +107,6 @@ struct BwdParams {
     double* stats;         // [BH][u_pad][2]       (log2 sum exp, -D/8) per kept query, kKeysOnly form; else nullptr
     int H, L, u_stride, u_pad, n_group, S1, blocks1, S2, blocks2, fill;
 };
-
-__device__ __forceinline__ int kept_count(const BwdParams& P, int b, int n)
-{
-    int ub = P.u[b];
-    ub = ub < 0 ? 0 : (ub > P.u_stride ? P.u_stride : ub);
-    return ub > n ? n : ub;
-}
-// kept query `t` of the head (an index into its list): its row, or -1 when the entry lies beyond u_b or outside [0, n)
-__device__ __forceinline__ int kept_row(const BwdParams& P, int head, int t, int n, int ub)
-{
-    if (t >= ub) return -1;
-    const int i = P.sel[(size_t)head * P.u_stride + t];
-    return (i < 0 || i >= n) ? -1 : i;
-}
 
 // Kept queries q0 .. q0 + ROWS - 1 of the head: their rows of Q and of G as float64 in LDS (zeros for an absent
 // entry), 8 threads per row.  `find` looks the rows up in the list, `request` asks for them, `put` writes them to
@@ -890,11 +848,7 @@ static hipError_t raise_bwd_limits()
     for (int k = 0; k < N; ++k) { const hipError_t e = ensure_lds_limit(fn[k], lds[k], raised[k]); if (e != hipSuccess) return e; }
     return hipSuccess;
 }
-hipError_t init_backward()
-{
-    const hipError_t e = raise_bwd_limits<float>();
-    return e != hipSuccess ? e : raise_bwd_limits<bf16_t>();
-}
+hipError_t init_backward() { return raise_bwd_limits<float>(); }
 
 template <typename T>
 static hipError_t launch_bwd_t(const BwdParams& P, int BH, int ks, hipStream_t stream)
@@ -1013,6 +967,8 @@ hipError_t launch_backward(const psa_shape_t& s, const BwdPlan& bp, const void* 
                            const int* lengths, const int* sel, const int* u, int u_stride, int fill, const void* G,
                            void* dQ, void* dK, void* dV, void* workspace, hipStream_t stream)
 {
+    if (s.dtype != PSA_F32)
+        return launch_backward_bf16(s, make_bwd16_plan(s, u_stride, bp.total), Q, K, V, lengths, sel, u, u_stride, fill, G, dQ, dK, dV, workspace, stream);
     unsigned char* w = static_cast<unsigned char*>(workspace);
     BwdParams P;
     P.Q = Q; P.K = K; P.V = V; P.G = G; P.lengths = lengths; P.sel = sel; P.u = u;
@@ -1024,8 +980,7 @@ hipError_t launch_backward(const psa_shape_t& s, const BwdPlan& bp, const void* 
     P.H = s.H; P.L = s.L_K; P.u_stride = u_stride; P.u_pad = bp.u_pad; P.n_group = bp.n_group;
     P.S1 = bp.S1; P.blocks1 = bp.blocks1; P.S2 = bp.S2; P.blocks2 = bp.blocks2;
     P.fill = fill;
-    const int BH = s.B * s.H;
-    return s.dtype == PSA_F32 ? launch_bwd_t<float>(P, BH, bp.ks, stream) : launch_bwd_t<bf16_t>(P, BH, bp.ks, stream);
+    return launch_bwd_t<float>(P, s.B * s.H, bp.ks, stream);
 }
 
 }  // namespace psa

@@ -138,6 +138,17 @@ hipError_t launch_backward(const psa_shape_t& s, const BwdPlan& bp, const void* 
                            const int* lengths, const int* sel, const int* u, int u_stride, int fill, const void* G,
                            void* dQ, void* dK, void* dV, void* workspace, hipStream_t stream);
 
+// The same for bfloat16 tensors (psa_backward_bf16.hip).  Per head: statistics from S1 splits of tiles1 tiles of 32 keys x n_group
+// groups of 64 kept queries, dQ from SQ splits of tilesq tiles, dK and dV from S2 work-groups of blocks2 blocks of 128 keys.
+struct Bwd16Plan {
+    int n_group, S1, tiles1, SQ, tilesq, n_dq, S2, blocks2;
+    size_t off_stat, off_gsum, off_dq, total;
+};
+Bwd16Plan make_bwd16_plan(const psa_shape_t& s, int u_stride, size_t room);
+hipError_t launch_backward_bf16(const psa_shape_t& s, const Bwd16Plan& bp, const void* Q, const void* K, const void* V,
+                                const int* lengths, const int* sel, const int* u, int u_stride, int fill, const void* G,
+                                void* dQ, void* dK, void* dV, void* workspace, hipStream_t stream);
+
 hipError_t launch_qkv_project(const psa_shape_t& s, const void* X, const psa_mhsa_weights_t& w,
                               void* Q, void* K, void* V, hipStream_t stream);
 hipError_t launch_out_project(const psa_shape_t& s, const void* A, const psa_mhsa_weights_t& w, void* Y, hipStream_t stream);
