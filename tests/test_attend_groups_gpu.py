@@ -1,0 +1,24 @@
+"""float32 heads in several query groups of 16: items whose u ends at, before and behind the edge of a group (groups that are
+empty in some items)."""
+import numpy as np
+import pytest
+
+from paper_2106_09236_amd import workloads as W
+from tests.test_parity_gpu import check_against_oracle
+from tests.test_plan import plan
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("B,H,L", [(24, 4, 750), (7, 3, 750), (46, 4, 640)])
+def test_groups_beyond_u(B, H, L):
+    p = plan(B, H, L, 12, "f32")
+    assert p["attend"] == "key_split" and p["queries_per_group"] == "16" and int(p["query_groups"]) == 3
+    cfg = W.small_config("groups", B, H, L, 12, 5.0, "f32", "peaky", True, 1, L)
+    w = W.make_workload(cfg, seed=90 + B)
+    w.lengths[:7] = [24, 25, 601, 602, L, 0, 1]                       # u = 16, 17, 32, 33, 33 or 34, none, 1
+    for b in range(B):
+        w.sample_idx[b] = np.minimum(w.sample_idx[b], max(0, int(w.lengths[b]) - 1))
+        for x in (w.Q, w.K, w.V):
+            x[b, :, int(w.lengths[b]):] = 0
+    check_against_oracle(w, label=f"groups B{B} H{H} L{L}")
