@@ -30,9 +30,9 @@ constexpr int kStateDoubles = 18;      // m, l, 16 accumulator values per lane
 constexpr int kF32SmemBytes = kF32Waves * kStateDoubles * 64 * 8;     // 73728: dynamic LDS
 
 // Record layout for float32 tensors, NQ = 16 * NCG queries:
-//   [ m[NQ] | l[NQ] as float64 | O / l as float32: per column tile ct a block of 1024 = [16 registers][64 lanes] ]
-// element e of query q: block q / 16, register 4 (e % 4) + e / 16, lane ((e / 4) % 4) * 16 + q % 16
-// (F32Tile::reg_of, grp_of), i.e. exactly the accumulator layout, so record stores are fully coalesced.
+//   [ m[NQ] | l[NQ] as float64 | O / l as float32: rows [NQ][64] ]
+// Records go through to memory: a wave merges adjacent elements, so that a lane's store is 16 (8) bytes and the reader's load
+// of a row 256 contiguous bytes (single floats in the order of the accumulators: attend 19.8 -> 17.4 us at B=16 H=4 L=512).
 // The work of one work-group; `smem`: kF32SmemBytes of LDS.
 template <int NCG>      // NCG: column tiles of 16 selected queries per query group, 1 or 2
 __device__ __forceinline__ void attend_f32_body(const AttendParams& P, double* smem, CommonScratch& cs)
@@ -49,7 +49,7 @@ __device__ __forceinline__ void attend_f32_body(const AttendParams& P, double* s
     const int H = P.H, L = P.L, n_split = P.n_split, n_qgroup = P.n_qgroup, rounds = P.rounds, part_stride = P.part_stride;
     constexpr int NQ = NCG * 16;
     constexpr int KT = kF32Waves / NCG;                 // key tiles per round of the work-group
-    constexpr int VPW = 16 / KT;                        // accumulator values each wave merges
+    constexpr int VPW = 16 / KT;                        // accumulator values each wave merges: adjacent elements
     // smem: [wave][kStateDoubles][64]
     const int b = head / H;
     const int n = valid_len(P.lengths, b, L);
@@ -132,23 +132,29 @@ __device__ __forceinline__ void attend_f32_body(const AttendParams& P, double* s
 #pragma unroll
     for (int w = 0; w < KT; ++w) wgt[w] = (wgt[w] == -INFINITY) ? 0.0 : exp2_f64(wgt[w] - mx);
 
+    // wave kt merges values dt0 .. dt0 + VPW - 1 of register r: elements e0 .. e0 + VPW - 1 of its query
+    const int r = kt * VPW / 4, dt0 = kt * VPW % 4, e0 = F32Tile::elem(dt0, r, g);
+    double l_tot = 0.0;
+#pragma unroll
+    for (int w = 0; w < KT; ++w) l_tot += wgt[w] * smem[((size_t)(w * NCG + ct) * kStateDoubles + 1) * 64 + lane];
+    l_tot += __shfl_xor(l_tot, 16, 64);
+    l_tot += __shfl_xor(l_tot, 32, 64);
+    const double inv = l_tot > 0.0 ? 1.0 / l_tot : 0.0;
+    float val[VPW];
+#pragma unroll
+    for (int k = 0; k < VPW; ++k) {
+        double acc = 0.0;
+#pragma unroll
+        for (int w = 0; w < KT; ++w)
+            acc += wgt[w] * smem[((size_t)(w * NCG + ct) * kStateDoubles + 2 + 4 * (dt0 + k) + r) * 64 + lane];
+        val[k] = (float)(acc * inv);
+    }
     if (n_split == 1) {
         // the only split of its head: no record, the rows go straight to `out`
-        double l_tot = 0.0;
+        if (qi >= 0 && qi < n) {
+            float* orow = static_cast<float*>(P.out) + ((size_t)head * L + qi) * kD + e0;
 #pragma unroll
-        for (int w = 0; w < KT; ++w) l_tot += wgt[w] * smem[((size_t)(w * NCG + ct) * kStateDoubles + 1) * 64 + lane];
-        l_tot += __shfl_xor(l_tot, 16, 64);
-        l_tot += __shfl_xor(l_tot, 32, 64);
-        const double inv = l_tot > 0.0 ? 1.0 / l_tot : 0.0;
-        float* orow = static_cast<float*>(P.out) + ((size_t)head * L + (qi >= 0 && qi < n ? qi : 0)) * kD;
-#pragma unroll
-        for (int k = 0; k < VPW; ++k) {
-            const int vi = kt * VPW + k;
-            double acc = 0.0;
-#pragma unroll
-            for (int w = 0; w < KT; ++w)
-                acc += wgt[w] * smem[((size_t)(w * NCG + ct) * kStateDoubles + 2 + vi) * 64 + lane];
-            if (qi >= 0 && qi < n) orow[F32Tile::elem(vi >> 2, vi & 3, g)] = (float)(acc * inv);   // register vi = 4 dt + r
+            for (int k = 0; k < VPW; k += 2) *reinterpret_cast<float2*>(orow + k) = make_float2(val[k], val[k + 1]);
         }
         return;
     }
@@ -156,28 +162,16 @@ __device__ __forceinline__ void attend_f32_body(const AttendParams& P, double* s
     // element, far inside the parity bound): half the bytes of a float64 O, which made up a third of this
     // kernel's memory traffic.
     double* rec = part + (((size_t)head * n_qgroup + qgroup) * n_split + split) * part_stride;
-    float* rec_O = reinterpret_cast<float*>(rec + 2 * NQ) + ct * 1024;
-    double l_tot = 0.0;
+    unsigned long long* rec_O = reinterpret_cast<unsigned long long*>(reinterpret_cast<float*>(rec + 2 * NQ) + (ct * 16 + c) * kD + e0);
 #pragma unroll
-    for (int w = 0; w < KT; ++w) l_tot += wgt[w] * smem[((size_t)(w * NCG + ct) * kStateDoubles + 1) * 64 + lane];
-    l_tot += __shfl_xor(l_tot, 16, 64);
-    l_tot += __shfl_xor(l_tot, 32, 64);
-    const double inv = l_tot > 0.0 ? 1.0 / l_tot : 0.0;
-#pragma unroll
-    for (int k = 0; k < VPW; ++k) {
-        const int vi = kt * VPW + k;
-        double acc = 0.0;
-#pragma unroll
-        for (int w = 0; w < KT; ++w)
-            acc += wgt[w] * smem[((size_t)(w * NCG + ct) * kStateDoubles + 2 + vi) * 64 + lane];
-        rec_store(rec_O + vi * 64 + lane, (float)(acc * inv));
-    }
+    for (int k = 0; k < VPW; k += 2)
+        rec_store(rec_O + k / 2, (unsigned long long)__float_as_uint(val[k]) | ((unsigned long long)__float_as_uint(val[k + 1]) << 32));
     if (kt == 0 && g == 0) { rec_store(rec + ct * 16 + c, mx); rec_store(rec + NQ + ct * 16 + c, l_tot); }
 
     PSA_TS(6);
     PSA_TS(7);
     // ---- the hand-over
-    ticket_and_merge<float, double, true, 512>(P, head, n, u, selp, NQ, cs);
+    ticket_and_merge<512>(P, head, n, u, selp, NQ, cs);
     PSA_TS(8);
 }
 
@@ -505,10 +499,10 @@ void merge_b16_kernel(const AttendParams P)
 // one head are hundreds of KB, too much for the single work-group that draws the
 // last ticket, so the merge gets a launch of its own and u * B * H work-groups.
 // =============================================================================
-template <typename T, typename R, bool ACC_LAYOUT>
 __global__ __launch_bounds__(256)
 void merge_kernel(const AttendParams P)
 {
+    using R = double;
     constexpr int kMaxSplit = 512;
     __shared__ R s_w[kMaxSplit];
     __shared__ R s_part[4][kD];
@@ -547,7 +541,7 @@ void merge_kernel(const AttendParams P)
     for (int k = 0; k < 2; ++k) {
         const int s = tid + 256 * k;
         const R wgt = (ms[k] == (R)-INFINITY) ? (R)0 : rec_exp2(ms[k] - mx);
-        if (s < P.n_split) s_w[s] = ACC_LAYOUT ? wgt * ls[k] : wgt;   // (records in accumulator layout hold O / l)
+        if (s < P.n_split) s_w[s] = wgt * ls[k];                     // (records hold O / l)
         lt += wgt * ls[k];
     }
     // sum of l over the work-group in a fixed order: lanes by xor tree, waves in order
@@ -561,8 +555,7 @@ void merge_kernel(const AttendParams P)
     R acc = 0;
     for (int s = wave; s < P.n_split; s += 4) {
         const R* rec = base + (size_t)s * P.part_stride + 2 * nq;
-        const R ov = ACC_LAYOUT ? (R)reinterpret_cast<const float*>(rec)[(q >> 4) * 1024 + F32Tile::reg_of(lane) * 64 + F32Tile::grp_of(lane) * 16 + (q & 15)]
-                                : rec[q * kD + lane];
+        const R ov = (R)reinterpret_cast<const float*>(rec)[q * kD + lane];
         acc += s_w[s] * ov;
     }
     s_part[wave][lane] = acc;
@@ -570,13 +563,7 @@ void merge_kernel(const AttendParams P)
     if (wave == 0) {
         const R tot = s_part[0][lane] + s_part[1][lane] + s_part[2][lane] + s_part[3][lane];
         const float val = lt > 0 ? (float)(tot / lt) : 0.f;
-        T* row = static_cast<T*>(P.out) + ((size_t)head * P.L + i) * kD;
-        if constexpr (sizeof(T) == 4) {
-            reinterpret_cast<float*>(row)[lane] = val;
-        } else {
-            const float nxt = __shfl_down(val, 1, 64);
-            if ((lane & 1) == 0) reinterpret_cast<uint32_t*>(row)[lane >> 1] = pack_bf16(val, nxt);
-        }
+        static_cast<float*>(P.out)[((size_t)head * P.L + i) * kD + lane] = val;
     }
 }
 
@@ -834,7 +821,7 @@ hipError_t launch_attend(const Plan& p, const Args& a, const Scratch& w)
     }
     if (p.separate_merge) {
         if (p.dtype == PSA_F32) {
-            hipLaunchKernelGGL((merge_kernel<float, double, true>), dim3(p.u_max, p.BH), dim3(256), 0, a.stream, P);
+            hipLaunchKernelGGL(merge_kernel, dim3(p.u_max, p.BH), dim3(256), 0, a.stream, P);
         } else {
             const int n_qtile = p.n_qgroup * (p.nq_group / 32);
             hipLaunchKernelGGL(merge_b16_kernel, dim3(8, n_qtile, p.BH), dim3(256), 0, a.stream, P);

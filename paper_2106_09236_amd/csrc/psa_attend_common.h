@@ -370,14 +370,13 @@ __device__ __forceinline__ double rec_exp2(double x) { return exp2_f64(x); }
 // a ticket; the one that draws the last ticket merges the head's records, in
 // split order, into the selected rows of `out`.  No work-group ever waits for
 // another, so the scheme cannot deadlock whatever the residency.
-// R: record element type.  ACC_LAYOUT (float32 tensors): O stored in accumulator layout (blocks
-// of [16 registers][64 lanes] per 16 queries) instead of [query][64], as float32 values O / l behind
-// the float64 m and l.
-template <typename T, typename R, bool ACC_LAYOUT, int NT>
+// (float32 tensors; bfloat16 heads do the same in their own layout, psa_attend.hip)
+template <int NT>
 __device__ __forceinline__ void ticket_and_merge(const AttendParams& P, int head, int n, int u, const SelList& selp,
                                                  int nq, CommonScratch& cs)
 {
-    using OT = OutTraits<T>;
+    using OT = OutTraits<float>;
+    using R = double;                                                // m, l; O / l is float32
     constexpr int LPR = OT::LPR, EPL = OT::EPL, RPP = NT / LPR;
     const int tid = threadIdx.x, sub = tid % LPR, row = tid / LPR;
     const int n_wg_head = P.n_split * P.n_qgroup;
@@ -402,7 +401,7 @@ __device__ __forceinline__ void ticket_and_merge(const AttendParams& P, int head
     __syncthreads();
     if (!cs.last) return;
 
-    T* out_head = static_cast<T*>(P.out) + (size_t)head * P.L * kD;
+    float* out_head = static_cast<float*>(P.out) + (size_t)head * P.L * kD;
     const R* part = static_cast<const R*>(P.part);
     for (int rank = row; rank < u; rank += RPP) {
         const int i = selp[rank];
@@ -423,17 +422,10 @@ __device__ __forceinline__ void ticket_and_merge(const AttendParams& P, int head
                 const R mv = rec_load(rec + q);
                 m4[k] = s0 + k < P.n_split ? mv : (R)-INFINITY;
                 l4[k] = rec_load(rec + nq + q);
-                if (ACC_LAYOUT) {
-                    // float32 values O / l.  EPL = 4 elements 4*sub + e: accumulator register 4e + sub/4 of lane
-                    // group sub%4 (lanes 16 (sub%4) + q%16)
-                    const float* o = reinterpret_cast<const float*>(rec + 2 * nq) + (q >> 4) * 1024 + (sub >> 2) * 64 + (sub & 3) * 16 + (q & 15);
-#pragma unroll
-                    for (int e = 0; e < EPL; ++e) o4[k][e] = (R)rec_load(o + e * 256);
-                } else {
-                    const R* o = rec + 2 * nq + q * kD + sub * EPL;
-#pragma unroll
-                    for (int e = 0; e < EPL; ++e) o4[k][e] = rec_load(o + e);
-                }
+                const unsigned long long* o = reinterpret_cast<const unsigned long long*>(reinterpret_cast<const float*>(rec + 2 * nq) + q * kD + sub * EPL);
+                const unsigned long long o01 = rec_load(o), o23 = rec_load(o + 1);
+                o4[k][0] = (R)__uint_as_float((unsigned)o01); o4[k][1] = (R)__uint_as_float((unsigned)(o01 >> 32));
+                o4[k][2] = (R)__uint_as_float((unsigned)o23); o4[k][3] = (R)__uint_as_float((unsigned)(o23 >> 32));
             }
             R cm = mx;
 #pragma unroll
@@ -447,7 +439,7 @@ __device__ __forceinline__ void ticket_and_merge(const AttendParams& P, int head
             for (int k = 0; k < 4; ++k) {
                 const R sc = (m4[k] == (R)-INFINITY) ? (R)0 : rec_exp2(m4[k] - cm);
                 lt += sc * l4[k];
-                const R wo = ACC_LAYOUT ? sc * l4[k] : sc;           // (those records hold O / l)
+                const R wo = sc * l4[k];                             // (records hold O / l)
 #pragma unroll
                 for (int e = 0; e < EPL; ++e) acc[e] += wo * o4[k][e];
             }

@@ -62,8 +62,6 @@ struct F32Tile {
 
     // Where an output element lives: accumulator register 4 dt + r of the lanes of group g.
     static __device__ __forceinline__ constexpr int elem(int dt, int r, int g) { return 16 * r + 4 * g + dt; }
-    static __device__ __forceinline__ constexpr int reg_of(int e) { return 4 * (e & 3) + (e >> 4); }
-    static __device__ __forceinline__ constexpr int grp_of(int e) { return (e >> 2) & 3; }
 
     __device__ __forceinline__ void init() {
         m_run = -INFINITY; l_run = 0.0;
