@@ -18,6 +18,8 @@
 // the next chunk's global loads in flight during the current chunk's products.
 // bfloat16 tensors: project_kernel.  float32 tensors: project_split_kernel, which
 // runs on the same bfloat16 MFMA with every operand split into three bfloat16 parts.
+#include <type_traits>
+
 #include "psa_device.h"
 #include "psa_internal.h"
 #include "psa_trace.h"
@@ -46,6 +48,7 @@ struct ProjLayout {
     static_assert(kEpiRows * kEpiStride <= kOperandElems, "the staging tile fits in the operand tiles");
 };
 
+// (Calls with many rows go to project_stream_kernel below.)
 // What bounds it (in-kernel time stamps and probes at B*L = 16384, d_model = 512, bfloat16): not
 // the contraction loop.  A loop with this mix of LDS reads, LDS writes, loads and one barrier per
 // 32 MFMAs sustains 1.6 PFLOP/s when it runs for thousands of chunks; with d_model = 256..512 a
@@ -233,6 +236,266 @@ void project_kernel(const ProjectParams P)
     }
     PSA_TS(4);
     PSA_TS_WALL(6);
+}
+
+// ---- bfloat16, many rows: 256 x 128 tiles of C, a resident work-group of 8 waves per compute unit that walks several of them.
+// With tiles of 4..8 chunks the kernel above spends as long on a tile's first loads and its stores as on its products.  Here the
+// chunks of all tiles of a work-group are one stream: loads run two chunks ahead, straight into LDS (no registers to hold),
+// across the tiles' borders, and a tile's stores complete under the next tile's products.
+// What bounds it: a wave's instructions, not its bytes.  With loads, operand reads and products all left out (a copy made to
+// time the rest) a chunk still took 1100 of 2000 cycles at first: a taken branch costs a wave some 80 cycles, and with one
+// barrier per chunk all waves pay it at the same time.  So the loop body has no branch (the choice of the next chunk's source is a
+// select, loads past the end are asked of an empty buffer, waits are constants, a tile's first chunk has a body of its own), its loads
+// stand between the products (asked for together they hold every wave up for 300 cycles), and the barrier stands before the last
+// step's products, which cover the first reads behind it: 1430 cycles per chunk, of which the products take 1024.
+// Measured at B*L = 16384, d_model = 512, Q, K and V: 49 thousand cycles instead of 62 (three tiles per work-group; 4.4 of
+// them before the first product, 2.0 per tile's end), but at 1.85 GHz instead of 2.2, which the card falls to under more
+// matrix work: 35.8 -> 30.9 us.
+constexpr int kStreamTM = 256, kStreamTN = 128;
+constexpr int kStreamThreads = 512;
+constexpr int kStreamStages = 3;
+constexpr int kStreamRowBytes = kProjChunk * 2;                            // 128: rows without padding, vectors swapped by row
+constexpr int kStreamStageBytes = (kStreamTM + kStreamTN) * kStreamRowBytes;       // 49152
+constexpr int kStreamMaxBias = 3840;                                       // bias values (floats) of all matrices
+constexpr int kStreamGroups = 256;                                         // resident work-groups: one per compute unit
+constexpr int kStreamEpiStride = 64 + 8;                                   // staged output row of a wave, elements
+static_assert(8 * 32 * kStreamEpiStride * 2 <= kStreamStageBytes, "the waves' staging tiles fit in one stage");
+static_assert(kStreamStages * kStreamStageBytes + kStreamTM * 4 + kStreamMaxBias * 4 <= 160 * 1024, "all of it fits in LDS");
+
+// An operand's rows from `base` on as a raw buffer of `bytes` bytes (reads beyond them give zeros), the same in all lanes.
+struct RowBuffer { unsigned lo, hi, bytes; };
+__device__ __forceinline__ RowBuffer row_buffer(const void* base, unsigned bytes)
+{
+    const unsigned long long a = reinterpret_cast<unsigned long long>(base);
+    return RowBuffer{(unsigned)a, (unsigned)(a >> 32) & 0xFFFFu, bytes};
+}
+// 16 bytes per lane from memory to LDS (lane l's at lds + 16 l), past the registers.  In assembly because the compiler, which
+// cannot tell the stages apart, waits for ALL loads of this kind before any read of LDS; so the waits below count them.
+// (M0 holds the LDS address; no other instruction of the kernel uses it.)
+__device__ __forceinline__ void load_to_lds(const RowBuffer& buf, unsigned lds, unsigned voffset, unsigned soffset)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    typedef unsigned int Rsrc __attribute__((ext_vector_type(4)));
+    const Rsrc r = {buf.lo, buf.hi, buf.bytes, 0x00020000u};
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+                 :: "s"(lds), "v"(voffset), "s"(r), "s"(soffset) : "memory");
+#endif
+}
+
+// A_HEADS: A is [B, H, L, 64], else rows; C_HEADS likewise.  Kd is at least 3 chunks.
+template <bool A_HEADS, bool C_HEADS>
+__global__ __launch_bounds__(kStreamThreads, 2)
+void project_stream_kernel(const ProjectParams P)
+{
+    using T = bf16_t;
+    typedef unsigned int Vec __attribute__((ext_vector_type(4)));
+    constexpr int TM = kStreamTM, TN = kStreamTN, CH = kProjChunk;
+    constexpr unsigned kBeyond = 0xF0000000u;              // an offset beyond any buffer here
+    extern __shared__ __attribute__((aligned(16))) unsigned char stream_smem[];
+    unsigned* const sRow = reinterpret_cast<unsigned*>(stream_smem + kStreamStages * kStreamStageBytes);     // the tile's rows in C
+    float* const sBias = reinterpret_cast<float*>(sRow + TM);
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int c = lane & 31, h = lane >> 5;
+    const int wm = wave >> 1, wn = wave & 1;               // this wave's 64 x 64 part of the tile
+    const int n_kc = P.Kd / CH;
+    const int n_nt = (P.N + TN - 1) / TN, n_mt = (P.M + TM - 1) / TM;
+    const int per_rows = n_nt * P.n_mat;
+    // This work-group's tiles.  All column tiles of a block of rows go to ONE XCD (work-groups are dealt to the 8 XCDs in turn),
+    // in consecutive slots of its work-groups, so that the block of A comes from memory once.
+    const int xcd = blockIdx.x & 7, first = blockIdx.x >> 3, step = gridDim.x >> 3;
+    const int slots = ((n_mt - xcd + 7) >> 3) * per_rows;   // of this XCD (n_mt - xcd + 7 >= 0)
+    if (first >= slots) return;
+    const int n_tiles = (slots - first + step - 1) / step;
+
+    struct Tile { int m0, n0, which; };
+    auto tile_of = [&](int k) {                            // k-th tile of this work-group
+        const int slot = first + k * step, mi = slot / per_rows, inner = slot - mi * per_rows;
+        const int which = inner / n_nt;
+        return Tile{(mi * 8 + xcd) * TM, (inner - which * n_nt) * TN, which};
+    };
+    // row m of a [B, H, L, 64] tensor, from its row m0 on, in bytes (M is at most B * L: rows beyond are caught by the caller)
+    auto head_row = [&](int m, int b0, int l0) {
+        const int b = m / P.L, l = m - b * P.L;
+        return ((unsigned)(b - b0) * (unsigned)P.H * (unsigned)P.L + (unsigned)(l - l0)) * (kD * 2u);
+    };
+    // ---- the loads, two chunks ahead.  An instruction of a wave fills 8 rows of a stage; lane l: vector l % 8 of row l / 8, which
+    // holds the row's vector (l % 8) ^ (row / 2 % 8), so that 16 lanes reading one vector of 16 consecutive rows touch all 64 banks.
+    const int srow = wave * 8 + (lane >> 3);               // + 64 per instruction
+    const unsigned svec = (unsigned)(((lane & 7) ^ ((srow >> 1) & 7)) * 16);
+    const unsigned lds0 = (unsigned)(size_t)(__attribute__((address_space(3))) unsigned char*)stream_smem + (unsigned)wave * 1024u;
+    unsigned va[4], vw[2], va_next[4];                     // (va changes from tile to tile where A is split into heads)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) va[j] = (unsigned)(srow + 64 * j) * (unsigned)P.Kd * 2u + svec;
+#pragma unroll
+    for (int j = 0; j < 2; ++j) vw[j] = (unsigned)(srow + 64 * j) * (unsigned)P.Kd * 2u + svec;
+    auto sources = [&](int k, RowBuffer& a, RowBuffer& w, unsigned (&v)[4]) {      // of the k-th tile; nothing beyond the last
+        const bool live = k < n_tiles;
+        const Tile t = tile_of(live ? k : 0);
+        const T* A = static_cast<const T*>(P.A);
+        if (A_HEADS) {
+            const int b0 = t.m0 / P.L, l0 = t.m0 - b0 * P.L;
+            a = row_buffer(A + ((size_t)b0 * P.H * P.L + l0) * kD, live ? 0x80000000u : 0u);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int m = t.m0 + srow + 64 * j;
+                v[j] = m < P.M ? head_row(m, b0, l0) + svec : kBeyond;
+            }
+        } else {
+            const int rows = P.M - t.m0 < TM ? P.M - t.m0 : TM;
+            a = row_buffer(A + (size_t)t.m0 * P.Kd, live ? (unsigned)rows * (unsigned)P.Kd * 2u : 0u);
+        }
+        const T* W = static_cast<const T*>(t.which == 0 ? P.W[0] : (t.which == 1 ? P.W[1] : P.W[2]));
+        const int cols = P.N - t.n0 < TN ? P.N - t.n0 : TN;
+        w = row_buffer(W + (size_t)t.n0 * P.Kd, live ? (unsigned)cols * (unsigned)P.Kd * 2u : 0u);
+    };
+    const unsigned a_step = A_HEADS ? (unsigned)P.L * kD * 2u : (unsigned)kStreamRowBytes;     // from chunk to chunk of a row of A
+    RowBuffer ra, rw, ra_next, rw_next;
+    sources(0, ra, rw, va);
+    int load_kc = 0;
+    unsigned load_lds = lds0, sa = 0, sw = 0;
+    auto request = [&](int part) {                         // a third of a chunk's loads
+        if (part < 2) {
+            load_to_lds(ra, load_lds + (2 * part) * 8192, va[2 * part], sa);
+            load_to_lds(ra, load_lds + (2 * part + 1) * 8192, va[2 * part + 1], sa);
+        } else {
+            load_to_lds(rw, load_lds + TM * kStreamRowBytes, vw[0], sw);
+            load_to_lds(rw, load_lds + TM * kStreamRowBytes + 8192, vw[1], sw);
+        }
+    };
+    auto advance = [&]() {                                 // to the next chunk, without a branch
+        load_lds = load_lds == lds0 + (kStreamStages - 1) * kStreamStageBytes ? lds0 : load_lds + kStreamStageBytes;
+        const bool wrap = load_kc + 1 == n_kc;
+        load_kc = wrap ? 0 : load_kc + 1;
+        sa = wrap ? 0u : sa + a_step;
+        sw = wrap ? 0u : sw + kStreamRowBytes;
+        ra.lo = wrap ? ra_next.lo : ra.lo; ra.hi = wrap ? ra_next.hi : ra.hi; ra.bytes = wrap ? ra_next.bytes : ra.bytes;
+        rw.lo = wrap ? rw_next.lo : rw.lo; rw.hi = wrap ? rw_next.hi : rw.hi; rw.bytes = wrap ? rw_next.bytes : rw.bytes;
+        if (A_HEADS) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) va[j] = wrap ? va_next[j] : va[j];
+        }
+    };
+    constexpr int kLoads = 6, kStores = 8;                 // vector memory instructions of a wave: per chunk, per tile
+
+    ra_next = ra; rw_next = rw;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) va_next[j] = va[j];
+    for (int k = 0; k < 2; ++k) { request(0); request(1); request(2); advance(); }       // (within the tile: n_kc >= 3)
+    // the bias values of all matrices, once: behind the first chunks' loads, the matrices' loads together (one that has no bias
+    // reads its weights)
+    for (int n = tid; n < P.N; n += kStreamThreads) {
+        T raw[3];
+#pragma unroll
+        for (int k = 0; k < 3; ++k) raw[k] = static_cast<const T*>(k < P.n_mat && P.bias[k] ? P.bias[k] : P.W[0])[n];
+#pragma unroll
+        for (int k = 0; k < 3; ++k) if (k < P.n_mat) sBias[k * P.N + n] = P.bias[k] ? bf16_lo((uint32_t)raw[k].x) : 0.f;
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    lds_barrier();
+
+    floatx16 acc[2][2];
+    bf16x8 a[2][2], b[2][2];
+    const unsigned char* const smem_a = stream_smem + (wm * 64 + c) * kStreamRowBytes;
+    const unsigned char* const smem_w = stream_smem + (TM + wn * 64 + c) * kStreamRowBytes;
+    int stage = 0;                                         // byte offset of the chunk's stage
+    auto operands = [&](int at, int kk) {
+        const int vo = at + ((2 * kk + h) ^ ((c >> 1) & 7)) * 16;     // (32 more rows leave row / 2 % 8 as it is)
+#pragma unroll
+        for (int x = 0; x < 2; ++x) {
+            a[kk & 1][x] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(smem_a + x * 32 * kStreamRowBytes + vo));
+            b[kk & 1][x] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(smem_w + x * 32 * kStreamRowBytes + vo));
+        }
+    };
+    // One chunk, its first operands read already: four steps of products, a step's operands read before the step before it, and the
+    // loads of the chunk after the next between them.  The barrier stands before the last step, whose products cover the read of
+    // the next chunk's first operands: there the next chunk is in LDS, for every wave, and this one has been read by all.
+    // FIRST of its tile: the stores of the tile before may still be in flight as well.
+    auto chunk = [&](auto first_of_tile, int tile) {
+        constexpr bool FIRST = decltype(first_of_tile)::value;
+        const int next = stage == (kStreamStages - 1) * kStreamStageBytes ? 0 : stage + kStreamStageBytes;
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk) {
+            if (kk < 3) operands(stage, kk + 1);
+            if (kk == 3) {
+                if (FIRST) asm volatile("s_waitcnt vmcnt(%0)" :: "n"(kLoads + kStores) : "memory");
+                else       asm volatile("s_waitcnt vmcnt(%0)" :: "n"(kLoads) : "memory");
+                lds_barrier();
+                operands(next, 0);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int x = 0; x < 2; ++x)
+#pragma unroll
+                for (int y = 0; y < 2; ++y) {
+                    if (FIRST && kk == 0) {
+                        floatx16 zero;
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) zero[r] = 0.f;
+                        acc[x][y] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b[0][y], a[0][x], zero, 0, 0, 0);
+                    } else {
+                        acc[x][y] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b[kk & 1][y], a[kk & 1][x], acc[x][y], 0, 0, 0);
+                    }
+                }
+            __builtin_amdgcn_sched_barrier(0);
+            if (kk < 3) request(kk);
+            if (FIRST && kk == 1) sources(tile + 1, ra_next, rw_next, va_next);      // (wanted by the advance below at the earliest: n_kc >= 3)
+        }
+        advance();
+        stage = next;
+    };
+    operands(0, 0);
+#pragma unroll 1
+    for (int tile = 0; tile < n_tiles; ++tile) {
+        const Tile t = tile_of(tile);
+        const int b0 = C_HEADS ? t.m0 / P.L : 0, l0 = t.m0 - b0 * P.L;
+        chunk(std::true_type{}, tile);
+        // (behind the first chunk's barrier: every wave is done with the tile before; read behind the next one's)
+        if (tid < TM) {
+            const int m = t.m0 + tid;
+            sRow[tid] = m < P.M ? (C_HEADS ? head_row(m, b0, l0) : (unsigned)tid * (unsigned)P.N * 2u) : kBeyond;
+        }
+#pragma unroll 1
+        for (int kc = 1; kc < n_kc; ++kc) chunk(std::false_type{}, tile);
+        // ---- the tile is done: bias, rounding, and rows of 128 bytes through this wave's part of the stage read last
+        T* C = static_cast<T*>(t.which == 0 ? P.C[0] : (t.which == 1 ? P.C[1] : P.C[2]));
+        const size_t base = C_HEADS ? ((size_t)b0 * P.H * P.L + l0) * kD : (size_t)t.m0 * P.N;
+        const __amdgpu_buffer_rsrc_t rc = __builtin_amdgcn_make_buffer_rsrc(C + base, 0, 0x7FFFFFFF, 0x00020000);
+        const int n0 = t.n0 + wn * 64;                     // this wave's 64 columns: one head
+        const bool live = n0 < P.N;
+        const unsigned col = C_HEADS ? (unsigned)(n0 >> 6) * (unsigned)P.L * (kD * 2u) : (unsigned)n0 * 2u;
+        const float* bp = sBias + t.which * P.N + (live ? n0 : 0) + 4 * h;
+        float4 bb[2][4];
+#pragma unroll
+        for (int y = 0; y < 2; ++y)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) bb[y][q] = *reinterpret_cast<const float4*>(bp + y * 32 + 8 * q);
+        unsigned ro[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) ro[k] = sRow[wm * 64 + k * 8 + (lane >> 3)];
+        const int last = stage == 0 ? (kStreamStages - 1) * kStreamStageBytes : stage - kStreamStageBytes;
+        T* out = reinterpret_cast<T*>(stream_smem + last) + wave * 32 * kStreamEpiStride;
+#pragma unroll
+        for (int x = 0; x < 2; ++x) {
+            if (x > 0) wave_lds_sync();
+#pragma unroll
+            for (int y = 0; y < 2; ++y)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const float v0 = acc[x][y][4 * q + 0] + bb[y][q].x, v1 = acc[x][y][4 * q + 1] + bb[y][q].y;
+                    const float v2 = acc[x][y][4 * q + 2] + bb[y][q].z, v3 = acc[x][y][4 * q + 3] + bb[y][q].w;
+                    *reinterpret_cast<uint2*>(out + c * kStreamEpiStride + y * 32 + 8 * q + 4 * h) = make_uint2(cvt_pk_bf16(v0, v1), cvt_pk_bf16(v2, v3));
+                }
+            wave_lds_sync();
+#pragma unroll
+            for (int it = 0; it < 4; ++it) {
+                const Vec v = *reinterpret_cast<const Vec*>(out + (it * 8 + (lane >> 3)) * kStreamEpiStride + (lane & 7) * 8);
+                const unsigned off = live && ro[4 * x + it] != kBeyond ? ro[4 * x + it] + col + (lane & 7) * 16u : kBeyond;
+                __builtin_amdgcn_raw_buffer_store_b128(v, rc, off, 0, 0);       // (always issued: the waits count on it)
+            }
+        }
+        lds_barrier();                                     // every wave is done with the stage, which the next chunk requests anew
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // (loads asked of the empty buffer)
 }
 
 // float32 tensors on the bfloat16 matrix cores.  A float32 value is the exact sum of three
@@ -455,6 +718,41 @@ static hipError_t launch_project_as(const ProjectParams& P, hipStream_t stream)
     return hipGetLastError();
 }
 
+// Offsets from a tile's first row must fit a buffer descriptor's range: a tile of 256 rows spans at most 256 / L + 2 items.
+static bool stream_fits(const ProjectParams& P)
+{
+    const long rows = 2l * P.L + 2 * kStreamTM;
+    return rows * P.H * kD * 2 < (1l << 30) && (long)P.N * P.Kd * 2 < (1l << 30) && P.n_mat * P.N <= kStreamMaxBias && P.Kd >= 3 * kProjChunk;
+}
+
+// The resident work-groups take one tile each per round.  From two rounds on (what the first round's loads and the last one's stores
+// cost is then shared) and where at least 7 of 8 tiles' worth of every round is needed:
+//   rows x columns x matrices (d_model)   rounds  needed   128 x 128 tiles -> this kernel (whole module but for the last)
+//   32768 x 512 x 3, x 1 (512)             6, 2     100%      213.4 -> 205.6 us
+//   16384 x 512 x 3 (512)                   3       100%      107.8 -> 105.0 us
+//   32768 x 256 x 3 (256)                   3       100%       91.8 ->  91.4 us
+//   10101 x 512 x 3 (512)                   2        93%       88.0 ->  86.1 us
+//   12000 x 512 x 3 (512)                   3        73%       97.9 ->  97.5 us
+//   16384 x 256 x 3 (256)                   2        75%       47.4 ->  48.8 us
+//   16384 x 512 x 1 (512)                   1       100%       14.9 ->  14.7 us
+static bool stream_pays(const ProjectParams& P)
+{
+    const int n_nt = (P.N + kStreamTN - 1) / kStreamTN, n_mt = (P.M + kStreamTM - 1) / kStreamTM;
+    const long slots = (long)((n_mt + 7) / 8) * n_nt * P.n_mat, per_xcd = kStreamGroups / 8;        // of the fullest XCD
+    const long rounds = (slots + per_xcd - 1) / per_xcd;
+    return rounds >= 2 && 8l * P.M * P.N * P.n_mat >= 7l * rounds * kStreamGroups * kStreamTM * kStreamTN;
+}
+
+template <bool A_HEADS, bool C_HEADS>
+static hipError_t launch_project_stream(const ProjectParams& P, hipStream_t stream)
+{
+    const int n_nt = (P.N + kStreamTN - 1) / kStreamTN, n_mt = (P.M + kStreamTM - 1) / kStreamTM;
+    const int lds = kStreamStages * kStreamStageBytes + kStreamTM * 4 + P.n_mat * P.N * (int)sizeof(float);
+    const long most = 8l * ((n_mt + 7) / 8) * n_nt * P.n_mat;
+    hipLaunchKernelGGL((project_stream_kernel<A_HEADS, C_HEADS>), dim3((unsigned)(most < kStreamGroups ? most : kStreamGroups)), dim3(kStreamThreads), lds, stream, P);
+    return hipGetLastError();
+}
+
 static hipError_t launch_project(const ProjectParams& P0, int n_mat, int dtype, hipStream_t stream)
 {
     ProjectParams P = P0;
@@ -466,6 +764,8 @@ static hipError_t launch_project(const ProjectParams& P0, int n_mat, int dtype, 
         if (wg128 >= 512) return launch_project_split<2, 2>(P, stream);
         return 2 * wg128 >= 512 ? launch_project_split<2, 1>(P, stream) : launch_project_split<1, 1>(P, stream);
     }
+    if (stream_pays(P) && stream_fits(P))
+        return P.a_heads ? launch_project_stream<true, false>(P, stream) : launch_project_stream<false, true>(P, stream);
     return wg128 >= 512 ? launch_project_as<2, 2>(P, stream) : launch_project_as<2, 1>(P, stream);
 }
 
