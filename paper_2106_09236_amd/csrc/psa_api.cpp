@@ -686,7 +686,8 @@ int probsparse_describe_plan(const psa_shape_t* shape, const psa_options_t* opt,
 
 int probsparse_init(void)
 {
-    if (psa::init_measure() != hipSuccess || psa::init_attend() != hipSuccess || psa::init_backward() != hipSuccess) return PSA_ERR_HIP;
+    if (psa::init_measure() != hipSuccess || psa::init_attend() != hipSuccess || psa::init_backward() != hipSuccess ||
+        psa::init_project() != hipSuccess) return PSA_ERR_HIP;
     void* ws = nullptr;
     if (psa::static_scratch_ptr(&ws) != hipSuccess) return PSA_ERR_HIP;      // this device's static scratch
     return PSA_OK;

@@ -118,6 +118,7 @@ Scratch carve(const Plan& p, void* workspace);
 hipError_t init_measure();
 hipError_t init_attend();
 hipError_t init_backward();
+hipError_t init_project();
 
 hipError_t launch_measure(const Plan& p, const Args& a, const Scratch& w);
 hipError_t launch_select(const Plan& p, const Args& a, const Scratch& w);

@@ -744,8 +744,23 @@ static bool stream_pays(const ProjectParams& P)
 }
 
 template <bool A_HEADS, bool C_HEADS>
+static hipError_t raise_stream_limit()
+{
+    static std::atomic<uint64_t> raised;
+    return ensure_lds_limit((const void*)project_stream_kernel<A_HEADS, C_HEADS>,
+                            kStreamStages * kStreamStageBytes + kStreamTM * 4 + kStreamMaxBias * (int)sizeof(float), raised);
+}
+hipError_t init_project()
+{
+    const hipError_t e = raise_stream_limit<false, true>();
+    return e != hipSuccess ? e : raise_stream_limit<true, false>();
+}
+
+template <bool A_HEADS, bool C_HEADS>
 static hipError_t launch_project_stream(const ProjectParams& P, hipStream_t stream)
 {
+    const hipError_t e = raise_stream_limit<A_HEADS, C_HEADS>();
+    if (e != hipSuccess) return e;
     const int n_nt = (P.N + kStreamTN - 1) / kStreamTN, n_mt = (P.M + kStreamTM - 1) / kStreamTM;
     const int lds = kStreamStages * kStreamStageBytes + kStreamTM * 4 + P.n_mat * P.N * (int)sizeof(float);
     const long most = 8l * ((n_mt + 7) / 8) * n_nt * P.n_mat;
