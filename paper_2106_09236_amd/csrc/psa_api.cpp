@@ -37,10 +37,18 @@ static bool good_rule(URule r)
     return (r.rule == PSA_U_LOG || r.rule == PSA_U_RATIO) && r.factor > 0.0 && isfinite(r.factor);
 }
 
+// float32 tensors, heads in one key split: work-groups that share the output elements of a query group, as many (1, 2, 4) as
+// the compute units hold (one each: LDS and registers).  Each forms all scores and 1/d of the second product, 32 + 32/d float64 MFMAs for
+// a tile of 32 keys instead of 64, and there is nothing to hand over.  Whole call, 1 -> d work-groups: B=1 H=4 L=128 (8 -> 32 of
+// them) 14.3 -> 13.3 us, B=1 H=4 L=333 24.1 -> 21.7, B=4 H=4 L=300 23.0 -> 20.3, B=8 H=4 L=200 (64 -> 256) 20.3 -> 18.6 us.
+static int elem_split(int64_t wgs) { return 4 * wgs <= 256 ? 4 : 2 * wgs <= 256 ? 2 : 1; }
+
 // float32 tensors: queries per group and key splits of the key-split attend kernel, by the time of its rounds of
 // work-groups (one per CU).  In microseconds, fitted to sweeps of both over 15 shapes: 5.5 to start a work-group and
 // pick the selection, 2.3 for each tile step of a SIMD (64 float64 MFMAs), and for a split the hand-over of records:
-// 3 and 1.5 for each trip of the last work-group's merge (32 queries x 4 splits), or the merge kernel.  A last round
+// 3 and 1.5 for each trip of the last work-group's merge (32 queries x 4 splits), or the merge kernel.  Heads in one split whose
+// elements four work-groups share take 0.75 of a step (by the MFMAs 0.63, which would keep B=2 H=4 L=800 in one split: 34.5 us
+// against 31.0; B=1 H=4 L=500 in two splits 23.1, in one 21.9 us).  A last round
 // of work-groups that is not full counts half: heads are often shorter than L.
 // Against groups of 32 and 512 work-groups for every shape: B=24 H=4 L=750 ragged 87 -> 75 us, B=16 H=4 L=1000
 // 83 -> 63, B=64 H=4 L=200 52 -> 36, B=1 H=4 L=333 26.0 -> 23.8 us.
@@ -63,7 +71,8 @@ static void split_f32(Plan* p, int n_tiles)
             const int tiles = n_tiles < rounds * tiles_wg ? n_tiles : rounds * tiles_wg;
             const int steps = (tiles * ncg + 3) / 4;
             const float fills = (float)(per_split * split) / 256.f;
-            const float cost = (fills <= 1.f ? 1.f : 0.5f * (fills + ceilf(fills))) * (5.5f + 2.3f * (float)steps) +
+            const float part = split == 1 && elem_split(per_split) == 4 ? 0.75f : 1.f;      // of a tile step
+            const float cost = (fills <= 1.f ? 1.f : 0.5f * (fills + ceilf(fills))) * (5.5f + 2.3f * part * (float)steps) +
                 (split == 1 ? 0.f : split > kTicketMaxSplit ? 6.f : 3.f + 1.5f * (float)((p->u_max + 31) / 32 * ((split + 3) / 4)));
             if (cost < best) {
                 best = cost;
@@ -195,7 +204,8 @@ static void build_plan(const psa_shape_t* s, URule urule, int u_stride, Cuts cut
         p->n_split = 1;
         p->tiles_per_wave = n_tiles;
     }
-    p->n_wg_head = p->n_split * p->n_qgroup;
+    p->d_split = p->dtype == PSA_F32 && !p->rows_mode && p->n_split == 1 ? elem_split((int64_t)p->BH * p->n_qgroup) : 1;
+    p->n_wg_head = p->n_split * p->n_qgroup * p->d_split;
     p->rows_per_wg = (p->L + p->n_wg_head - 1) / p->n_wg_head;
 
     const size_t row_bytes = p->dtype == PSA_F32 ? 256 : 128;

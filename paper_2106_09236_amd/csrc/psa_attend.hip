@@ -26,22 +26,26 @@ namespace psa {
 // loads, exponentials and merges.
 // =============================================================================
 constexpr int kF32Waves = 8;
-constexpr int kStateDoubles = 18;      // m, l, 16 accumulator values per lane
+constexpr int kStateDoubles = 18;      // m, l, 16 accumulator values per lane (16 / DS of them where the elements are split)
 constexpr int kF32SmemBytes = kF32Waves * kStateDoubles * 64 * 8;     // 73728: dynamic LDS
 
 // Record layout for float32 tensors, NQ = 16 * NCG queries:
 //   [ m[NQ] | l[NQ] as float64 | O / l as float32: rows [NQ][64] ]
 // Records go through to memory: a wave merges adjacent elements, so that a lane's store is 16 (8) bytes and the reader's load
 // of a row 256 contiguous bytes (single floats in the order of the accumulators: attend 19.8 -> 17.4 us at B=16 H=4 L=512).
+// DS > 1: heads in one key split whose work-groups leave compute units idle.  DS work-groups share a query group; each forms all
+// its scores, but of the second product only its 1/DS of the output elements, and writes those: nothing to hand over.
 // The work of one work-group; `smem`: kF32SmemBytes of LDS.
-template <int NCG>      // NCG: column tiles of 16 selected queries per query group, 1 or 2
+template <int NCG, int DS>      // NCG: column tiles of 16 selected queries per query group, 1 or 2
 __device__ __forceinline__ void attend_f32_body(const AttendParams& P, double* smem, CommonScratch& cs)
 {
     // (a division only where both cuts are in use)
     const HeadBlock hb = head_block(P);
     const int head = hb.head, wg_in_head = hb.wg;
-    const int qgroup = P.n_qgroup == 1 ? 0 : P.n_split == 1 ? wg_in_head : wg_in_head / P.n_split;
-    const int split = wg_in_head - qgroup * P.n_split;
+    const int qgroup = P.n_qgroup == 1 ? 0 : P.n_split == 1 ? wg_in_head / DS : wg_in_head / P.n_split;
+    const int split = DS > 1 ? 0 : wg_in_head - qgroup * P.n_split;
+    const int dp = DS > 1 ? wg_in_head % DS : 0;              // which part of the output elements
+    using Tile = F32TileOf<DS>;
     const float* Q = static_cast<const float*>(P.Q);
     const float* K = static_cast<const float*>(P.K);
     const float* V = static_cast<const float*>(P.V);
@@ -49,7 +53,8 @@ __device__ __forceinline__ void attend_f32_body(const AttendParams& P, double* s
     const int H = P.H, L = P.L, n_split = P.n_split, n_qgroup = P.n_qgroup, rounds = P.rounds, part_stride = P.part_stride;
     constexpr int NQ = NCG * 16;
     constexpr int KT = kF32Waves / NCG;                 // key tiles per round of the work-group
-    constexpr int VPW = 16 / KT;                        // accumulator values each wave merges: adjacent elements
+    constexpr int NV = 16 / DS;                         // accumulator values of a lane
+    constexpr int VPW = NV >= KT ? NV / KT : 1;         // of which each wave merges: adjacent elements (DS = 4: the first 4 waves)
     // smem: [wave][kStateDoubles][64]
     const int b = head / H;
     const int n = valid_len(P.lengths, b, L);
@@ -65,18 +70,18 @@ __device__ __forceinline__ void attend_f32_body(const AttendParams& P, double* s
     // the prologue's own small loads are in flight and streams in while the prologue
     // picks I_sparse; then the query row (needs the index).
     PSA_TS(0);
-    F32Tile tile;
+    Tile tile;
     tile.init();
     const int j_first = (split * rounds * KT + kt) * kTile;
     const __amdgpu_buffer_rsrc_t kr = head_rows<256>(Kh, n), vr = head_rows<256>(Vh, n);
     int u;
     const SelList selp = attend_prologue<512>(P, head, n, wg_in_head, cs, u,
-                                              [&]() { F32Tile::load_k_into(tile.kreg, kr, j_first, c, g); });
+                                              [&]() { Tile::load_k_into(tile.kreg, kr, j_first, c, g); });
     PSA_TS(1);
     const int qrank = qgroup * NQ + ct * 16 + c;
     const int qi = qrank < u ? selp[qrank] : -1;
     tile.load_q(head_rows<256>(Qh, n), qi, g);
-    tile.load_v(vr, j_first, c, g);                           // behind K and Q in the queue, needed last
+    tile.load_v(vr, j_first, c, g, dp);                       // behind K and Q in the queue, needed last
 
     // ---- stage a4 for this work-group's share of the rows: the stores go out now
     // and complete under the matrix work below
@@ -98,16 +103,16 @@ __device__ __forceinline__ void attend_f32_body(const AttendParams& P, double* s
 #pragma unroll
                 for (int v = 0; v < 4; ++v) tile.kreg[sb][v] = knext[sb][v];
         }
-        if (rd + 1 < rounds) F32Tile::load_k_into(knext, kr, j0 + KT * kTile, c, g);        // (zeros past the end)
-        if (rd == 0) tile.step<true>(vr, j0, n, c, g);
-        else         tile.step<false>(vr, j0, n, c, g);
+        if (rd + 1 < rounds) Tile::load_k_into(knext, kr, j0 + KT * kTile, c, g);        // (zeros past the end)
+        if (rd == 0) tile.template step<true>(vr, j0, n, c, g, dp);
+        else         tile.template step<false>(vr, j0, n, c, g, dp);
     }
     PSA_TS(3);
     // nothing to merge and no row to write (nor a record that anyone reads) in a query group beyond the item's u
     if (n_split == 1 && qgroup * NQ >= u) return;             // work-group-uniform
     const float m_run = tile.m_run;
     const double l_run = tile.l_run;
-    doublex4 (&oacc)[4] = tile.oacc;
+    doublex4 (&oacc)[Tile::ND] = tile.oacc;
 
     // ---- merge the KT waves that share a column tile.  Every wave publishes its
     // state (m, l, 16 accumulator values per lane) in register layout, then wave
@@ -116,12 +121,13 @@ __device__ __forceinline__ void attend_f32_body(const AttendParams& P, double* s
     mine[0 * 64 + lane] = (double)m_run;
     mine[1 * 64 + lane] = l_run;
 #pragma unroll
-    for (int dt = 0; dt < 4; ++dt)
+    for (int dt = 0; dt < Tile::ND; ++dt)
 #pragma unroll
         for (int r = 0; r < 4; ++r) mine[(2 + 4 * dt + r) * 64 + lane] = oacc[dt][r];
     PSA_TS(4);
     __syncthreads();
     PSA_TS(5);
+    if (kt * VPW >= NV) return;                               // wave-uniform (DS > 1 only: no barrier follows)
 
     double wgt[KT], mx = -INFINITY;
 #pragma unroll
@@ -133,7 +139,7 @@ __device__ __forceinline__ void attend_f32_body(const AttendParams& P, double* s
     for (int w = 0; w < KT; ++w) wgt[w] = (wgt[w] == -INFINITY) ? 0.0 : exp2_f64(wgt[w] - mx);
 
     // wave kt merges values dt0 .. dt0 + VPW - 1 of register r: elements e0 .. e0 + VPW - 1 of its query
-    const int r = kt * VPW / 4, dt0 = kt * VPW % 4, e0 = F32Tile::elem(dt0, r, g);
+    const int r = kt * VPW / Tile::ND, dt0 = kt * VPW % Tile::ND, e0 = Tile::elem(dp * Tile::ND + dt0, r, g);
     double l_tot = 0.0;
 #pragma unroll
     for (int w = 0; w < KT; ++w) l_tot += wgt[w] * smem[((size_t)(w * NCG + ct) * kStateDoubles + 1) * 64 + lane];
@@ -154,10 +160,12 @@ __device__ __forceinline__ void attend_f32_body(const AttendParams& P, double* s
         if (qi >= 0 && qi < n) {
             float* orow = static_cast<float*>(P.out) + ((size_t)head * L + qi) * kD + e0;
 #pragma unroll
-            for (int k = 0; k < VPW; k += 2) *reinterpret_cast<float2*>(orow + k) = make_float2(val[k], val[k + 1]);
+            for (int k = 0; k + 1 < VPW; k += 2) *reinterpret_cast<float2*>(orow + k) = make_float2(val[k], val[k + 1]);
+            if (VPW == 1) *orow = val[0];
         }
         return;
     }
+    if constexpr (DS == 1) {
     // The record keeps m and l in float64 and O divided by the split's own l in float32 (6e-8 relative per
     // element, far inside the parity bound): half the bytes of a float64 O, which made up a third of this
     // kernel's memory traffic.
@@ -173,15 +181,16 @@ __device__ __forceinline__ void attend_f32_body(const AttendParams& P, double* s
     // ---- the hand-over
     ticket_and_merge<512>(P, head, n, u, selp, NQ, cs);
     PSA_TS(8);
+    }
 }
 
-template <int NCG>
+template <int NCG, int DS>
 __global__ __launch_bounds__(512)
 void attend_f32_kernel(const AttendParams P)
 {
     __shared__ CommonScratch cs;
     extern __shared__ __attribute__((aligned(16))) double smem[];
-    attend_f32_body<NCG>(P, smem, cs);
+    attend_f32_body<NCG, DS>(P, smem, cs);
 }
 
 // =============================================================================
@@ -769,18 +778,22 @@ void attend_rows_bf16_kernel(const AttendParams P)
     }
 }
 
-// The four attend kernels that use more than the default 64 KB of dynamic LDS, and the
-// devices on which each has had its limit raised.
-static std::atomic<uint64_t> g_attend_raised[4];
+// The attend kernels that use more than the default 64 KB of dynamic LDS, and the
+// devices on which each has had its limit raised.  float32: 3 * (NCG - 1) + log2(DS); bfloat16 behind them.
+typedef void (*AttendKernel)(const AttendParams);
+constexpr int kAttendKernels = 8, kAttendB16 = 6;
+static const AttendKernel g_attend[kAttendKernels] = {
+    attend_f32_kernel<1, 1>, attend_f32_kernel<1, 2>, attend_f32_kernel<1, 4>,
+    attend_f32_kernel<2, 1>, attend_f32_kernel<2, 2>, attend_f32_kernel<2, 4>,
+    attend_bf16_kernel<1>, attend_bf16_kernel<2>};
+static std::atomic<uint64_t> g_attend_raised[kAttendKernels];
 static hipError_t raise_attend_limit(int k)
 {
-    const void* fn[4] = {(const void*)attend_f32_kernel<1>, (const void*)attend_f32_kernel<2>,
-                         (const void*)attend_bf16_kernel<1>, (const void*)attend_bf16_kernel<2>};
-    return ensure_lds_limit(fn[k], k < 2 ? kF32SmemBytes : kB16SmemBytes, g_attend_raised[k]);
+    return ensure_lds_limit((const void*)g_attend[k], k < kAttendB16 ? kF32SmemBytes : kB16SmemBytes, g_attend_raised[k]);
 }
 hipError_t init_attend()
 {
-    for (int k = 0; k < 4; ++k) { const hipError_t e = raise_attend_limit(k); if (e != hipSuccess) return e; }
+    for (int k = 0; k < kAttendKernels; ++k) { const hipError_t e = raise_attend_limit(k); if (e != hipSuccess) return e; }
     return hipSuccess;
 }
 
@@ -805,20 +818,12 @@ hipError_t launch_attend(const Plan& p, const Args& a, const Scratch& w)
         return hipGetLastError();
     }
     const dim3 grid = attend_grid(p.n_wg_head, p.BH, P.head_shift);
-    if (p.dtype == PSA_F32) {
-        // 72 KB of dynamic LDS: above the 64 KB default
-        const int which = p.nq_group == 16 ? 0 : 1;
-        const hipError_t e = raise_attend_limit(which);
-        if (e != hipSuccess) return e;
-        if (which == 0) hipLaunchKernelGGL(attend_f32_kernel<1>, grid, dim3(512), kF32SmemBytes, a.stream, P);
-        else            hipLaunchKernelGGL(attend_f32_kernel<2>, grid, dim3(512), kF32SmemBytes, a.stream, P);
-    } else {
-        const int which = p.nq_group == 32 ? 0 : 1;
-        const hipError_t e = raise_attend_limit(2 + which);
-        if (e != hipSuccess) return e;
-        if (which == 0) hipLaunchKernelGGL(attend_bf16_kernel<1>, grid, dim3(512), kB16SmemBytes, a.stream, P);
-        else            hipLaunchKernelGGL(attend_bf16_kernel<2>, grid, dim3(512), kB16SmemBytes, a.stream, P);
-    }
+    // 72 and 108 KB of dynamic LDS: above the 64 KB default
+    const int which = p.dtype == PSA_F32 ? (p.nq_group == 16 ? 0 : 3) + (p.d_split == 1 ? 0 : p.d_split / 2)
+                                         : kAttendB16 + (p.nq_group == 32 ? 0 : 1);
+    const hipError_t e = raise_attend_limit(which);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(g_attend[which], grid, dim3(512), p.dtype == PSA_F32 ? kF32SmemBytes : kB16SmemBytes, a.stream, P);
     if (p.separate_merge) {
         if (p.dtype == PSA_F32) {
             hipLaunchKernelGGL(merge_kernel, dim3(p.u_max, p.BH), dim3(256), 0, a.stream, P);

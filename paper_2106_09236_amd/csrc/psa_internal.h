@@ -56,7 +56,8 @@ struct Plan {
     int stream_lists;     // 1: the lists (and one V column sum per list, in vseg) come from the streaming measure kernel
     int n_split;          // attend work-groups per head along the key axis
     int tiles_per_wave;   // rounds of key tiles an attend work-group walks
-    int n_wg_head;        // attend work-groups per head = n_split * n_qgroup
+    int d_split;          // work-groups that share the output elements of a query group (float32 heads in one key split), else 1
+    int n_wg_head;        // attend work-groups per head = n_split * n_qgroup * d_split
     int rows_per_wg;      // output rows each of them fills
     int separate_merge;   // 1: too many splits for the last work-group of a head; a merge kernel follows
     int given_indices;    // 1: I_sparse comes from the caller (no measure, no selection)

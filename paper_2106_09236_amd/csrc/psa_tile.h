@@ -45,20 +45,23 @@ __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_ex
 // of keys can promise; the exponent is evaluated in float64 as well.
 //   lane (c, g) = (lane % 16, lane / 16)
 //   A[i][k]: i = c, k = g      B[k][j]: k = g, j = c      D[i][j]: i = 4r + g, j = c  (r = 0..3)
-// One object = one column tile of 16 queries walked by one wave, 32 keys a step.
+// One object = one column tile of 16 queries walked by one wave, 32 keys a step.  DS > 1: it forms 1/DS of the output elements,
+// those of accumulators dp * 4/DS .. + 4/DS - 1 (`dp`: which part).
 // =============================================================================
-struct F32Tile {
+template <int DS>
+struct F32TileOf {
+    static constexpr int ND = 4 / DS;       // accumulators
     double qreg[16];        // B of the first product: qreg[4v + e] = Q[q][16v + 4g + e]
     float4 kreg[2][4];      // A of the first product: key j0 + 16sb + c, elements 16v + 4g .. +3 (the
                             // contraction order is free; this one makes the four lanes g of a row
                             // read 64 contiguous bytes per load instruction)
-    float4 vreg[2][4];      // A of the second product: key j0 + 16sb + 4r + g, elements 4c .. 4c+3 (one
+    float vreg[2][4][ND];   // A of the second product: key j0 + 16sb + 4r + g, elements 4c .. 4c+3 (one
                             // 16-byte load per key row; 4r + g is the row order of the S^T accumulator
-                            // registers).  Component dt feeds accumulator dt, whose row m then stands
-                            // for element 4m + dt.
+                            // registers), of which this part's.  Component dt feeds accumulator dt, whose row m then
+                            // stands for element 4m + dt.
     float m_run;
     double l_run;
-    doublex4 oacc[4];       // O^T: element elem(dt, r, g) = 16r + 4g + dt of query c in oacc[dt][r]
+    doublex4 oacc[ND];      // O^T: element elem(dt, r, g) = 16r + 4g + dt of query c in oacc[dt - dp * ND][r]
 
     // Where an output element lives: accumulator register 4 dt + r of the lanes of group g.
     static __device__ __forceinline__ constexpr int elem(int dt, int r, int g) { return 16 * r + 4 * g + dt; }
@@ -66,7 +69,7 @@ struct F32Tile {
     __device__ __forceinline__ void init() {
         m_run = -INFINITY; l_run = 0.0;
 #pragma unroll
-        for (int dt = 0; dt < 4; ++dt) oacc[dt] = doublex4{0.0, 0.0, 0.0, 0.0};
+        for (int dt = 0; dt < ND; ++dt) oacc[dt] = doublex4{0.0, 0.0, 0.0, 0.0};
     }
     // Rows come through a buffer descriptor over the head's valid rows (head_rows), which reads zeros beyond them:
     // no clamp, no select and, above all, no branch around a load (the compiler made one of every guarded load
@@ -86,11 +89,22 @@ struct F32Tile {
 #pragma unroll
             for (int v = 0; v < 4; ++v) dst[sb][v] = buffer_load16<float4>(k, (j0 + 16 * sb + c) * 256 + 16 * g + 64 * v);
     }
-    __device__ __forceinline__ void load_v(__amdgpu_buffer_rsrc_t v, int j0, int c, int g) {
+    __device__ __forceinline__ void load_v(__amdgpu_buffer_rsrc_t v, int j0, int c, int g, int dp = 0) {
 #pragma unroll
         for (int sb = 0; sb < 2; ++sb)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) vreg[sb][r] = buffer_load16<float4>(v, (j0 + 16 * sb + 4 * r + g) * 256 + 16 * c);
+            for (int r = 0; r < 4; ++r) {
+                const int ofs = (j0 + 16 * sb + 4 * r + g) * 256 + 16 * c;
+                if constexpr (DS == 1) {
+                    const float4 x = buffer_load16<float4>(v, ofs);
+                    vreg[sb][r][0] = x.x; vreg[sb][r][1] = x.y; vreg[sb][r][2] = x.z; vreg[sb][r][3] = x.w;
+                } else if constexpr (DS == 2) {
+                    const float2 x = __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(v, ofs + 8 * dp, 0, 0));
+                    vreg[sb][r][0] = x.x; vreg[sb][r][1] = x.y;
+                } else {
+                    vreg[sb][r][0] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(v, ofs + 4 * dp, 0, 0));
+                }
+            }
     }
     // First product for both 16-key sub-tiles of the K tile in kreg (two independent
     // MFMA chains): s[sb][r] = q . k of key j0 + 16sb + 4r + g, unscaled.
@@ -113,10 +127,10 @@ struct F32Tile {
     // otherwise it is requested here, once the first product has been issued, so
     // that it arrives under the MFMAs and the softmax.
     template <bool V_PRELOADED = false>
-    __device__ __forceinline__ void step(__amdgpu_buffer_rsrc_t vrows, int j0, int n, int c, int g) {
+    __device__ __forceinline__ void step(__amdgpu_buffer_rsrc_t vrows, int j0, int n, int c, int g, int dp = 0) {
         doublex4 s[2];
         scores(s);
-        if (!V_PRELOADED) load_v(vrows, j0, c, g);
+        if (!V_PRELOADED) load_v(vrows, j0, c, g, dp);
         // online softmax in base 2 over the 32 keys.  The subtracted constant only
         // has to be the same for every key of a query, so the running max is kept
         // in float32 while the exponent itself is formed in float64.  Scores beyond
@@ -150,20 +164,20 @@ struct F32Tile {
             }
         l_run = l_run * alpha + lsum;
         m_run = m_new;
-        // second product: four independent chains (one per 16 output elements)
+        // second product: independent chains (one per 16 output elements)
 #pragma unroll
-        for (int dt = 0; dt < 4; ++dt) oacc[dt] *= alpha;
+        for (int dt = 0; dt < ND; ++dt) oacc[dt] *= alpha;
 #pragma unroll
         for (int sb = 0; sb < 2; ++sb)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                oacc[0] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)vreg[sb][r].x, p[sb][r], oacc[0], 0, 0, 0);
-                oacc[1] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)vreg[sb][r].y, p[sb][r], oacc[1], 0, 0, 0);
-                oacc[2] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)vreg[sb][r].z, p[sb][r], oacc[2], 0, 0, 0);
-                oacc[3] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)vreg[sb][r].w, p[sb][r], oacc[3], 0, 0, 0);
+#pragma unroll
+                for (int dt = 0; dt < ND; ++dt)
+                    oacc[dt] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)vreg[sb][r][dt], p[sb][r], oacc[dt], 0, 0, 0);
             }
     }
 };
+using F32Tile = F32TileOf<1>;
 
 // =============================================================================
 // bfloat16 tensors: v_mfma_f32_32x32x16_bf16, float32 accumulation; the
