@@ -201,14 +201,24 @@ __device__ __forceinline__ SelList attend_prologue(const AttendParams& P, int he
                 // p = ceil(u / lists), at least u candidates are no smaller than T = the least of the lists'
                 // p-th keys, so only each list's prefix of keys >= T takes part; a candidate's place among
                 // those is its place among all (everything that comes before it is >= T as well).
-                if (tid < 8) {
-                    const int pp = (u + nl - 1) / nl - 1;
-                    unsigned tl = 0xFFFFFFFFu;
-                    for (int l2 = 0; l2 < nl; ++l2) { const unsigned k2 = pp < len ? cs.ckey[l2 * len + pp] : 0u; tl = k2 < tl ? k2 : tl; }
-                    int lo = 0, hi = tid < nl ? len : 0;                // entries of list tid with key >= T
-                    const unsigned* lst = cs.ckey + (tid < nl ? tid : 0) * len;
-                    while (lo < hi) { const int mid = (lo + hi) >> 1; if (lst[mid] >= tl) lo = mid + 1; else hi = mid; }
-                    cs.plen[tid] = lo;
+                // A wave counts the prefix of its list, an entry to a lane (one thread per list, with a binary search: 0.4 to 0.6 us
+                // more of every work-group; B=8 H=8 L=2048 bfloat16 55.3 -> 54.8 us, B=1 H=4 L=333 float32 21.6 -> 21.0).
+                const int lane = tid & 63;
+#pragma unroll 1
+                for (int my = __builtin_amdgcn_readfirstlane(tid >> 6); my < 8; my += NT / 64) {
+                    const int pp = (u + nl - 1) / nl - 1, l2 = (lane & 7) < nl ? lane & 7 : 0;
+                    const unsigned* lst = cs.ckey + (my < nl ? my : 0) * len;
+                    unsigned tl = cs.ckey[l2 * len + (pp < len ? pp : len - 1)];
+                    tl = pp < len ? tl : 0u;
+                    tl = min(tl, (unsigned)__builtin_amdgcn_update_dpp(0, (int)tl, 0xB1, 0xF, 0xF, false));     // over 8 lanes
+                    tl = min(tl, (unsigned)__builtin_amdgcn_update_dpp(0, (int)tl, 0x4E, 0xF, 0xF, false));
+                    tl = min(tl, (unsigned)__builtin_amdgcn_update_dpp(0, (int)tl, 0x141, 0xF, 0xF, false));
+                    int count = 0;
+                    for (int e0 = 0; e0 < len; e0 += 64) {
+                        const int at = e0 + lane;
+                        count += __popcll(__ballot(at < len && lst[at < len ? at : 0] >= tl));
+                    }
+                    if (lane == 0) cs.plen[my] = my < nl ? count : 0;
                 }
                 lds_barrier();
                 int off[9];

@@ -44,3 +44,17 @@ def test_shared_elements(B, H, L, groups, fill):
             for x in (w.Q, w.K, w.V):
                 x[b, :, int(w.lengths[b]):] = 0
     check_against_oracle(w, label=f"shared B{B} H{H} L{L} {fill}", fill=fill)
+
+
+@pytest.mark.parametrize("B,H,L,r,lists,length", [(1, 2, 5000, 0.05, 8, 250), (1, 1, 300, 0.3, 5, 64), (2, 2, 700, 0.1, 0, 0)])
+@pytest.mark.parametrize("first", [0, 1, 2])
+def test_most_of_the_selection_from_one_list(B, H, L, r, lists, length, first):
+    # more than 4 candidate lists, whose entries are counted 64 at a time: nearly all selected queries in the first, a middle or
+    # the last part of the head, so that one list takes part with all its entries and others with none
+    p = plan(B, H, L, 12, "f32", r_sparse=r)
+    if lists:
+        assert (int(p["lists"]), int(p["list_len"])) == (lists, length)
+    w = W.make_workload(W.small_config("onelist", B, H, L, 12, 5.0, "f32", "normal"), seed=70 + first)
+    at = (0, L // 2, L - L // 8)[first]
+    w.Q[:, :, at:at + L // 8] *= 6
+    check_against_oracle(w, label=f"one list L{L} at {at}", r_sparse=r)
