@@ -28,8 +28,11 @@
 //     group's query rows as float64 in LDS, where the work-group has put them once;
 //   * run two work-groups of 4 waves (one per SIMD) on a CU, so that one fills the matrix pipe while the other
 //     stages rows, waits at a barrier or stores, and cut the key axis so that their number fills whole rounds of
-//     the CUs.
-// Measured (whole call): B=16 H=4 L=512, 256 kept queries 225 -> 167 us.
+//     the CUs;
+//   * keep a head's work-groups on one XCD where the heads divide evenly: each L2 fetches the rows of its own heads, not
+//     the kept rows of Q and G of all (the first product of a work-group waits for 8 us, not for 14).
+// Measured (whole call): B=16 H=4 L=512, 256 kept queries 225 -> 162 us, the last step 3.5 of them; B=8 H=8 L=300, 120 kept
+// 102.0 -> 98.2 in that step, B=24 H=8 L=200, 100 kept 133.1 -> 129.9 us.
 #include <type_traits>
 
 #include "psa_backward_common.h"
@@ -106,7 +109,10 @@ struct BwdParams {
     double* dq_part;       // [BH][S2][u_pad][64], or nullptr: dQ rows are written directly
     double* stats;         // [BH][u_pad][2]       (log2 sum exp, -D/8) per kept query, kKeysOnly form; else nullptr
     int H, L, u_stride, u_pad, n_group, S1, blocks1, S2, blocks2, fill;
+    int head_shift;        // 3: eight heads on the fastest axis of the grid, so that a head's work-groups share one XCD's L2; else 0
 };
+__device__ __forceinline__ int bwd_head(const BwdParams& P, int y) { return (y << P.head_shift) + (int)(blockIdx.x & ((1u << P.head_shift) - 1u)); }
+__device__ __forceinline__ int bwd_index(const BwdParams& P) { return (int)(blockIdx.x >> P.head_shift); }
 
 // Kept queries q0 .. q0 + ROWS - 1 of the head: their rows of Q and of G as float64 in LDS (zeros for an absent
 // entry), 8 threads per row.  `find` looks the rows up in the list, `request` asks for them, `put` writes them to
@@ -198,7 +204,7 @@ __device__ __forceinline__ int opaque(int x) { asm volatile("" : "+v"(x)); retur
 constexpr double kBwdNoMax = -1e300;
 
 // ---- partial softmax statistics per kept query and key split; column sums of G over the rows the mean fill serves.
-// grid (key splits, groups of 64 kept queries, heads)
+// grid (key splits, groups of 64 kept queries, heads), eight heads (or one) on the first axis
 template <typename T>
 __global__ __launch_bounds__(kBwdThreads, 2)
 void bwd_stats_kernel(const BwdParams P)
@@ -207,7 +213,7 @@ void bwd_stats_kernel(const BwdParams P)
     __shared__ unsigned s_bits[kBwdChunk / 32];
     double* sQ = bwd_smem;
     double* sG = bwd_smem + kBwdStatGroup * kBwdQRow;
-    const int split = blockIdx.x, group = blockIdx.y, head = blockIdx.z;
+    const int split = bwd_index(P), group = blockIdx.y, head = bwd_head(P, blockIdx.z);
     const int b = head / P.H, L = P.L;
     const int n = valid_len(P.lengths, b, L);
     const int ub = kept_count(P, b, n);
@@ -392,14 +398,14 @@ __device__ __forceinline__ bwd_x2 stat_of(const BwdParams& P, int head, int t, i
 // and are, unchanged, the B operand of the product that contracts over keys.  Wave w takes the 16 keys 16 w .. + 15 of
 // every 64; the waves' shares of dQ are added in wave order at the end, so nothing goes through memory.  The price is
 // the two score products, formed a third time (48 MFMAs for a tile of 16 queries x 16 keys instead of 16).
-// grid (tiles of 16 kept queries, heads)
+// grid (tiles of 16 kept queries, heads), heads as above
 template <typename T>
 __global__ __launch_bounds__(kBwdThreads, 2)
 void bwd_dq_kernel(const BwdParams P)
 {
     __shared__ bwd_x2 s_stat[kBwdQ];
     __shared__ double s_acc[kBwdWaves][16][64];                      // the waves' accumulators, register by register
-    const int q0 = blockIdx.x * kBwdQ, head = blockIdx.y;
+    const int q0 = bwd_index(P) * kBwdQ, head = bwd_head(P, blockIdx.y);
     const int b = head / P.H, L = P.L;
     const int n = valid_len(P.lengths, b, L);
     const int ub = kept_count(P, b, n);
@@ -491,7 +497,7 @@ void bwd_dq_kernel(const BwdParams P)
 // unchanged, the B operand of the products that contract over queries (dK, dV).  For dQ, which contracts over keys,
 // the waves put their g values into LDS; wave w then takes elements 16 w .. + 15 of both tiles over all keys of the
 // block, so that nothing has to be added up across waves.
-// grid (key splits, heads), blocks2 key blocks per work-group, which adds to the dQ it wrote for the block before.
+// grid (key splits, heads), heads as above, blocks2 key blocks per work-group, which adds to the dQ it wrote for the block before.
 template <typename T, int KS, BwdForm FORM>
 __global__ __launch_bounds__(kBwdThreads, 2)
 void bwd_main_kernel(const BwdParams P)
@@ -506,7 +512,7 @@ void bwd_main_kernel(const BwdParams P)
     double* sg = sG + kBwdGroup * kBwdQRow;                          // [2 tiles][16 queries][GR]
     float* sK = reinterpret_cast<float*>(sg + kBwdGroup * GR);       // [keys][kBwdKRow]
     bwd_x2* s_stat = reinterpret_cast<bwd_x2*>(sK + SH::kKeys * kBwdKRow);       // [queries] (log2 sum exp, -D/8)
-    const int split = blockIdx.x, head = blockIdx.y;
+    const int split = bwd_index(P), head = bwd_head(P, blockIdx.y);
     const int b = head / P.H, L = P.L;
     const int n = valid_len(P.lengths, b, L);
     const int ub = kept_count(P, b, n);
@@ -818,10 +824,10 @@ template <typename T>
 __global__ __launch_bounds__(256)
 void bwd_dq_reduce_kernel(const BwdParams P)
 {
-    const int head = blockIdx.y;
+    const int head = bwd_head(P, blockIdx.y);
     const int n = valid_len(P.lengths, head / P.H, P.L);
     const int ub = kept_count(P, head / P.H, n);
-    const int t = blockIdx.x * 16 + (threadIdx.x >> 4), e0 = 4 * (threadIdx.x & 15);
+    const int t = bwd_index(P) * 16 + (threadIdx.x >> 4), e0 = 4 * (threadIdx.x & 15);
     const int qi = kept_row(P, head, t, n, ub);
     if (qi < 0) return;
     const double* dp = P.dq_part + ((size_t)head * P.S2 * P.u_pad + t) * kD + e0;
@@ -855,10 +861,12 @@ static hipError_t launch_bwd_t(const BwdParams& P, int BH, int ks, hipStream_t s
 {
     const hipError_t e = raise_bwd_limits<T>();
     if (e != hipSuccess) return e;
-    const dim3 grid(P.S2, BH), block(kBwdThreads);
-    hipLaunchKernelGGL(bwd_stats_kernel<T>, dim3(P.S1, P.n_group, BH), block, kBwdStatsLds, stream, P);
+    auto dealt = [&](int x) { return (unsigned)x << P.head_shift; };
+    const unsigned heads = (unsigned)BH >> P.head_shift;
+    const dim3 grid(dealt(P.S2), heads), block(kBwdThreads);
+    hipLaunchKernelGGL(bwd_stats_kernel<T>, dim3(dealt(P.S1), P.n_group, heads), block, kBwdStatsLds, stream, P);
     if (P.stats) {
-        hipLaunchKernelGGL(bwd_dq_kernel<T>, dim3(P.u_pad / kBwdQ, BH), block, 0, stream, P);
+        hipLaunchKernelGGL(bwd_dq_kernel<T>, dim3(dealt(P.u_pad / kBwdQ), heads), block, 0, stream, P);
         if (ks == 4) hipLaunchKernelGGL((bwd_main_kernel<T, 4, kKeysOnly>), grid, block, BwdShare<4>::kFixed + kBwdGroup * 16, stream, P);
         else         hipLaunchKernelGGL((bwd_main_kernel<T, 2, kKeysOnly>), grid, block, BwdShare<2>::kFixed + kBwdGroup * 16, stream, P);
     } else if (P.u_pad > kBwdKeepStats)
@@ -867,7 +875,7 @@ static hipError_t launch_bwd_t(const BwdParams& P, int BH, int ks, hipStream_t s
         hipLaunchKernelGGL((bwd_main_kernel<T, 4, kFused>), grid, block, BwdShare<4>::kFixed + P.u_pad * 16, stream, P);
     else
         hipLaunchKernelGGL((bwd_main_kernel<T, 2, kFused>), grid, block, BwdShare<2>::kFixed + P.u_pad * 16, stream, P);
-    if (P.dq_part) hipLaunchKernelGGL(bwd_dq_reduce_kernel<T>, dim3(P.u_pad / kBwdQ, BH), dim3(256), 0, stream, P);
+    if (P.dq_part) hipLaunchKernelGGL(bwd_dq_reduce_kernel<T>, dim3(dealt(P.u_pad / kBwdQ), heads), dim3(256), 0, stream, P);
     return hipGetLastError();
 }
 
@@ -979,7 +987,7 @@ hipError_t launch_backward(const psa_shape_t& s, const BwdPlan& bp, const void* 
     P.stats = bp.keys_only ? reinterpret_cast<double*>(w + bp.off_stats) : nullptr;
     P.H = s.H; P.L = s.L_K; P.u_stride = u_stride; P.u_pad = bp.u_pad; P.n_group = bp.n_group;
     P.S1 = bp.S1; P.blocks1 = bp.blocks1; P.S2 = bp.S2; P.blocks2 = bp.blocks2;
-    P.fill = fill;
+    P.fill = fill; P.head_shift = (s.B * s.H) % 8 == 0 ? 3 : 0;
     return launch_bwd_t<float>(P, s.B * s.H, bp.ks, stream);
 }
 
