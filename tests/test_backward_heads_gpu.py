@@ -13,4 +13,4 @@ pytestmark = pytest.mark.gpu
     (1, 8, 1700, 850), (1, 9, 1700, 850),                                # dQ from a kernel of its own
 ])
 def test_heads_in_eights(B, H, L, u):
-    tiles.test_tiles(B, H, L, u, "f32")
+    tiles.test_tiles("f32", B, H, L, u)
