@@ -518,15 +518,19 @@ struct SplitLayout {
     static_assert(kEpiRows * kEpiStride * 4 <= 3 * kPlane * 2, "the staging tile fits in the operand planes");
 };
 
-template <int WM, int WN>
-__global__ __launch_bounds__(256, 2)
+// KG = 2, for few rows: two groups of 4 waves take every other chunk, each with planes of its own, and their sums are added at the end.
+// What bounds such a call is the chain of one work-group's chunks (split, LDS, reads, twelve dependent MFMAs: 0.5 us each),
+// which the second group halves; four groups gained less (B=1 H=4 L=333: 39.9, 37.4, 38.2 us with one, two, four).  The
+// sums are half as long, so their error is no larger.
+template <int WM, int WN, int KG>
+__global__ __launch_bounds__(256 * KG, 2)
 void project_split_kernel(const ProjectParams P)
 {
     using LY = SplitLayout<WM, WN>;
     typedef float Vec __attribute__((ext_vector_type(4)));
     constexpr int CH = 32, S = LY::kRow, TM = LY::kTM, TN = LY::kTN;
     constexpr int NA = TM / 32, NW = TN / 32;              // float4 vectors per thread and chunk: rows of A, rows of W
-    __shared__ __attribute__((aligned(16))) uint16_t smem[3 * LY::kPlane];
+    __shared__ __attribute__((aligned(16))) uint16_t s_planes[KG][3 * LY::kPlane];
     __shared__ __attribute__((aligned(16))) float sBias[TN];
 
     PSA_TS(0);
@@ -544,10 +548,13 @@ void project_split_kernel(const ProjectParams P)
     const float* bias = static_cast<const float*>(which == 0 ? P.bias[0] : (which == 1 ? P.bias[1] : P.bias[2]));
     float* C = static_cast<float*>(which == 0 ? P.C[0] : (which == 1 ? P.C[1] : P.C[2]));
     const int n0 = (inner % n_nt) * TN, m0 = mt * TM;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int kg = KG == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 8);       // which chunks: kg, kg + KG, ...
+    uint16_t* const smem = s_planes[kg];
+    const int tid = threadIdx.x & 255, lane = tid & 63, wave = tid >> 6;
     const int c = lane & 31, h = lane >> 5;
     const int wm = wave >> 1, wn = wave & 1;
-    const int n_kc = P.Kd / CH;
+    const int rounds = P.Kd / (CH * KG);                   // (Kd is a multiple of 64: as many for each group)
+    static_assert(64 % (CH * KG) == 0, "whole rounds");
 
     // this thread's share of the tiles: float4 `col` of rows row0 + 32 j
     const int row0 = tid >> 3, col = tid & 7;
@@ -578,8 +585,8 @@ void project_split_kernel(const ProjectParams P)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
-    auto fetch = [&](int kc) {
-        const int k0 = kc * CH;
+    auto fetch = [&](int round) {
+        const int k0 = (KG * round + kg) * CH;
         const size_t ka = P.a_heads ? (size_t)(k0 >> 6) * head_stride + (k0 & 63) : (size_t)k0;
 #pragma unroll
         for (int j = 0; j < NA; ++j) ra[j] = *reinterpret_cast<const Vec*>(a_ptr[j] + ka);
@@ -604,9 +611,9 @@ void project_split_kernel(const ProjectParams P)
         bias_raw = (bias ? bias : W)[nb < P.N ? nb : P.N - 1];    // unconditional, clamped; W stands in for a missing bias
     }
     fetch(0);
-    if (tid < TN) sBias[tid] = (bias && n0 + tid < P.N) ? bias_raw : 0.f;
-    for (int kc = 0; kc < n_kc; ++kc) {
-        if (kc < 2) PSA_TS(1 + kc);
+    if (kg == 0 && tid < TN) sBias[tid] = (bias && n0 + tid < P.N) ? bias_raw : 0.f;
+    for (int round = 0; round < rounds; ++round) {
+        if (round < 2) PSA_TS(1 + round);
         __syncthreads();                                  // the previous chunk's reads of LDS are done
         {
             uint16_t* sa = smem + row0 * S + col * 4;
@@ -617,7 +624,7 @@ void project_split_kernel(const ProjectParams P)
             for (int j = 0; j < NW; ++j) put_split(sw + 32 * j * S, rw[j]);
         }
         __syncthreads();
-        if (kc + 1 < n_kc) fetch(kc + 1);                 // travels during the products
+        if (round + 1 < rounds) fetch(round + 1);         // travels during the products
         __builtin_amdgcn_sched_barrier(0);                // (keeps the loads above them)
         const uint16_t* ar = smem + (wm * 32 * WM + c) * S + 8 * h;
         const uint16_t* wr = smem + (TM + wn * 32 * WN + c) * S + 8 * h;
@@ -648,6 +655,25 @@ void project_split_kernel(const ProjectParams P)
         }
     }
     PSA_TS(3);
+    if constexpr (KG > 1) {
+        // the groups' shares of the tile together, in order of the groups: each through its own planes' LDS
+        static_assert(WM == 1 && WN == 1 && 4 * 16 * 64 * 4 <= 3 * LY::kPlane * 2, "a group's sums fit in its planes");
+        __syncthreads();
+        float* const mine = reinterpret_cast<float*>(smem) + (wave * 16) * 64 + lane;
+        if (kg > 0) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) mine[r * 64] = acc[0][0][r];
+        }
+        __syncthreads();
+        if (kg == 0) {
+#pragma unroll
+            for (int k = 1; k < KG; ++k) {
+                const float* other = reinterpret_cast<const float*>(s_planes[k]) + (wave * 16) * 64 + lane;
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[0][0][r] += other[r * 64];
+            }
+        }
+    }
 
     // ---- epilogue (as in project_kernel): bias in registers, the tile through LDS one row of
     // waves at a time, stores of whole 128-byte lines
@@ -663,7 +689,7 @@ void project_split_kernel(const ProjectParams P)
 #pragma unroll
     for (int p = 0; p < 2; ++p) {
         __syncthreads();                                  // the operand planes (or the previous pass) are no longer read
-        if (wm == p) {
+        if (kg == 0 && wm == p) {
 #pragma unroll
             for (int i = 0; i < WM; ++i)
 #pragma unroll
@@ -677,6 +703,7 @@ void project_split_kernel(const ProjectParams P)
                     }
         }
         __syncthreads();
+        if (KG > 1 && kg > 0) continue;                   // wave-uniform
         const int vec = tid % VROW;
         const int n = n0 + vec * 4;                       // N is a multiple of 64: a vector is inside or outside
 #pragma unroll
@@ -700,12 +727,12 @@ void project_split_kernel(const ProjectParams P)
     PSA_TS_WALL(6);
 }
 
-template <int WM, int WN>
+template <int WM, int WN, int KG = 1>
 static hipError_t launch_project_split(const ProjectParams& P, hipStream_t stream)
 {
     using LY = SplitLayout<WM, WN>;
     const int n_nt = (P.N + LY::kTN - 1) / LY::kTN, n_mt = (P.M + LY::kTM - 1) / LY::kTM;
-    hipLaunchKernelGGL((project_split_kernel<WM, WN>), dim3(8 * ((n_mt + 7) / 8) * n_nt * P.n_mat), dim3(256), 0, stream, P);
+    hipLaunchKernelGGL((project_split_kernel<WM, WN, KG>), dim3(8 * ((n_mt + 7) / 8) * n_nt * P.n_mat), dim3(256 * KG), 0, stream, P);
     return hipGetLastError();
 }
 
@@ -777,7 +804,11 @@ static hipError_t launch_project(const ProjectParams& P0, int n_mat, int dtype, 
     if (dtype == PSA_F32) {
         // (128 x 64 tiles give 2 wg128 work-groups, 64 x 64 tiles 4 wg128)
         if (wg128 >= 512) return launch_project_split<2, 2>(P, stream);
-        return 2 * wg128 >= 512 ? launch_project_split<2, 1>(P, stream) : launch_project_split<1, 1>(P, stream);
+        if (2 * wg128 >= 512) return launch_project_split<2, 1>(P, stream);
+        // (two groups of waves while their work-groups, two to a compute unit, are there at once: whole module, B=1 H=4 L=333, 96
+        // and 24 of them, 39.9 -> 37.4 us; B=1 H=8 L=333 52.1 -> 45.2; B=8 H=4 L=300, 456, 43.6 -> 42.1; B=8 H=8 L=300, 912, 75.6 -> 77.0)
+        const long wg64 = (long)((P.N + 63) / 64) * ((P.M + 63) / 64) * n_mat;
+        return wg64 <= 512 ? launch_project_split<1, 1, 2>(P, stream) : launch_project_split<1, 1>(P, stream);
     }
     if (stream_pays(P) && stream_fits(P))
         return P.a_heads ? launch_project_stream<true, false>(P, stream) : launch_project_stream<false, true>(P, stream);

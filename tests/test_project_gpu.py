@@ -1,5 +1,5 @@
-"""The projections of bfloat16 tensors with many rows (256 x 128 tiles, several to a work-group) against the same rows in calls
-that are too small for that kernel, which tests/test_parity_gpu.py compares with the oracle.  Both add the products of a row in
+"""The projections at the edges of their kernels.  bfloat16 tensors with many rows (256 x 128 tiles, several to a work-group)
+against the same rows in calls that are too small for that kernel, which tests/test_parity_gpu.py compares with the oracle.  Both add the products of a row in
 the same order, so the results are the same bits: no tolerance."""
 import pytest
 import torch
@@ -35,3 +35,26 @@ def test_many_rows_equal_few_rows(B, L, H, bias):
             for name, m, f in zip("QKV", many, few):
                 assert torch.equal(m[b:b + n, :, l:l + 2000], f), (name, b, l)
             assert torch.equal(many[3][b:b + n, l:l + 2000], few[3]), ("Y", b, l)
+
+
+@pytest.mark.parametrize("B,L,H", [(1, 1, 1), (1, 65, 2), (2, 33, 3), (1, 63, 8),
+                                   (1, 2688, 4), (1, 2689, 4)])                    # 504 and 516 work-groups for Q, K and V: the last with two groups and the first with one
+def test_few_rows_of_float32(B, L, H):
+    # two groups of waves add every other chunk of a contraction.  Against float64, element by element: every product is off by at
+    # most 3 * 2^-25 (three bfloat16 parts of a factor, six of nine products) and every addition of at most 6 dm + 2 by 2^-24
+    # of the sum of the products' sizes (first order; twice that is allowed)
+    dm = H * 64
+    g = torch.Generator(device="cuda")
+    g.manual_seed(L)
+    X = torch.randn((B, L, dm), generator=g, device="cuda")
+    A = torch.randn((B, H, L, 64), generator=g, device="cuda")
+    Ws = [torch.randn((dm, dm), generator=g, device="cuda") / dm ** 0.5 for _ in range(4)]
+    bs = [torch.randn(dm, generator=g, device="cuda") for _ in range(4)]
+    weights = psa.make_weights(*Ws, *bs)
+    got = psa.probsparse_qkv_project(X, weights) + (psa.probsparse_out_project(A, weights),)
+    rows = [X, X, X, A.transpose(1, 2).reshape(B, L, dm)]
+    for k, name in enumerate("QKVY"):
+        have = got[k].double() if k == 3 else got[k].double().transpose(1, 2).reshape(B, L, dm)
+        x, w, b = rows[k].double(), Ws[k].double(), bs[k].double()
+        size = x.abs() @ w.abs().T + b.abs()
+        assert bool(((have - (x @ w.T + b)).abs() <= 2 * (1.5 + 6 * dm + 2) * 2.0 ** -24 * size).all()), name
