@@ -8,8 +8,8 @@
 // Both operands have the contraction index contiguous (W is stored [d_out, d_in]),
 // which is the layout the MFMA operands want.  A work-group of 4 waves computes a
 // 128 x 128 tile of C, each wave a 64 x 64 quarter as 2 x 2 MFMA tiles of 32 x 32
-// (128 x 64 with 2 x 1 MFMA tiles per wave for shapes that would otherwise leave
-// compute units without work).  The products are taken as C^T = W A^T (rows of W on
+// (128 x 64 with 2 x 1 MFMA tiles per wave, or 64 x 64, for shapes that would
+// otherwise leave compute units without work).  The products are taken as C^T = W A^T (rows of W on
 // the MFMA row axis), so that a lane ends up with one row of C and runs of four
 // consecutive columns:
 //   v_mfma_f32_32x32x16_bf16, lane (c, h) = (lane % 32, lane / 32):
@@ -812,6 +812,11 @@ static hipError_t launch_project(const ProjectParams& P0, int n_mat, int dtype, 
     }
     if (stream_pays(P) && stream_fits(P))
         return P.a_heads ? launch_project_stream<true, false>(P, stream) : launch_project_stream<false, true>(P, stream);
+    // Few rows: 64 x 64 tiles, four times as many work-groups with half of the loads and a quarter of the stores each, as long
+    // as all are there at once (four to a compute unit).  Whole module, 128 x 64 -> 64 x 64: B=1 H=4 L=40 20.8 -> 19.2 us, B=1
+    // H=8 L=333 33.6 -> 31.0, B=4 H=8 L=400 (624 of them for Q, K and V) 37.2 -> 34.8, B=3 H=8 L=2000 (752 for the output
+    // matrix) 70.5 -> 69.2; B=24 H=8 L=500 (1504 for the output matrix) 78.3 -> 78.8.
+    if (wg128 <= 256) return launch_project_as<1, 1>(P, stream);
     return wg128 >= 512 ? launch_project_as<2, 2>(P, stream) : launch_project_as<2, 1>(P, stream);
 }
 
