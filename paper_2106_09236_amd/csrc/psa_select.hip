@@ -113,23 +113,26 @@ void select_segments_kernel(const float* __restrict__ M, const int* __restrict__
     const float* Mh = M + (size_t)head * L + i0;
     block_select<NT, 2>(Mh, false, n_here, u_here, cand_len, s_sel, sc, part_sum);
     __syncthreads();
-    // s_sel: the kept queries of the segment, ascending.  Rank them by (key descending, index ascending).
-    unsigned key = 0u;
-    int q = -1;
-    if (tid < u_here) { q = s_sel[tid]; key = order_key(Mh[q]); }
-    if (tid < kSegCandMax) s_key[tid] = key;
+    // s_sel: the kept queries of the segment, ascending.  Rank them by (key descending, index ascending): 16 lanes to a query, each
+    // against every 16th key, where a thread to a query met all keys in turn (this and the scans of block_select by DPP:
+    // B=1 H=8 L=16384, 49 kept, 9.7 -> 6.9 us).
+    if (tid < kSegCandMax) s_key[tid] = tid < u_here ? order_key(Mh[s_sel[tid]]) : 0u;
     __syncthreads();
     uint2* co = cand + ((size_t)head * n_seg + seg) * cand_len;
-    if (tid < u_here) {
+    for (int me = tid >> 4; me < u_here; me += NT / 16) {
+        const unsigned key = s_key[me];
         int rank = 0;
-        for (int t = 0; t < u_here; ++t) {
+        for (int t = tid & 15; t < u_here; t += 16) {
             const unsigned ko = s_key[t];
-            rank += (ko > key || (ko == key && t < tid)) ? 1 : 0;
+            rank += (ko > key || (ko == key && t < me)) ? 1 : 0;
         }
-        co[rank] = make_uint2(key, (unsigned)(i0 + q));
-    } else if (tid < cand_len) {
-        co[tid] = make_uint2(0u, 0xFFFFFFFFu);             // empty slot
+        rank += __builtin_amdgcn_update_dpp(0, rank, 0xB1, 0xF, 0xF, false);      // over the 16 lanes
+        rank += __builtin_amdgcn_update_dpp(0, rank, 0x4E, 0xF, 0xF, false);
+        rank += __builtin_amdgcn_update_dpp(0, rank, 0x141, 0xF, 0xF, false);
+        rank += __builtin_amdgcn_update_dpp(0, rank, 0x140, 0xF, 0xF, false);
+        if ((tid & 15) == 0) co[rank] = make_uint2(key, (unsigned)(i0 + s_sel[me]));
     }
+    for (int t = u_here + tid; t < cand_len; t += NT) co[t] = make_uint2(0u, 0xFFFFFFFFu);      // empty slots
 }
 
 // Caller-given index sets (Sec. 4.4: a layer reuses the index set of the layer
