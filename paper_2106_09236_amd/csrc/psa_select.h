@@ -35,7 +35,7 @@ __device__ __forceinline__ int n_selected(URule r, int n, int u_max) {
 // Inclusive prefix sum, and running maximum, over the lanes of a wave (the last lane holds the whole wave's).  By DPP moves within
 // the register file, 6 of them: a shuffle goes through the LDS unit, and the six of a scan follow one another.  The select
 // kernel does some five such scans, each at a point where the whole work-group waits (64 heads of 2048 queries, half of them
-// kept: 8.1 -> 6.4 us).
+// kept: 8.1 -> 6.4 us, the whole call 105.7 -> 104.1).
 template <int CTRL, int ROWS>
 __device__ __forceinline__ unsigned dpp_or_zero(unsigned v) { return (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xF, false); }
 __device__ __forceinline__ unsigned wave_scan_add(unsigned v) {
