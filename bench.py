@@ -453,8 +453,8 @@ def variant_line(args, cfg, w, timer):
             assert rc == 0, rc
         # Q, K, V, dOut in; dQ, dK, dV out
         alg_bytes = 7 * nq * 64 * s
-        what = f"gradients of the attention and fill steps for the forward's own index sets (u = {u}), mean fill, float64 arithmetic"
-        plan = "stats + dq + dkv (+ dq reduce)"
+        what = f"gradients of the attention and fill steps for the forward's own index sets (u = {u}), mean fill, {'float64' if cfg.dtype == 'f32' else 'float32'} arithmetic"
+        plan = "stats + main (+ dq reduce)"
         extra_flops = 4 * 4 * cfg.B * cfg.H * u * cfg.L * 64 - 4 * cfg.B * cfg.H * u * cfg.L * 64     # five products, two of them twice
     else:
         um = psa.u_max(shape, cfg.c)
@@ -481,8 +481,6 @@ def variant_line(args, cfg, w, timer):
     tf, gbs = flops / (us * 1e-6) / 1e12, alg_bytes / (us * 1e-6) / 1e9
     # (the module mixes float32/bfloat16 GEMM flops with the attention's: no single matrix peak applies, so its
     # line is priced against HBM by algorithmic bytes)
-    if args.variant == "bwd":
-        peak = FP64_MFMA_PEAK_TFLOPS                          # float64 MFMA for both tensor types
     if args.variant != "mhsa" and tf / peak > gbs / HBM_PEAK_GBS:
         roofline = {"kernel": "whole call", "bound": "mfma", "achieved": round(tf, 3), "peak": peak, "unit": "TFLOP/s",
                     "frac": round(tf / peak, 4), "traffic": None}
@@ -495,7 +493,7 @@ def variant_line(args, cfg, w, timer):
         "warmup": args.warmup, "ms_per_step": round(us * 1e-3, 6), "latency_us": round(us, 3),
         "latency_us_min": round(t["min"], 3), "latency_us_max": round(t["max"], 3),
         "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
-        "dtype": "f64" if (cfg.dtype == "f32" or args.variant == "bwd") else "f32", "data": "synthetic",
+        "dtype": "f64" if cfg.dtype == "f32" else "f32", "data": "synthetic",
         "config": {"workload": workload_label(cfg), "tensor_dtype": cfg.dtype,
                    "variant": f"{args.variant}: {what}", "queries_per_step": nq, "input_copies_rotated": n_sets,
                    "launch": f"hip graph of {args.steps} steps, median of {timer.replays} replays", "kernel_plan": plan},

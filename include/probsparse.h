@@ -209,9 +209,11 @@ int probsparse_attn_fwd_with_indices(const void* Q, const void* K, const void* V
  *             must be distinct (an entry outside [0, len_b) is ignored)
  *   dOut      [B, H, L_Q, D] DEVICE, the tensors' dtype
  *   dQ, dK, dV  [B, H, L, D] DEVICE, the tensors' dtype; every element is written
- * The softmax weights are recomputed from Q and K (the forward keeps no statistics); all
- * arithmetic is float64 for both tensor types (the difference G_i.v_j - sum_j' p_ij' G_i.v_j'
- * cancels almost completely for sharply peaked rows).  shape->U is ignored.
+ * The softmax weights are recomputed from Q and K (the forward keeps no statistics).
+ * Arithmetic: float64 for float32 tensors; float32 for bfloat16 tensors, with the difference
+ * G_i.v_j - sum_j' p_ij' G_i.v_j', which cancels almost completely for sharply peaked rows,
+ * taken relative to a value of the row (errors are those of the last rounding to bfloat16, as
+ * with float64).  With infinities in the inputs a gradient may be NaN.  shape->U is ignored.
  * Workspace: partial sums of dQ, at most a quarter of the memory that Q, K, V, dOut, dQ, dK and dV
  * take together or 256 MiB, whichever is more, and statistics (up to 40 bytes for each kept
  * query and 512 for each head, or 5 MB where that is more). */

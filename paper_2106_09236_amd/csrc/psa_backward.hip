@@ -30,9 +30,9 @@
 //     stages rows, waits at a barrier or stores, and cut the key axis so that their number fills whole rounds of
 //     the CUs;
 //   * keep a head's work-groups on one XCD where the heads divide evenly: each L2 fetches the rows of its own heads, not
-//     the kept rows of Q and G of all (the first product of a work-group waits for 8 us, not for 14).
-// Measured (whole call): B=16 H=4 L=512, 256 kept queries 225 -> 162 us, the last step 3.5 of them; B=8 H=8 L=300, 120 kept
-// 102.0 -> 98.2 in that step, B=24 H=8 L=200, 100 kept 133.1 -> 129.9 us.
+//     the kept rows of Q and G of all (the first product of a work-group waits for 11 us, not for 14.5).
+// Measured (whole call): B=16 H=4 L=512, 256 kept queries 225 -> 161.5 us, the last point 4 of them; B=8 H=8 L=300, 120 kept
+// 102.2 -> 97.5 by that point, B=24 H=8 L=200, 100 kept 133.2 -> 129.2 us.
 #include <type_traits>
 
 #include "psa_backward_common.h"
