@@ -27,12 +27,12 @@
 //   * widen every operand once: a wave keeps the 16 key rows it owns as float64 in registers and finds the
 //     group's query rows as float64 in LDS, where the work-group has put them once;
 //   * run two work-groups of 4 waves (one per SIMD) on a CU, so that one fills the matrix pipe while the other
-//     stages rows, waits at a barrier or stores, and cut the key axis so that their number fills whole rounds of
-//     the CUs;
+//     stages rows, waits at a barrier or stores (or, for full batches, one of 8 waves, which has half the partial sums of
+//     dQ), and cut the key axis so that their number fills whole rounds of the CUs;
 //   * keep a head's work-groups on one XCD where the heads divide evenly: each L2 fetches the rows of its own heads, not
 //     the kept rows of Q and G of all (the first product of a work-group waits for 11 us, not for 14.5).
-// Measured (whole call): B=16 H=4 L=512, 256 kept queries 225 -> 161.5 us, the last point 4 of them; B=8 H=8 L=300, 120 kept
-// 102.2 -> 97.5 by that point, B=24 H=8 L=200, 100 kept 133.2 -> 129.2 us.
+// Measured (whole call): B=16 H=4 L=512, 256 kept queries 225 -> 150 us, the last point 4 and the 8 waves 11 of them; B=8 H=8 L=300, 120 kept
+// 102.2 -> 97.5 by the last point, B=24 H=8 L=200, 100 kept 133.2 -> 129.2 us.
 #include <type_traits>
 
 #include "psa_backward_common.h"
@@ -58,14 +58,16 @@ constexpr int kBwdKeepStats = 768;   // most kept queries whose statistics the g
 typedef double bwd_x4 __attribute__((ext_vector_type(4)));
 typedef double bwd_x2 __attribute__((ext_vector_type(2)));
 
-// How the 4 waves of the gradient kernel's work-group share its keys and the two tiles of a group: KS waves of 16
+// How the 4 (KS = 8: 8) waves of the gradient kernel's work-group share its keys and the two tiles of a group: KS waves of 16
 // keys each; with KS = 2 two waves have the same keys and one query tile each.
 template <int KS> struct BwdShare {
-    static constexpr int kSlots = kBwdWaves / KS;                        // 1, 2
-    static constexpr int kKeys = 16 * KS;                                // keys per block: 64, 32
+    static constexpr int kWaves = KS > kBwdWaves ? KS : kBwdWaves;       // 8 (KS = 8), else 4
+    static constexpr int kThreads = 64 * kWaves;
+    static constexpr int kSlots = kWaves / KS;                           // 1, 2
+    static constexpr int kKeys = 16 * KS;                                // keys per block: 128, 64, 32
     static constexpr int kPerSlot = kBwdTiles / kSlots;                  // tiles a wave takes of a group: 2, 1
     static constexpr int kGRow = kKeys + 2;                              // doubles between the rows (queries) of a g tile
-    static constexpr int kFixed = 2 * kBwdGroup * kBwdQRow * 8 + kBwdGroup * kGRow * 8 + kKeys * kBwdKRow * 4;   // 68096, 51200
+    static constexpr int kFixed = 2 * kBwdGroup * kBwdQRow * 8 + kBwdGroup * kGRow * 8 + kKeys * kBwdKRow * 4;   // 101888, 68096, 51200
     static constexpr int kLds = kFixed + kBwdKeepStats * 16;             // the most: u_pad statistics of 16 bytes
 };
 
@@ -115,14 +117,16 @@ __device__ __forceinline__ int bwd_head(const BwdParams& P, int y) { return (y <
 __device__ __forceinline__ int bwd_index(const BwdParams& P) { return (int)(blockIdx.x >> P.head_shift); }
 
 // Kept queries q0 .. q0 + ROWS - 1 of the head: their rows of Q and of G as float64 in LDS (zeros for an absent
-// entry), 8 threads per row.  `find` looks the rows up in the list, `request` asks for them, `put` writes them to
+// entry), 8 or 16 threads per row.  `find` looks the rows up in the list, `request` asks for them, `put` writes them to
 // LDS (the caller's barrier makes them visible); a caller may have other work between the three.
-template <typename T, int ROWS>
+template <typename T, int ROWS, int NT>
 struct QueryStage {
-    static constexpr int kPasses = ROWS * 8 / kBwdThreads;
+    static constexpr int kPer = NT > ROWS * 8 ? 16 : 8;      // threads per row
+    static constexpr int kPasses = ROWS * kPer / NT, kElems = kD / kPer;
+    static_assert(kPasses * NT == ROWS * kPer, "whole passes");
     int qi[kPasses];                          // list entries as they lie in memory, rows (or -1) from `request` on
-    BwdRow<T, 8> a[kPasses], b[kPasses];
-    static __device__ __forceinline__ int row_of(int k) { return k * (kBwdThreads / 8) + ((int)threadIdx.x >> 3); }
+    BwdRow<T, kElems> a[kPasses], b[kPasses];
+    static __device__ __forceinline__ int row_of(int k) { return k * (NT / kPer) + (int)threadIdx.x / kPer; }
     __device__ __forceinline__ void find(const BwdParams& P, int head, int q0) {
 #pragma unroll
         for (int k = 0; k < kPasses; ++k) {
@@ -131,22 +135,22 @@ struct QueryStage {
         }
     }
     __device__ __forceinline__ void request(const T* Qh, const T* Gh, int q0, int n, int ub) {
-        const int part = threadIdx.x & 7;
+        const int part = threadIdx.x % kPer;
 #pragma unroll
         for (int k = 0; k < kPasses; ++k) {
             if (q0 + row_of(k) >= ub || qi[k] < 0 || qi[k] >= n) qi[k] = -1;
-            a[k].load(Qh + (size_t)(qi[k] >= 0 ? qi[k] : 0) * kD + 8 * part);
-            b[k].load(Gh + (size_t)(qi[k] >= 0 ? qi[k] : 0) * kD + 8 * part);
+            a[k].load(Qh + (size_t)(qi[k] >= 0 ? qi[k] : 0) * kD + kElems * part);
+            b[k].load(Gh + (size_t)(qi[k] >= 0 ? qi[k] : 0) * kD + kElems * part);
         }
     }
     __device__ __forceinline__ void put(double* sQ, double* sG) const {
-        const int part = threadIdx.x & 7;
+        const int part = threadIdx.x % kPer;
 #pragma unroll
         for (int k = 0; k < kPasses; ++k) {
-            bwd_x2* dq = reinterpret_cast<bwd_x2*>(sQ + row_of(k) * kBwdQRow + 8 * part);
-            bwd_x2* dg = reinterpret_cast<bwd_x2*>(sG + row_of(k) * kBwdQRow + 8 * part);
+            bwd_x2* dq = reinterpret_cast<bwd_x2*>(sQ + row_of(k) * kBwdQRow + kElems * part);
+            bwd_x2* dg = reinterpret_cast<bwd_x2*>(sG + row_of(k) * kBwdQRow + kElems * part);
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
+            for (int e = 0; e < kElems / 2; ++e) {
                 dq[e] = qi[k] >= 0 ? bwd_x2{(double)a[k].at(2 * e), (double)a[k].at(2 * e + 1)} : bwd_x2{0.0, 0.0};
                 dg[e] = qi[k] >= 0 ? bwd_x2{(double)b[k].at(2 * e), (double)b[k].at(2 * e + 1)} : bwd_x2{0.0, 0.0};
             }
@@ -252,7 +256,7 @@ void bwd_stats_kernel(const BwdParams P)
     };
     if (k_first < k_end) request(k_first + 16 * wave);               // (n > 0)
     if (n_t > 0) {
-        QueryStage<T, kBwdStatGroup> qs;
+        QueryStage<T, kBwdStatGroup, kBwdThreads> qs;
         qs.find(P, head, q0);
         qs.request(Qh, Gh, q0, n, ub);
         qs.put(sQ, sG);
@@ -499,11 +503,12 @@ void bwd_dq_kernel(const BwdParams P)
 // block, so that nothing has to be added up across waves.
 // grid (key splits, heads), heads as above, blocks2 key blocks per work-group, which adds to the dQ it wrote for the block before.
 template <typename T, int KS, BwdForm FORM>
-__global__ __launch_bounds__(kBwdThreads, 2)
+__global__ __launch_bounds__(BwdShare<KS>::kThreads, 2)
 void bwd_main_kernel(const BwdParams P)
 {
     using SH = BwdShare<KS>;
-    constexpr int GR = SH::kGRow;
+    constexpr int GR = SH::kGRow, NT = SH::kThreads;
+    constexpr int DT = kBwdTiles * kBwdWaves / SH::kWaves;           // query tiles of a group whose dQ a wave forms: 2, or 1 of 8 waves
     extern __shared__ __attribute__((aligned(16))) double bwd_smem[];
     __shared__ double s_gm[kD];
     __shared__ unsigned s_bits[kBwdChunk / 32];                      // the kept ones among 2048 rows
@@ -518,6 +523,7 @@ void bwd_main_kernel(const BwdParams P)
     const int ub = kept_count(P, b, n);
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int ks = wave % KS, slot = wave / KS;
+    const int we = wave & 3, wt = wave >> 2;                         // of dQ: elements 16 we .. + 15 of tiles wt .. wt + DT - 1
     const T* Qh = static_cast<const T*>(P.Q) + (size_t)head * L * kD;
     const T* Kh = static_cast<const T*>(P.K) + (size_t)head * L * kD;
     const T* Vh = static_cast<const T*>(P.V) + (size_t)head * L * kD;
@@ -542,17 +548,17 @@ void bwd_main_kernel(const BwdParams P)
             }
             s_gm[tid] = t / (double)n;
         }
-        if (FORM == kFused) for (int t = tid; t < P.u_pad; t += kBwdThreads) s_stat[t] = stat_of(P, head, t, n, ub);
+        if (FORM == kFused) for (int t = tid; t < P.u_pad; t += NT) s_stat[t] = stat_of(P, head, t, n, ub);
         request(r_first);
     }
 
     if (FORM != kKeysOnly && r_first >= n && P.dq_part) {                                 // no valid key here: zeros
-        for (int t = tid >> 4; t < ub; t += kBwdThreads / 16) {
+        for (int t = tid >> 4; t < ub; t += NT / 16) {
             bwd_x2* dp = reinterpret_cast<bwd_x2*>(P.dq_part + (((size_t)head * P.S2 + split) * P.u_pad + t) * kD + 4 * (tid & 15));
             dp[0] = dp[1] = bwd_x2{0.0, 0.0};
         }
     }
-    QueryStage<T, kBwdGroup> qs;
+    QueryStage<T, kBwdGroup, NT> qs;
     if (r_first < n) { qs.find(P, head, 0); qs.request(Qh, Gh, 0, n, ub); qs.put(sQ, sG); }
 
     // (Barriers order LDS only: the stores of a block and the loads of the next need not be waited for.  Positions
@@ -567,7 +573,7 @@ void bwd_main_kernel(const BwdParams P)
             // mark the kept rows among the next 2048
             if (tid < kBwdChunk / 32) s_bits[tid] = 0u;
             lds_barrier();
-            for (int t = tid; t < ub; t += kBwdThreads) {
+            for (int t = tid; t < ub; t += NT) {
                 const int i = P.sel[(size_t)head * P.u_stride + t] - r0;
                 if (i >= 0 && i < kBwdChunk && r0 + i < n) atomicOr(&s_bits[i >> 5], 1u << (i & 31));
             }
@@ -593,7 +599,7 @@ void bwd_main_kernel(const BwdParams P)
             widen16(kn, kd);
             widen16(vn, vd);
 
-            bwd_x2 old[kBwdTiles][2];                                // what this very lane wrote of dQ for the block before
+            bwd_x2 old[DT][2];                                // what this very lane wrote of dQ for the block before
             int q_next = 0;
             bool stage_next = false;
             // this wave's share of dQ, elements 16 wave .. + 15 of both tiles of group q0 (the A operand's rows are taken
@@ -605,21 +611,21 @@ void bwd_main_kernel(const BwdParams P)
                     return;
                 }
                 const int lo = opaque(lane), c = lo & 15, g = lo >> 4;
-                const double* gr = sg + c * GR + g;
-                const float* kr = sK + g * kBwdKRow + 16 * wave + 4 * (c & 3) + (c >> 2);
-                bwd_x4 dq[kBwdTiles];
+                const double* gr = sg + (16 * wt + c) * GR + g;
+                const float* kr = sK + g * kBwdKRow + 16 * we + 4 * (c & 3) + (c >> 2);
+                bwd_x4 dq[DT];
 #pragma unroll
-                for (int i = 0; i < kBwdTiles; ++i) dq[i] = bwd_x4{0.0, 0.0, 0.0, 0.0};
+                for (int i = 0; i < DT; ++i) dq[i] = bwd_x4{0.0, 0.0, 0.0, 0.0};
                 auto product = [&](auto tiles) {
-                    constexpr int NT = decltype(tiles)::value;
+                    constexpr int NQ = decltype(tiles)::value;
                     float ka[2][4];
-                    double gb[2][NT][4];
+                    double gb[2][NQ][4];
                     auto fetch = [&](int kq) {
 #pragma unroll
                         for (int r = 0; r < 4; ++r) {
                             ka[kq & 1][r] = kr[(16 * kq + 4 * r) * kBwdKRow];
 #pragma unroll
-                            for (int i = 0; i < NT; ++i) gb[kq & 1][i][r] = gr[16 * i * GR + 16 * kq + 4 * r];
+                            for (int i = 0; i < NQ; ++i) gb[kq & 1][i][r] = gr[16 * i * GR + 16 * kq + 4 * r];
                         }
                     };
                     fetch(0);
@@ -631,18 +637,22 @@ void bwd_main_kernel(const BwdParams P)
                         for (int r = 0; r < 4; ++r) {
                             const double kv = (double)ka[kq & 1][r];
 #pragma unroll
-                            for (int i = 0; i < NT; ++i) dq[i] = __builtin_amdgcn_mfma_f64_16x16x4f64(kv, gb[kq & 1][i][r], dq[i], 0, 0, 0);
+                            for (int i = 0; i < NQ; ++i) dq[i] = __builtin_amdgcn_mfma_f64_16x16x4f64(kv, gb[kq & 1][i][r], dq[i], 0, 0, 0);
                         }
                     }
                 };
-                if (q0 + 16 < ub) product(std::integral_constant<int, 2>{});
-                else              product(std::integral_constant<int, 1>{});
+                if constexpr (DT == 2) {
+                    if (q0 + 16 < ub) product(std::integral_constant<int, 2>{});
+                    else              product(std::integral_constant<int, 1>{});
+                } else if (q0 + 16 * wt < ub) {                      // wave-uniform
+                    product(std::integral_constant<int, 1>{});
+                }
                 if (stage_next) qs.put(sQ, sG);                      // (their readers are behind the barrier before this)
-                const int e_own = 16 * wave + 4 * g;
+                const int e_own = 16 * we + 4 * g;
 #pragma unroll
-                for (int i = 0; i < kBwdTiles; ++i) {
-                    const int t = q0 + 16 * i;
-                    if (t >= ub) break;                              // work-group-uniform
+                for (int i = 0; i < DT; ++i) {
+                    const int t = q0 + 16 * (wt + i);
+                    if (t >= ub) continue;                           // wave-uniform
                     if (P.dq_part == nullptr) {                      // the only block of the head
                         const int qi = kept_row(P, head, t + c, n, ub);
                         const float v[4] = {(float)dq[i][0], (float)dq[i][1], (float)dq[i][2], (float)dq[i][3]};
@@ -720,10 +730,10 @@ void bwd_main_kernel(const BwdParams P)
                 // under this group's dQ travel: what was written of it for the block before, and the rows of what
                 // comes next
                 if (FORM != kKeysOnly && blk > 0) {
-                    const int lo = opaque(lane), e_own = 16 * wave + 4 * (lo >> 4);
+                    const int lo = opaque(lane), e_own = 16 * we + 4 * (lo >> 4);
 #pragma unroll
-                    for (int i = 0; i < kBwdTiles; ++i) {
-                        const int t = (q0 + 16 * i < ub ? q0 + 16 * i : q0) + (lo & 15);
+                    for (int i = 0; i < DT; ++i) {
+                        const int t = (q0 + 16 * (wt + i) < ub ? q0 + 16 * (wt + i) : q0) + (lo & 15);
                         const bwd_x2* dp = reinterpret_cast<const bwd_x2*>(P.dq_part + (((size_t)head * P.S2 + split) * P.u_pad + t) * kD + e_own);
                         old[i][0] = dp[0]; old[i][1] = dp[1];
                     }
@@ -845,12 +855,13 @@ void bwd_dq_reduce_kernel(const BwdParams P)
 template <typename T>
 static hipError_t raise_bwd_limits()
 {
-    constexpr int N = 6;
+    constexpr int N = 7;
     static std::atomic<uint64_t> raised[N];            // per instantiation: devices already served
     const void* fn[N] = {(const void*)bwd_stats_kernel<T>, (const void*)bwd_main_kernel<T, 4, kFused>,
                          (const void*)bwd_main_kernel<T, 2, kFused>, (const void*)bwd_main_kernel<T, 4, kFusedMany>,
-                         (const void*)bwd_main_kernel<T, 4, kKeysOnly>, (const void*)bwd_main_kernel<T, 2, kKeysOnly>};
-    const int lds[N] = {kBwdStatsLds, BwdShare<4>::kLds, BwdShare<2>::kLds, BwdShare<4>::kLds, BwdShare<4>::kLds, BwdShare<2>::kLds};
+                         (const void*)bwd_main_kernel<T, 4, kKeysOnly>, (const void*)bwd_main_kernel<T, 2, kKeysOnly>,
+                         (const void*)bwd_main_kernel<T, 8, kFused>};
+    const int lds[N] = {kBwdStatsLds, BwdShare<4>::kLds, BwdShare<2>::kLds, BwdShare<4>::kLds, BwdShare<4>::kLds, BwdShare<2>::kLds, BwdShare<8>::kLds};
     for (int k = 0; k < N; ++k) { const hipError_t e = ensure_lds_limit(fn[k], lds[k], raised[k]); if (e != hipSuccess) return e; }
     return hipSuccess;
 }
@@ -871,6 +882,8 @@ static hipError_t launch_bwd_t(const BwdParams& P, int BH, int ks, hipStream_t s
         else         hipLaunchKernelGGL((bwd_main_kernel<T, 2, kKeysOnly>), grid, block, BwdShare<2>::kFixed + kBwdGroup * 16, stream, P);
     } else if (P.u_pad > kBwdKeepStats)
         hipLaunchKernelGGL((bwd_main_kernel<T, 4, kFusedMany>), grid, block, BwdShare<4>::kFixed + kBwdGroup * 16, stream, P);
+    else if (ks == 8)
+        hipLaunchKernelGGL((bwd_main_kernel<T, 8, kFused>), grid, dim3(BwdShare<8>::kThreads), BwdShare<8>::kFixed + P.u_pad * 16, stream, P);
     else if (ks == 4)
         hipLaunchKernelGGL((bwd_main_kernel<T, 4, kFused>), grid, block, BwdShare<4>::kFixed + P.u_pad * 16, stream, P);
     else
@@ -959,6 +972,19 @@ BwdPlan make_bwd_plan(const psa_shape_t& s, int u_stride)
             p.keys_only = 1; p.ks = ks; p.blocks2 = 1; p.S2 = nb;
         }
     }
+    // Fused form, blocks of 128 keys on work-groups of 8 waves, one to a CU, instead of two of 4 waves: half the partial sums of dQ to
+    // write and to add up, the group's query rows staged once instead of twice.  Where they take no more rounds (a CU with one
+    // of the smaller work-groups is faster than one with two; these come whole), and only for calls without lengths, which
+    // alone are known to be full batches: with lengths the smaller ones spread better.  Whole call: B=16 H=4 L=512, 256 kept
+    // 162.9 -> 150.4 us; B=16 H=8 L=256, 128 kept 93.7 -> 86.5; B=8 H=8 L=1024, 512 kept 571.6 -> 533.0; B=32 H=4 L=512, 205 kept
+    // 263.5 -> 249.2; two rounds for one and a half, B=24 H=8 L=200, 100 kept 129.6 -> 136.6; lengths of 64 .. 512 at B=8 H=8
+    // L=512, 256 kept 132.2 -> 139.7, of 50 .. 400 at B=16 H=8 L=400, 200 kept 194.7 -> 209.3.
+    p.wide_S2 = 0;
+    if (!p.keys_only && p.ks == 4 && p.u_pad <= kBwdKeepStats && p.S2 > 1) {
+        const int nb = (s.L_K + BwdShare<8>::kKeys - 1) / BwdShare<8>::kKeys, S = (nb + p.blocks2 - 1) / p.blocks2;
+        const int64_t wgs = BH * S;
+        if (wgs >= 256 && (double)((wgs + 255) / 256) <= bwd_rounds(BH * p.S2)) p.wide_S2 = S;
+    }
     // dQ goes straight to memory where one block holds all keys of a head
     p.parts = !p.keys_only && (p.S2 > 1 || p.blocks2 > 1);
     auto al = [](size_t x) { return (x + 255) & ~(size_t)255; };
@@ -983,12 +1009,14 @@ hipError_t launch_backward(const psa_shape_t& s, const BwdPlan& bp, const void* 
     P.dQ = dQ; P.dK = dK; P.dV = dV;
     P.stats_part = reinterpret_cast<double*>(w + bp.off_stats_part);
     P.gsum_part = reinterpret_cast<double*>(w + bp.off_gsum);
-    P.dq_part = bp.parts ? reinterpret_cast<double*>(w + bp.off_dq_part) : nullptr;
+    const bool wide = bp.wide_S2 > 0 && lengths == nullptr;          // (fewer key splits than the scratch has room for)
+    const bool parts = wide ? bp.wide_S2 > 1 || bp.blocks2 > 1 : bp.parts;
+    P.dq_part = parts ? reinterpret_cast<double*>(w + bp.off_dq_part) : nullptr;
     P.stats = bp.keys_only ? reinterpret_cast<double*>(w + bp.off_stats) : nullptr;
     P.H = s.H; P.L = s.L_K; P.u_stride = u_stride; P.u_pad = bp.u_pad; P.n_group = bp.n_group;
-    P.S1 = bp.S1; P.blocks1 = bp.blocks1; P.S2 = bp.S2; P.blocks2 = bp.blocks2;
+    P.S1 = bp.S1; P.blocks1 = bp.blocks1; P.S2 = wide ? bp.wide_S2 : bp.S2; P.blocks2 = bp.blocks2;
     P.fill = fill; P.head_shift = (s.B * s.H) % 8 == 0 ? 3 : 0;
-    return launch_bwd_t<float>(P, s.B * s.H, bp.ks, stream);
+    return launch_bwd_t<float>(P, s.B * s.H, wide ? 8 : bp.ks, stream);
 }
 
 }  // namespace psa

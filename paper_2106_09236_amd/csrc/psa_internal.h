@@ -133,6 +133,7 @@ hipError_t launch_prep_indices(const Plan& p, const Args& a, const Scratch& w); 
 // of the workspace (parts: dQ goes through partial sums; keys_only: a kernel of its own computes it).
 struct BwdPlan {
     int n_group, u_pad, S1, blocks1, S2, blocks2, ks, parts, keys_only;
+    int wide_S2;          // > 0: calls without lengths take blocks of 128 keys in this many splits
     size_t off_stats_part, off_gsum, off_stats, off_dq_part, total;
 };
 BwdPlan make_bwd_plan(const psa_shape_t& s, int u_stride);

@@ -1,8 +1,12 @@
-"""The backward of float32 tensors with heads in eights, whose work-groups are dealt to the XCDs head by head, and with one head
+"""The backward of float32 tensors in full batches, whose work-groups may take 128 keys on 8 waves, and with heads in eights, whose work-groups are dealt to the XCDs head by head, and with one head
 less or more: every head's rows must come from its own work-groups."""
+import numpy as np
 import pytest
+import torch
 
 import tests.test_backward_tiles_gpu as tiles
+from paper_2106_09236_amd import workloads as W
+from tests.test_backward_gpu import check_backward
 
 pytestmark = pytest.mark.gpu
 
@@ -14,3 +18,22 @@ pytestmark = pytest.mark.gpu
 ])
 def test_heads_in_eights(B, H, L, u):
     tiles.test_tiles("f32", B, H, L, u)
+
+
+@pytest.mark.parametrize("fill", ["mean", "value"])
+@pytest.mark.parametrize("B,H,L,u", [
+    (8, 8, 512, 256), (16, 4, 511, 17), (16, 4, 385, 300), (8, 8, 1024, 768),     # four and eight blocks of 128 keys a head
+    (32, 8, 128, 64), (32, 8, 127, 15), (64, 4, 65, 33),                 # one block: dQ goes straight to memory
+    (64, 4, 200, 100), (32, 8, 129, 32), (16, 16, 1000, 20),             # two blocks, one key in the second, several blocks to a work-group
+])
+def test_full_batches(B, H, L, u, fill):
+    # calls without lengths: blocks of 128 keys on 8 waves, where they fill the chip
+    w = W.make_workload(W.small_config("full", B, H, L, 4, 5.0, "f32", "mixture"), seed=500 + L + u)
+    r = np.random.Generator(np.random.PCG64(L + u))
+    ub = min(u, L)
+    sel = np.full((B, H, u), -1, dtype=np.int32)
+    for b in range(B):
+        for h in range(H):
+            sel[b, h, :ub] = r.permutation(L)[:ub]
+            sel[b, h, 6:ub:7] = -1
+    check_backward(w, torch.from_numpy(sel).cuda(), torch.full((B,), ub, dtype=torch.int32, device="cuda"), fill, label=f"full B{B} H{H} L{L} u{u} {fill}")
