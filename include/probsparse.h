@@ -213,7 +213,9 @@ int probsparse_attn_fwd_with_indices(const void* Q, const void* K, const void* V
  * Arithmetic: float64 for float32 tensors; float32 for bfloat16 tensors, with the difference
  * G_i.v_j - sum_j' p_ij' G_i.v_j', which cancels almost completely for sharply peaked rows,
  * taken relative to a value of the row (errors are those of the last rounding to bfloat16, as
- * with float64).  With infinities in the inputs a gradient may be NaN.  shape->U is ignored.
+ * with float64).  bfloat16 heads whose values float32 does not carry that far (scores beyond
+ * 700, rows of K or V that differ by less than about 1 % of their size, infinities, extreme
+ * scales) are computed in float64, at up to 9 times the time.  shape->U is ignored.
  * Workspace: partial sums of dQ, at most a quarter of the memory that Q, K, V, dOut, dQ, dK and dV
  * take together or 256 MiB, whichever is more, and statistics (up to 40 bytes for each kept
  * query and 512 for each head, or 5 MB where that is more). */

@@ -4,7 +4,7 @@
 //                         walk the kept queries (dK, dV, the fill's share, zero rows)
 //   bwd16_reduce_kernel   adds the partial sums of dQ, where the keys of a head were split among work-groups
 //
-// Arithmetic: float32 throughout.  Products of two bfloat16 values are exact in the MFMA's float32 accumulator; a float32
+// Arithmetic: float32, for heads that it carries (below).  Products of two bfloat16 values are exact in the MFMA's float32 accumulator; a float32
 // operand (the weights p and what multiplies them) enters as three bfloat16 planes cut from its 24 significant bits, whose sum
 // is the value itself.  What made float32 unusable for these gradients (errors of 4 times the gradient's size where attention
 // is sharply peaked) is the difference c_ij - D_i, c_ij = G_i . v_j, of nearly equal numbers: a softmax row with p = 1 - e on one key
@@ -26,12 +26,16 @@
 // not kept: dK and dV from waves of their own, four to a SIMD (47 us); two key splits for dQ and their sum 29 + 4 us; work-groups
 // of one block of keys 31 us, dQ's work-groups last 33 us.
 //
-// A plane of a weight that is zero times an infinite dOut or K is NaN: with infinities in the inputs gradients that were
-// infinite are NaN.
+// Heads that float32 does not carry (scores beyond 2^10, rows of K or V with much more in common than they differ, infinities, extreme
+// scales; needs_float64) are found by the statistics kernel as it goes, at no measurable cost, and computed in float64 by branches of
+// the same two kernels.  With all heads like that: B=8 H=8 L=2048, 39 kept 226 us; B=16 H=4 L=512, 256 kept 210; B=1 H=8 L=16384,
+// 49 kept 266 (138, 162 and 181 by the float64 kernels of float32 tensors, made for bfloat16).
 //
 // MFMA lanes: psa_tile.h.  Scores are formed with the kept queries on the columns where queries are walked over keys, with
 // the keys on the columns in the other kind; either way the accumulator registers are, unchanged, the B operand of the
 // products that follow.
+#include <type_traits>
+
 #include "psa_backward_common.h"
 #include "psa_tile.h"
 
@@ -44,19 +48,25 @@ constexpr int kM16Group = 64;                                    // kept queries
 constexpr int kRowF = kD + 4;                                    // floats between staged float rows
 constexpr int kBitRows = 2048;                                   // rows per bit mask of kept rows
 
-// Softmax statistics of one kept query over some keys, relative to maximum m (base 2) and reference c*.  l and w are float64
-// between tiles and from there on: an error of D' is an error of the sum of a query's g, which multiplies what its keys
-// have in common (mixtures of 32 centres, 16384 keys: float32 sums 5 times the error of dQ there).
-struct Stat16 { float m, c; double l, w; };
-__device__ __forceinline__ float stat_factor(float m, float M) { return m == -INFINITY ? 0.f : fast_exp2(m - M); }
+// Softmax statistics of one kept query over some keys while a wave walks them, relative to maximum m (base 2) and reference c*.
+// l and w are float64 between tiles and from there on: an error of D' is an error of the sum of a query's g, which multiplies what
+// its keys have in common (mixtures of 32 centres, 16384 keys: float32 sums 5 times the error of dQ there).
+struct Run16 { float m, c; double l, w; };
+// ... and as they are kept: relative to maximum m, l = sum e, w = sum e c (float64 needs no reference); in memory l is negative where
+// the work-group asks for float64 (below)
+struct Stat16 { double m, l, w; };
+constexpr double kNoMax16 = -1e300;                                  // the maximum over no key: finite, so that differences stay numbers
+// (EXACT: a maximum of float64 scores; else it is a float32 number, or none)
+template <bool EXACT>
+__device__ __forceinline__ double stat_factor(double m, double M) { return EXACT ? exp2_f64(m - M) : (double)fast_exp2((float)(m - M)); }
+template <bool EXACT>
 __device__ __forceinline__ Stat16 stat_merge(const Stat16& a, const Stat16& b)
 {
     Stat16 t;
-    t.m = fmaxf(a.m, b.m);
-    t.c = a.m >= b.m ? a.c : b.c;
-    const double fa = stat_factor(a.m, t.m), fb = stat_factor(b.m, t.m);
+    t.m = fmax(a.m, b.m);
+    const double fa = stat_factor<EXACT>(a.m, t.m), fb = stat_factor<EXACT>(b.m, t.m);
     t.l = fa * a.l + fb * b.l;
-    t.w = fa * fma((double)a.c - (double)t.c, a.l, a.w) + fb * fma((double)b.c - (double)t.c, b.l, b.w);
+    t.w = fa * a.w + fb * b.w;
     return t;
 }
 
@@ -66,7 +76,7 @@ struct Bwd16Params {
     bf16_t* dQ; bf16_t* dK; bf16_t* dV;
     Stat16* stat;          // [BH][S1][u_stride]  per kept query and key split
     double* gsum_part;     // [BH][S1 n_group][64]  column sums of G over valid rows outside I_sparse
-    float* dq_part;        // [BH][SQ][u_stride][64]  dQ of the key splits (SQ > 1)
+    double* dq_part;       // [BH][SQ][u_stride][64]  dQ of the key splits (SQ > 1)
     int H, L, BH, u_stride, n_group, S1, tiles1, SQ, tilesq, S2, blocks2, fill, n_dq;    // n_dq: work-groups that compute dQ
 };
 
@@ -159,11 +169,196 @@ __device__ __forceinline__ void to_operands(const uint4 (&kx)[4], const uint4 (&
     get_operand(va, s, lane & 31, lane >> 5);
 }
 
+// ---- Heads that float32 does not carry.  A float32 score's error grows with the score (of 1e5: 1 % of the weight), that of c with
+// what the rows of V have in common beside their differences, that of dQ with the same in K; a zero plane of a weight times an
+// infinite dOut is NaN.  So a work-group of the statistics kernel keeps the largest squared norms of the rows it reads and, of its
+// waves' first tiles, the widest range of a query's scores and of its c over four keys (Seen16).  What fails needs_float64 is computed in
+// float64 by the functions named exact_... on the float64 matrix cores, in the same launches: the statistics by the work-group itself, the
+// gradients for the whole head.  Measured of this look: comparisons of whole rows with a tile's first, and maxima over all lanes of every
+// wave at the end, cost 0.8 to 1.4 us of a call; four keys of a lane, and maxima kept by lane in LDS and put together by one wave each
+// while another merges the streams, are within the noise (B=1 H=4 L=128 14.3 -> 14.2 us, B=8 H=8 L=2048 40.3 -> 40.3).
+struct Seen16 { unsigned q2, g2, k2, v2, s_range, c_range; };        // bits of floats that are not negative, which order like the values (NaN the largest)
+constexpr float kMaxNorm2 = 1.2089258e24f;                           // 2^80: no product or sum of the gradients nears the end of float32
+constexpr float kMaxScore2 = 1048576.f / (kScaleLog2e * kScaleLog2e);          // |q|^2 |k|^2 of scores up to 2^10, base 2: an error of a weight of 2^-13,
+                                                                     // a sixteenth of the last rounding
+constexpr float kMinProduct2 = 7.5231638e-37f;                       // 2^-120, of |G|^2 |V|^2 that is not 0: all planes of g lie above the smallest normal number
+constexpr float kRangeC = 1.f / 512, kRangeS = 1.f / 256;            // range / product of the norms, 0.1 and more for unrelated rows; the range of c (of the
+                                                                     // scores) is at most |G| (|Q|) times the largest distance of two rows of V (K)
+__device__ __forceinline__ bool needs_float64(const Seen16& y, bool& same_v, bool& same_k)
+{
+    const float q2 = __uint_as_float(y.q2), g2 = __uint_as_float(y.g2), k2 = __uint_as_float(y.k2), v2 = __uint_as_float(y.v2),
+                s = __uint_as_float(y.s_range), c = __uint_as_float(y.c_range);
+    if (!(q2 <= kMaxNorm2 && g2 <= kMaxNorm2 && k2 <= kMaxNorm2 && v2 <= kMaxNorm2 && q2 * k2 <= kMaxScore2)) return true;
+    same_v = c == 0.f && v2 > 0.f && g2 > 0.f;                       // no range: fine where all rows are the same, which is to be seen
+    same_k = s == 0.f && k2 > 0.f && q2 > 0.f;
+    return (g2 * v2 > 0.f && g2 * v2 < kMinProduct2) || (c > 0.f && c < kRangeC * __builtin_amdgcn_sqrtf(g2) * __builtin_amdgcn_sqrtf(v2)) ||
+           (s > 0.f && s < kRangeS * __builtin_amdgcn_sqrtf(q2) * __builtin_amdgcn_sqrtf(k2));
+}
+// squared norm of half a row, on four independent chains
+__device__ __forceinline__ float dot_half(const uint4 (&a)[4])
+{
+    float t[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) t[k] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, a[k].x), __builtin_bit_cast(bf16x2, a[k].x), 0.f, false);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) t[k] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, a[k].y), __builtin_bit_cast(bf16x2, a[k].y), t[k], false);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) t[k] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, a[k].z), __builtin_bit_cast(bf16x2, a[k].z), t[k], false);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) t[k] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, a[k].w), __builtin_bit_cast(bf16x2, a[k].w), t[k], false);
+    return (t[0] + t[1]) + (t[2] + t[3]);
+}
+__device__ __forceinline__ float dot_eighth(const uint4& a)
+{
+    float t = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, a.x), __builtin_bit_cast(bf16x2, a.x), 0.f, false);
+    t = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, a.y), __builtin_bit_cast(bf16x2, a.y), t, false);
+    t = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, a.z), __builtin_bit_cast(bf16x2, a.z), t, false);
+    return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, a.w), __builtin_bit_cast(bf16x2, a.w), t, false);
+}
+__device__ __forceinline__ unsigned umax(unsigned a, unsigned b) { return a > b ? a : b; }
+// maximum over the wave, in every lane
+__device__ __forceinline__ unsigned wave_umax(unsigned x)
+{
+    x = umax(x, __float_as_uint(dpp_mov<0xB1>(__uint_as_float(x))));
+    x = umax(x, __float_as_uint(dpp_mov<0x4E>(__uint_as_float(x))));
+    x = umax(x, __float_as_uint(dpp_mov<0x141>(__uint_as_float(x))));
+    x = umax(x, __float_as_uint(dpp_mov<0x140>(__uint_as_float(x))));
+    const auto r = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+    x = umax(r[0], r[1]);
+    const auto q = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+    return umax(q[0], q[1]);
+}
+// Does any of rows first .. end - 1 differ from row `first`?  Asked of the threads of a work-group, 8 a row; this thread's answer.
+__device__ __forceinline__ bool rows_differ(__amdgpu_buffer_rsrc_t rows, int first, int end)
+{
+    const int part = 16 * ((int)threadIdx.x & 7);
+    const uint4 a = buffer_load16<uint4>(rows, first * 128 + part);
+    uint32_t bits = 0;
+    for (int r = first + ((int)threadIdx.x >> 3); r < end; r += kB16Threads / 8) {
+        const uint4 x = buffer_load16<uint4>(rows, r * 128 + part);
+        bits |= (x.x ^ a.x) | (x.y ^ a.y) | (x.z ^ a.z) | (x.w ^ a.w);
+    }
+    return bits != 0u;
+}
+// float64 products: v_mfma_f64_16x16x4f64, lane (c, g) = (lane % 16, lane / 16): A[i][k]: i = c, k = g   B[k][j]: k = g, j = c
+// D[i][j]: i = 4r + g, j = c.  A score product takes elements 16 g .. 16 g + 15 of a row on both sides.
+__device__ __forceinline__ doublex4 mfma64(double a, double b, const doublex4& c) { return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0); }
+__device__ __forceinline__ void widen8(const uint4& a, double* d)
+{
+    const uint32_t x[4] = {a.x, a.y, a.z, a.w};
+#pragma unroll
+    for (int k = 0; k < 4; ++k) { d[2 * k] = (double)bf16_lo(x[k]); d[2 * k + 1] = (double)bf16_hi(x[k]); }
+}
+__device__ __forceinline__ void widen16(const uint4 (&a)[2], double (&d)[16]) { widen8(a[0], d); widen8(a[1], d + 8); }
+__device__ __forceinline__ void load16(uint4 (&x)[2], __amdgpu_buffer_rsrc_t rows, int row, int g)
+{
+    const int ofs = row < 0 ? -32 : row * 128 + 32 * g;
+#pragma unroll
+    for (int k = 0; k < 2; ++k) x[k] = buffer_load16<uint4>(rows, ofs + (row < 0 ? 0 : 16 * k));
+}
+__device__ __forceinline__ void read16(const uint16_t* row, int g, double (&d)[16])
+{
+    const uint4 x[2] = {*reinterpret_cast<const uint4*>(row + 16 * g), *reinterpret_cast<const uint4*>(row + 16 * g + 8)};
+    widen16(x, d);
+}
+// four elements (8 bytes)
+__device__ __forceinline__ void widen4(const uint2& x, double (&d)[4]) {
+    d[0] = (double)bf16_lo(x.x); d[1] = (double)bf16_hi(x.x); d[2] = (double)bf16_lo(x.y); d[3] = (double)bf16_hi(x.y);
+}
+__device__ __forceinline__ uint2 round4(const doublex4& v) {
+    return make_uint2(cvt_pk_bf16((float)v[0], (float)v[1]), cvt_pk_bf16((float)v[2], (float)v[3]));
+}
+__device__ __forceinline__ uint4 round8(const double (&v)[8]) {
+    return make_uint4(cvt_pk_bf16((float)v[0], (float)v[1]), cvt_pk_bf16((float)v[2], (float)v[3]),
+                      cvt_pk_bf16((float)v[4], (float)v[5]), cvt_pk_bf16((float)v[6], (float)v[7]));
+}
+// Does any work-group of the statistics ask for float64 in this head?  Wave-uniform, and the same in every wave.  `asked`: the sign of
+// what the first 64 of them left, requested ahead.
+__device__ __forceinline__ int asked_by(const Bwd16Params& P, int head, int groups, int k)
+{
+    const Stat16* st = P.stat + ((size_t)head * P.S1 + k / groups) * P.u_stride + k % groups * kM16Group;      // its first query's
+    return reinterpret_cast<const int*>(&st->l)[1];
+}
+__device__ __forceinline__ int first_asked(const Bwd16Params& P, int head, int ub, int lane)
+{
+    const int groups = ub > 0 ? (ub + kM16Group - 1) / kM16Group : 1;
+    return asked_by(P, head, groups, lane < P.S1 * groups ? lane : 0);
+}
+__device__ __forceinline__ bool head_exact(const Bwd16Params& P, int head, int ub, int lane, int asked)
+{
+    const int groups = (ub + kM16Group - 1) / kM16Group;
+    for (int k = lane + 64; k < P.S1 * groups; k += 64) asked |= asked_by(P, head, groups, k);
+    return __ballot(asked < 0) != 0ull;
+}
+// Statistics of the 64 staged queries over every eighth tile of 16 keys from j0 on, to out[query]: keys on the rows of the score products
+__device__ __forceinline__ void exact_stats(const uint16_t* sQ, const uint16_t* sG, __amdgpu_buffer_rsrc_t Kr, __amdgpu_buffer_rsrc_t Vr, int j0,
+                                            int j_end, int n_q, int lane, Stat16* out)
+{
+    const int c = lane & 15, g = lane >> 4;
+    Stat16 st[4];
+#pragma unroll
+    for (int tt = 0; tt < 4; ++tt) st[tt] = Stat16{kNoMax16, 0.0, 0.0};
+#pragma unroll 1
+    for (; j0 < j_end; j0 += 16 * kB16Waves) {                       // wave-uniform
+        uint4 kx[2], vx[2];
+        double kd[16], vd[16];
+        load16(kx, Kr, j0 + c, g);
+        load16(vx, Vr, j0 + c, g);
+        widen16(kx, kd);
+        widen16(vx, vd);
+#pragma unroll
+        for (int tt = 0; tt < 4; ++tt) {
+            if (16 * tt >= n_q) break;                               // work-group-uniform
+            double qd[16], gd[16];
+            read16(sQ + (16 * tt + c) * kB16Stride, g, qd);
+            read16(sG + (16 * tt + c) * kB16Stride, g, gd);
+            doublex4 s = {0.0, 0.0, 0.0, 0.0}, cc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+            for (int e = 0; e < 16; ++e) { s = mfma64(kd[e], qd[e], s); cc = mfma64(vd[e], gd[e], cc); }
+            Stat16& y = st[tt];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                if (j0 + 4 * r + g < j_end) {
+                    const double x = s[r] * kScaleLog2eD, m = fmax(y.m, x), a = exp2_f64(y.m - m), e = exp2_f64(x - m);
+                    y.l = fma(y.l, a, e);
+                    y.w = fma(y.w, a, e * cc[r]);
+                    y.m = m;
+                }
+            }
+        }
+    }
+#pragma unroll
+    for (int tt = 0; tt < 4; ++tt) {
+#pragma unroll
+        for (int off = 16; off < 64; off <<= 1) {                    // (both lanes of a pair merge the same two in the same order)
+            const Stat16 o{__shfl_xor(st[tt].m, off, 64), __shfl_xor(st[tt].l, off, 64), __shfl_xor(st[tt].w, off, 64)};
+            st[tt] = (lane & off) ? stat_merge<true>(o, st[tt]) : stat_merge<true>(st[tt], o);
+        }
+        if (g == 0) out[16 * tt + c] = st[tt];
+    }
+}
+
 // (head, index within the head) of work-group `id`: all work-groups of a head on one XCD where the heads divide evenly
 __device__ __forceinline__ void head_of(int id, int BH, int per_head, int& head, int& x)
 {
     if (BH % 8 == 0) { const int slot = id >> 3; head = slot / per_head * 8 + (id & 7); x = slot % per_head; }
     else             { head = id / per_head; x = id % per_head; }
+}
+
+// the waves' statistics of staged query k together, in wave order
+template <bool EXACT>
+__device__ __forceinline__ Stat16 merged_streams(const uint16_t (*s_tiles)[32 * kB16Stride], int k)
+{
+    Stat16 x[kB16Waves], t{kNoMax16, 0.0, 0.0};
+#pragma unroll
+    for (int w = 0; w < kB16Waves; ++w) { x[w] = reinterpret_cast<const Stat16*>(s_tiles[w])[k]; t.m = fmax(t.m, x[w].m); }
+#pragma unroll
+    for (int w = 0; w < kB16Waves; ++w) {
+        const double f = stat_factor<EXACT>(x[w].m, t.m);
+        t.l = fma(f, x[w].l, t.l);
+        t.w = fma(f, x[w].w, t.w);
+    }
+    return t;
 }
 
 // ---- statistics.  A work-group takes up to 64 kept queries (rows of Q and G in LDS) over the keys of one split; each of its
@@ -176,6 +371,7 @@ void bwd16_stats_kernel(const Bwd16Params P)
     __shared__ __attribute__((aligned(16))) uint16_t s_tiles[kB16Waves][32 * kB16Stride];    // a tile for each wave, its statistics in the end
     __shared__ double s_gs[kB16Waves][kD];
     __shared__ unsigned s_bits[kBitRows / 32];
+    __shared__ unsigned s_seen[6][64];                               // maxima over the waves, by lane; then over the lanes in column 0
     int head, x;
     head_of(blockIdx.x, P.BH, P.S1 * P.n_group, head, x);
     const int split = x / P.n_group, group = x % P.n_group;
@@ -216,17 +412,23 @@ void bwd16_stats_kernel(const Bwd16Params P)
         for (int k = 0; k < NB; ++k) g[k] = buffer_load16<uint4>(Gr, (r0 + k * RPP + (tid >> 3)) * 128 + 16 * (tid & 7));
     };
     if (r_first < r_end) request(r_first);
+    Seen16 seen = {0u, 0u, 0u, 0u, 0u, 0u};                          // (of this lane's rows)
+    if (tid < 6 * 64) s_seen[0][tid] = 0u;
     if (any) {
         *reinterpret_cast<uint4*>(sQ + (tid >> 3) * kB16Stride + 8 * (tid & 7)) = xq;
         *reinterpret_cast<uint4*>(sG + (tid >> 3) * kB16Stride + 8 * (tid & 7)) = xg;
         lds_barrier();
+        seen.q2 = __float_as_uint(dot_eighth(xq));                   // (an eighth of the row: summed at the end)
+        seen.g2 = __float_as_uint(dot_eighth(xg));
     }
 
-    Stat16 st[2] = {{-INFINITY, 0.f, 0.0, 0.0}, {-INFINITY, 0.f, 0.0, 0.0}};     // (l and w of this lane's keys)
-    auto tile_step = [&](int step) {
+    Run16 st[2] = {{-INFINITY, 0.f, 0.0, 0.0}, {-INFINITY, 0.f, 0.0, 0.0}};      // (l and w of this lane's keys)
+    auto tile_step = [&](auto first_step, int step) {
         const int j0 = 32 * t;
         uint4 ka[4], va[4];
         to_operands(kx, vx, s_tiles[wave], ka, va, lane);
+        seen.k2 = umax(seen.k2, __float_as_uint(dot_half(ka)));      // (half of the row; rows beyond the item are zeros)
+        seen.v2 = umax(seen.v2, __float_as_uint(dot_half(va)));
         load_rows(kx, Kr, t + kB16Waves < t_end, j0 + 32 * kB16Waves, lane);
         load_rows(vx, Vr, t + kB16Waves < t_end, j0 + 32 * kB16Waves, lane);
 #pragma unroll
@@ -243,10 +445,22 @@ void bwd16_stats_kernel(const Bwd16Params P)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) s[r] = j0 + 8 * (r >> 2) + 4 * h + (r & 3) < n ? s[r] : -INFINITY;
             }
-            Stat16& y = st[qt];
+            Run16& y = st[qt];
             float tmax = s[0];
 #pragma unroll
             for (int r = 1; r < 16; ++r) tmax = fmaxf(tmax, s[r]);
+            if (decltype(first_step)::value) {
+                // ranges over four of this lane's keys, all of one query
+                float s_lo = s[0], s_hi = s[0], c_lo = cc[0], c_hi = cc[0];
+#pragma unroll
+                for (int r = 1; r < 4; ++r) {
+                    const bool ok = j0 + 4 * h + r < n;              // (key r = 0 may be masked as well: then all are)
+                    s_lo = fminf(s_lo, ok ? s[r] : s[0]); s_hi = fmaxf(s_hi, ok ? s[r] : s[0]);
+                    c_lo = fminf(c_lo, ok ? cc[r] : cc[0]); c_hi = fmaxf(c_hi, ok ? cc[r] : cc[0]);
+                }
+                seen.s_range = umax(seen.s_range, __float_as_uint(j0 + 4 * h < n ? fmaxf(s_hi - s_lo, 0.f) : 0.f));
+                seen.c_range = umax(seen.c_range, __float_as_uint(j0 + 4 * h < n ? fmaxf(c_hi - c_lo, 0.f) : 0.f));
+            }
             const float tm = max_xor32(tmax) * kScaleLog2e;
             const bool centre = (step & (step - 1)) == 0;            // wave-uniform
             if (centre || __ballot(tm > y.m + kLagLog2) != 0ull) {
@@ -261,7 +475,7 @@ void bwd16_stats_kernel(const Bwd16Params P)
                 const float lt = (float)(y.l + __shfl_xor(y.l, 32, 64)), wt = (float)(y.w + __shfl_xor(y.w, 32, 64));
                 const float mean = lt > 0.f ? y.c + wt / lt : y.c;
                 const float m_new = grow ? tm : y.m, c_new = grow ? cr : mean;
-                const double a = grow ? stat_factor(y.m, m_new) : 1.f;
+                const double a = grow ? (y.m == -INFINITY ? 0.f : fast_exp2(y.m - m_new)) : 1.f;
                 y.w = a * fma((double)y.c - (double)c_new, y.l, y.w);
                 y.l *= a;
                 y.m = m_new; y.c = c_new;
@@ -279,7 +493,7 @@ void bwd16_stats_kernel(const Bwd16Params P)
     };
     // the first step before the column sums, whose rows arrive behind the first key rows (and the next under the sums)
     const bool first = any && t < t_end;                             // wave-uniform
-    if (first) { tile_step(0); t += kB16Waves; }
+    if (first) { tile_step(std::true_type{}, 0); t += kB16Waves; }
 
     if (sums) {
         double acc[8];
@@ -334,39 +548,158 @@ void bwd16_stats_kernel(const Bwd16Params P)
     if (!any) return;
 
 #pragma unroll 1
-    for (int step = 1; t < t_end; t += kB16Waves, ++step) tile_step(step);       // wave-uniform
+    for (int step = 1; t < t_end; t += kB16Waves, ++step) tile_step(std::false_type{}, step);        // wave-uniform
     // the key streams together, in wave order
 #pragma unroll
     for (int qt = 0; qt < 2; ++qt) {
-        st[qt].l += __shfl_xor(st[qt].l, 32, 64);
-        st[qt].w += __shfl_xor(st[qt].w, 32, 64);
-        if (h == 0) reinterpret_cast<Stat16*>(s_tiles[wave])[32 * qt + c] = st[qt];
+        Run16& y = st[qt];
+        y.l += __shfl_xor(y.l, 32, 64);
+        y.w += __shfl_xor(y.w, 32, 64);
+        if (h == 0) reinterpret_cast<Stat16*>(s_tiles[wave])[32 * qt + c] = Stat16{y.m == -INFINITY ? kNoMax16 : (double)y.m, y.l, fma((double)y.c, y.l, y.w)};
+    }
+    {
+        // (NaN, which a maximum of floats would drop, is the largest of the bits)
+        const unsigned most[6] = {__float_as_uint(group_sum8(__uint_as_float(seen.q2))), __float_as_uint(group_sum8(__uint_as_float(seen.g2))),
+                                  seen.k2, seen.v2, seen.s_range, seen.c_range};
+#pragma unroll
+        for (int k = 0; k < 6; ++k) atomicMax(&s_seen[k][lane], most[k]);
     }
     lds_barrier();
-    if (tid < kM16Group && q0 + tid < ub) {
-        Stat16 tot = reinterpret_cast<const Stat16*>(s_tiles[0])[tid];
-#pragma unroll
-        for (int k = 1; k < kB16Waves; ++k) tot = stat_merge(tot, reinterpret_cast<const Stat16*>(s_tiles[k])[tid]);
-        P.stat[((size_t)head * P.S1 + split) * P.u_stride + q0 + tid] = tot;
+    // one wave puts the key streams together while others find the maxima
+    Stat16* const stat = P.stat + ((size_t)head * P.S1 + split) * P.u_stride + q0;
+    if (wave < 6) {
+        const unsigned most = wave_umax(s_seen[wave][lane]);
+        if (lane == 0) s_seen[wave][0] = most;
+    } else if (wave == 7 && q0 + lane < ub) {
+        stat[lane] = merged_streams<false>(s_tiles, lane);
+    }
+    lds_barrier();
+    seen = {s_seen[0][0], s_seen[1][0], s_seen[2][0], s_seen[3][0], s_seen[4][0], s_seen[5][0]};
+    seen.k2 = __float_as_uint(2.f * __uint_as_float(seen.k2));       // (a row has two halves)
+    seen.v2 = __float_as_uint(2.f * __uint_as_float(seen.v2));
+    bool same_v = false, same_k = false;
+    bool f64 = needs_float64(seen, same_v, same_k);                  // work-group-uniform
+    const int j_first = 32 * t_first, j_end = 32 * t_end < n ? 32 * t_end : n;
+    if (!f64 && (same_v || same_k))                                  // work-group-uniform
+        f64 = __syncthreads_or((same_v && rows_differ(Vr, j_first, j_end)) || (same_k && rows_differ(Kr, j_first, j_end))) != 0;
+    if (!f64) return;
+    exact_stats(sQ, sG, Kr, Vr, j_first + 16 * wave, j_end, ub - q0, lane, reinterpret_cast<Stat16*>(s_tiles[wave]));
+    lds_barrier();
+    if (wave == 7 && q0 + lane < ub) {                               // (the same threads as before)
+        Stat16 tot = merged_streams<true>(s_tiles, lane);
+        tot.l = copysign(tot.l, -1.0);
+        stat[lane] = tot;
     }
 }
 
-// The key splits' statistics of kept query t together, by 4 adjacent threads (`sub` 0 .. 3), which all get (log2 sum exp, and
-// c* + D' as the sum of two floats, since its own last bit would count); an absent entry has no weight on any key.
+// The key splits' statistics of kept query t together, by 4 adjacent threads (`sub` 0 .. 3), which all get them
+template <bool EXACT>
+__device__ __forceinline__ Stat16 merged_stat(const Bwd16Params& P, int head, int t, int sub)
+{
+    const Stat16* sp = P.stat + (size_t)head * P.S1 * P.u_stride + t;
+    Stat16 st{kNoMax16, 0.0, 0.0};
+#pragma unroll 4
+    for (int s = sub; s < P.S1; s += 4) {
+        Stat16 x = sp[(size_t)s * P.u_stride];
+        x.l = fabs(x.l);
+        st = stat_merge<EXACT>(st, x);
+    }
+#pragma unroll
+    for (int off = 1; off < 4; off <<= 1) {                          // (both threads of a pair merge the same two in the same order)
+        const Stat16 o{__shfl_xor(st.m, off, 64), __shfl_xor(st.l, off, 64), __shfl_xor(st.w, off, 64)};
+        st = (sub & off) ? stat_merge<EXACT>(o, st) : stat_merge<EXACT>(st, o);
+    }
+    return st;
+}
+// (log2 sum exp, and D as the sum of two floats, since its own last bit would count); an absent entry has no weight on any key
 __device__ __forceinline__ float4 stat_of(const Bwd16Params& P, int head, int t, int row, int sub)
 {
     if (row < 0) return make_float4(INFINITY, 0.f, 0.f, 0.f);
-    const Stat16* sp = P.stat + (size_t)head * P.S1 * P.u_stride + t;
-    Stat16 st{-INFINITY, 0.f, 0.0, 0.0};
-#pragma unroll 4
-    for (int s = sub; s < P.S1; s += 4) st = stat_merge(st, sp[(size_t)s * P.u_stride]);
-#pragma unroll
-    for (int off = 1; off < 4; off <<= 1) {                          // (both threads of a pair merge the same two in the same order)
-        const Stat16 o{__shfl_xor(st.m, off, 64), __shfl_xor(st.c, off, 64), __shfl_xor(st.l, off, 64), __shfl_xor(st.w, off, 64)};
-        st = (sub & off) ? stat_merge(o, st) : stat_merge(st, o);
+    const Stat16 st = merged_stat<false>(P, head, t, sub);
+    const double ref = st.w / st.l;
+    return make_float4((float)st.m + log2f((float)st.l), (float)ref, (float)(ref - (double)(float)ref), 0.f);
+}
+// (log2 sum exp, D) in float64
+__device__ __forceinline__ double2 exact_stat_of(const Bwd16Params& P, int head, int t, int row, int sub)
+{
+    if (row < 0) return make_double2(INFINITY, 0.0);
+    const Stat16 st = merged_stat<true>(P, head, t, sub);
+    return make_double2(st.m + log2(st.l), st.w / st.l);
+}
+
+// dQ of kept queries q0 .. q0 + 31 over keys j_first .. j_end - 1 in float64: two waves take the same 16 queries and every other tile of
+// 16 keys.  Keys on the rows of the score products, so that a lane's four g are the B operand of the product over keys.
+__device__ __forceinline__ void exact_queries(const Bwd16Params& P, int head, int split, int q0, int n, int ub, size_t base, int j_first, int j_end,
+                                              __amdgpu_buffer_rsrc_t Kr, __amdgpu_buffer_rsrc_t Vr, double2* s_stat, double* s_acc)
+{
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), c = lane & 15, g = lane >> 4;
+    const int qt = 16 * (wave & 1), stream = wave >> 1;
+    double qd[16], gd[16];
+    {
+        const int row = kept_row(P, head, q0 + qt + c, n, ub);
+        uint4 x[2], y[2];
+        load16(x, head_rows<128>(P.Q + base, n), row, g);
+        load16(y, head_rows<128>(P.G + base, n), row, g);
+        widen16(x, qd);
+        widen16(y, gd);
     }
-    const double ref = (double)st.c + st.w / st.l;
-    return make_float4(st.m + log2f((float)st.l), (float)ref, (float)(ref - (double)(float)ref), 0.f);
+    if (tid < 128) {
+        const int k = q0 + (tid >> 2);
+        const double2 y = exact_stat_of(P, head, k, kept_row(P, head, k, n, ub), tid & 3);
+        if ((tid & 3) == 0) s_stat[tid >> 2] = y;
+    }
+    lds_barrier();
+    const double2 st = s_stat[qt + c];
+    doublex4 acc[4];                                              // acc[dt][r]: element 4 (4r + g) + dt of query c
+#pragma unroll
+    for (int dt = 0; dt < 4; ++dt) acc[dt] = doublex4{0.0, 0.0, 0.0, 0.0};
+    uint4 kx[2], vx[2];
+    uint2 k4[4];                                                     // elements 4c .. 4c + 3 of keys 4r + g
+    auto request = [&](int j0) {
+        load16(kx, Kr, j0 + c, g);
+        load16(vx, Vr, j0 + c, g);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) k4[r] = __builtin_bit_cast(uint2, __builtin_amdgcn_raw_buffer_load_b64(Kr, (j0 + 4 * r + g) * 128 + 8 * c, 0, 0));
+    };
+    request(j_first + 16 * stream);                                  // (rows beyond the item are zeros)
+#pragma unroll 1
+    for (int j0 = j_first + 16 * stream; j0 < j_end; j0 += 32) {     // wave-uniform
+        double kd[16], vd[16], ka[4][4];
+        widen16(kx, kd);
+        widen16(vx, vd);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) widen4(k4[r], ka[r]);
+        request(j0 + 32);
+        doublex4 s = {0.0, 0.0, 0.0, 0.0}, cc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int e = 0; e < 16; ++e) { s = mfma64(kd[e], qd[e], s); cc = mfma64(vd[e], gd[e], cc); }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const double p = exp2_f64(fma(s[r], kScaleLog2eD, -st.x)), gv = j0 + 4 * r + g < j_end ? p * (cc[r] - st.y) : 0.0;
+#pragma unroll
+            for (int dt = 0; dt < 4; ++dt) acc[dt] = mfma64(ka[r][dt], gv, acc[dt]);
+        }
+    }
+#pragma unroll
+    for (int dt = 0; dt < 4; ++dt)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) s_acc[(32 * stream + qt + c) * kD + 16 * r + 4 * g + dt] = acc[dt][r];
+    lds_barrier();
+    const int e0 = 8 * (tid & 7), k = q0 + (tid >> 3);               // 8 threads a query
+    double v[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = s_acc[(tid >> 3) * kD + e0 + e] + s_acc[(32 + (tid >> 3)) * kD + e0 + e];
+    if (k >= ub) return;
+    if (P.SQ > 1) {
+        double* const dst = P.dq_part + (((size_t)head * P.SQ + split) * P.u_stride + k) * kD + e0;
+#pragma unroll
+        for (int e = 0; e < 8; e += 2) *reinterpret_cast<double2*>(dst + e) = make_double2(v[e], v[e + 1]);
+    } else {
+        const int row = kept_row(P, head, k, n, ub);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] *= 0.125;
+        if (row >= 0) *reinterpret_cast<uint4*>(P.dQ + base + (size_t)row * kD + e0) = round8(v);
+    }
 }
 
 // ---- dQ of 32 kept queries over the keys of one split: four key streams, added up in wave order through LDS
@@ -386,13 +719,18 @@ __device__ __forceinline__ void bwd16_queries(const Bwd16Params& P, uint16_t* s_
     int t = split * P.tilesq + wave;
     const int t_end = (split + 1) * P.tilesq < t_all ? (split + 1) * P.tilesq : t_all;
     uint4 kx[4], vx[4], qreg[4], greg[4];
+    // (the list entries arrive with the answer, and what follows from both behind the branch: requested before it, the rows
+    // would be spilled around the float64 code)
+    const int asked = first_asked(P, head, ub, lane), row = kept_row(P, head, q0 + c, n, ub);
+    if (head_exact(P, head, ub, lane, asked)) {                          // work-group-uniform
+        exact_queries(P, head, split, q0, n, ub, base, 32 * split * P.tilesq, 32 * t_end < n ? 32 * t_end : n, Kr, Vr, reinterpret_cast<double2*>(s_stat),
+                      reinterpret_cast<double*>(s_out));
+        return;
+    }
+    load_half_row(qreg, head_rows<128>(P.Q + base, n), row, h);
+    load_half_row(greg, head_rows<128>(P.G + base, n), row, h);
     load_rows(kx, Kr, t < t_end, 32 * t, lane);
     load_rows(vx, Vr, t < t_end, 32 * t, lane);
-    {
-        const int row = kept_row(P, head, q0 + c, n, ub);
-        load_half_row(qreg, head_rows<128>(P.Q + base, n), row, h);
-        load_half_row(greg, head_rows<128>(P.G + base, n), row, h);
-    }
     if (tid < 128) {
         const int k = q0 + (tid >> 2);
         const float4 y = stat_of(P, head, k, kept_row(P, head, k, n, ub), tid & 3);
@@ -459,15 +797,129 @@ __device__ __forceinline__ void bwd16_queries(const Bwd16Params& P, uint16_t* s_
     }
     if (k >= ub) return;
     if (P.SQ > 1) {
-        float4* dst = reinterpret_cast<float4*>(P.dq_part + (((size_t)head * P.SQ + split) * P.u_stride + k) * kD + e0);
-        dst[0] = make_float4(v[0], v[1], v[2], v[3]);
-        dst[1] = make_float4(v[4], v[5], v[6], v[7]);
+        double* const dst = P.dq_part + (((size_t)head * P.SQ + split) * P.u_stride + k) * kD + e0;
+#pragma unroll
+        for (int e = 0; e < 8; e += 2) *reinterpret_cast<double2*>(dst + e) = make_double2((double)v[e], (double)v[e + 1]);
     } else {
         const int row = kept_row(P, head, k, n, ub);
         if (row >= 0)
             *reinterpret_cast<uint4*>(P.dQ + base + (size_t)row * kD + e0) =
                 make_uint4(cvt_pk_bf16(0.125f * v[0], 0.125f * v[1]), cvt_pk_bf16(0.125f * v[2], 0.125f * v[3]),
                            cvt_pk_bf16(0.125f * v[4], 0.125f * v[5]), cvt_pk_bf16(0.125f * v[6], 0.125f * v[7]));
+    }
+}
+
+// the mean fill's share of element e of dV: every valid v_j receives 1/n of each filled row's gradient
+__device__ __forceinline__ double fill_share(const Bwd16Params& P, int head, int n, int e)
+{
+    double s = 0.0;
+    if (P.fill != PSA_FILL_MEAN || n <= 0) return s;
+    const int parts = P.S1 * P.n_group;
+    const double* gs = P.gsum_part + (size_t)head * parts * kD + e;
+#pragma unroll 8
+    for (int k = 0; k < parts; ++k) s += gs[(size_t)k * kD];          // fixed order
+    return s / (double)n;
+}
+// marks the kept rows among r0 .. r0 + 2047 (every wave is done with the marks before, and sees these)
+__device__ __forceinline__ void mark_kept_rows(const Bwd16Params& P, int head, int r0, int n, int ub, unsigned* s_bits)
+{
+    const int tid = threadIdx.x;
+    lds_barrier();
+    if (tid < kBitRows / 32) s_bits[tid] = 0u;
+    lds_barrier();
+    for (int k = tid; k < ub; k += kM16Threads) {
+        const int i = P.sel[(size_t)head * P.u_stride + k] - r0;
+        if (i >= 0 && i < kBitRows && r0 + i < n) atomicOr(&s_bits[i >> 5], 1u << (i & 31));
+    }
+    lds_barrier();
+}
+
+// dK, dV and zero rows of dQ for keys r_first .. r_end - 1 in float64, 16 keys to a wave at a time.  Queries on the rows of the score
+// products, so that a lane's four p and g are the B operands of the products over queries.
+__device__ __forceinline__ void exact_keys(const Bwd16Params& P, int head, int n, int ub, size_t base, int r_first, int r_end, __amdgpu_buffer_rsrc_t Kr,
+                                           __amdgpu_buffer_rsrc_t Vr, __amdgpu_buffer_rsrc_t Qr, __amdgpu_buffer_rsrc_t Gr, uint16_t* s_rows,
+                                           double2* s_stat, double* s_share, unsigned* s_bits)
+{
+    static_assert(kM16Threads == 4 * kM16Group && kBitRows % (16 * kM16Waves) == 0, "four threads stage a row; a step lies in one bit mask");
+    uint16_t* const sQ = s_rows;
+    uint16_t* const sG = s_rows + kM16Group * kB16Stride;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), c = lane & 15, g = lane >> 4;
+    if (tid < kD) s_share[tid] = fill_share(P, head, n, tid);
+#pragma unroll 1
+    for (int r0 = r_first; r0 < r_end; r0 += 16 * kM16Waves) {       // work-group-uniform
+        if ((r0 - r_first) % kBitRows == 0) mark_kept_rows(P, head, r0, n, ub, s_bits);
+        const int j0 = r0 + 16 * wave, j = j0 + c;
+        double kd[16], vd[16];
+        {
+            uint4 kx[2], vx[2];
+            load16(kx, Kr, j, g);
+            load16(vx, Vr, j, g);
+            widen16(kx, kd);
+            widen16(vx, vd);
+        }
+        doublex4 dk[4], dv[4];                                    // [dt][r]: element 4 (4r + g) + dt of key c
+#pragma unroll
+        for (int dt = 0; dt < 4; ++dt) { dk[dt] = doublex4{0.0, 0.0, 0.0, 0.0}; dv[dt] = doublex4{0.0, 0.0, 0.0, 0.0}; }
+#pragma unroll 1
+        for (int q0 = 0; q0 < ub && r0 < n; q0 += kM16Group) {       // work-group-uniform
+            lds_barrier();                                           // what was staged before has been read
+            {
+                const int k = tid >> 2, part = tid & 3, row = kept_row(P, head, q0 + k, n, ub), at = row < 0 ? -32 : row * 128 + 32 * part;
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    *reinterpret_cast<uint4*>(sQ + k * kB16Stride + 16 * part + 8 * i) = buffer_load16<uint4>(Qr, at + (row < 0 ? 0 : 16 * i));
+                    *reinterpret_cast<uint4*>(sG + k * kB16Stride + 16 * part + 8 * i) = buffer_load16<uint4>(Gr, at + (row < 0 ? 0 : 16 * i));
+                }
+                const double2 st = exact_stat_of(P, head, q0 + k, row, part);
+                if (part == 0) s_stat[k] = st;
+            }
+            lds_barrier();
+            if (j0 >= n) continue;                                   // wave-uniform
+#pragma unroll 1
+            for (int tt = 0; tt < 4; ++tt) {
+                if (q0 + 16 * tt >= ub) break;                       // work-group-uniform
+                double qd[16], gd[16];
+                read16(sQ + (16 * tt + c) * kB16Stride, g, qd);
+                read16(sG + (16 * tt + c) * kB16Stride, g, gd);
+                doublex4 s = {0.0, 0.0, 0.0, 0.0}, cc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+                for (int e = 0; e < 16; ++e) { s = mfma64(qd[e], kd[e], s); cc = mfma64(gd[e], vd[e], cc); }
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int k = 16 * tt + 4 * r + g;
+                    const double2 st = s_stat[k];
+                    const double p = exp2_f64(fma(s[r], kScaleLog2eD, -st.x)), gv = st.x == INFINITY ? 0.0 : p * (cc[r] - st.y);
+                    double qa[4], ga[4];                             // elements 4c .. 4c + 3 of query 4r + g
+                    widen4(*reinterpret_cast<const uint2*>(sQ + k * kB16Stride + 4 * c), qa);
+                    widen4(*reinterpret_cast<const uint2*>(sG + k * kB16Stride + 4 * c), ga);
+#pragma unroll
+                    for (int dt = 0; dt < 4; ++dt) { dk[dt] = mfma64(qa[dt], gv, dk[dt]); dv[dt] = mfma64(ga[dt], p, dv[dt]); }
+                }
+            }
+        }
+        if (j >= P.L) continue;
+        const int bit = (j - r_first) % kBitRows;
+        const bool kept = (s_bits[bit >> 5] >> (bit & 31)) & 1u;
+        double a[4][4], b[4][4];                                     // [r][dt]: elements 16r + 4g + dt
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int dt = 0; dt < 4; ++dt) { a[r][dt] = 0.125 * dk[dt][r]; b[r][dt] = dv[dt][r] + s_share[16 * r + 4 * g + dt]; }      // (0 under the value fill)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int e0 = 16 * r + 4 * g;
+            if (P.fill != PSA_FILL_MEAN && !kept) {                  // the value fill hands v_j the gradient of its own row
+                double own[4];
+                widen4(__builtin_bit_cast(uint2, __builtin_amdgcn_raw_buffer_load_b64(Gr, j * 128 + 2 * e0, 0, 0)), own);
+#pragma unroll
+                for (int dt = 0; dt < 4; ++dt) b[r][dt] += own[dt];
+            }
+            const uint2 z = make_uint2(0u, 0u);
+            const size_t at = base + (size_t)j * kD + e0;
+            *reinterpret_cast<uint2*>(P.dK + at) = j < n ? round4(doublex4{a[r][0], a[r][1], a[r][2], a[r][3]}) : z;
+            *reinterpret_cast<uint2*>(P.dV + at) = j < n ? round4(doublex4{b[r][0], b[r][1], b[r][2], b[r][3]}) : z;
+            if (!kept) *reinterpret_cast<uint2*>(P.dQ + at) = z;
+        }
     }
 }
 
@@ -487,12 +939,19 @@ __device__ __forceinline__ void bwd16_keys(const Bwd16Params& P, uint16_t* s_row
     const __amdgpu_buffer_rsrc_t Kr = head_rows<128>(P.K + base, n), Vr = head_rows<128>(P.V + base, n);
     const __amdgpu_buffer_rsrc_t Qr = head_rows<128>(P.Q + base, n), Gr = head_rows<128>(P.G + base, n);
     const int r_first = x * P.blocks2 * kM16Keys;
+    const bool any = ub > 0 && r_first < n;                          // work-group-uniform
+    const int asked = first_asked(P, head, ub, lane), row0 = kept_row(P, head, tid >> 2, n, ub);
+    if (any && head_exact(P, head, ub, lane, asked)) {                   // work-group-uniform
+        const int r_end = r_first + P.blocks2 * kM16Keys;
+        exact_keys(P, head, n, ub, base, r_first, r_end < L ? r_end : L, Kr, Vr, Qr, Gr, s_rows, reinterpret_cast<double2*>(s_lse),
+                   reinterpret_cast<double*>(s_outs), s_bits);
+        return;
+    }
 
     // kept queries q0 .. q0 + 63: their rows of Q and G (4 threads a row, 32 bytes each) and their statistics (the key splits' by 4 threads)
     uint4 rq[2], rg[2];
     float4 st4;
-    auto request = [&](int q0) {
-        const int row = kept_row(P, head, q0 + (tid >> 2), n, ub);
+    auto request = [&](int q0, int row) {
         const int ofs = row < 0 ? -32 : row * 128 + 32 * (tid & 3);
 #pragma unroll
         for (int k = 0; k < 2; ++k) { rq[k] = buffer_load16<uint4>(Qr, ofs + (row < 0 ? 0 : 16 * k)); rg[k] = buffer_load16<uint4>(Gr, ofs + (row < 0 ? 0 : 16 * k)); }
@@ -507,25 +966,13 @@ __device__ __forceinline__ void bwd16_keys(const Bwd16Params& P, uint16_t* s_row
         }
         if (part == 0) { s_lse[row] = st4.x; s_ref[row] = st4.y; s_ref[kM16Group + row] = st4.z; }
     };
-    const bool any = ub > 0 && r_first < n;                          // work-group-uniform
-    if (any) request(0);
+    if (any) request(0, row0);
     uint4 ka[4], va[4];
     float* so = s_outs + wave * 32 * kRowF;
     uint4 kn[4], vn[4];
     load_rows(kn, Kr, true, r_first + 32 * wave, lane);
     load_rows(vn, Vr, true, r_first + 32 * wave, lane);
-    if (tid < kD) {
-        // the mean fill's share of dV: every valid v_j receives 1/n of each filled row's gradient
-        double s = 0.0;
-        if (P.fill == PSA_FILL_MEAN && n > 0) {
-            const int parts = P.S1 * P.n_group;
-            const double* gs = P.gsum_part + (size_t)head * parts * kD + tid;
-#pragma unroll 8
-            for (int k = 0; k < parts; ++k) s += gs[(size_t)k * kD];  // fixed order
-            s /= (double)n;
-        }
-        s_gm[tid] = (float)s;
-    }
+    if (tid < kD) s_gm[tid] = (float)fill_share(P, head, n, tid);
     if (any) put();
     to_operands(kn, vn, reinterpret_cast<uint16_t*>(so), ka, va, lane);
     const bool one_group = ub <= kM16Group;
@@ -534,17 +981,7 @@ __device__ __forceinline__ void bwd16_keys(const Bwd16Params& P, uint16_t* s_row
     for (int blk = 0; blk < P.blocks2; ++blk) {
         const int r0 = r_first + blk * kM16Keys, j0 = r0 + 32 * wave;
         if (r0 >= L) break;                                          // work-group-uniform
-        if ((blk * kM16Keys) % kBitRows == 0) {
-            // mark the kept rows among the next 2048 (the barrier also covers what was staged)
-            lds_barrier();
-            if (tid < kBitRows / 32) s_bits[tid] = 0u;
-            lds_barrier();
-            for (int k = tid; k < ub; k += kM16Threads) {
-                const int i = P.sel[(size_t)head * P.u_stride + k] - r0;
-                if (i >= 0 && i < kBitRows && r0 + i < n) atomicOr(&s_bits[i >> 5], 1u << (i & 31));
-            }
-            lds_barrier();
-        }
+        if ((blk * kM16Keys) % kBitRows == 0) mark_kept_rows(P, head, r0, n, ub, s_bits);     // (its barriers cover what was staged as well)
         // element 32 dt + 8 (r / 4) + 4h + r % 4 of key j0 + c
         load_rows(kn, Kr, blk + 1 < P.blocks2, j0 + kM16Keys, lane);
         load_rows(vn, Vr, blk + 1 < P.blocks2, j0 + kM16Keys, lane);
@@ -553,7 +990,10 @@ __device__ __forceinline__ void bwd16_keys(const Bwd16Params& P, uint16_t* s_row
 #pragma unroll 1
             for (int q0 = 0; q0 < ub; q0 += kM16Group) {              // work-group-uniform
                 const bool more = !one_group && (q0 + kM16Group < ub || (blk + 1 < P.blocks2 && r0 + kM16Keys < n));
-                if (more) request(q0 + kM16Group < ub ? q0 + kM16Group : 0);
+                if (more) {
+                    const int q_next = q0 + kM16Group < ub ? q0 + kM16Group : 0;
+                    request(q_next, kept_row(P, head, q_next + (tid >> 2), n, ub));
+                }
                 if (j0 < n) {                                        // wave-uniform: some key of the wave is valid
 #pragma unroll 1
                     for (int tt = 0; tt < 2; ++tt) {
@@ -673,23 +1113,26 @@ void bwd16_reduce_kernel(const Bwd16Params P)
     const int k = 32 * (blockIdx.x % per_head) + ((int)threadIdx.x >> 3), e0 = 8 * (threadIdx.x & 7);
     const int row = kept_row(P, head, k, n, ub);
     if (row < 0) return;
-    const float* p = P.dq_part + ((size_t)head * P.SQ * P.u_stride + k) * kD + e0;
+    const double* p = P.dq_part + ((size_t)head * P.SQ * P.u_stride + k) * kD + e0;
     const size_t step = (size_t)P.u_stride * kD;
-    float v[8];
+    double v[8];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) v[e] = 0.f;
+    for (int e = 0; e < 8; ++e) v[e] = 0.0;
 #pragma unroll 8
     for (int s = 0; s < P.SQ; ++s) {
-        const float4 a = *reinterpret_cast<const float4*>(p + s * step), b = *reinterpret_cast<const float4*>(p + s * step + 4);
-        v[0] += a.x; v[1] += a.y; v[2] += a.z; v[3] += a.w; v[4] += b.x; v[5] += b.y; v[6] += b.z; v[7] += b.w;
+#pragma unroll
+        for (int e = 0; e < 8; e += 2) {
+            const double2 x = *reinterpret_cast<const double2*>(p + s * step + e);
+            v[e] += x.x; v[e + 1] += x.y;
+        }
     }
-    *reinterpret_cast<uint4*>(P.dQ + ((size_t)head * P.L + row) * kD + e0) =
-        make_uint4(cvt_pk_bf16(0.125f * v[0], 0.125f * v[1]), cvt_pk_bf16(0.125f * v[2], 0.125f * v[3]),
-                   cvt_pk_bf16(0.125f * v[4], 0.125f * v[5]), cvt_pk_bf16(0.125f * v[6], 0.125f * v[7]));
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] *= 0.125;
+    *reinterpret_cast<uint4*>(P.dQ + ((size_t)head * P.L + row) * kD + e0) = round8(v);
 }
 
-// Key splits and blocks per work-group, and where the scratch lies, within `room` bytes (what make_bwd_plan has given such
-// calls since before these kernels: they need less).
+// Key splits and blocks per work-group, and where the scratch lies: within `room` bytes (what make_bwd_plan has given such calls since
+// before these kernels).
 Bwd16Plan make_bwd16_plan(const psa_shape_t& s, int u_stride, size_t room)
 {
     Bwd16Plan p;
@@ -709,7 +1152,7 @@ Bwd16Plan make_bwd16_plan(const psa_shape_t& s, int u_stride, size_t room)
         size_t off = 0;
         p.off_stat = off; off += al((size_t)BH * p.S1 * u_stride * sizeof(Stat16));
         p.off_gsum = off; off += al((size_t)BH * p.S1 * p.n_group * kD * sizeof(double));
-        p.off_dq = off;   off += p.SQ > 1 ? al((size_t)BH * p.SQ * u_stride * kD * sizeof(float)) : 0;
+        p.off_dq = off;   off += p.SQ > 1 ? al((size_t)BH * p.SQ * u_stride * kD * sizeof(double)) : 0;
         p.total = off;
         if (off <= room || (S1 == 1 && SQ == 1)) break;
         if (SQ > 1) --SQ; else --S1;
@@ -735,7 +1178,7 @@ hipError_t launch_backward_bf16(const psa_shape_t& s, const Bwd16Plan& bp, const
     P.dQ = static_cast<bf16_t*>(dQ); P.dK = static_cast<bf16_t*>(dK); P.dV = static_cast<bf16_t*>(dV);
     P.stat = reinterpret_cast<Stat16*>(w + bp.off_stat);
     P.gsum_part = reinterpret_cast<double*>(w + bp.off_gsum);
-    P.dq_part = reinterpret_cast<float*>(w + bp.off_dq);
+    P.dq_part = reinterpret_cast<double*>(w + bp.off_dq);
     P.H = s.H; P.L = s.L_K; P.BH = s.B * s.H; P.u_stride = u_stride; P.n_group = bp.n_group;
     P.S1 = bp.S1; P.tiles1 = bp.tiles1; P.SQ = bp.SQ; P.tilesq = bp.tilesq; P.S2 = bp.S2; P.blocks2 = bp.blocks2;
     P.fill = fill; P.n_dq = bp.n_dq;
