@@ -98,9 +98,10 @@ constexpr double kBwdScaleLog2e = 0.125 * 1.4426950408889634074;     // scores t
 
 // What bwd_main_kernel does beside dK and dV:
 //   kFused      dQ as well; the statistics of all kept queries (up to kBwdKeepStats) are put together in LDS once
+//   kFusedOne   the same with one block a split (KS = 8)
 //   kFusedMany  the same with more kept queries: the statistics of a group are put together anew for every block
 //   kKeysOnly   nothing: bwd_dq_kernel has computed dQ and left the statistics in memory
-enum BwdForm { kFused, kFusedMany, kKeysOnly };
+enum BwdForm { kFused, kFusedMany, kKeysOnly, kFusedOne };
 
 struct BwdParams {
     const void* Q; const void* K; const void* V; const void* G;
@@ -108,7 +109,7 @@ struct BwdParams {
     void* dQ; void* dK; void* dV;
     double* stats_part;    // [BH][S1][u_pad][3]  (max, sum, weighted c) per kept query and key split, base 2
     double* gsum_part;     // [BH][S1][64]        column sums of G over the valid rows outside I_sparse, per key split
-    double* dq_part;       // [BH][S2][u_pad][64], or nullptr: dQ rows are written directly
+    double* dq_part;       // [BH][S2][u_pad][64], or nullptr: dQ rows are written directly (KS = 8: two slots a split, below)
     double* stats;         // [BH][u_pad][2]       (log2 sum exp, -D/8) per kept query, kKeysOnly form; else nullptr
     int H, L, u_stride, u_pad, n_group, S1, blocks1, S2, blocks2, fill;
     int head_shift;        // 3: eight heads on the fastest axis of the grid, so that a head's work-groups share one XCD's L2; else 0
@@ -507,6 +508,8 @@ __global__ __launch_bounds__(BwdShare<KS>::kThreads, 2)
 void bwd_main_kernel(const BwdParams P)
 {
     using SH = BwdShare<KS>;
+    constexpr bool kKeep = FORM == kFused || FORM == kFusedOne;
+    const int blocks2 = FORM == kFusedOne ? 1 : P.blocks2;
     constexpr int GR = SH::kGRow, NT = SH::kThreads;
     constexpr int DT = kBwdTiles * kBwdWaves / SH::kWaves;           // query tiles of a group whose dQ a wave forms: 2, or 1 of 8 waves
     extern __shared__ __attribute__((aligned(16))) double bwd_smem[];
@@ -530,7 +533,7 @@ void bwd_main_kernel(const BwdParams P)
     const T* Gh = static_cast<const T*>(P.G) + (size_t)head * L * kD;
 
     // the key rows of a block: requested ahead (clamped: harmless if none is valid)
-    const int r_first = split * P.blocks2 * SH::kKeys;
+    const int r_first = split * blocks2 * SH::kKeys;
     BwdRow<T, 16> kn, vn;
     auto request = [&](int r0) {
         const int lo = opaque(lane), j = r0 + 16 * ks + (lo & 15), row = j < n ? j : (n > 0 ? n - 1 : 0);
@@ -548,7 +551,7 @@ void bwd_main_kernel(const BwdParams P)
             }
             s_gm[tid] = t / (double)n;
         }
-        if (FORM == kFused) for (int t = tid; t < P.u_pad; t += NT) s_stat[t] = stat_of(P, head, t, n, ub);
+        if (kKeep) for (int t = tid; t < P.u_pad; t += NT) s_stat[t] = stat_of(P, head, t, n, ub);
         request(r_first);
     }
 
@@ -566,7 +569,7 @@ void bwd_main_kernel(const BwdParams P)
     // would cost registers, and a spilled register is worse than its few instructions, since reading it back waits
     // for the stores before it.)
 #pragma unroll 1
-    for (int blk = 0; blk < P.blocks2; ++blk) {
+    for (int blk = 0; blk < blocks2; ++blk) {
         const int r0 = r_first + blk * SH::kKeys;
         if (r0 >= L) break;                                          // work-group-uniform
         if ((blk * SH::kKeys) % kBwdChunk == 0) {
@@ -584,7 +587,7 @@ void bwd_main_kernel(const BwdParams P)
         for (int dt = 0; dt < 4; ++dt) { dk[dt] = bwd_x4{0.0, 0.0, 0.0, 0.0}; dv[dt] = bwd_x4{0.0, 0.0, 0.0, 0.0}; }
         if (r0 < n && ub > 0) {                                      // work-group-uniform
             const bool wave_live = r0 + 16 * ks < n;                 // wave-uniform: some key of the wave is valid
-            const bool more = blk + 1 < P.blocks2 && r0 + SH::kKeys < n;     // another block with a valid key follows
+            const bool more = blk + 1 < blocks2 && r0 + SH::kKeys < n;     // another block with a valid key follows
             // B operands of the score products: this lane's key row.  A row beyond n stands for the last valid one:
             // what comes of it is not stored, and for dQ the staged row is zero.
             double kd[16], vd[16];
@@ -613,7 +616,17 @@ void bwd_main_kernel(const BwdParams P)
                 const int lo = opaque(lane), c = lo & 15, g = lo >> 4;
                 const double* gr = sg + (16 * wt + c) * GR + g;
                 const float* kr = sK + g * kBwdKRow + 16 * we + 4 * (c & 3) + (c >> 2);
-                bwd_x4 dq[DT];
+                bwd_x4 dq[DT], dq2 = {0.0, 0.0, 0.0, 0.0};           // dq2: the block's second 64 keys (KS = 8)
+                // KS = 8: what this very lane wrote for the block before, and, in the last block, for the split's first half
+                // (requested here, under the products: kept from before the barrier they are spilled)
+                bwd_x2 first[2];
+                if (KS == 8 && blk > 0) {
+                    const int t = (q0 + 16 * wt < ub ? q0 + 16 * wt : q0) + c;
+                    const double* dp = P.dq_part + (((size_t)head * P.S2 + 2 * split) * P.u_pad + t) * kD + 16 * we + 4 * g;
+                    const bwd_x2* op = reinterpret_cast<const bwd_x2*>(2 * blk > blocks2 ? dp + (size_t)P.u_pad * kD : dp);
+                    old[0][0] = op[0]; old[0][1] = op[1];
+                    if (!more && 2 * blk >= blocks2) { first[0] = reinterpret_cast<const bwd_x2*>(dp)[0]; first[1] = reinterpret_cast<const bwd_x2*>(dp)[1]; }
+                }
 #pragma unroll
                 for (int i = 0; i < DT; ++i) dq[i] = bwd_x4{0.0, 0.0, 0.0, 0.0};
                 auto product = [&](auto tiles) {
@@ -637,7 +650,10 @@ void bwd_main_kernel(const BwdParams P)
                         for (int r = 0; r < 4; ++r) {
                             const double kv = (double)ka[kq & 1][r];
 #pragma unroll
-                            for (int i = 0; i < NQ; ++i) dq[i] = __builtin_amdgcn_mfma_f64_16x16x4f64(kv, gb[kq & 1][i][r], dq[i], 0, 0, 0);
+                            for (int i = 0; i < NQ; ++i) {
+                                bwd_x4& sum = kq < 4 ? dq[i] : dq2;
+                                sum = __builtin_amdgcn_mfma_f64_16x16x4f64(kv, gb[kq & 1][i][r], sum, 0, 0, 0);
+                            }
                         }
                     }
                 };
@@ -653,6 +669,28 @@ void bwd_main_kernel(const BwdParams P)
                 for (int i = 0; i < DT; ++i) {
                     const int t = q0 + 16 * (wt + i);
                     if (t >= ub) continue;                           // wave-uniform
+                    if constexpr (KS == 8) {
+                        // The sums of the 4-wave form in its order, so that a call gives the same bits with lengths that are all L
+                        // and without: a block is two of its blocks, a split two of its splits (`half` of its blocks each), which
+                        // meet in the last block.
+                        const int half = blocks2, u = 2 * blk;     // the block's first 64 keys are number u of the split's
+                        const bwd_x4 before = bwd_x4{old[i][0][0], old[i][0][1], old[i][1][0], old[i][1][1]};
+                        if (blk > 0 && u != half) dq[i] += before;
+                        double* const slot = P.dq_part + (((size_t)head * P.S2 + 2 * split) * P.u_pad + t + c) * kD + e_own;
+                        auto store = [](double* p, const bwd_x4& v) {
+                            reinterpret_cast<bwd_x2*>(p)[0] = bwd_x2{v[0], v[1]};
+                            reinterpret_cast<bwd_x2*>(p)[1] = bwd_x2{v[2], v[3]};
+                        };
+                        if (u + 1 == half && more) {                // the halves meet within the block
+                            store(slot, dq[i]);
+                            store(slot + (size_t)P.u_pad * kD, dq2);
+                            continue;
+                        }
+                        dq[i] += dq2;
+                        if (u >= half && !more) dq[i] += bwd_x4{first[0][0], first[0][1], first[1][0], first[1][1]};
+                        if (P.dq_part != nullptr) { store(u >= half && more ? slot + (size_t)P.u_pad * kD : slot, dq[i]); continue; }
+                        dq[i] += bwd_x4{0.0, 0.0, 0.0, 0.0};         // (the reduction's sums start from +0)
+                    }
                     if (P.dq_part == nullptr) {                      // the only block of the head
                         const int qi = kept_row(P, head, t + c, n, ub);
                         const float v[4] = {(float)dq[i][0], (float)dq[i][1], (float)dq[i][2], (float)dq[i][3]};
@@ -672,7 +710,7 @@ void bwd_main_kernel(const BwdParams P)
                 q_next = q0 + kBwdGroup < ub ? q0 + kBwdGroup : 0;
                 stage_next = ub > kBwdGroup && (q_next > 0 || more); // work-group-uniform
                 if (stage_next) qs.find(P, head, q_next);
-                const bwd_x2* stat = s_stat + (FORM == kFused ? q0 : 0);
+                const bwd_x2* stat = s_stat + (kKeep ? q0 : 0);
                 if (FORM == kFusedMany && tid < kBwdGroup) s_stat[tid] = stat_of(P, head, q0 + tid, n, ub);
                 if (FORM == kKeysOnly && tid < kBwdGroup && q0 + (tid & ~(kBwdQ - 1)) < ub)      // (bwd_dq_kernel wrote whole tiles)
                     s_stat[tid] = reinterpret_cast<const bwd_x2*>(P.stats)[(size_t)head * P.u_pad + q0 + tid];
@@ -729,7 +767,7 @@ void bwd_main_kernel(const BwdParams P)
                 }
                 // under this group's dQ travel: what was written of it for the block before, and the rows of what
                 // comes next
-                if (FORM != kKeysOnly && blk > 0) {
+                if (FORM != kKeysOnly && KS < 8 && blk > 0) {
                     const int lo = opaque(lane), e_own = 16 * we + 4 * (lo >> 4);
 #pragma unroll
                     for (int i = 0; i < DT; ++i) {
@@ -829,8 +867,9 @@ void bwd_main_kernel(const BwdParams P)
     }
 }
 
-// adds the key splits of dQ in split order; 16 threads per kept query, 4 elements each
-template <typename T>
+// adds the key splits of dQ in split order, two and two first (a split of the 8-wave form is the sum of two; PAIRS: the sums are
+// still to be formed); 16 threads per kept query, 4 elements each
+template <typename T, bool PAIRS>
 __global__ __launch_bounds__(256)
 void bwd_dq_reduce_kernel(const BwdParams P)
 {
@@ -843,9 +882,17 @@ void bwd_dq_reduce_kernel(const BwdParams P)
     const double* dp = P.dq_part + ((size_t)head * P.S2 * P.u_pad + t) * kD + e0;
     const size_t step = (size_t)P.u_pad * kD;
     double acc[4] = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll 4
-    for (int s = 0; s < P.S2; ++s) {
-        const bwd_x2 x = *reinterpret_cast<const bwd_x2*>(dp + s * step), y = *reinterpret_cast<const bwd_x2*>(dp + s * step + 2);
+    constexpr int kBatch = PAIRS ? 2 : 4;
+#pragma unroll kBatch
+    for (int s = 0; s < P.S2; s += 2) {
+        bwd_x2 x = *reinterpret_cast<const bwd_x2*>(dp + s * step), y = *reinterpret_cast<const bwd_x2*>(dp + s * step + 2);
+        if (PAIRS) {
+            const bool one = s + 1 == P.S2;
+            const double* second = dp + (one ? s : s + 1) * step;
+            const bwd_x2 x2 = *reinterpret_cast<const bwd_x2*>(second), y2 = *reinterpret_cast<const bwd_x2*>(second + 2);
+            x += one ? bwd_x2{0.0, 0.0} : x2;
+            y += one ? bwd_x2{0.0, 0.0} : y2;
+        }
         acc[0] += x[0]; acc[1] += x[1]; acc[2] += y[0]; acc[3] += y[1];
     }
     const float v[4] = {(float)acc[0], (float)acc[1], (float)acc[2], (float)acc[3]};
@@ -855,26 +902,26 @@ void bwd_dq_reduce_kernel(const BwdParams P)
 template <typename T>
 static hipError_t raise_bwd_limits()
 {
-    constexpr int N = 7;
+    constexpr int N = 8;
     static std::atomic<uint64_t> raised[N];            // per instantiation: devices already served
     const void* fn[N] = {(const void*)bwd_stats_kernel<T>, (const void*)bwd_main_kernel<T, 4, kFused>,
                          (const void*)bwd_main_kernel<T, 2, kFused>, (const void*)bwd_main_kernel<T, 4, kFusedMany>,
                          (const void*)bwd_main_kernel<T, 4, kKeysOnly>, (const void*)bwd_main_kernel<T, 2, kKeysOnly>,
-                         (const void*)bwd_main_kernel<T, 8, kFused>};
-    const int lds[N] = {kBwdStatsLds, BwdShare<4>::kLds, BwdShare<2>::kLds, BwdShare<4>::kLds, BwdShare<4>::kLds, BwdShare<2>::kLds, BwdShare<8>::kLds};
+                         (const void*)bwd_main_kernel<T, 8, kFused>, (const void*)bwd_main_kernel<T, 8, kFusedOne>};
+    const int lds[N] = {kBwdStatsLds, BwdShare<4>::kLds, BwdShare<2>::kLds, BwdShare<4>::kLds, BwdShare<4>::kLds, BwdShare<2>::kLds, BwdShare<8>::kLds, BwdShare<8>::kLds};
     for (int k = 0; k < N; ++k) { const hipError_t e = ensure_lds_limit(fn[k], lds[k], raised[k]); if (e != hipSuccess) return e; }
     return hipSuccess;
 }
 hipError_t init_backward() { return raise_bwd_limits<float>(); }
 
 template <typename T>
-static hipError_t launch_bwd_t(const BwdParams& P, int BH, int ks, hipStream_t stream)
+static hipError_t launch_bwd_t(const BwdParams& P, int BH, int ks, int splits, hipStream_t stream)
 {
     const hipError_t e = raise_bwd_limits<T>();
     if (e != hipSuccess) return e;
     auto dealt = [&](int x) { return (unsigned)x << P.head_shift; };
     const unsigned heads = (unsigned)BH >> P.head_shift;
-    const dim3 grid(dealt(P.S2), heads), block(kBwdThreads);
+    const dim3 grid(dealt(splits), heads), block(kBwdThreads);
     hipLaunchKernelGGL(bwd_stats_kernel<T>, dim3(dealt(P.S1), P.n_group, heads), block, kBwdStatsLds, stream, P);
     if (P.stats) {
         hipLaunchKernelGGL(bwd_dq_kernel<T>, dim3(dealt(P.u_pad / kBwdQ), heads), block, 0, stream, P);
@@ -882,13 +929,17 @@ static hipError_t launch_bwd_t(const BwdParams& P, int BH, int ks, hipStream_t s
         else         hipLaunchKernelGGL((bwd_main_kernel<T, 2, kKeysOnly>), grid, block, BwdShare<2>::kFixed + kBwdGroup * 16, stream, P);
     } else if (P.u_pad > kBwdKeepStats)
         hipLaunchKernelGGL((bwd_main_kernel<T, 4, kFusedMany>), grid, block, BwdShare<4>::kFixed + kBwdGroup * 16, stream, P);
+    else if (ks == 8 && P.blocks2 == 1)
+        hipLaunchKernelGGL((bwd_main_kernel<T, 8, kFusedOne>), grid, dim3(BwdShare<8>::kThreads), BwdShare<8>::kFixed + P.u_pad * 16, stream, P);
     else if (ks == 8)
         hipLaunchKernelGGL((bwd_main_kernel<T, 8, kFused>), grid, dim3(BwdShare<8>::kThreads), BwdShare<8>::kFixed + P.u_pad * 16, stream, P);
     else if (ks == 4)
         hipLaunchKernelGGL((bwd_main_kernel<T, 4, kFused>), grid, block, BwdShare<4>::kFixed + P.u_pad * 16, stream, P);
     else
         hipLaunchKernelGGL((bwd_main_kernel<T, 2, kFused>), grid, block, BwdShare<2>::kFixed + P.u_pad * 16, stream, P);
-    if (P.dq_part) hipLaunchKernelGGL(bwd_dq_reduce_kernel<T>, dim3(dealt(P.u_pad / kBwdQ), heads), dim3(256), 0, stream, P);
+    const dim3 grid_r(dealt(P.u_pad / kBwdQ), heads);
+    if (P.dq_part && ks == 8) hipLaunchKernelGGL((bwd_dq_reduce_kernel<T, false>), grid_r, dim3(256), 0, stream, P);
+    else if (P.dq_part)       hipLaunchKernelGGL((bwd_dq_reduce_kernel<T, true>), grid_r, dim3(256), 0, stream, P);
     return hipGetLastError();
 }
 
@@ -976,8 +1027,8 @@ BwdPlan make_bwd_plan(const psa_shape_t& s, int u_stride)
     // write and to add up, the group's query rows staged once instead of twice.  Where they take no more rounds (a CU with one
     // of the smaller work-groups is faster than one with two; these come whole), and only for calls without lengths, which
     // alone are known to be full batches: with lengths the smaller ones spread better.  Whole call: B=16 H=4 L=512, 256 kept
-    // 162.9 -> 150.4 us; B=16 H=8 L=256, 128 kept 93.7 -> 86.5; B=8 H=8 L=1024, 512 kept 571.6 -> 533.0; B=32 H=4 L=512, 205 kept
-    // 263.5 -> 249.2; two rounds for one and a half, B=24 H=8 L=200, 100 kept 129.6 -> 136.6; lengths of 64 .. 512 at B=8 H=8
+    // 162.9 -> 150.4 us, and 147 where one block a split is compiled on its own (no registers spilled); B=16 H=8 L=256, 128 kept
+    // 93.7 -> 86.5, 84; B=8 H=8 L=1024, 512 kept 571.6 -> 533.0; B=32 H=4 L=512, 205 kept 263.5 -> 249.2; two rounds for one and a half, B=24 H=8 L=200, 100 kept 129.6 -> 136.6; lengths of 64 .. 512 at B=8 H=8
     // L=512, 256 kept 132.2 -> 139.7, of 50 .. 400 at B=16 H=8 L=400, 200 kept 194.7 -> 209.3.
     p.wide_S2 = 0;
     if (!p.keys_only && p.ks == 4 && p.u_pad <= kBwdKeepStats && p.S2 > 1) {
@@ -1014,9 +1065,9 @@ hipError_t launch_backward(const psa_shape_t& s, const BwdPlan& bp, const void* 
     P.dq_part = parts ? reinterpret_cast<double*>(w + bp.off_dq_part) : nullptr;
     P.stats = bp.keys_only ? reinterpret_cast<double*>(w + bp.off_stats) : nullptr;
     P.H = s.H; P.L = s.L_K; P.u_stride = u_stride; P.u_pad = bp.u_pad; P.n_group = bp.n_group;
-    P.S1 = bp.S1; P.blocks1 = bp.blocks1; P.S2 = wide ? bp.wide_S2 : bp.S2; P.blocks2 = bp.blocks2;
+    P.S1 = bp.S1; P.blocks1 = bp.blocks1; P.S2 = bp.S2; P.blocks2 = bp.blocks2;
     P.fill = fill; P.head_shift = (s.B * s.H) % 8 == 0 ? 3 : 0;
-    return launch_bwd_t<float>(P, s.B * s.H, wide ? 8 : bp.ks, stream);
+    return launch_bwd_t<float>(P, s.B * s.H, wide ? 8 : bp.ks, wide ? bp.wide_S2 : bp.S2, stream);
 }
 
 }  // namespace psa

@@ -5,6 +5,7 @@ import pytest
 import torch
 
 import tests.test_backward_tiles_gpu as tiles
+from paper_2106_09236_amd import binding as psa
 from paper_2106_09236_amd import workloads as W
 from tests.test_backward_gpu import check_backward
 
@@ -37,3 +38,28 @@ def test_full_batches(B, H, L, u, fill):
             sel[b, h, :ub] = r.permutation(L)[:ub]
             sel[b, h, 6:ub:7] = -1
     check_backward(w, torch.from_numpy(sel).cuda(), torch.full((B,), ub, dtype=torch.int32, device="cuda"), fill, label=f"full B{B} H{H} L{L} u{u} {fill}")
+
+
+@pytest.mark.parametrize("B,H,L,u", [
+    (32, 8, 128, 64), (64, 4, 65, 33),                                   # one block of 128 keys: dQ goes straight to memory
+    (16, 4, 512, 256), (16, 4, 511, 17), (4, 8, 996, 100),               # one block a split
+    (8, 8, 1024, 512), (8, 8, 871, 40), (8, 8, 1946, 60), (8, 8, 1702, 100),      # two and four, also with an odd number of the smaller splits
+    (4, 8, 2907, 17), (8, 8, 2225, 40), (16, 8, 1702, 33),               # three, five and seven: a split's halves meet within a block
+    (32, 8, 1302, 20),                                                   # eleven, all in one split
+])
+def test_full_lengths_give_the_same_bits(B, H, L, u):
+    # lengths that are all L and no lengths: blocks of 64 keys and of 128, whose sums are formed in the same order
+    g = torch.Generator(device="cuda")
+    g.manual_seed(L + u)
+    Q, K, V, G = (torch.randn((B, H, L, 64), generator=g, device="cuda") for _ in range(4))
+    # half of a key's elements with much in common, which cancels in dQ: sums in another order differ in float32 bits there
+    Q[..., :32] = 0.0
+    K[..., :32] += 30000.0
+    sel = torch.rand((B, H, L), generator=g, device="cuda").topk(u, dim=-1).indices.to(torch.int32).contiguous()
+    ub = torch.full((B,), u, dtype=torch.int32, device="cuda")
+    full = torch.full((B,), L, dtype=torch.int32, device="cuda")
+    for fill in (psa.FILL_MEAN, psa.FILL_VALUE):
+        none = psa.probsparse_attn_bwd(Q, K, V, None, sel, ub, G, fill)
+        same = psa.probsparse_attn_bwd(Q, K, V, full, sel, ub, G, fill)
+        for name, a, b in zip(("dQ", "dK", "dV"), none, same):
+            assert torch.equal(a, b), (name, int((a != b).sum()))
