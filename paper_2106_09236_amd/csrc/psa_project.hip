@@ -271,14 +271,14 @@ __device__ __forceinline__ RowBuffer row_buffer(const void* base, unsigned bytes
 }
 // 16 bytes per lane from memory to LDS (lane l's at lds + 16 l), past the registers.  In assembly because the compiler, which
 // cannot tell the stages apart, waits for ALL loads of this kind before any read of LDS; so the waits below count them.
-// (M0 holds the LDS address.)
+// (M0 holds the LDS address: an operand, so that the compiler writes it and knows.)
 __device__ __forceinline__ void load_to_lds(const RowBuffer& buf, unsigned lds, unsigned voffset, unsigned soffset)
 {
 #if defined(__HIP_DEVICE_COMPILE__)
     typedef unsigned int Rsrc __attribute__((ext_vector_type(4)));
     const Rsrc r = {buf.lo, buf.hi, buf.bytes, 0x00020000u};
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
-                 :: "s"(lds), "v"(voffset), "s"(r), "s"(soffset) : "memory", "m0");
+    asm volatile("s_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+                 :: "{m0}"(lds), "v"(voffset), "s"(r), "s"(soffset) : "memory");
 #endif
 }
 
