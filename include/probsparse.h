@@ -281,7 +281,9 @@ int dense_attn_fwd(const void* Q, const void* K, const void* V, const int32_t* l
  * one line of `key=value` words in `buf` (NUL-terminated), e.g. which measure kernel
  * (`measure=lds|lds_half|stream|none`), how I_sparse is found (`select=lists|kernel|
  * segments|given_inline|given_prep`), which attend kernel (`attend=key_split|rows|
- * rows_half_keys`) and how partial results are merged.  For tests and for reading
+ * rows_half_keys`) and how partial results are merged.  Where the buffer has room (512
+ * bytes are enough) the kernels of the projections of probsparse_mhsa_fwd at this shape
+ * follow and, with u_stride > 0, those of probsparse_attn_bwd.  For tests and for reading
  * profiles; the words are not a stable interface.  A call with `lengths` launches the
  * same kernels as one without.  `opt` gives the selection rule
  * (steps a1..a4); with u_stride > 0 the plan is that of

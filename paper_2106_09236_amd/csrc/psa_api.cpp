@@ -691,7 +691,24 @@ int probsparse_describe_plan(const psa_shape_t* shape, const psa_options_t* opt,
                            "attend=%s queries_per_group=%d query_groups=%d key_splits=%d rounds=%d merge=%s workspace=%zu",
                            p.u_max, measure, p.n_chunk, p.chunks_per_wg, select, p.cand_len > 0 ? p.n_lists : 0, p.cand_len,
                            p.n_seg, attend, p.nq_group, p.n_qgroup, p.n_split, p.tiles_per_wave, merge, p.total);
-    return (n < 0 || (size_t)n >= buf_bytes) ? PSA_ERR_ARG : PSA_OK;
+    if (n < 0 || (size_t)n >= buf_bytes) return PSA_ERR_ARG;
+    // the rest where there is room for it: the module's projections, and the backward for index sets of this stride
+    char more[320];
+    int m = snprintf(more, sizeof(more), " element_shares=%d qkv_project=%s out_project=%s", p.d_split, project_route_name(*shape, 3),
+                     project_route_name(*shape, 1));
+    if (u_stride > 0) {
+        const BwdPlan bp = make_bwd_plan(*shape, u_stride);
+        if (shape->dtype == PSA_F32) {
+            m += snprintf(more + m, sizeof(more) - m, " backward=%s backward_splits=%d backward_blocks=%d backward_keys=%d backward_keys_no_lengths=%d",
+                          bp.keys_only ? "two_kernels" : "fused", bp.S2, bp.blocks2, 16 * bp.ks, bp.wide_S2 > 0 ? 128 : 16 * bp.ks);
+        } else {
+            const Bwd16Plan b16 = make_bwd16_plan(*shape, u_stride, bp.total);
+            m += snprintf(more + m, sizeof(more) - m, " backward=bf16 backward_splits=%d backward_blocks=%d backward_keys=128 backward_dq_splits=%d",
+                          b16.S2, b16.blocks2, b16.SQ);
+        }
+    }
+    if (m > 0 && (size_t)(n + m) < buf_bytes) memcpy(buf + n, more, (size_t)m + 1);
+    return PSA_OK;
 }
 
 int probsparse_init(void)

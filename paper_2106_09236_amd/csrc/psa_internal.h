@@ -155,5 +155,6 @@ hipError_t launch_backward_bf16(const psa_shape_t& s, const Bwd16Plan& bp, const
 hipError_t launch_qkv_project(const psa_shape_t& s, const void* X, const psa_mhsa_weights_t& w,
                               void* Q, void* K, void* V, hipStream_t stream);
 hipError_t launch_out_project(const psa_shape_t& s, const void* A, const psa_mhsa_weights_t& w, void* Y, hipStream_t stream);
+const char* project_route_name(const psa_shape_t& s, int n_mat);         // the kernel for n_mat = 3 (Q, K, V) or 1 (output) matrices
 
 }  // namespace psa

@@ -795,52 +795,78 @@ static hipError_t launch_project_stream(const ProjectParams& P, hipStream_t stre
     return hipGetLastError();
 }
 
-static hipError_t launch_project(const ProjectParams& P0, int n_mat, int dtype, hipStream_t stream)
+// Which kernel a launch takes: project_kernel and project_split_kernel by their tiles
+enum ProjectRoute { kStream, kTiles22, kTiles21, kTiles11, kSplit22, kSplit21, kSplit11, kSplit11TwoGroups };
+static ProjectRoute project_route(const ProjectParams& P, int dtype)
 {
-    ProjectParams P = P0;
-    P.n_mat = n_mat;
     // 128 x 128 tiles when they give every compute unit at least two work-groups, else 128 x 64
-    const long wg128 = (long)((P.N + 127) / 128) * ((P.M + 127) / 128) * n_mat;
+    const long wg128 = (long)((P.N + 127) / 128) * ((P.M + 127) / 128) * P.n_mat;
     if (dtype == PSA_F32) {
         // (128 x 64 tiles give 2 wg128 work-groups, 64 x 64 tiles 4 wg128)
-        if (wg128 >= 512) return launch_project_split<2, 2>(P, stream);
-        if (2 * wg128 >= 512) return launch_project_split<2, 1>(P, stream);
+        if (wg128 >= 512) return kSplit22;
+        if (2 * wg128 >= 512) return kSplit21;
         // (two groups of waves while their work-groups, two to a compute unit, are there at once: whole module, B=1 H=4 L=333, 96
         // and 24 of them, 39.9 -> 37.4 us; B=1 H=8 L=333 52.1 -> 45.2; B=8 H=4 L=300, 456, 43.6 -> 42.1; B=8 H=8 L=300, 912, 75.6 -> 77.0)
-        const long wg64 = (long)((P.N + 63) / 64) * ((P.M + 63) / 64) * n_mat;
-        return wg64 <= 512 ? launch_project_split<1, 1, 2>(P, stream) : launch_project_split<1, 1>(P, stream);
+        const long wg64 = (long)((P.N + 63) / 64) * ((P.M + 63) / 64) * P.n_mat;
+        return wg64 <= 512 ? kSplit11TwoGroups : kSplit11;
     }
-    if (stream_pays(P) && stream_fits(P))
-        return P.a_heads ? launch_project_stream<true, false>(P, stream) : launch_project_stream<false, true>(P, stream);
+    if (stream_pays(P) && stream_fits(P)) return kStream;
     // Few rows: 64 x 64 tiles, four times as many work-groups with half of the loads and a quarter of the stores each, as long
     // as all are there at once (four to a compute unit).  Whole module, 128 x 64 -> 64 x 64: B=1 H=4 L=40 20.8 -> 19.2 us, B=1
     // H=8 L=333 33.6 -> 31.0, B=4 H=8 L=400 (624 of them for Q, K and V) 37.2 -> 34.8, B=3 H=8 L=2000 (752 for the output
     // matrix) 70.5 -> 69.2; B=24 H=8 L=500 (1504 for the output matrix) 78.3 -> 78.8.
-    if (wg128 <= 256) return launch_project_as<1, 1>(P, stream);
-    return wg128 >= 512 ? launch_project_as<2, 2>(P, stream) : launch_project_as<2, 1>(P, stream);
+    if (wg128 <= 256) return kTiles11;
+    return wg128 >= 512 ? kTiles22 : kTiles21;
+}
+
+static hipError_t launch_project(const ProjectParams& P, int dtype, hipStream_t stream)
+{
+    switch (project_route(P, dtype)) {
+        case kStream:  return P.a_heads ? launch_project_stream<true, false>(P, stream) : launch_project_stream<false, true>(P, stream);
+        case kTiles22: return launch_project_as<2, 2>(P, stream);
+        case kTiles21: return launch_project_as<2, 1>(P, stream);
+        case kTiles11: return launch_project_as<1, 1>(P, stream);
+        case kSplit22: return launch_project_split<2, 2>(P, stream);
+        case kSplit21: return launch_project_split<2, 1>(P, stream);
+        case kSplit11: return launch_project_split<1, 1>(P, stream);
+        default:       return launch_project_split<1, 1, 2>(P, stream);
+    }
+}
+
+// the sizes of the launch for Q, K and V (three matrices) or for the output matrix (one)
+static ProjectParams project_sizes(const psa_shape_t& s, int n_mat)
+{
+    ProjectParams P{};
+    P.M = s.B * s.L_K; P.N = P.Kd = s.H * kD; P.L = s.L_K; P.H = s.H;
+    P.n_mat = n_mat; P.a_heads = n_mat == 1; P.c_heads = n_mat != 1;
+    return P;
+}
+const char* project_route_name(const psa_shape_t& s, int n_mat)
+{
+    static const char* const names[] = {"stream", "tiles_128x128", "tiles_128x64", "tiles_64x64", "tiles_128x128", "tiles_128x64", "tiles_64x64",
+                                        "tiles_64x64_two_groups"};
+    return names[project_route(project_sizes(s, n_mat), s.dtype)];
 }
 
 hipError_t launch_qkv_project(const psa_shape_t& s, const void* X, const psa_mhsa_weights_t& w,
                               void* Q, void* K, void* V, hipStream_t stream)
 {
-    ProjectParams P;
+    ProjectParams P = project_sizes(s, 3);
     P.A = X;
     P.W[0] = w.Wq; P.W[1] = w.Wk; P.W[2] = w.Wv;
     P.bias[0] = w.bq; P.bias[1] = w.bk; P.bias[2] = w.bv;
     P.C[0] = Q; P.C[1] = K; P.C[2] = V;
-    P.M = s.B * s.L_K; P.N = s.H * kD; P.Kd = s.H * kD; P.L = s.L_K; P.H = s.H; P.a_heads = 0; P.c_heads = 1;
-    return launch_project(P, 3, s.dtype, stream);
+    return launch_project(P, s.dtype, stream);
 }
 
 hipError_t launch_out_project(const psa_shape_t& s, const void* A, const psa_mhsa_weights_t& w, void* Y, hipStream_t stream)
 {
-    ProjectParams P;
+    ProjectParams P = project_sizes(s, 1);
     P.A = A;
-    P.W[0] = w.Wo; P.W[1] = P.W[2] = nullptr;
-    P.bias[0] = w.bo; P.bias[1] = P.bias[2] = nullptr;
-    P.C[0] = Y; P.C[1] = P.C[2] = nullptr;
-    P.M = s.B * s.L_K; P.N = s.H * kD; P.Kd = s.H * kD; P.L = s.L_K; P.H = s.H; P.a_heads = 1; P.c_heads = 0;
-    return launch_project(P, 1, s.dtype, stream);
+    P.W[0] = w.Wo;
+    P.bias[0] = w.bo;
+    P.C[0] = Y;
+    return launch_project(P, s.dtype, stream);
 }
 
 }  // namespace psa

@@ -25,15 +25,16 @@ def test_groups_beyond_u(B, H, L):
 
 
 @pytest.mark.parametrize("fill", ["mean", "value"])
-@pytest.mark.parametrize("B,H,L,groups", [
-    (1, 4, 1, 32), (1, 1, 33, 32), (16, 5, 32, 32),      # groups of 32, four and two work-groups to a group of queries
-    (1, 1, 65, 16), (2, 4, 128, 16), (3, 4, 257, 16),    # groups of 16, four: two tiles and a key, half of the waves, a second step
-    (8, 4, 200, 16), (8, 8, 129, 16),                    # ... at most 256 work-groups, and two to a group
+@pytest.mark.parametrize("B,H,L,groups,shares", [
+    (1, 4, 1, 32, 4), (1, 1, 33, 32, 4), (16, 5, 32, 32, 2),       # groups of 32, four and two work-groups to a group of queries
+    (1, 1, 65, 16, 4), (2, 4, 128, 16, 4), (3, 4, 257, 16, 4),     # groups of 16, four: two tiles and a key, half of the waves, a second step
+    (8, 4, 200, 16, 4), (8, 8, 129, 16, 2),                        # ... at most 256 work-groups, and two to a group
 ])
-def test_shared_elements(B, H, L, groups, fill):
+def test_shared_elements(B, H, L, groups, shares, fill):
     # heads in one key split whose output elements several work-groups share; items of 0, 1 and 2 frames among them
     p = plan(B, H, L, 9, "f32")
     assert p["attend"] == "key_split" and p["merge"] == "none" and int(p["queries_per_group"]) == groups
+    assert int(p["element_shares"]) == shares
     assert 2 * B * H * int(p["query_groups"]) <= 256
     cfg = W.small_config("shared", B, H, L, 9, 5.0, "f32", "peaky", B > 1, max(1, L // 2), L)
     w = W.make_workload(cfg, seed=40 + L)

@@ -125,6 +125,30 @@ def test_many_head_sweep_reaches_rows_kernels_and_inline_index_sets():
     assert any(sel in ("lists", "kernel") and att == "rows_half_keys" for sel, att in seen)
 
 
+def test_plan_tells_the_kernels_of_the_module_and_of_the_backward():
+    p = plan(8, 8, 2048, 40, "bf16", u_stride=39)
+    assert (p["qkv_project"], p["out_project"], p["backward"], p["backward_dq_splits"]) == ("stream", "tiles_128x128", "bf16", "1")
+    assert plan(1, 8, 16384, 50, "bf16", u_stride=49)["backward_dq_splits"] == "8"
+    p = plan(16, 4, 512, 32, "f32", u_stride=256)
+    assert (p["backward"], p["backward_keys"], p["backward_keys_no_lengths"]) == ("fused", "64", "128")
+    assert plan(1, 4, 2000, 32, "f32", u_stride=1000)["backward"] == "two_kernels"
+    assert "backward" not in plan(16, 4, 512, 32, "f32")
+    p = plan(1, 4, 333, 30, "f32")
+    assert (p["element_shares"], p["qkv_project"], p["out_project"]) == ("4", "tiles_64x64_two_groups", "tiles_64x64_two_groups")
+
+
+def test_a_buffer_for_the_attention_alone_is_enough():
+    # the words of the module and the backward are left out where the buffer ends before them
+    shape, buf = psa.make_shape(8, 8, 2048, 40, psa.PSA_BF16), ctypes.create_string_buffer(512)
+    f = psa.load().probsparse_describe_plan
+    assert f(ctypes.byref(shape), None, 39, buf, 512) == 0
+    full = buf.value
+    n = full.index(b" element_shares=")
+    for size, want in ((len(full) + 1, full), (len(full), full[:n]), (n + 1, full[:n])):
+        assert f(ctypes.byref(shape), None, 39, buf, size) == 0 and buf.value == want
+    assert f(ctypes.byref(shape), None, 39, buf, n) == ERR_ARG
+
+
 def test_describe_plan_argument_errors():
     lib = psa.load()
     shape = psa.make_shape(1, 1, 64, 8, psa.PSA_F32)

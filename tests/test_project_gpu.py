@@ -6,19 +6,23 @@ import torch
 
 from paper_2106_09236_amd import binding as psa
 from paper_2106_09236_amd import workloads as W
+from tests.test_plan import plan
 
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("B,L,H,bias", [
-    (8, 2048, 8, True),            # whole tiles, three per work-group
-    (13, 777, 8, False),           # a ragged last block of rows, work-groups with one tile and with two
-    (4, 8190, 8, True),            # the output matrix as well: two rounds; every tile but the first starts inside an item
-    (16000, 4, 4, True),           # items of 4 frames: 64 to a tile; both launches
-    (7, 1100, 15, True),           # a ragged last column tile: 960 of 1024 columns
-    (64, 2000, 4, False),          # ten tiles and more to a work-group
+@pytest.mark.parametrize("B,L,H,bias,out", [
+    (8, 2048, 8, True, False),     # whole tiles, three per work-group
+    (13, 777, 8, False, False),    # a ragged last block of rows, work-groups with one tile and with two
+    (4, 8190, 8, True, True),      # the output matrix as well: two rounds; every tile but the first starts inside an item
+    (16000, 4, 4, True, True),     # items of 4 frames: 64 to a tile; both launches
+    (7, 1100, 15, True, False),    # a ragged last column tile: 960 of 1024 columns
+    (64, 2000, 4, False, True),    # ten tiles and more to a work-group
 ])
-def test_many_rows_equal_few_rows(B, L, H, bias):
+def test_many_rows_equal_few_rows(B, L, H, bias, out):
+    # `out`: the output matrix takes that kernel as well
+    p = plan(B, H, L, 4, "bf16")
+    assert p["qkv_project"] == "stream" and (p["out_project"] == "stream") == out
     raw = W.make_mhsa_inputs(1, 1, H, "bf16", 5 + L, bias)
     dev = {k: None if v is None else torch.from_numpy(v.view("int16")).view(torch.bfloat16).cuda() for k, v in raw.items()}
     weights = psa.make_weights(*[dev[k] for k in ("Wq", "Wk", "Wv", "Wo", "bq", "bk", "bv", "bo")])
@@ -28,6 +32,8 @@ def test_many_rows_equal_few_rows(B, L, H, bias):
     A = torch.randn((B, H, L, 64), generator=g, device="cuda").to(torch.bfloat16)
     many = psa.probsparse_qkv_project(X, weights) + (psa.probsparse_out_project(A, weights),)
     n = max(1, 2000 // L)                     # items per call: at most 2000 rows, or one item cut into such pieces
+    p = plan(n, H, min(L, 2000), 4, "bf16")
+    assert p["qkv_project"] != "stream" and p["out_project"] != "stream"
     for b in range(0, B, n):
         for l in range(0, L, 2000):
             x, a = X[b:b + n, l:l + 2000].contiguous(), A[b:b + n, :, l:l + 2000].contiguous()
@@ -43,6 +49,8 @@ def test_few_rows_of_float32(B, L, H):
     # two groups of waves add every other chunk of a contraction.  Against float64, element by element: every product is off by at
     # most 3 * 2^-25 (three bfloat16 parts of a factor, six of nine products) and every addition of at most 6 dm + 2 by 2^-24
     # of the sum of the products' sizes (first order; twice that is allowed)
+    p = plan(B, H, L, 4, "f32")
+    assert (p["qkv_project"] == "tiles_64x64_two_groups") == (L <= 2688) and p["out_project"] == "tiles_64x64_two_groups"
     dm = H * 64
     g = torch.Generator(device="cuda")
     g.manual_seed(L)
