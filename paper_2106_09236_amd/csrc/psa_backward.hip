@@ -73,8 +73,7 @@ template <int KS> struct BwdShare {
 
 // N contiguous elements (N = 4, 8 or 16) as they lie in memory, widened where they are used (so that a request
 // stays a request until then), and a 4-element store
-template <typename T, int N> struct BwdRow;
-template <int N> struct BwdRow<float, N> {
+template <int N> struct BwdRow {
     float4 x[N / 4];
     __device__ __forceinline__ void load(const float* p) {
 #pragma unroll
@@ -120,13 +119,13 @@ __device__ __forceinline__ int bwd_index(const BwdParams& P) { return (int)(bloc
 // Kept queries q0 .. q0 + ROWS - 1 of the head: their rows of Q and of G as float64 in LDS (zeros for an absent
 // entry), 8 or 16 threads per row.  `find` looks the rows up in the list, `request` asks for them, `put` writes them to
 // LDS (the caller's barrier makes them visible); a caller may have other work between the three.
-template <typename T, int ROWS, int NT>
+template <int ROWS, int NT>
 struct QueryStage {
     static constexpr int kPer = NT > ROWS * 8 ? 16 : 8;      // threads per row
     static constexpr int kPasses = ROWS * kPer / NT, kElems = kD / kPer;
     static_assert(kPasses * NT == ROWS * kPer, "whole passes");
     int qi[kPasses];                          // list entries as they lie in memory, rows (or -1) from `request` on
-    BwdRow<T, kElems> a[kPasses], b[kPasses];
+    BwdRow<kElems> a[kPasses], b[kPasses];
     static __device__ __forceinline__ int row_of(int k) { return k * (NT / kPer) + (int)threadIdx.x / kPer; }
     __device__ __forceinline__ void find(const BwdParams& P, int head, int q0) {
 #pragma unroll
@@ -135,7 +134,7 @@ struct QueryStage {
             qi[k] = P.sel[(size_t)head * P.u_stride + (t < P.u_stride ? t : P.u_stride - 1)];
         }
     }
-    __device__ __forceinline__ void request(const T* Qh, const T* Gh, int q0, int n, int ub) {
+    __device__ __forceinline__ void request(const float* Qh, const float* Gh, int q0, int n, int ub) {
         const int part = threadIdx.x % kPer;
 #pragma unroll
         for (int k = 0; k < kPasses; ++k) {
@@ -160,8 +159,7 @@ struct QueryStage {
 };
 
 // Widens a wave's key rows into registers, once: the compiler would rather repeat the conversion at every use.
-template <typename T>
-__device__ __forceinline__ void widen16(const BwdRow<T, 16>& x, double (&d)[16])
+__device__ __forceinline__ void widen16(const BwdRow<16>& x, double (&d)[16])
 {
 #pragma unroll
     for (int t = 0; t < 16; ++t) { d[t] = (double)x.at(t); asm volatile("" : "+v"(d[t])); }
@@ -210,7 +208,6 @@ constexpr double kBwdNoMax = -1e300;
 
 // ---- partial softmax statistics per kept query and key split; column sums of G over the rows the mean fill serves.
 // grid (key splits, groups of 64 kept queries, heads), eight heads (or one) on the first axis
-template <typename T>
 __global__ __launch_bounds__(kBwdThreads, 2)
 void bwd_stats_kernel(const BwdParams P)
 {
@@ -223,10 +220,10 @@ void bwd_stats_kernel(const BwdParams P)
     const int n = valid_len(P.lengths, b, L);
     const int ub = kept_count(P, b, n);
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, c = lane & 15, g = lane >> 4;
-    const T* Qh = static_cast<const T*>(P.Q) + (size_t)head * L * kD;
-    const T* Kh = static_cast<const T*>(P.K) + (size_t)head * L * kD;
-    const T* Vh = static_cast<const T*>(P.V) + (size_t)head * L * kD;
-    const T* Gh = static_cast<const T*>(P.G) + (size_t)head * L * kD;
+    const float* Qh = static_cast<const float*>(P.Q) + (size_t)head * L * kD;
+    const float* Kh = static_cast<const float*>(P.K) + (size_t)head * L * kD;
+    const float* Vh = static_cast<const float*>(P.V) + (size_t)head * L * kD;
+    const float* Gh = static_cast<const float*>(P.G) + (size_t)head * L * kD;
     const int k_first = split * P.blocks1 * kBwdKeys;
     int k_end = k_first + P.blocks1 * kBwdKeys;
     k_end = k_end < n ? k_end : n;
@@ -239,8 +236,8 @@ void bwd_stats_kernel(const BwdParams P)
     // the wave's 16 key rows (lane: 16 elements of row c) and, for the column sums, the same 16 rows of G (lane:
     // elements 4c .. 4c + 3 of rows 4 i + g); the next block's are requested before the current one is worked on
     // (on a clamped row: harmless past the end)
-    BwdRow<T, 16> kn, vn;
-    BwdRow<T, 4> gn[4];
+    BwdRow<16> kn, vn;
+    BwdRow<4> gn[4];
     auto request = [&](int j0) {
         if (n_t > 0) {
             const int row = j0 + c < n ? j0 + c : n - 1;
@@ -257,7 +254,7 @@ void bwd_stats_kernel(const BwdParams P)
     };
     if (k_first < k_end) request(k_first + 16 * wave);               // (n > 0)
     if (n_t > 0) {
-        QueryStage<T, kBwdStatGroup, kBwdThreads> qs;
+        QueryStage<kBwdStatGroup, kBwdThreads> qs;
         qs.find(P, head, q0);
         qs.request(Qh, Gh, q0, n, ub);
         qs.put(sQ, sG);
@@ -404,7 +401,6 @@ __device__ __forceinline__ bwd_x2 stat_of(const BwdParams& P, int head, int t, i
 // every 64; the waves' shares of dQ are added in wave order at the end, so nothing goes through memory.  The price is
 // the two score products, formed a third time (48 MFMAs for a tile of 16 queries x 16 keys instead of 16).
 // grid (tiles of 16 kept queries, heads), heads as above
-template <typename T>
 __global__ __launch_bounds__(kBwdThreads, 2)
 void bwd_dq_kernel(const BwdParams P)
 {
@@ -416,16 +412,16 @@ void bwd_dq_kernel(const BwdParams P)
     const int ub = kept_count(P, b, n);
     if (q0 >= ub) return;                                            // work-group-uniform (n > 0 behind this)
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, c = lane & 15, g = lane >> 4;
-    const T* Qh = static_cast<const T*>(P.Q) + (size_t)head * L * kD;
-    const T* Kh = static_cast<const T*>(P.K) + (size_t)head * L * kD;
-    const T* Vh = static_cast<const T*>(P.V) + (size_t)head * L * kD;
-    const T* Gh = static_cast<const T*>(P.G) + (size_t)head * L * kD;
+    const float* Qh = static_cast<const float*>(P.Q) + (size_t)head * L * kD;
+    const float* Kh = static_cast<const float*>(P.K) + (size_t)head * L * kD;
+    const float* Vh = static_cast<const float*>(P.V) + (size_t)head * L * kD;
+    const float* Gh = static_cast<const float*>(P.G) + (size_t)head * L * kD;
 
     // operands of 16 keys: the lane's key row for the score products (16 elements of key c), and for the product that
     // contracts over keys elements 4c .. 4c + 3 of keys 4r + g; the next keys' are requested before these are worked
     // on (on a clamped row: harmless past the end)
-    BwdRow<T, 16> kn, vn;
-    BwdRow<T, 4> k4n[4];
+    BwdRow<16> kn, vn;
+    BwdRow<4> k4n[4];
     auto request = [&](int j0) {
         const int row = j0 + c < n ? j0 + c : n - 1;
         kn.load(Kh + (size_t)row * kD + 16 * g);
@@ -440,7 +436,7 @@ void bwd_dq_kernel(const BwdParams P)
     const int qi = kept_row(P, head, q0 + c, n, ub);
     double qd[16], gd[16];                                           // B operands of the score products: query c (zeros for an absent entry)
     {
-        BwdRow<T, 16> qf, gf;
+        BwdRow<16> qf, gf;
         qf.load(Qh + (size_t)(qi >= 0 ? qi : 0) * kD + 16 * g);
         gf.load(Gh + (size_t)(qi >= 0 ? qi : 0) * kD + 16 * g);
 #pragma unroll
@@ -458,8 +454,8 @@ void bwd_dq_kernel(const BwdParams P)
     for (int dt = 0; dt < 4; ++dt) acc[dt] = bwd_x4{0.0, 0.0, 0.0, 0.0};
 #pragma unroll 1
     for (int j0 = 16 * wave; j0 < n; j0 += 16 * kBwdWaves) {         // wave-uniform
-        BwdRow<T, 16> kf = kn, vf = vn;
-        BwdRow<T, 4> k4[4];
+        BwdRow<16> kf = kn, vf = vn;
+        BwdRow<4> k4[4];
 #pragma unroll
         for (int r = 0; r < 4; ++r) k4[r] = k4n[r];
         if (j0 + 16 * kBwdWaves < n) request(j0 + 16 * kBwdWaves);
@@ -493,7 +489,7 @@ void bwd_dq_kernel(const BwdParams P)
         for (int w = 0; w < kBwdWaves; ++w) t += s_acc[w][4 * dt + wave][lane];
         v[dt] = (float)t;
     }
-    if (qi >= 0) bwd_store4(static_cast<T*>(P.dQ) + ((size_t)head * L + qi) * kD + 16 * wave + 4 * g, v);
+    if (qi >= 0) bwd_store4(static_cast<float*>(P.dQ) + ((size_t)head * L + qi) * kD + 16 * wave + 4 * g, v);
 }
 
 // ---- dK and dV of blocks of 16 KS keys over all kept queries of the head, and dQ over those keys.
@@ -503,7 +499,7 @@ void bwd_dq_kernel(const BwdParams P)
 // the waves put their g values into LDS; wave w then takes elements 16 w .. + 15 of both tiles over all keys of the
 // block, so that nothing has to be added up across waves.
 // grid (key splits, heads), heads as above, blocks2 key blocks per work-group, which adds to the dQ it wrote for the block before.
-template <typename T, int KS, BwdForm FORM>
+template <int KS, BwdForm FORM>
 __global__ __launch_bounds__(BwdShare<KS>::kThreads, 2)
 void bwd_main_kernel(const BwdParams P)
 {
@@ -527,14 +523,14 @@ void bwd_main_kernel(const BwdParams P)
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int ks = wave % KS, slot = wave / KS;
     const int we = wave & 3, wt = wave >> 2;                         // of dQ: elements 16 we .. + 15 of tiles wt .. wt + DT - 1
-    const T* Qh = static_cast<const T*>(P.Q) + (size_t)head * L * kD;
-    const T* Kh = static_cast<const T*>(P.K) + (size_t)head * L * kD;
-    const T* Vh = static_cast<const T*>(P.V) + (size_t)head * L * kD;
-    const T* Gh = static_cast<const T*>(P.G) + (size_t)head * L * kD;
+    const float* Qh = static_cast<const float*>(P.Q) + (size_t)head * L * kD;
+    const float* Kh = static_cast<const float*>(P.K) + (size_t)head * L * kD;
+    const float* Vh = static_cast<const float*>(P.V) + (size_t)head * L * kD;
+    const float* Gh = static_cast<const float*>(P.G) + (size_t)head * L * kD;
 
     // the key rows of a block: requested ahead (clamped: harmless if none is valid)
     const int r_first = split * blocks2 * SH::kKeys;
-    BwdRow<T, 16> kn, vn;
+    BwdRow<16> kn, vn;
     auto request = [&](int r0) {
         const int lo = opaque(lane), j = r0 + 16 * ks + (lo & 15), row = j < n ? j : (n > 0 ? n - 1 : 0);
         kn.load(Kh + (size_t)row * kD + 16 * (lo >> 4));
@@ -561,7 +557,7 @@ void bwd_main_kernel(const BwdParams P)
             dp[0] = dp[1] = bwd_x2{0.0, 0.0};
         }
     }
-    QueryStage<T, kBwdGroup, NT> qs;
+    QueryStage<kBwdGroup, NT> qs;
     if (r_first < n) { qs.find(P, head, 0); qs.request(Qh, Gh, 0, n, ub); qs.put(sQ, sG); }
 
     // (Barriers order LDS only: the stores of a block and the loads of the next need not be waited for.  Positions
@@ -694,7 +690,7 @@ void bwd_main_kernel(const BwdParams P)
                     if (P.dq_part == nullptr) {                      // the only block of the head
                         const int qi = kept_row(P, head, t + c, n, ub);
                         const float v[4] = {(float)dq[i][0], (float)dq[i][1], (float)dq[i][2], (float)dq[i][3]};
-                        if (qi >= 0) bwd_store4(static_cast<T*>(P.dQ) + ((size_t)head * L + qi) * kD + e_own, v);
+                        if (qi >= 0) bwd_store4(static_cast<float*>(P.dQ) + ((size_t)head * L + qi) * kD + e_own, v);
                     } else {
                         if (blk > 0) dq[i] += bwd_x4{old[i][0][0], old[i][0][1], old[i][1][0], old[i][1][1]};
                         bwd_x2* dp = reinterpret_cast<bwd_x2*>(P.dq_part + (((size_t)head * P.S2 + split) * P.u_pad + t + c) * kD + e_own);
@@ -814,7 +810,7 @@ void bwd_main_kernel(const BwdParams P)
         // pieces of one row; they go through the g tiles' LDS, 16 rows of 64 floats per wave (pieces of 16 bytes
         // swapped by row, for the banks), so that a store instruction writes whole rows, 16 bytes per lane.
         if (slot == 0) {
-            constexpr int EPV = 16 / sizeof(T), LPR = kD / EPV, RPI = 64 / LPR;      // elements per lane, lanes per row, rows per instruction
+            constexpr int EPV = 4, LPR = kD / EPV, RPI = 64 / LPR;      // elements per lane, lanes per row, rows per instruction
             const int lo = opaque(lane), c = lo & 15, g = lo >> 4;
             float* stage = reinterpret_cast<float*>(sg) + (size_t)ks * 16 * kD;
             const int row_l = lo / LPR, e_l = (lo % LPR) * EPV;
@@ -822,7 +818,7 @@ void bwd_main_kernel(const BwdParams P)
             const unsigned bits = (s_bits[bit0 >> 5] >> (bit0 & 31)) & 0xFFFFu;      // kept rows among these 16 (none at or beyond n)
             // the value fill hands v_j the gradient of its own row
             const bool use_own = P.fill != PSA_FILL_MEAN && j0 + c < n && !((bits >> c) & 1u);
-            BwdRow<T, 4> own[4];
+            BwdRow<4> own[4];
             if (use_own) {
 #pragma unroll
                 for (int r = 0; r < 4; ++r) own[r].load(Gh + (size_t)(j0 + c) * kD + 16 * r + 4 * g);
@@ -844,8 +840,8 @@ void bwd_main_kernel(const BwdParams P)
                     *piece(c, 4 * r + g) = make_float4((float)v[0], (float)v[1], (float)v[2], (float)v[3]);
                 }
                 wave_lds_sync();
-                T* base = static_cast<T*>(half == 0 ? P.dK : P.dV) + ((size_t)head * L + j0) * kD + e_l;
-                T* base_q = static_cast<T*>(P.dQ) + ((size_t)head * L + j0) * kD + e_l;
+                float* base = static_cast<float*>(half == 0 ? P.dK : P.dV) + ((size_t)head * L + j0) * kD + e_l;
+                float* base_q = static_cast<float*>(P.dQ) + ((size_t)head * L + j0) * kD + e_l;
 #pragma unroll
                 for (int it = 0; it < 16 / RPI; ++it) {
                     const int row = it * RPI + row_l;
@@ -869,7 +865,7 @@ void bwd_main_kernel(const BwdParams P)
 
 // adds the key splits of dQ in split order, two and two first (a split of the 8-wave form is the sum of two; PAIRS: the sums are
 // still to be formed); 16 threads per kept query, 4 elements each
-template <typename T, bool PAIRS>
+template <bool PAIRS>
 __global__ __launch_bounds__(256)
 void bwd_dq_reduce_kernel(const BwdParams P)
 {
@@ -896,50 +892,48 @@ void bwd_dq_reduce_kernel(const BwdParams P)
         acc[0] += x[0]; acc[1] += x[1]; acc[2] += y[0]; acc[3] += y[1];
     }
     const float v[4] = {(float)acc[0], (float)acc[1], (float)acc[2], (float)acc[3]};
-    bwd_store4(static_cast<T*>(P.dQ) + ((size_t)head * P.L + qi) * kD + e0, v);
+    bwd_store4(static_cast<float*>(P.dQ) + ((size_t)head * P.L + qi) * kD + e0, v);
 }
 
-template <typename T>
 static hipError_t raise_bwd_limits()
 {
     constexpr int N = 8;
-    static std::atomic<uint64_t> raised[N];            // per instantiation: devices already served
-    const void* fn[N] = {(const void*)bwd_stats_kernel<T>, (const void*)bwd_main_kernel<T, 4, kFused>,
-                         (const void*)bwd_main_kernel<T, 2, kFused>, (const void*)bwd_main_kernel<T, 4, kFusedMany>,
-                         (const void*)bwd_main_kernel<T, 4, kKeysOnly>, (const void*)bwd_main_kernel<T, 2, kKeysOnly>,
-                         (const void*)bwd_main_kernel<T, 8, kFused>, (const void*)bwd_main_kernel<T, 8, kFusedOne>};
+    static std::atomic<uint64_t> raised[N];            // per kernel: devices already served
+    const void* fn[N] = {(const void*)bwd_stats_kernel, (const void*)bwd_main_kernel<4, kFused>,
+                         (const void*)bwd_main_kernel<2, kFused>, (const void*)bwd_main_kernel<4, kFusedMany>,
+                         (const void*)bwd_main_kernel<4, kKeysOnly>, (const void*)bwd_main_kernel<2, kKeysOnly>,
+                         (const void*)bwd_main_kernel<8, kFused>, (const void*)bwd_main_kernel<8, kFusedOne>};
     const int lds[N] = {kBwdStatsLds, BwdShare<4>::kLds, BwdShare<2>::kLds, BwdShare<4>::kLds, BwdShare<4>::kLds, BwdShare<2>::kLds, BwdShare<8>::kLds, BwdShare<8>::kLds};
     for (int k = 0; k < N; ++k) { const hipError_t e = ensure_lds_limit(fn[k], lds[k], raised[k]); if (e != hipSuccess) return e; }
     return hipSuccess;
 }
-hipError_t init_backward() { return raise_bwd_limits<float>(); }
+hipError_t init_backward() { return raise_bwd_limits(); }
 
-template <typename T>
-static hipError_t launch_bwd_t(const BwdParams& P, int BH, int ks, int splits, hipStream_t stream)
+static hipError_t launch_bwd(const BwdParams& P, int BH, int ks, int splits, hipStream_t stream)
 {
-    const hipError_t e = raise_bwd_limits<T>();
+    const hipError_t e = raise_bwd_limits();
     if (e != hipSuccess) return e;
     auto dealt = [&](int x) { return (unsigned)x << P.head_shift; };
     const unsigned heads = (unsigned)BH >> P.head_shift;
     const dim3 grid(dealt(splits), heads), block(kBwdThreads);
-    hipLaunchKernelGGL(bwd_stats_kernel<T>, dim3(dealt(P.S1), P.n_group, heads), block, kBwdStatsLds, stream, P);
+    hipLaunchKernelGGL(bwd_stats_kernel, dim3(dealt(P.S1), P.n_group, heads), block, kBwdStatsLds, stream, P);
     if (P.stats) {
-        hipLaunchKernelGGL(bwd_dq_kernel<T>, dim3(dealt(P.u_pad / kBwdQ), heads), block, 0, stream, P);
-        if (ks == 4) hipLaunchKernelGGL((bwd_main_kernel<T, 4, kKeysOnly>), grid, block, BwdShare<4>::kFixed + kBwdGroup * 16, stream, P);
-        else         hipLaunchKernelGGL((bwd_main_kernel<T, 2, kKeysOnly>), grid, block, BwdShare<2>::kFixed + kBwdGroup * 16, stream, P);
+        hipLaunchKernelGGL(bwd_dq_kernel, dim3(dealt(P.u_pad / kBwdQ), heads), block, 0, stream, P);
+        if (ks == 4) hipLaunchKernelGGL((bwd_main_kernel<4, kKeysOnly>), grid, block, BwdShare<4>::kFixed + kBwdGroup * 16, stream, P);
+        else         hipLaunchKernelGGL((bwd_main_kernel<2, kKeysOnly>), grid, block, BwdShare<2>::kFixed + kBwdGroup * 16, stream, P);
     } else if (P.u_pad > kBwdKeepStats)
-        hipLaunchKernelGGL((bwd_main_kernel<T, 4, kFusedMany>), grid, block, BwdShare<4>::kFixed + kBwdGroup * 16, stream, P);
+        hipLaunchKernelGGL((bwd_main_kernel<4, kFusedMany>), grid, block, BwdShare<4>::kFixed + kBwdGroup * 16, stream, P);
     else if (ks == 8 && P.blocks2 == 1)
-        hipLaunchKernelGGL((bwd_main_kernel<T, 8, kFusedOne>), grid, dim3(BwdShare<8>::kThreads), BwdShare<8>::kFixed + P.u_pad * 16, stream, P);
+        hipLaunchKernelGGL((bwd_main_kernel<8, kFusedOne>), grid, dim3(BwdShare<8>::kThreads), BwdShare<8>::kFixed + P.u_pad * 16, stream, P);
     else if (ks == 8)
-        hipLaunchKernelGGL((bwd_main_kernel<T, 8, kFused>), grid, dim3(BwdShare<8>::kThreads), BwdShare<8>::kFixed + P.u_pad * 16, stream, P);
+        hipLaunchKernelGGL((bwd_main_kernel<8, kFused>), grid, dim3(BwdShare<8>::kThreads), BwdShare<8>::kFixed + P.u_pad * 16, stream, P);
     else if (ks == 4)
-        hipLaunchKernelGGL((bwd_main_kernel<T, 4, kFused>), grid, block, BwdShare<4>::kFixed + P.u_pad * 16, stream, P);
+        hipLaunchKernelGGL((bwd_main_kernel<4, kFused>), grid, block, BwdShare<4>::kFixed + P.u_pad * 16, stream, P);
     else
-        hipLaunchKernelGGL((bwd_main_kernel<T, 2, kFused>), grid, block, BwdShare<2>::kFixed + P.u_pad * 16, stream, P);
+        hipLaunchKernelGGL((bwd_main_kernel<2, kFused>), grid, block, BwdShare<2>::kFixed + P.u_pad * 16, stream, P);
     const dim3 grid_r(dealt(P.u_pad / kBwdQ), heads);
-    if (P.dq_part && ks == 8) hipLaunchKernelGGL((bwd_dq_reduce_kernel<T, false>), grid_r, dim3(256), 0, stream, P);
-    else if (P.dq_part)       hipLaunchKernelGGL((bwd_dq_reduce_kernel<T, true>), grid_r, dim3(256), 0, stream, P);
+    if (P.dq_part && ks == 8) hipLaunchKernelGGL((bwd_dq_reduce_kernel<false>), grid_r, dim3(256), 0, stream, P);
+    else if (P.dq_part)       hipLaunchKernelGGL((bwd_dq_reduce_kernel<true>), grid_r, dim3(256), 0, stream, P);
     return hipGetLastError();
 }
 
@@ -1067,7 +1061,7 @@ hipError_t launch_backward(const psa_shape_t& s, const BwdPlan& bp, const void* 
     P.H = s.H; P.L = s.L_K; P.u_stride = u_stride; P.u_pad = bp.u_pad; P.n_group = bp.n_group;
     P.S1 = bp.S1; P.blocks1 = bp.blocks1; P.S2 = bp.S2; P.blocks2 = bp.blocks2;
     P.fill = fill; P.head_shift = (s.B * s.H) % 8 == 0 ? 3 : 0;
-    return launch_bwd_t<float>(P, s.B * s.H, wide ? 8 : bp.ks, wide ? bp.wide_S2 : bp.S2, stream);
+    return launch_bwd(P, s.B * s.H, wide ? 8 : bp.ks, wide ? bp.wide_S2 : bp.S2, stream);
 }
 
 }  // namespace psa
