@@ -31,8 +31,8 @@ constexpr int kF32SmemBytes = kF32Waves * kStateDoubles * 64 * 8;     // 73728: 
 
 // Record layout for float32 tensors, NQ = 16 * NCG queries:
 //   [ m[NQ] | l[NQ] as float64 | O / l as float32: rows [NQ][64] ]
-// Records go through to memory: a wave merges adjacent elements, so that a lane's store is 16 (8) bytes and the reader's load
-// of a row 256 contiguous bytes (single floats in the order of the accumulators: attend 19.8 -> 17.4 us at B=16 H=4 L=512).
+// Records go through to memory: a wave merges adjacent elements, so that a lane's stores are two of 8 bytes (one) side by side and the
+// reader's load of a row 256 contiguous bytes (single floats in the order of the accumulators: attend 19.8 -> 17.4 us at B=16 H=4 L=512).
 // DS > 1: heads in one key split whose work-groups leave compute units idle.  DS work-groups share a query group; each forms all
 // its scores, but of the second product only its 1/DS of the output elements, and writes those: nothing to hand over.
 // The work of one work-group; `smem`: kF32SmemBytes of LDS.

@@ -493,11 +493,11 @@ void bwd_dq_kernel(const BwdParams P)
 }
 
 // ---- dK and dV of blocks of 16 KS keys over all kept queries of the head, and dQ over those keys.
-// Wave w takes keys 16 (w % KS) .. + 15 of the block and, of the two query tiles of a group, both (KS = 4) or tile
+// Wave w takes keys 16 (w % KS) .. + 15 of the block and, of the two query tiles of a group, both (KS = 4, 8) or tile
 // w / 2 (KS = 2).  Scores are formed upright (queries on the rows), so that a lane's four p and g values are,
 // unchanged, the B operand of the products that contract over queries (dK, dV).  For dQ, which contracts over keys,
-// the waves put their g values into LDS; wave w then takes elements 16 w .. + 15 of both tiles over all keys of the
-// block, so that nothing has to be added up across waves.
+// the waves put their g values into LDS; wave w then takes, over all keys of the block, elements 16 (w % 4) .. + 15 of
+// both tiles, or of 8 waves of tile w / 4, so that nothing has to be added up across waves.
 // grid (key splits, heads), heads as above, blocks2 key blocks per work-group, which adds to the dQ it wrote for the block before.
 template <int KS, BwdForm FORM>
 __global__ __launch_bounds__(BwdShare<KS>::kThreads, 2)
@@ -601,7 +601,7 @@ void bwd_main_kernel(const BwdParams P)
             bwd_x2 old[DT][2];                                // what this very lane wrote of dQ for the block before
             int q_next = 0;
             bool stage_next = false;
-            // this wave's share of dQ, elements 16 wave .. + 15 of both tiles of group q0 (the A operand's rows are taken
+            // this wave's share of dQ, elements 16 we .. + 15 of tiles wt .. of group q0 (the A operand's rows are taken
             // in such an order that a lane's four values are elements e_own .. e_own + 3 of query c); two MFMA chains,
             // 16 keys at a time, the next 16 keys' operands read while these products run
             auto finish_group = [&](int q0) {
