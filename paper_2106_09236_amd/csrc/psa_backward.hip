@@ -31,7 +31,7 @@
 //     dQ), and cut the key axis so that their number fills whole rounds of the CUs;
 //   * keep a head's work-groups on one XCD where the heads divide evenly: each L2 fetches the rows of its own heads, not
 //     the kept rows of Q and G of all (the first product of a work-group waits for 11 us, not for 14.5).
-// Measured (whole call): B=16 H=4 L=512, 256 kept queries 225 -> 150 us, the last point 4 and the 8 waves 11 of them; B=8 H=8 L=300, 120 kept
+// Measured (whole call): B=16 H=4 L=512, 256 kept queries 225 -> 147 us, the last point 4 and the 8 waves 15 of them; B=8 H=8 L=300, 120 kept
 // 102.2 -> 97.5 by the last point, B=24 H=8 L=200, 100 kept 133.2 -> 129.2 us.
 #include <type_traits>
 
