@@ -337,7 +337,7 @@ def gpu_block(cfg, w, args, timer):
     kernels["attend"]["mfma_dtype"] = "f64" if cfg.dtype == "f32" else "bf16"
     # the measure stage is a gather: its second bound is what the CUs' vector-memory path can return
     # (every sampled key row crosses it once), beside the HBM bound of the compulsory bytes
-    if plan["measure"] == "stream":
+    if plan["measure"] == "stream" and plan["measure_parts"] == "0":
         gb = queries * cfg.U * 64 * (4 if cfg.dtype == "f32" else 2)
         tm = stage_us["measure"]["median"]
         kernels["measure"]["gather_bytes"] = gb

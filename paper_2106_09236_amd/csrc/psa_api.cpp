@@ -133,8 +133,26 @@ static int stream_cut_f32(const Plan& p)
     return cpw;
 }
 
+// Streamed heads whose K fits LDS in two parts: passes of 128 queries that a work-group of the measure kernel which gathers from
+// there takes, or 0 where the heads stay with the gather out of L2.  Its time hardly depends on the samples (8.4 us to start
+// with K and the first indices, 4 for each pass, 2.3 for the ranking; a gather out of L2 gives way with fewer samples: B=8 H=8
+// L=2048 bfloat16, whole call, with 39 samples 55.4 -> 48.4 us, with 28 48.1 | 48.1, with 12 40.4 | 47.8; B=16 H=4 L=750 float32 with 34
+// 49.5 -> 44.0, with 24 45.3 -> 43.8, with 16 42.5 | 43.9), so it takes calls with more than 28.  A CU holds one of its work-groups,
+// which K has to be copied for, so they have to fill more than half of the chip: float32 B=8 H=4 L=640 (96 work-groups) 36.1 | 36.6,
+// B=12 H=4 L=750 (144) 47.9 -> 43.7; bfloat16 B=2 H=8 L=2048 (128) 33.6 | 35.1, B=3 (192) 41.3 -> 35.6 us.
+// Four passes instead of two, bfloat16, where the whole ones of two take more than a round of an XCD's 32 CUs: B=8 H=8 L=2048 (64 of
+// them) 54.9 -> 48.4 us, B=12 H=8 L=1040 61.5 -> 56.8; but B=8 H=8 L=1040 (32, and 8 with 16 queries) 43.7 | 44.4, and 35.4 | 44.3
+// where lengths leave those empty.
+static int part_passes(const Plan& p, size_t k_bytes)
+{
+    const int heads = (p.BH + 7) / 8, span = kPartChunks * kMeasureQueries, groups = (p.L + span - 1) / span;
+    if (k_bytes > 2 * (size_t)kLdsMaxBytes || p.U <= kPartMinSamples || p.U > kPartMaxSamples || (int64_t)p.BH * groups <= 128) return 0;
+    const int whole = heads * (p.L / span + (p.L % span > span / 2 ? 1 : 0));
+    return p.dtype == PSA_F32 || whole <= 32 ? 2 : 4;
+}
+
 // How much of a plan is cut anew (see make_plan).
-enum Cuts { kFirstCuts = 0, kShortChunks = 1, kStreamCut = 2, kSplitCut = 3 };
+enum Cuts { kFirstCuts = 0, kShortChunks = 1, kStreamCut = 2, kSplitCut = 3, kPartCut = 4 };
 
 static void build_plan(const psa_shape_t* s, URule urule, int u_stride, Cuts cuts, Plan* p)
 {
@@ -242,6 +260,7 @@ static void build_plan(const psa_shape_t* s, URule urule, int u_stride, Cuts cut
         cpw = cpw < 1 ? 1 : (cpw > 16 ? 16 : cpw);
         p->chunks_per_wg = cpw < p->n_chunk ? cpw : p->n_chunk;
     }
+    p->part_passes = cuts >= kPartCut && !p->measure_lds && !p->given_indices ? part_passes(*p, k_bytes) : 0;
     // sorted per-chunk candidate lists: only with the LDS measure kernel (few chunks per head)
     p->cand_len = 0;
     if (p->measure_lds) {
@@ -253,9 +272,10 @@ static void build_plan(const psa_shape_t* s, URule urule, int u_stride, Cuts cut
     // Streamed heads: a work-group of the measure kernel ranks the queries of its own chunks and hands on its
     // best u as one sorted list, exactly as a chunk of the LDS kernel does (see stream_list_len)
     if (!p->measure_lds && !p->given_indices) {
-        const int len = stream_list_len(*p, p->chunks_per_wg, p->dtype == PSA_F32 && cuts >= kStreamCut ? kListMaxF32 : kListMax);
+        const int span = p->part_passes > 0 ? kPartChunks : p->chunks_per_wg;
+        const int len = stream_list_len(*p, span, p->dtype == PSA_F32 && cuts >= kStreamCut ? kListMaxF32 : kListMax);
         if (len > 0) {
-            p->cand_len = len; p->n_lists = (p->n_chunk + p->chunks_per_wg - 1) / p->chunks_per_wg; p->stream_lists = 1;
+            p->cand_len = len; p->n_lists = (p->n_chunk + span - 1) / span; p->stream_lists = 1;
         }
     }
     p->n_seg = 0;
@@ -290,7 +310,7 @@ static void build_plan(const psa_shape_t* s, URule urule, int u_stride, Cuts cut
     p->part_elem = p->dtype == PSA_F32 ? sizeof(double) : sizeof(float);
     size_t off = 0;
     p->off_M = off;      off += align256((size_t)p->BH * p->L * sizeof(float));
-    p->off_vpart = off;  off += align256((size_t)p->BH * p->n_chunk * kD * sizeof(double));
+    p->off_vpart = off;  off += p->part_passes > 0 && p->stream_lists ? 0 /* the lists bring their own sums */ : align256((size_t)p->BH * p->n_chunk * kD * sizeof(double));
     p->off_vseg = off;   off += align256((size_t)p->BH * (p->stream_lists ? p->n_lists : p->n_seg) * kD * sizeof(double));
     p->off_mu = off;     off += align256((size_t)p->BH * kD * sizeof(float));
     p->off_sel = off;    off += align256((size_t)p->BH * p->u_max * sizeof(int));
@@ -313,7 +333,7 @@ bool make_plan(const psa_shape_t* s, URule urule, int u_stride, Plan* p)
     if (u_stride < 0 || u_stride > s->L_K) return false;
     build_plan(s, urule, u_stride, kFirstCuts, p);
     const size_t size = p->total;
-    for (int cuts = kSplitCut; cuts >= kShortChunks; --cuts) {
+    for (int cuts = kPartCut; cuts >= kShortChunks; --cuts) {
         build_plan(s, urule, u_stride, (Cuts)cuts, p);
         if (p->total <= size) break;
     }
@@ -694,7 +714,7 @@ int probsparse_describe_plan(const psa_shape_t* shape, const psa_options_t* opt,
     if (n < 0 || (size_t)n >= buf_bytes) return PSA_ERR_ARG;
     // the rest where there is room for it: the module's projections, and the backward for index sets of this stride
     char more[320];
-    int m = snprintf(more, sizeof(more), " element_shares=%d qkv_project=%s out_project=%s", p.d_split, project_route_name(*shape, 3),
+    int m = snprintf(more, sizeof(more), " element_shares=%d measure_parts=%d qkv_project=%s out_project=%s", p.d_split, p.part_passes, project_route_name(*shape, 3),
                      project_route_name(*shape, 1));
     if (u_stride > 0) {
         const BwdPlan bp = make_bwd_plan(*shape, u_stride);

@@ -85,6 +85,18 @@ __device__ __forceinline__ float max_xor16(float x) {
     return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
 
+// Sum of x and its value in the lane 32 (16) away, in every lane, the same way
+__device__ __forceinline__ double sum_xor32(double x) {
+    const auto lo = __builtin_amdgcn_permlane32_swap(__double2loint(x), __double2loint(x), false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap(__double2hiint(x), __double2hiint(x), false, false);
+    return __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
+}
+__device__ __forceinline__ double sum_xor16(double x) {
+    const auto lo = __builtin_amdgcn_permlane16_swap(__double2loint(x), __double2loint(x), false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap(__double2hiint(x), __double2hiint(x), false, false);
+    return __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
+}
+
 // 2^x in float64 for x <= ~0 (anything below -1000, -inf included, gives 0; NaN stays NaN):
 // x = n + f with |f| <= 1/2 by adding and taking away 1.5 * 2^52, 2^f by the polynomial of degree 6 with
 // constant term 1 whose largest relative error on [-1/2, 1/2] is least (2.0e-9; 2^0 is exactly 1; the softmax weights need 1e-6, see

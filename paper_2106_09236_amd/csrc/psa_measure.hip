@@ -96,6 +96,70 @@ __device__ __forceinline__ void block_v_colsum(const T* __restrict__ Vh, int r0,
     v_colsum_finish<NT>(out64, s_red);
 }
 
+// Local ranking for stage a2: any query among the head's u largest is among the u largest of the n_ch chunks (1 .. RMAX / 64)
+// of 64 queries that start at query q0, so they hand on their first cand_len queries in order of decreasing measure (ties:
+// lower index first) as (order key, query index) pairs.  s_rank: an entry (order key, ~position) per query, 0 for none; the
+// caller has put a barrier behind it.  Two steps: every chunk ranks its own keys (two lanes per key, 32 comparisons each)
+// into a sorted list in LDS; then the lists are merged, the position of an entry being its own rank plus, per
+// other list, the number of entries before it (a binary search per list, four lanes per entry).  Ranking all 256 keys
+// against each other took 3 us at the end of every work-group; this takes under one.
+template <int NT, int RMAX>
+__device__ __forceinline__ void rank_chunks(const unsigned long long* s_rank, unsigned long long* s_list, int n_ch, int q0, int n,
+                                            uint2* __restrict__ cand_out, int cand_len)
+{
+    static_assert(2 * RMAX <= NT && RMAX <= 5 * kMeasureQueries, "two lanes per query, at most five lists");
+    const int tid = threadIdx.x;
+    const int n_pos = n_ch * kMeasureQueries;
+    const int n_here = n - q0 < n_pos ? n - q0 : n_pos;              // valid queries
+    const int keep = cand_len < kMeasureQueries ? cand_len : kMeasureQueries;    // entries a chunk's list can contribute
+    {
+        const int h2 = tid & 1, pos = tid >> 1;                      // two lanes per position
+        const bool ok = tid < 2 * RMAX && pos < n_pos;
+        const unsigned long long mine = s_rank[ok ? pos : 0];
+        const unsigned long long* row = s_rank + (ok ? pos & ~(kMeasureQueries - 1) : 0);
+        int beat = 0;
+#pragma unroll 8
+        for (int t = 0; t < kMeasureQueries / 2; ++t) beat += row[2 * t + h2] > mine ? 1 : 0;
+        beat += __builtin_amdgcn_update_dpp(0, beat, 0xB1, 0xF, 0xF, false);             // sum over the pair
+        for (int t = tid; t < n_pos; t += NT) s_list[t] = 0ull;
+        lds_barrier();
+        if (ok && h2 == 0 && beat < keep) s_list[(pos / kMeasureQueries) * kMeasureQueries + beat] = mine;
+        lds_barrier();
+    }
+    // merge: entry ci = (list, rank) -> position among all lists; keys are unique (they carry their position)
+    for (int t0 = 0; t0 < n_ch * keep * 4; t0 += NT) {               // work-group-uniform trip count
+        const int t = t0 + tid;
+        const int ci = t >> 2, c2 = t & 3;
+        const int lst = ci / keep, rk = ci - lst * keep;
+        const bool ok = ci < n_ch * keep;
+        const unsigned long long mine = ok ? s_list[lst * kMeasureQueries + rk] : 0ull;
+        auto before = [&](int list) -> int {                         // entries of a list that come before mine
+            if (list == lst) return rk;
+            const unsigned long long* other = s_list + list * kMeasureQueries;
+            int lo = 0, hi = keep;
+            while (lo < hi) { const int mid = (lo + hi) >> 1; if (other[mid] > mine) lo = mid + 1; else hi = mid; }
+            return lo;
+        };
+        int cnt = ok && c2 < n_ch ? before(c2) : 0;
+        if (RMAX > 4 * kMeasureQueries && ok && c2 == 0 && n_ch > 4) cnt += before(4);
+        cnt += __builtin_amdgcn_update_dpp(0, cnt, 0xB1, 0xF, 0xF, false);               // sum over the quad
+        cnt += __builtin_amdgcn_update_dpp(0, cnt, 0x4E, 0xF, 0xF, false);
+        if (ok && c2 == 0 && (unsigned)(mine >> 32) != 0u && cnt < cand_len) {
+            const int pos = (int)~(unsigned)mine;                    // the key's low word is ~position
+            cand_out[cnt] = make_uint2((unsigned)(mine >> 32), (unsigned)(q0 + pos));
+        }
+    }
+    for (int t = n_here + tid; t < cand_len; t += NT) cand_out[t] = make_uint2(0u, 0xFFFFFFFFu);     // empty slots
+}
+
+// (order key, ~position) of a measure: -0 -> +0; larger measure = larger key; 0 = not a candidate; of equal keys the
+// lower position is the larger
+__device__ __forceinline__ unsigned long long rank_entry(float m, int pos) {
+    const unsigned ub = __float_as_uint(m + 0.0f);
+    const unsigned key = (ub & 0x80000000u) ? ~ub : (ub | 0x80000000u);
+    return ((unsigned long long)key << 32) | (unsigned)~pos;
+}
+
 constexpr int kStreamThreads = 512;
 constexpr int kQueriesPerWave = 8;
 static_assert(kMeasureQueries == (kStreamThreads / 64) * kQueriesPerWave, "one query per 8 lanes, eight waves");
@@ -661,12 +725,8 @@ void measure_pipe_kernel(const T* __restrict__ Q, const T* __restrict__ K, const
             if (active && cnt > 0) m = (mx - sm / (float)cnt) * 0.125f;     // 1/sqrt(64), exact
             M[(size_t)head * L + i] = m;
             if (cand_out && active) {
-                // order key of the measure (-0 -> +0; larger measure = larger key; 0 = not a candidate);
-                // equal keys: the lower query is the larger
-                const unsigned ub = __float_as_uint(m + 0.0f);
-                const unsigned key = (ub & 0x80000000u) ? ~ub : (ub | 0x80000000u);
                 const int pos = (chunk - chunk0) * kMeasureQueries + ql;
-                s_rank[pos] = ((unsigned long long)key << 32) | (unsigned)~pos;
+                s_rank[pos] = rank_entry(m, pos);
             }
         }
     };
@@ -699,58 +759,9 @@ void measure_pipe_kernel(const T* __restrict__ Q, const T* __restrict__ K, const
 
     }
     PSA_TS(2);
-    // ---- local ranking for stage a2 (as in the LDS kernel): any query among the head's u largest is among
-    // this work-group's u largest, so it hands on its first cand_len queries in order of decreasing measure
-    // (ties: lower index first) as (order key, query index) pairs.  The last barrier of the loop has made
-    // every gather wave's keys visible.  Two steps: every chunk of 64 ranks its own keys (two lanes per key,
-    // 32 comparisons each) into a sorted list in LDS; then the up to 4 (float32: 5) lists are merged, the position of an
-    // entry being its own rank plus, per other list, the number of entries before it (a binary search per
-    // list, four lanes per entry).  Ranking all 256 keys against each other took 3 us at the end of every
-    // work-group; this takes under one.
+    // ---- local ranking for stage a2; the last barrier of the loop has made every gather wave's keys visible
     if (cand_out) {
-        const int n_ch = chunk_end - chunk0;                         // chunks in use: 1 .. RMAX / 64
-        const int n_pos = n_ch * kMeasureQueries;
-        int n_here = n - chunk0 * kMeasureQueries;                   // valid queries of this work-group
-        n_here = n_here < n_pos ? n_here : n_pos;
-        const int keep = cand_len < kMeasureQueries ? cand_len : kMeasureQueries;    // entries a chunk's list can contribute
-        {
-            const int h2 = tid & 1, pos = tid >> 1;                  // two lanes per position
-            const bool ok = tid < 2 * RMAX && pos < n_pos;
-            const unsigned long long mine = s_rank[ok ? pos : 0];
-            const unsigned long long* row = s_rank + (ok ? pos & ~(kMeasureQueries - 1) : 0);
-            int beat = 0;
-#pragma unroll 8
-            for (int t = 0; t < kMeasureQueries / 2; ++t) beat += row[2 * t + h2] > mine ? 1 : 0;
-            beat += __builtin_amdgcn_update_dpp(0, beat, 0xB1, 0xF, 0xF, false);             // sum over the pair
-            for (int t = tid; t < n_ch * kMeasureQueries; t += kPipeThreads) s_list[t] = 0ull;
-            lds_barrier();
-            if (ok && h2 == 0 && beat < keep) s_list[(pos / kMeasureQueries) * kMeasureQueries + beat] = mine;
-            lds_barrier();
-        }
-        // merge: entry ci = (list, rank) -> position among all lists; keys are unique (they carry their position)
-        for (int t0 = 0; t0 < n_ch * keep * 4; t0 += kPipeThreads) { // work-group-uniform trip count
-            const int t = t0 + tid;
-            const int ci = t >> 2, c2 = t & 3;
-            const int lst = ci / keep, rk = ci - lst * keep;
-            const bool ok = ci < n_ch * keep;
-            const unsigned long long mine = ok ? s_list[lst * kMeasureQueries + rk] : 0ull;
-            auto before = [&](int list) -> int {                     // entries of a list that come before mine
-                if (list == lst) return rk;
-                const unsigned long long* other = s_list + list * kMeasureQueries;
-                int lo = 0, hi = keep;
-                while (lo < hi) { const int mid = (lo + hi) >> 1; if (other[mid] > mine) lo = mid + 1; else hi = mid; }
-                return lo;
-            };
-            int cnt = ok && c2 < n_ch ? before(c2) : 0;
-            if (RMAX > 4 * kMeasureQueries && ok && c2 == 0 && n_ch > 4) cnt += before(4);
-            cnt += __builtin_amdgcn_update_dpp(0, cnt, 0xB1, 0xF, 0xF, false);               // sum over the quad
-            cnt += __builtin_amdgcn_update_dpp(0, cnt, 0x4E, 0xF, 0xF, false);
-            if (ok && c2 == 0 && (unsigned)(mine >> 32) != 0u && cnt < cand_len) {
-                const int pos = (int)~(unsigned)mine;                // the key's low word is ~position
-                cand_out[cnt] = make_uint2((unsigned)(mine >> 32), (unsigned)(chunk0 * kMeasureQueries + pos));
-            }
-        }
-        for (int t = n_here + tid; t < cand_len; t += kPipeThreads) cand_out[t] = make_uint2(0u, 0xFFFFFFFFu);   // empty slots
+        rank_chunks<kPipeThreads, RMAX>(s_rank, s_list, chunk_end - chunk0, chunk0 * kMeasureQueries, n, cand_out, cand_len);
         if (tid < kD) vlist_out[tid] = s_vtot[tid];                  // (written by the loader wave before the last barrier)
     }
     PSA_TS(3);
@@ -761,6 +772,353 @@ void measure_pipe_kernel(const T* __restrict__ Q, const T* __restrict__ K, const
 template <int T4>                                          // value of lane T4 of the quad, in all four lanes
 __device__ __forceinline__ int quad_bcast(int x) {
     return __builtin_amdgcn_update_dpp(0, x, T4 * 0x55, 0xF, 0xF, false);
+}
+
+// -----------------------------------------------------------------------------
+// Heads whose K fits LDS in two parts (float32 512 < L <= 1024, bfloat16 1024 < L <= 2048): a gather from LDS in two
+// steps.  A part is 32 of the 64 elements of every key row, so that every sample needs both parts and both steps cost
+// the same: the scores of the work-group's queries (128 for each of NPASS passes; a quad of lanes per query, 8 waves) are
+// formed to half from the first part, the other part replaces it, and the halves are added.
+//   * What bounds such a work-group is not the gather but what feeds it: the return path serves a line per two cycles,
+//     whatever is used of it, so that parts of key rows and index entries fetched as the quads use them took 20 of 49 us.
+//     K therefore crosses it once, in whole rows: half of the lanes load an even piece and then an odd one, the others the
+//     other way round, so that every lane has as much of the first part, which goes to LDS, as of the second, which waits
+//     in registers.  The sample indices of a wave's 16 queries come as they lie in memory, one pass ahead, and reach the quads
+//     through a stage of the wave's own in LDS (per-lane loads: 40 us instead of 33 for the kernel at B=8 H=8 L=2048).
+//   * Lane s of a quad ends up with the scores of the samples 4 k + s (a transposing exchange, 9 instructions for 4 samples), so the
+//     maximum and the sum run over at most 10 registers.
+//   * A round's rows are requested while the round before is multiplied; 8 waves with 256 registers each and this overlap
+//     do as well as 16 waves with 128, which spill.  LDS reads (two quads at a time: float32 parts, 128 bytes, are read in
+//     pieces that quads take in alternating order and never meet on a bank; bfloat16 parts, 64 bytes, of two random rows meet
+//     once in four) and the issue of vector instructions are about level: rows that meet on a bank always cost 15 %, and
+//     sample orders that save the exchange's selections at the price of bank conflicts nothing either way.
+//   * Ranking for stage a2 with a wave per chunk of 64 queries.
+// B=8 H=8 L=2048 bfloat16, 39 samples: 36 -> 28 us against the gather out of L2; B=16 H=4 L=750 float32, 34: 26 -> 20 us.
+// -----------------------------------------------------------------------------
+constexpr int kPartThreads = 512;
+constexpr int kPartQueries = kPartThreads / 4;                       // of a pass
+constexpr int kPartStage = (16 * kPartMaxSamples * 4 + 1023) / 1024 * 1024;      // bytes of the sample indices of a wave's 16 queries
+
+// KT: 16-byte pieces of K per thread (24 or 32: 192 or 256 KB, half of which is in LDS)
+// NR: sample rounds of a quad, U <= 4 NR (a constant, since a branch between two rounds keeps the compiler from requesting one ahead)
+template <typename T, int KT, int NPASS, int NR>
+__global__ __launch_bounds__(kPartThreads)
+void measure_parts_kernel(const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V,
+                          const int* __restrict__ lengths, const int* __restrict__ idx,
+                          float* __restrict__ M, double* __restrict__ vpart, int* __restrict__ ticket,
+                          uint2* __restrict__ cand, int cand_len, double* __restrict__ vlist,
+                          int H, int L, int U, int chunks_per_head, int n_heads)
+{
+    using RT = RowTraits<T>;
+    using Vec = typename std::conditional<sizeof(T) == 4, float4, uint4>::type;
+    using VVec = typename std::conditional<sizeof(T) == 4, float4, uint2>::type;           // 4 elements of V
+    constexpr int PB = RT::kRowBytes / 2;                // bytes of a row's part
+    constexpr int NP = PB / 64;                          // 16-byte pieces per lane and part: 2 (float32) or 1
+    constexpr int LPR = RT::kRowBytes / 16;              // lanes per row of K
+    constexpr int RPL = kPartThreads / LPR;              // rows that a load of all threads covers
+    constexpr int kChunks = NPASS * kPartQueries / kMeasureQueries;      // of this work-group
+    constexpr int kRank = NPASS * kPartQueries;
+    extern __shared__ __attribute__((aligned(16))) unsigned char sK[];                     // [rows][PB]
+    __shared__ __attribute__((aligned(16))) unsigned char s_idx[kPartThreads / 64][kPartStage];      // sample indices, a stage to a wave
+    // once the gather is over, in the place of K
+    double (*s_red)[kPartThreads / 64][kD] = reinterpret_cast<double (*)[kPartThreads / 64][kD]>(sK);          // [NPASS]
+    unsigned long long* s_rank = reinterpret_cast<unsigned long long*>(sK + sizeof(double) * NPASS * (kPartThreads / 64) * kD);
+    unsigned long long* s_list = s_rank + kRank;
+
+    // all work-groups of a head on one XCD; the last groups of all heads come last
+    const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3, head_rounds = (n_heads + 7) >> 3;
+    const int group = slot / head_rounds;
+    const int head = (slot - group * head_rounds) * 8 + xcd;
+    const int chunk0 = group * kChunks;
+    if (head >= n_heads) return;                  // grid is padded to a multiple of 8 heads (work-group-uniform)
+    int chunk_end = chunk0 + kChunks;
+    chunk_end = chunk_end < chunks_per_head ? chunk_end : chunks_per_head;
+    const int n = valid_len(lengths, head / H, L);
+    const int tid = threadIdx.x;
+    const int lane = tid & 63, wave = tid >> 6;
+    const int s = lane & 3;
+    if (chunk0 == 0 && tid == 0) ticket[head] = 0;                   // the attend stage counts work-groups per head
+
+    // chunks that are padding as a whole
+    const int first_pad = (n + kMeasureQueries - 1) / kMeasureQueries;
+    for (int chunk = (chunk0 > first_pad ? chunk0 : first_pad); chunk < chunk_end; ++chunk) {
+        const int i = chunk * kMeasureQueries + tid;
+        if (tid < kMeasureQueries && i < L) M[(size_t)head * L + i] = 0.f;
+        if (!cand && tid < kD) vpart[((size_t)head * chunks_per_head + chunk) * kD + tid] = 0.0;
+    }
+    const int lists_per_head = (chunks_per_head + kPartChunks - 1) / kPartChunks;
+    const int list0 = chunk0 / kPartChunks;
+    const int lists_here = (chunk_end - chunk0 + kPartChunks - 1) / kPartChunks;
+    uint2* cand_out = cand ? cand + ((size_t)head * lists_per_head + list0) * cand_len : nullptr;
+    double* vlist_out = cand ? vlist + ((size_t)head * lists_per_head + list0) * kD : nullptr;
+    const int here = (chunk_end < first_pad ? chunk_end : first_pad) - chunk0;             // chunks with a valid query
+    if (here <= 0) {                                                 // work-group-uniform: empty lists
+        if (cand) {
+            for (int t = tid; t < lists_here * cand_len; t += kPartThreads) cand_out[t] = make_uint2(0u, 0xFFFFFFFFu);
+            for (int t = tid; t < lists_here * kD; t += kPartThreads) vlist_out[t] = 0.0;
+        }
+        return;
+    }
+    // n > 0 from here on
+
+    // the head's valid rows as raw buffers: offsets at or beyond n rows read zeros
+    auto rows_of = [&](const T* base) {
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(base + (size_t)head * L * kD), 0, n * RT::kRowBytes, 0x00020000);
+    };
+    const __amdgpu_buffer_rsrc_t krsrc = rows_of(K), qrsrc = rows_of(Q), vrsrc = rows_of(V);
+    const __amdgpu_buffer_rsrc_t irsrc = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<int*>(idx + (size_t)head * L * U), 0, L * U * 4, 0x00020000);
+    const int q0 = chunk0 * kMeasureQueries;
+    const int ql = tid >> 2;                                         // query within a pass
+    const int qrot = (lane >> 2) & (NP - 1);                         // quads take the pieces in alternating order
+    auto piece_ofs = [&](int v) { return 64 * ((v + qrot) & (NP - 1)) + 16 * s; };
+
+    // ---- what a pass needs of its queries, one pass ahead: the sample indices of the wave's 16 queries (as they lie in memory)
+    // and the lane's pieces of a part of its query's row
+    uint4 in[kPartStage / 1024];
+    Vec qn[NP];
+    auto load_query = [&](int a, int part, bool indices) {
+        const int i = q0 + a * kPartQueries + ql;
+        if (indices)
+#pragma unroll
+            for (int k = 0; k < kPartStage / 1024; ++k)              // (reads past the head's indices give 0)
+                in[k] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(
+                            irsrc, (q0 + a * kPartQueries + 16 * wave) * U * 4 + 16 * lane, 1024 * k, kStreamOnce));
+#pragma unroll
+        for (int v = 0; v < NP; ++v)
+            qn[v] = __builtin_bit_cast(Vec, __builtin_amdgcn_raw_buffer_load_b128(qrsrc, i * RT::kRowBytes + piece_ofs(v), part * PB, kStreamOnce));
+    };
+    load_query(0, 0, true);
+    const int krow = tid / LPR, kcol = tid % LPR;
+    const bool odd_half = kcol >= LPR / 2;
+    Vec kv[KT];
+    {
+        const int even = krow * RT::kRowBytes + 16 * kcol, odd = (krow ^ 1) * RT::kRowBytes + 16 * (kcol ^ (LPR / 2));
+#pragma unroll
+        for (int k = 0; k < KT; ++k)
+            kv[k] = __builtin_bit_cast(Vec, __builtin_amdgcn_raw_buffer_load_b128(krsrc, k & 1 ? odd : even, k * RPL * RT::kRowBytes, 0));
+    }
+    PSA_TS(0);
+    // lane s of a quad: the samples 4 k + s, as byte offsets into a part; bit k of `usable`: that of round k counts
+    int jofs[NR];
+    Vec q[NP];
+    unsigned usable = 0;
+    const int own = (U - s + 3) >> 2;                                // rounds in which this lane has a sample: 0 .. NR
+    auto take_indices = [&](int a) {
+        usable = 0;
+        wave_lds_sync();
+#pragma unroll
+        for (int k = 0; k < kPartStage / 1024; ++k) *reinterpret_cast<uint4*>(&s_idx[wave][1024 * k + 16 * lane]) = in[k];
+        wave_lds_sync();
+        const int* row = reinterpret_cast<const int*>(s_idx[wave]) + (lane >> 2) * U + s;
+#pragma unroll
+        for (int k = 0; k < NR; ++k) {                               // (entries at or beyond U belong to the next row, or to none)
+            const int j = row[4 * k];
+            const bool ok = (unsigned)j < (unsigned)n;
+            jofs[k] = ok ? j * PB : 0;
+            usable |= ok ? 1u << k : 0u;
+        }
+        usable &= q0 + a * kPartQueries + ql < n ? (1u << own) - 1u : 0u;
+    };
+    auto take_row = [&]() {
+#pragma unroll
+        for (int v = 0; v < NP; ++v) q[v] = qn[v];
+    };
+    // ---- the first part of K -> LDS; the second stays in the even registers
+    const int lds0 = (krow ^ (odd_half ? 1 : 0)) * PB + (odd_half ? RPL * PB : 0) + 16 * (kcol % (LPR / 2));
+    const int lds1 = (krow ^ (odd_half ? 0 : 1)) * PB + (odd_half ? 0 : RPL * PB) + 16 * (kcol % (LPR / 2));
+    auto pick = [](bool c, const Vec& x, const Vec& y) {
+        Vec r;
+        r.x = c ? x.x : y.x; r.y = c ? x.y : y.y; r.z = c ? x.z : y.z; r.w = c ? x.w : y.w;
+        return r;
+    };
+#pragma unroll
+    for (int k = 0; k < KT; k += 2) {
+        *reinterpret_cast<Vec*>(sK + lds0 + k * RPL * PB) = pick(odd_half, kv[k + 1], kv[k]);
+        kv[k] = pick(odd_half, kv[k], kv[k + 1]);
+    }
+    PSA_TS(1);
+    lds_barrier();
+    PSA_TS(2);
+
+    float score[NPASS][NR];
+    auto gather = [&](float (&sc)[NR], auto second) {
+        Vec kr[2][4][NP];
+        auto request = [&](int k) {
+            int jk;
+            asm volatile("" : "=v"(jk) : "0"(jofs[k]));              // (else the addresses of a last pass's rounds are kept for its second step)
+            const int j[4] = {quad_bcast<0>(jk), quad_bcast<1>(jk), quad_bcast<2>(jk), quad_bcast<3>(jk)};
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+#pragma unroll
+                for (int v = 0; v < NP; ++v) kr[k & 1][t][v] = *reinterpret_cast<const Vec*>(sK + (uint32_t)(j[t] + piece_ofs(v)));
+        };
+        request(0);
+#pragma unroll
+        for (int k = 0; k < NR; ++k) {
+            if (k + 1 < NR) request(k + 1);
+            __builtin_amdgcn_sched_barrier(0);
+            float d[4];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                float x = 0.f;
+#pragma unroll
+                for (int v = 0; v < NP; ++v) {
+                    const Vec r = kr[k & 1][t][v];
+                    if constexpr (sizeof(T) == 4) {
+                        x = fmaf(q[v].x, r.x, x); x = fmaf(q[v].y, r.y, x); x = fmaf(q[v].z, r.z, x); x = fmaf(q[v].w, r.w, x);
+                    } else {
+                        x = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, q[v].x), __builtin_bit_cast(bf16x2, r.x), x, false);
+                        x = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, q[v].y), __builtin_bit_cast(bf16x2, r.y), x, false);
+                        x = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, q[v].z), __builtin_bit_cast(bf16x2, r.z), x, false);
+                        x = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, q[v].w), __builtin_bit_cast(bf16x2, r.w), x, false);
+                    }
+                }
+                d[t] = x;
+            }
+            // lane s gets the quad's sum of d[s]
+            const bool b0 = s & 1, b1 = s & 2;
+            const float r01 = (b0 ? d[1] : d[0]) + dpp_mov<0xB1>(b0 ? d[0] : d[1]);
+            const float r23 = (b0 ? d[3] : d[2]) + dpp_mov<0xB1>(b0 ? d[2] : d[3]);
+            const float r = (b1 ? r23 : r01) + dpp_mov<0x4E>(b1 ? r01 : r23);
+            sc[k] = decltype(second)::value ? sc[k] + r : r;
+        }
+    };
+    // (a wave whose 16 queries of a pass are all padding has nothing to gather)
+    auto wave_active = [&](int a) { return q0 + a * kPartQueries + 16 * wave < n; };
+    // ---- first step, the passes in order: part 0
+#pragma unroll
+    for (int a = 0; a < NPASS; ++a) {
+        take_indices(a);
+        take_row();
+        if (a + 1 < NPASS) load_query(a + 1, 0, true); else load_query(a, 1, false);
+        if (wave_active(a)) gather(score[a], std::false_type{});
+    }
+    PSA_TS(3);
+    lds_barrier();                                                   // every wave is done with the first part
+#pragma unroll
+    for (int k = 0; k < KT; k += 2) *reinterpret_cast<Vec*>(sK + lds1 + k * RPL * PB) = kv[k];
+    lds_barrier();
+    PSA_TS(4);
+    double vsum[NPASS][4];
+    float meas[NPASS];
+    // ---- second step, the passes in reverse (the last one's indices are there): part 1, the measure, and the column sums of V
+#pragma unroll
+    for (int a = NPASS - 1; a >= 0; --a) {
+        if (a + 1 < NPASS) take_indices(a);
+        take_row();
+        VVec vv[4];                                                  // 16 V rows per wave, 16 lanes to a row
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int ofs = (q0 + a * kPartQueries + 16 * wave + 4 * k + (lane >> 4)) * RT::kRowBytes + (int)sizeof(VVec) * (lane & 15);
+            if constexpr (sizeof(T) == 4) vv[k] = __builtin_bit_cast(VVec, __builtin_amdgcn_raw_buffer_load_b128(vrsrc, ofs, 0, kStreamOnce));
+            else                          vv[k] = __builtin_bit_cast(VVec, __builtin_amdgcn_raw_buffer_load_b64(vrsrc, ofs, 0, kStreamOnce));
+        }
+        if (a > 0) load_query(a - 1, 1, true);
+        if (wave_active(a)) gather(score[a], std::true_type{});
+
+        float mx = -INFINITY, sm = 0.f;
+#pragma unroll
+        for (int k = 0; k < NR; ++k) {
+            const bool ok = usable >> k & 1;
+            mx = ok ? fmaxf(mx, score[a][k]) : mx;
+            sm += ok ? score[a][k] : 0.f;
+        }
+        int cnt = __popc(usable);
+        mx = fmaxf(mx, dpp_mov<0xB1>(mx)); sm += dpp_mov<0xB1>(sm); cnt += __builtin_amdgcn_update_dpp(0, cnt, 0xB1, 0xF, 0xF, false);
+        mx = fmaxf(mx, dpp_mov<0x4E>(mx)); sm += dpp_mov<0x4E>(sm); cnt += __builtin_amdgcn_update_dpp(0, cnt, 0x4E, 0xF, 0xF, false);
+        meas[a] = cnt > 0 ? (mx - sm / (float)cnt) * 0.125f : 0.f;                         // 1/sqrt(64), exact
+        const int i = q0 + a * kPartQueries + ql;
+        if (s == 0 && i < L) M[(size_t)head * L + i] = meas[a];
+        double (&acc)[4] = vsum[a];
+        acc[0] = acc[1] = acc[2] = acc[3] = 0.0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            if constexpr (sizeof(T) == 4) {
+                acc[0] += (double)vv[k].x; acc[1] += (double)vv[k].y; acc[2] += (double)vv[k].z; acc[3] += (double)vv[k].w;
+            } else {
+                acc[0] += (double)bf16_lo(vv[k].x); acc[1] += (double)bf16_hi(vv[k].x);
+                acc[2] += (double)bf16_lo(vv[k].y); acc[3] += (double)bf16_hi(vv[k].y);
+            }
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[e] = sum_xor32(sum_xor16(acc[e]));
+    }
+    PSA_TS(5);
+    lds_barrier();                                                   // every wave is done with K
+#pragma unroll
+    for (int a = 0; a < NPASS; ++a) {
+        const int pos = a * kPartQueries + ql;
+        if (s == 0) s_rank[pos] = q0 + pos < n ? rank_entry(meas[a], pos) : 0ull;
+        if (lane < 16) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) s_red[a][wave][4 * lane + e] = vsum[a][e];
+        }
+    }
+    lds_barrier();
+    PSA_TS(6);
+    // ... the four waves of a chunk in order, a chunk to a wave, or all chunks of a list
+    auto chunk_sum = [&](int c) {
+        double t = 0.0;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) t += s_red[c >> 1][4 * (c & 1) + w][lane];
+        return t;
+    };
+    if (!cand) {                                                     // (a list's sum stands for those of its chunks)
+        if (wave < here) vpart[((size_t)head * chunks_per_head + chunk0 + wave) * kD + lane] = chunk_sum(wave);
+        return;
+    }
+    if (wave >= kPartThreads / 64 - lists_here) {
+        const int l = kPartThreads / 64 - 1 - wave;
+        double t = 0.0;
+        for (int c = 4 * l; c < 4 * l + 4 && c < here; ++c) t += chunk_sum(c);
+        vlist_out[l * kD + lane] = t;
+    }
+
+    // ---- ranking for stage a2, a chunk to a wave, a query to a lane: the sorted list of each chunk ...
+    const int keep = cand_len < kMeasureQueries ? cand_len : kMeasureQueries;              // entries a chunk's list can contribute
+    unsigned long long mine = 0ull;
+    if (wave < here) {
+        const unsigned long long* row = s_rank + wave * kMeasureQueries;
+        mine = row[lane];
+        int beat = 0;
+#pragma unroll 16
+        for (int t = 0; t < kMeasureQueries; ++t) beat += row[t] > mine ? 1 : 0;
+        // keys are unique (they carry their position), but for a last chunk's positions without a query: those rank as they lie
+        s_list[wave * kMeasureQueries + (mine != 0ull ? beat : lane)] = mine;
+    }
+    lds_barrier();
+    // ... and the merge of a list's four: the position of an entry is its own rank plus, per other chunk, the entries before it,
+    // counted by three binary searches side by side (one after the other, four lanes to an entry, took 2000 cycles more)
+    if (wave < here && lane < keep) {
+        mine = s_list[wave * kMeasureQueries + lane];
+        int pos[3] = {0, 0, 0};
+        const unsigned long long* other[3];
+        bool there[3];
+#pragma unroll
+        for (int o = 0; o < 3; ++o) {
+            const int c = (wave & ~3) + ((wave + 1 + o) & 3);
+            there[o] = c < here;
+            other[o] = s_list + (there[o] ? c : wave) * kMeasureQueries;
+        }
+#pragma unroll
+        for (int step = kMeasureQueries / 2; step >= 1; step >>= 1)
+#pragma unroll
+            for (int o = 0; o < 3; ++o) pos[o] += other[o][pos[o] + step - 1] > mine ? step : 0;
+#pragma unroll
+        for (int o = 0; o < 3; ++o) pos[o] += other[o][pos[o]] > mine ? 1 : 0;             // (the 64th entry)
+        const int at = lane + (there[0] ? pos[0] : 0) + (there[1] ? pos[1] : 0) + (there[2] ? pos[2] : 0);
+        if ((unsigned)(mine >> 32) != 0u && at < cand_len) {
+            const int p = (int)~(unsigned)mine;                      // the key's low word is ~position
+            cand_out[(wave >> 2) * cand_len + at] = make_uint2((unsigned)(mine >> 32), (unsigned)(q0 + p));
+        }
+    }
+    for (int l = 0; l < lists_here; ++l) {                           // empty slots
+        int n_here = n - q0 - l * kPartChunks * kMeasureQueries;
+        n_here = n_here < 0 ? 0 : n_here;
+        for (int t = n_here + tid; t < cand_len; t += kPartThreads) cand_out[l * cand_len + t] = make_uint2(0u, 0xFFFFFFFFu);
+    }
+    PSA_TS(7);
 }
 
 // -----------------------------------------------------------------------------
@@ -1129,9 +1487,23 @@ static hipError_t raise_pipe_limit()
     static std::atomic<uint64_t> raised;               // per instantiation: devices already served
     return ensure_lds_limit((const void*)measure_pipe_kernel<T>, 2 * pipe_stage_bytes<T>(kPipeMaxU), raised);
 }
+template <typename T>
+static hipError_t raise_parts_limit()
+{
+    static std::atomic<uint64_t> raised[5];            // per instantiation: devices already served
+    hipError_t e = ensure_lds_limit((const void*)measure_parts_kernel<T, 24, 2, 9>, 24 * 8 * kPartThreads, raised[0]);
+    if (e == hipSuccess) e = ensure_lds_limit((const void*)measure_parts_kernel<T, 32, 2, 9>, 32 * 8 * kPartThreads, raised[1]);
+    if (e == hipSuccess) e = ensure_lds_limit((const void*)measure_parts_kernel<T, 24, 2, 10>, 24 * 8 * kPartThreads, raised[2]);
+    if (e == hipSuccess) e = ensure_lds_limit((const void*)measure_parts_kernel<T, 32, 2, 10>, 32 * 8 * kPartThreads, raised[3]);
+    if constexpr (sizeof(T) == 2)
+        if (e == hipSuccess) e = ensure_lds_limit((const void*)measure_parts_kernel<T, 32, 4, 10>, 32 * 8 * kPartThreads, raised[4]);
+    return e;
+}
 hipError_t init_measure()
 {
-    hipError_t e = raise_measure_limit<float>();
+    hipError_t e = raise_parts_limit<float>();
+    if (e == hipSuccess) e = raise_parts_limit<bf16_t>();
+    if (e == hipSuccess) e = raise_measure_limit<float>();
     if (e == hipSuccess) e = raise_measure_limit<bf16_t>();
     if (e == hipSuccess) e = raise_pipe_limit<float>();
     if (e == hipSuccess) e = raise_pipe_limit<bf16_t>();
@@ -1167,6 +1539,27 @@ static hipError_t launch_measure_t(const Plan& p, const Args& a, const Scratch& 
         return hipGetLastError();
     }
     const int chunks = p.n_chunk;                          // ceil(L / 64)
+    if (p.part_passes > 0) {
+        const hipError_t e = raise_parts_limit<T>();
+        if (e != hipSuccess) return e;
+        const int span = p.part_passes * (kPartQueries / kMeasureQueries), groups = (chunks + span - 1) / span;
+#define PSA_PARTS(KT, NPASS, NR)                                                                                           \
+        hipLaunchKernelGGL((measure_parts_kernel<T, KT, NPASS, NR>), dim3((unsigned)(head_rounds * groups * 8)), dim3(kPartThreads), \
+                           KT * 8 * kPartThreads, a.stream, (const T*)a.Q, (const T*)a.K, (const T*)a.V, a.lengths, a.idx, \
+                           w.M, w.vpart, w.ticket, p.stream_lists ? w.cand : nullptr, p.cand_len, w.vseg,                  \
+                           p.H, p.L, p.U, chunks, p.BH)
+        if constexpr (sizeof(T) == 2) {
+            if (p.part_passes == 4) {
+                PSA_PARTS(32, 4, 10);
+                return hipGetLastError();
+            }
+        }
+        const bool small = p.L * RowTraits<T>::kRowBytes <= 24 * 16 * kPartThreads;
+        if (p.U <= 36) { if (small) PSA_PARTS(24, 2, 9); else PSA_PARTS(32, 2, 9); }
+        else           { if (small) PSA_PARTS(24, 2, 10); else PSA_PARTS(32, 2, 10); }
+#undef PSA_PARTS
+        return hipGetLastError();
+    }
     // up to 64 samples per query: persistent work-groups with loader waves; beyond, one work-group per chunk
     if (p.U <= kPipeMaxU) {
         const int groups = (chunks + p.chunks_per_wg - 1) / p.chunks_per_wg;
