@@ -80,12 +80,14 @@ __device__ __forceinline__ void attend_f32_body(const AttendParams& P, double* s
     PSA_TS(1);
     const int qrank = qgroup * NQ + ct * 16 + c;
     const int qi = qrank < u ? selp[qrank] : -1;
-    tile.load_q(head_rows<256>(Qh, n), qi, g);
+    float4 qraw[4];
+    Tile::request_q(qraw, head_rows<256>(Qh, n), qi, g);
     tile.load_v(vr, j_first, c, g, dp);                       // behind K and Q in the queue, needed last
 
     // ---- stage a4 for this work-group's share of the rows: the stores go out now
     // and complete under the matrix work below
     fill_rows<float, 512>(P, static_cast<float*>(P.out) + (size_t)head * L * kD, Vh, selp, u, n, wg_in_head, cs);
+    tile.take_q(qraw);
 
     PSA_TS(2);
     // the K tile of the next round is requested before the current round's products
@@ -325,7 +327,7 @@ __device__ __forceinline__ void attend_bf16_body(const AttendParams& P, unsigned
     for (int qt = 0; qt < NQT; ++qt) {
         const int r = qgroup * NQ + qt * 32 + c;
         const int qi = r < u ? selp[r] : -1;
-        tile.load_q(qt, Qh, qi, qi >= 0 && qi < n, h);
+        tile.load_q(qt, head_rows<128>(Qh, n), qi, h);
     }
     // ---- stage a4 for this work-group's share of the rows: the stores go out now
     // and complete under the matrix work below
@@ -623,8 +625,10 @@ void attend_rows_f32_kernel(const AttendParams P)
     const int rank = qblock * 64 + wq * 16 + c;
     int qi = rank < u ? selp[rank] : -1;
     if (qi >= n) qi = -1;
-    tile.load_q(head_rows<256>(Qh, n), qi, g);
+    float4 qraw[4];
+    F32Tile::request_q(qraw, head_rows<256>(Qh, n), qi, g);
     fill_rows<float, NT>(P, oh, Vh, selp, u, n, qblock, cs);
+    tile.take_q(qraw);
     const bool live = qblock * 64 + wq * 16 < u;          // wave-uniform: some rank of this wave is in use
     if (KSPLIT == 1 && !live) return;
     if (live) {
@@ -723,7 +727,7 @@ void attend_rows_bf16_kernel(const AttendParams P)
     const int rank = qblock * 128 + wq * 32 + c;
     int qi = rank < u ? selp[rank] : -1;
     if (qi >= n) qi = -1;
-    tile.load_q(0, Qh, qi, qi >= 0, h);
+    tile.load_q(0, head_rows<128>(Qh, n), qi, h);
     fill_rows<bf16_t, NT>(P, oh, Vh, selp, u, n, qblock, cs);
     if (qblock * 128 >= u) return;                        // work-group-uniform: no rank of this block is in use
     put(0, xk, xv);

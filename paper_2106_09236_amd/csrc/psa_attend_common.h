@@ -86,6 +86,12 @@ __device__ __forceinline__ SelList attend_prologue(const AttendParams& P, int he
     const int tid = threadIdx.x;
     const int b = head / P.H;
     SelList selp{(const __attribute__((address_space(3))) int*)cs.sel, nullptr};
+    // For fill_rows: cs.flag[t] = 1 where row r0 + t is selected, for the first 512 rows of this work-group's share.  They are
+    // cleared before a barrier that lies ahead of the selection anyway (or comes early, when no wave waits for another) and set by whoever
+    // writes an entry of the list: a pass of its own over the list with a barrier took 2000 cycles.
+    const int flag_r0 = wg_in_head * P.rows_per_wg;
+    auto clear_flags = [&]() { for (int t = tid; t < 512; t += NT) cs.flag[t] = 0; };
+    auto set_flag = [&](int i) { if (i >= 0 && (unsigned)(i - flag_r0) < 512u) cs.flag[i - flag_r0] = 1; };
     // The last wave sums the per-chunk float64 column sums of V (fixed order).  The
     // first 8 chunks are requested BEFORE the K tile (loads complete in issue order,
     // so anything requested after the tile would wait for all of it).
@@ -118,6 +124,8 @@ __device__ __forceinline__ SelList attend_prologue(const AttendParams& P, int he
         for (int k = 0; k < SPT; ++k) { const int t = k * NT + tid; sv[k] = gsel[t < P.u_max ? t : P.u_max - 1]; }
         int ub = P.given_u[b];
         if (e >= 0) load_vpart(vp0, 0);
+        clear_flags();
+        lds_barrier();
         ub = ub < 0 ? 0 : ub;
         ub = ub > P.u_max ? P.u_max : ub;
         u = ub > n ? n : ub;
@@ -126,10 +134,10 @@ __device__ __forceinline__ SelList attend_prologue(const AttendParams& P, int he
 #pragma unroll
         for (int k = 0; k < SPT; ++k) {
             const int t = k * NT + tid;
-            if (t < P.u_max) cs.sel[t] = (t < u && sv[k] >= 0 && sv[k] < n) ? sv[k] : -1;
+            const int i = (t < u && sv[k] >= 0 && sv[k] < n) ? sv[k] : -1;
+            if (t < P.u_max) { cs.sel[t] = i; set_flag(i); }
         }
         if (e >= 0) cs.mean[e] = n > 0 ? (float)(vsum / (double)n) : 0.f;
-        for (int t = tid; t < 512; t += NT) cs.flag[t] = 0;         // for fill_rows: its first block needs no barrier of its own
         lds_barrier();
         if (wg_in_head == 0) {                       // publish for later calls that reuse the sets
             for (int t = tid; t < P.u_max; t += NT) P.sel[(size_t)head * P.u_max + t] = cs.sel[t];
@@ -159,6 +167,7 @@ __device__ __forceinline__ SelList attend_prologue(const AttendParams& P, int he
             // tile requests of all work-groups does not delay them
             issue_tile();
             for (int t = tid; t < P.u_max; t += NT) cs.sel[t] = -1;
+            clear_flags();
             if (e >= 0) cs.mean[e] = n > 0 ? (float)(vsum / (double)n) : 0.f;
             PSA_TS(9);
             lds_barrier();
@@ -193,7 +202,7 @@ __device__ __forceinline__ SelList attend_prologue(const AttendParams& P, int he
                     cnt += __builtin_amdgcn_update_dpp(0, cnt, 0xB1, 0xF, 0xF, false);      // sum over the group's lanes
                     cnt += __builtin_amdgcn_update_dpp(0, cnt, 0x4E, 0xF, 0xF, false);
                     if (gs == 3) cnt += __builtin_amdgcn_update_dpp(0, cnt, 0x141, 0xF, 0xF, false);
-                    if (c2 == 0 && ci < total && key != 0u && qidx >= 0 && cnt < u) cs.sel[cnt] = qidx;
+                    if (c2 == 0 && ci < total && key != 0u && qidx >= 0 && cnt < u) { cs.sel[cnt] = qidx; set_flag(qidx); }
                 }
             } else {
                 // More than 4 lists and more candidates than threads can take in one trip (8 lists of 49: seven
@@ -254,12 +263,11 @@ __device__ __forceinline__ SelList attend_prologue(const AttendParams& P, int he
                     cnt += __builtin_amdgcn_update_dpp(0, cnt, 0xB1, 0xF, 0xF, false);      // sum over the group's lanes
                     cnt += __builtin_amdgcn_update_dpp(0, cnt, 0x4E, 0xF, 0xF, false);
                     if (gs == 3) cnt += __builtin_amdgcn_update_dpp(0, cnt, 0x141, 0xF, 0xF, false);
-                    if (c2 == 0 && ci < total2 && key != 0u && qidx >= 0 && cnt < u) cs.sel[cnt] = qidx;
+                    if (c2 == 0 && ci < total2 && key != 0u && qidx >= 0 && cnt < u) { cs.sel[cnt] = qidx; set_flag(qidx); }
                 }
             }
             PSA_TS(11);
         }
-        for (int t = tid; t < 512; t += NT) cs.flag[t] = 0;         // for fill_rows: its first block needs no barrier of its own
         lds_barrier();
         PSA_TS(12);
         if (wg_in_head == 0) {                       // publish for the taps and for later calls that reuse I_sparse
@@ -273,15 +281,17 @@ __device__ __forceinline__ SelList attend_prologue(const AttendParams& P, int he
         const int s0v = gsel[tid < P.u_max ? tid : P.u_max - 1];
         u = P.ucount[b];
         const float mv = P.mu[(size_t)head * kD + (tid & (kD - 1))];
+        clear_flags();
+        lds_barrier();
         issue_tile();
-        if (P.u_max <= kSelLdsMax) {
-            if (tid < P.u_max) cs.sel[tid] = s0v;
-            for (int t = tid + NT; t < P.u_max; t += NT) cs.sel[t] = gsel[t];
-        } else {
-            selp.global = (const __attribute__((address_space(1))) int*)gsel;
+        const bool in_lds = P.u_max <= kSelLdsMax;
+        if (!in_lds) selp.global = (const __attribute__((address_space(1))) int*)gsel;
+        for (int t = tid; t < P.u_max; t += NT) {                    // (-1 beyond u)
+            const int i = t == tid ? s0v : gsel[t];
+            if (in_lds) cs.sel[t] = i;
+            set_flag(i);
         }
         if (tid < kD) cs.mean[tid] = mv;
-        for (int t = tid; t < 512; t += NT) cs.flag[t] = 0;         // for fill_rows (see above)
         lds_barrier();
     }
     return selp;
@@ -317,8 +327,8 @@ __device__ __forceinline__ void fill_rows_impl(T* out_head, const T* V_head, con
     float mean[EPL], zero[EPL];
 #pragma unroll
     for (int e = 0; e < EPL; ++e) { mean[e] = cs.mean[sub * EPL + e]; zero[e] = 0.f; }
-    // cs.flag[t] = 1: row lo + t of the current block of 512 rows is selected.  The prologue left the
-    // flags at zero behind a barrier, so the first block (the only one, as a rule) starts marking at once.
+    // cs.flag[t] = 1: row lo + t of the current block of 512 rows is selected.  The prologue left those of the first block (the
+    // only one, as a rule) behind a barrier.
     for (int blk = 0; blk < rows; blk += 512) {
         const int nb = rows - blk < 512 ? rows - blk : 512;
         const int lo = r0 + blk;
@@ -326,12 +336,12 @@ __device__ __forceinline__ void fill_rows_impl(T* out_head, const T* V_head, con
             lds_barrier();                                // the previous block's flags have been read
             for (int t = tid; t < nb; t += NT) cs.flag[t] = 0;
             lds_barrier();
+            for (int t = tid; t < u; t += NT) {
+                const int i = selp[t];
+                if (i >= lo && i < lo + nb) cs.flag[i - lo] = 1;
+            }
+            lds_barrier();
         }
-        for (int t = tid; t < u; t += NT) {
-            const int i = selp[t];
-            if (i >= lo && i < lo + nb) cs.flag[i - lo] = 1;
-        }
-        lds_barrier();
         if (VALUE_FILL) {
             // copies of 16 bytes, the loads unconditional on a clamped row and four in flight
 #pragma unroll 4
@@ -352,12 +362,45 @@ __device__ __forceinline__ void fill_rows_impl(T* out_head, const T* V_head, con
         }
     }
 }
+// Mean fill of at most RPP * IT <= 512 rows: IT stores per thread and nothing but stores, those of rows that get none going
+// beyond the buffer, which drops them.  With their number known the compiler waits for the loads asked for before them (the
+// selected rows of Q) without waiting for the stores.
+template <typename T, int NT, int IT>
+__device__ __forceinline__ void fill_mean_rows(T* out_head, int n, int L, int r0, int rows, const CommonScratch& cs)
+{
+    using OT = OutTraits<T>;
+    constexpr int LPR = OT::LPR, EPL = OT::EPL, RPP = NT / LPR, RB = kD * (int)sizeof(T);
+    static_assert(RPP * IT <= 512, "one flag per row");
+    typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
+    const int tid = threadIdx.x, sub = tid % LPR, row = tid / LPR;
+    const __amdgpu_buffer_rsrc_t out = __builtin_amdgcn_make_buffer_rsrc(out_head, 0, L * RB, 0x00020000);
+    uintx4 mean;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+        if constexpr (sizeof(T) == 4) mean[w] = __float_as_uint(cs.mean[sub * EPL + w]);
+        else mean[w] = pack_bf16(cs.mean[sub * EPL + 2 * w], cs.mean[sub * EPL + 2 * w + 1]);
+    }
+#pragma unroll
+    for (int k = 0; k < IT; ++k) {
+        const int rl = row + k * RPP, i = r0 + rl;
+        const bool pad = i >= n;
+        const bool skip = rl >= rows || i >= L || (!pad && cs.flag[rl]);
+        const uintx4 x = pad ? uintx4{0u, 0u, 0u, 0u} : mean;
+        __builtin_amdgcn_raw_buffer_store_b128(x, out, skip ? (int)0x80000000u : i * RB + 16 * sub, 0, 0);      // (L * RB <= 2^30)
+    }
+}
 template <typename T, int NT>
 __device__ __forceinline__ void fill_rows(const AttendParams& P, T* out_head, const T* V_head, const SelList& selp,
                                           int u, int n, int wg_in_head, CommonScratch& cs)
 {
     if (P.fill == PSA_FILL_VALUE)
         fill_rows_impl<T, NT, true>(out_head, V_head, selp, u, n, P.L, wg_in_head * P.rows_per_wg, P.rows_per_wg, cs);
+    else if (P.rows_per_wg <= 4 * (NT / OutTraits<T>::LPR) && P.rows_per_wg <= 512)
+        fill_mean_rows<T, NT, 4>(out_head, n, P.L, wg_in_head * P.rows_per_wg, P.rows_per_wg, cs);
+    else if (P.rows_per_wg <= 8 * (NT / OutTraits<T>::LPR) && P.rows_per_wg <= 512)
+        fill_mean_rows<T, NT, 8>(out_head, n, P.L, wg_in_head * P.rows_per_wg, P.rows_per_wg, cs);
+    else if (P.rows_per_wg <= 512)
+        fill_mean_rows<T, NT, 512 * OutTraits<T>::LPR / NT>(out_head, n, P.L, wg_in_head * P.rows_per_wg, P.rows_per_wg, cs);
     else
         fill_rows_impl<T, NT, false>(out_head, V_head, selp, u, n, P.L, wg_in_head * P.rows_per_wg, P.rows_per_wg, cs);
 }

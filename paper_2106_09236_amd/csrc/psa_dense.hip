@@ -73,7 +73,7 @@ void dense_bf16_kernel(const bf16_t* __restrict__ Q, const bf16_t* __restrict__ 
 
     Bf16Tile<1> tile;
     tile.init();
-    tile.load_q(0, Qh, q, q < n, h);
+    tile.load_q(0, head_rows<128>(Qh, n), q, h);
 
     // thread t stages 16 bytes of row t / 8 of the tile
     const int srow = tid >> 3, scol = tid & 7;

@@ -92,7 +92,7 @@ void exact_measure_bf16_kernel(const bf16_t* __restrict__ Q, const bf16_t* __res
     const bf16_t* Kh = K + (size_t)head * L * kD;
 
     Bf16Tile<1> tile;
-    tile.load_q(0, Qh, q, q < n, h);
+    tile.load_q(0, head_rows<128>(Qh, n), q, h);
     float m = -INFINITY, l = 0.f;
     double ssum = 0.0;
     uint4 knext[4];

@@ -74,14 +74,23 @@ struct F32TileOf {
     // Rows come through a buffer descriptor over the head's valid rows (head_rows), which reads zeros beyond them:
     // no clamp, no select and, above all, no branch around a load (the compiler made one of every guarded load
     // and waited for each before the next).  An absent query (qi < 0) is a row beyond the end as well.
-    __device__ __forceinline__ void load_q(__amdgpu_buffer_rsrc_t q, int qi, int g) {
+    // In two steps, so that other work can lie between the request and the wait for it.
+    static __device__ __forceinline__ void request_q(float4 (&x)[4], __amdgpu_buffer_rsrc_t q, int qi, int g) {
         const int ofs = qi >= 0 ? qi * 256 + 16 * g : -16;
 #pragma unroll
+        for (int v = 0; v < 4; ++v) x[v] = buffer_load16<float4>(q, ofs + (qi >= 0 ? 64 * v : 0));
+    }
+    __device__ __forceinline__ void take_q(const float4 (&x)[4]) {
+#pragma unroll
         for (int v = 0; v < 4; ++v) {
-            const float4 x = buffer_load16<float4>(q, ofs + (qi >= 0 ? 64 * v : 0));
-            qreg[4 * v + 0] = (double)x.x; qreg[4 * v + 1] = (double)x.y;
-            qreg[4 * v + 2] = (double)x.z; qreg[4 * v + 3] = (double)x.w;
+            qreg[4 * v + 0] = (double)x[v].x; qreg[4 * v + 1] = (double)x[v].y;
+            qreg[4 * v + 2] = (double)x[v].z; qreg[4 * v + 3] = (double)x[v].w;
         }
+    }
+    __device__ __forceinline__ void load_q(__amdgpu_buffer_rsrc_t q, int qi, int g) {
+        float4 x[4];
+        request_q(x, q, qi, g);
+        take_q(x);
     }
     static __device__ __forceinline__ void load_k_into(float4 (&dst)[2][4], __amdgpu_buffer_rsrc_t k, int j0, int c, int g) {
 #pragma unroll
@@ -207,14 +216,12 @@ struct Bf16Tile {
                 for (int r = 0; r < 16; ++r) oacc[qt][dt][r] = 0.f;
         }
     }
-    __device__ __forceinline__ void load_q(int qt, const bf16_t* Qh, int qi, bool ok, int h) {
-        const uint4* src = reinterpret_cast<const uint4*>(Qh + (size_t)(ok ? qi : 0) * kD) + 4 * h;
+    // Through a buffer descriptor over the head's valid rows (head_rows): zeros for a row beyond them or an absent query
+    // (qi < 0).  Nothing is done with the rows here, so nothing waits for them before the first product.
+    __device__ __forceinline__ void load_q(int qt, __amdgpu_buffer_rsrc_t q, int qi, int h) {
+        const int ofs = qi >= 0 ? qi * 128 + 64 * h : -16;
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            uint4 x = src[v];
-            if (!ok) x = make_uint4(0u, 0u, 0u, 0u);
-            qreg[qt][v] = x;
-        }
+        for (int v = 0; v < 4; ++v) qreg[qt][v] = buffer_load16<uint4>(q, ofs + (qi >= 0 ? 16 * v : 0));
     }
     // ---- operands straight from global memory (the prob-sparse attend kernel).
     // K tile as the A operand of the first product: lane (c, h) reads the 64
