@@ -52,8 +52,12 @@ static int elem_split(int64_t wgs) { return 4 * wgs <= 256 ? 4 : 2 * wgs <= 256 
 // of work-groups that is not full counts half: heads are often shorter than L.
 // Against groups of 32 and 512 work-groups for every shape: B=24 H=4 L=750 ragged 87 -> 75 us, B=16 H=4 L=1000
 // 83 -> 63, B=64 H=4 L=200 52 -> 36, B=1 H=4 L=333 26.0 -> 23.8 us.
+// Given sets whose work-groups form the column sums themselves (own_sums): what the launch that clears the tickets costs, which
+// a cut without hand-over does not need (B=16 H=4 L=512, 32 kept: one split 17.7 us, four splits 20.2).
+constexpr float kTicketLaunch = 2.f;
 static void split_f32(Plan* p, int n_tiles)
 {
+    const float ticket = p->given_indices && (size_t)p->L * 256 <= kOwnSumBytes ? kTicketLaunch : 0.f;
     float best = INFINITY;
     for (int ncg = 2; ncg >= 1; --ncg) {                      // (of equals the larger groups: they read K and V less often)
         const int nq = 16 * ncg, tiles_wg = 8 / ncg;
@@ -73,7 +77,7 @@ static void split_f32(Plan* p, int n_tiles)
             const float fills = (float)(per_split * split) / 256.f;
             const float part = split == 1 && elem_split(per_split) == 4 ? 0.75f : 1.f;      // of a tile step
             const float cost = (fills <= 1.f ? 1.f : 0.5f * (fills + ceilf(fills))) * (5.5f + 2.3f * part * (float)steps) +
-                (split == 1 ? 0.f : split > kTicketMaxSplit ? 6.f : 3.f + 1.5f * (float)((p->u_max + 31) / 32 * ((split + 3) / 4)));
+                (split == 1 ? 0.f : split > kTicketMaxSplit ? 6.f : ticket + 3.f + 1.5f * (float)((p->u_max + 31) / 32 * ((split + 3) / 4)));
             if (cost < best) {
                 best = cost;
                 p->nq_group = nq; p->n_qgroup = n_qgroup; p->n_split = split; p->tiles_per_wave = rounds;
@@ -304,6 +308,16 @@ static void build_plan(const psa_shape_t* s, URule urule, int u_stride, Cuts cut
     // for one wave to add up: no prep kernel (one launch less: conformer_s 27.8 -> 25 us)
     p->given_inline = p->given_indices && p->u_max <= kSelLdsMax && p->n_chunk <= 64;
     p->separate_merge = p->n_split > kTicketMaxSplit;
+    // Given sets, mean fill, short heads: each attend work-group reads all of its head's V for the column sums it needs (out of its L2,
+    // where the head's other work-groups and its own products find V then) instead of a launch that does.  In microseconds: a
+    // CU takes in 105 KB, the launch costs 3.5 and reads V at 5 TB/s.  Whole call, launch -> own: B=16 H=4 L=512 float32, 32 kept
+    // 21.2 -> 17.7 us, B=1 H=4 L=128 10.5 -> 8.1, B=32 H=8 L=512 with 100 kept (4 work-groups a head) 118 -> 114, but B=64 H=8 L=400 with
+    // 200 kept (7) 349 | 354; bfloat16 B=32 H=4 L=512 15.8 -> 11.1, B=128 H=8 L=1024 135 -> 104, B=8 H=8 L=1024 with 512 kept 27.0 -> 22.7.
+    p->own_sums = 0;
+    if (p->given_inline && p->rows_mode != 1 && (size_t)p->L * row_bytes <= kOwnSumBytes) {
+        const float heads = (float)p->BH * (float)p->L * (float)row_bytes;
+        p->own_sums = heads * (float)p->n_wg_head / (256.f * 105e3f) + 0.5f <= 3.5f + heads / 5e6f;
+    }
 
     // float32 tensors: m, l as float64 and 64 float32 values per query (34 doubles); bfloat16: 66 floats
     p->part_stride = (size_t)p->nq_group * (p->dtype == PSA_F32 ? 2 + kD / 2 : kD + 2);
@@ -438,7 +452,9 @@ static int run_indices(const void* Q, const void* K, const void* V, const int32_
     a.urule = URule{PSA_U_LOG, 1.0}; a.fill = fill; a.given_sel = sel; a.given_u = u;
     a.stream = static_cast<hipStream_t>(stream);
     const Scratch w = carve(p, workspace);
-    if (launch_vsum(p, a, w) != hipSuccess) return PSA_ERR_HIP;
+    // before the attend stage: the V column sums where something reads them, the tickets where any are drawn
+    const bool tickets = p.n_split > 1 && !p.separate_merge;
+    if (((fill == PSA_FILL_MEAN && !p.own_sums) || tickets) && launch_vsum(p, a, w) != hipSuccess) return PSA_ERR_HIP;
     if (!p.given_inline && launch_prep_indices(p, a, w) != hipSuccess) return PSA_ERR_HIP;
     if (launch_attend(p, a, w) != hipSuccess) return PSA_ERR_HIP;
     return PSA_OK;
@@ -714,7 +730,7 @@ int probsparse_describe_plan(const psa_shape_t* shape, const psa_options_t* opt,
     if (n < 0 || (size_t)n >= buf_bytes) return PSA_ERR_ARG;
     // the rest where there is room for it: the module's projections, and the backward for index sets of this stride
     char more[320];
-    int m = snprintf(more, sizeof(more), " element_shares=%d measure_parts=%d qkv_project=%s out_project=%s", p.d_split, p.part_passes, project_route_name(*shape, 3),
+    int m = snprintf(more, sizeof(more), " element_shares=%d measure_parts=%d own_sums=%d qkv_project=%s out_project=%s", p.d_split, p.part_passes, p.own_sums, project_route_name(*shape, 3),
                      project_route_name(*shape, 1));
     if (u_stride > 0) {
         const BwdPlan bp = make_bwd_plan(*shape, u_stride);

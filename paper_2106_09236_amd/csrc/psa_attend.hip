@@ -75,7 +75,7 @@ __device__ __forceinline__ void attend_f32_body(const AttendParams& P, double* s
     const int j_first = (split * rounds * KT + kt) * kTile;
     const __amdgpu_buffer_rsrc_t kr = head_rows<256>(Kh, n), vr = head_rows<256>(Vh, n);
     int u;
-    const SelList selp = attend_prologue<512>(P, head, n, wg_in_head, cs, u,
+    const SelList selp = attend_prologue<float, 512, 16>(P, head, n, wg_in_head, cs, u,
                                               [&]() { Tile::load_k_into(tile.kreg, kr, j_first, c, g); });
     PSA_TS(1);
     const int qrank = qgroup * NQ + ct * 16 + c;
@@ -315,7 +315,7 @@ __device__ __forceinline__ void attend_bf16_body(const AttendParams& P, unsigned
     uint4 kn[4], vn[4];
     PSA_TS(0);
     int u;
-    const SelList selp = attend_prologue<512>(P, head, n, wg_in_head, cs, u, [&]() {
+    const SelList selp = attend_prologue<bf16_t, 512, 16>(P, head, n, wg_in_head, cs, u, [&]() {
         Bf16Tile<NQT>::load_k_operand(kn, Kh, tile0 * kTile, n, c, h);
         Bf16Tile<NQT>::load_v_rows(vn, Vh, tile0 * kTile, n, lane);
     });
@@ -620,7 +620,7 @@ void attend_rows_f32_kernel(const AttendParams P)
     const __amdgpu_buffer_rsrc_t kr = head_rows<256>(Kh, n), vr = head_rows<256>(Vh, n);
     float4 knext[2][4];
     int u;
-    const SelList selp = attend_prologue<NT>(P, head, n, qblock, cs, u,
+    const SelList selp = attend_prologue<float, NT, KSPLIT == 1 ? 0 : 16>(P, head, n, qblock, cs, u,
                                           [&]() { F32Tile::load_k_into(knext, kr, j_begin, c, g); });
     const int rank = qblock * 64 + wq * 16 + c;
     int qi = rank < u ? selp[rank] : -1;
@@ -721,7 +721,7 @@ void attend_rows_bf16_kernel(const AttendParams P)
     };
     uint4 xk, xv;
     int u;
-    const SelList selp = attend_prologue<NT>(P, head, n, qblock, cs, u, [&]() { fetch(j_begin, xk, xv); });
+    const SelList selp = attend_prologue<bf16_t, NT, 8>(P, head, n, qblock, cs, u, [&]() { fetch(j_begin, xk, xv); });
     Bf16Tile<1> tile;
     tile.init();
     const int rank = qblock * 128 + wq * 32 + c;
@@ -813,6 +813,8 @@ hipError_t launch_attend(const Plan& p, const Args& a, const Scratch& w)
     P.fused_select = p.fused_select; P.rows_per_wg = p.rows_per_wg; P.urule = a.urule; P.fill = a.fill;
     P.cand = w.cand; P.cand_len = p.cand_len; P.separate_merge = p.separate_merge; P.nq = p.nq_group;
     P.given_sel = p.given_inline ? a.given_sel : nullptr; P.given_u = a.given_u;
+    P.own_sums = p.own_sums && a.fill == PSA_FILL_MEAN;
+    if (p.given_inline && a.fill == PSA_FILL_VALUE) P.n_vpart = 0;
     P.head_shift = p.BH % 8 == 0 && (p.n_qgroup > 1 || p.dtype == PSA_F32) ? 3 : 0;
     if (p.rows_mode) {
         const dim3 rgrid = attend_grid(p.n_qgroup, p.BH, P.head_shift);

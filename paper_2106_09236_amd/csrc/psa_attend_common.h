@@ -8,6 +8,7 @@
 #include "psa_device.h"
 #include "psa_internal.h"
 #include "psa_select.h"
+#include "psa_tile.h"
 
 namespace psa {
 
@@ -22,7 +23,8 @@ struct AttendParams {
     int* ticket;             // [BH] zero on entry (stage a1 clears it, the last work-group resets it)
     const uint2* cand;       // [BH, n_chunk, cand_len] sorted per-chunk candidates (cand_len > 0), else unused
     const int* given_sel;    // non-null: caller's index sets [BH, u_max], checked inside the attend work-groups ...
-    const int* given_u;      // ... with their lengths [B]; vpart then holds the V column sums, n_chunk of them per head
+    const int* given_u;      // ... with their lengths [B]; vpart then holds the V column sums, n_chunk of them per head,
+    int own_sums;            // or (1) each work-group forms those of its head itself; value fill: 0, and n_vpart is 0
     void* part;              // partial records
     void* out;
     int H, L, u_max, n_split, n_qgroup, rounds, part_stride, n_chunk, fused_select, rows_per_wg, cand_len;
@@ -50,7 +52,7 @@ inline dim3 attend_grid(int wgs, int BH, int head_shift) { return dim3((unsigned
 struct CommonScratch {
     float mean[kD];
     int sel[kSelLdsMax];             // I_sparse of the head
-    unsigned ckey[kMaxCandidates];   // candidate lists of the head: order keys ...
+    alignas(16) unsigned ckey[kMaxCandidates];   // candidate lists of the head: order keys ...
     int cidx[kMaxCandidates];        // ... and query indices (-1 = empty slot)
     unsigned char flag[512];
     int plen[8];                     // per list: how many of its first entries can be among the u best
@@ -66,6 +68,49 @@ struct SelList {
     __device__ __forceinline__ int operator[](int t) const { return global ? global[t] : lds[t]; }
 };
 
+// Column sums, in float64 and a fixed order, of a head's valid V rows, by the whole work-group: per wave into red[wave], to be added
+// behind a barrier.  IT loads per thread in flight at once, zeros beyond the valid rows; `issue_tile` asks for the first tile behind
+// the first of them.  MORE: there may be more than IT * RPP rows.
+template <typename T, int NT, int IT, bool MORE, typename F>
+__device__ __forceinline__ void head_v_sums(const T* V_head, int n, int rows, double (*red)[kD], F&& issue_tile)
+{
+    constexpr int RB = kD * (int)sizeof(T), LPR = RB / 16, EPL = kD / LPR, RPP = NT / LPR;
+    const int tid = threadIdx.x, lane = tid & 63, sub = tid % LPR, row = tid / LPR;
+    const __amdgpu_buffer_rsrc_t vr = head_rows<RB>(V_head, n);
+    uint4 x[IT];
+#pragma unroll
+    for (int k = 0; k < IT; ++k) x[k] = buffer_load16<uint4>(vr, (row + k * RPP) * RB + 16 * sub);
+    issue_tile();
+    double acc[EPL];
+#pragma unroll
+    for (int e = 0; e < EPL; ++e) acc[e] = 0.0;
+    auto add = [&]() {
+#pragma unroll
+        for (int k = 0; k < IT; ++k) {
+            const uint32_t w[4] = {x[k].x, x[k].y, x[k].z, x[k].w};
+#pragma unroll
+            for (int e = 0; e < EPL; ++e)
+                acc[e] += (double)(sizeof(T) == 4 ? __uint_as_float(w[e % 4]) : (e & 1) ? bf16_hi(w[e / 2]) : bf16_lo(w[e / 2]));
+        }
+    };
+    add();
+#pragma unroll 1
+    for (int r0 = IT * RPP; MORE && r0 < rows; r0 += IT * RPP) {
+#pragma unroll
+        for (int k = 0; k < IT; ++k) x[k] = buffer_load16<uint4>(vr, (r0 + row + k * RPP) * RB + 16 * sub);
+        add();
+    }
+#pragma unroll
+    for (int e = 0; e < EPL; ++e) {
+        if (LPR == 8) acc[e] = sum_xor8(acc[e]);
+        acc[e] = sum_xor32(sum_xor16(acc[e]));
+    }
+    if (lane < LPR) {
+#pragma unroll
+        for (int e = 0; e < EPL; ++e) red[tid >> 6][sub * EPL + e] = acc[e];
+    }
+}
+
 // ---- prologue: I_sparse and the mean of the valid V rows.
 // Two ways, by the shape of the problem (decided on the host):
 //  * candidate lists (short heads measured by the LDS kernel): the measure stage
@@ -78,8 +123,10 @@ struct SelList {
 // `issue_tile` is called once the prologue's own loads are in flight: the caller
 // requests its first K tile there, so that the tile streams in behind them while
 // the selection runs (barriers inside are LDS-only and do not wait for it).
+// LOADS: 16-byte loads of V a thread may have in flight where the work-group forms the column sums itself (8 in the bfloat16 kernel of
+// which two work-groups share a CU: with 16 it has 131 registers, and room for one); 0: it never does.
 // Returns the head's selected indices and u.
-template <int NT, typename F>
+template <typename T, int NT, int LOADS, typename F>
 __device__ __forceinline__ SelList attend_prologue(const AttendParams& P, int head, int n, int wg_in_head,
                                                       CommonScratch& cs, int& u, F&& issue_tile)
 {
@@ -123,14 +170,36 @@ __device__ __forceinline__ SelList attend_prologue(const AttendParams& P, int he
 #pragma unroll
         for (int k = 0; k < SPT; ++k) { const int t = k * NT + tid; sv[k] = gsel[t < P.u_max ? t : P.u_max - 1]; }
         int ub = P.given_u[b];
-        if (e >= 0) load_vpart(vp0, 0);
+        // a wave's own sums go where candidate lists would lie
+        double (*red)[kD] = reinterpret_cast<double (*)[kD]>(cs.ckey);
+        static_assert(sizeof(cs.ckey) >= NT / 64 * kD * sizeof(double), "a row of sums per wave");
         clear_flags();
+        const bool own_sums = LOADS > 0 && P.own_sums;
+        if (own_sums) {
+            if constexpr (LOADS > 0) {
+                const T* Vh = static_cast<const T*>(P.V) + (size_t)head * P.L * kD;
+                constexpr int RPP = NT / (kD * (int)sizeof(T) / 16);
+                constexpr bool MORE = (size_t)LOADS * RPP * kD * sizeof(T) < kOwnSumBytes;
+                if (P.L <= 4 * RPP)                    head_v_sums<T, NT, 4, false>(Vh, n, P.L, red, issue_tile);
+                else if (LOADS == 8 || P.L <= 8 * RPP) head_v_sums<T, NT, 8, LOADS == 8 && MORE>(Vh, n, P.L, red, issue_tile);
+                else                                   head_v_sums<T, NT, LOADS, MORE>(Vh, n, P.L, red, issue_tile);
+            }
+        } else if (e >= 0 && P.n_vpart > 0) {
+            load_vpart(vp0, 0);
+        }
         lds_barrier();
         ub = ub < 0 ? 0 : ub;
         ub = ub > P.u_max ? P.u_max : ub;
         u = ub > n ? n : ub;
-        if (e >= 0) sum_vpart();
-        issue_tile();
+        if (own_sums) {
+            if (e >= 0) {
+#pragma unroll
+                for (int w = 0; w < NT / 64; ++w) vsum += red[w][e];
+            }
+        } else {
+            if (e >= 0 && P.n_vpart > 0) sum_vpart();
+            issue_tile();
+        }
 #pragma unroll
         for (int k = 0; k < SPT; ++k) {
             const int t = k * NT + tid;

@@ -97,6 +97,13 @@ __device__ __forceinline__ double sum_xor16(double x) {
     return __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
 }
 
+// ... and over those 8 apart: a rotation by 8 within each row of 16 lanes
+__device__ __forceinline__ double sum_xor8(double x) {
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), 0x128, 0xF, 0xF, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), 0x128, 0xF, 0xF, false);
+    return x + __hiloint2double(hi, lo);
+}
+
 // 2^x in float64 for x <= ~0 (anything below -1000, -inf included, gives 0; NaN stays NaN):
 // x = n + f with |f| <= 1/2 by adding and taking away 1.5 * 2^52, 2^f by the polynomial of degree 6 with
 // constant term 1 whose largest relative error on [-1/2, 1/2] is least (2.0e-9; 2^0 is exactly 1; the softmax weights need 1e-6, see

@@ -22,6 +22,7 @@ constexpr int kTicketMaxSplit = 8;         // up to this many key splits the las
 constexpr int kMaxSplit = 512;             // key splits per head the merge kernel handles
 constexpr int kMaxCandidates = 2048;       // lists * cand_len an attend work-group can merge in LDS
 constexpr int kRowsModeMin = 64;           // from this many selected queries per head on, the attend stage may keep a head's keys in one work-group
+constexpr size_t kOwnSumBytes = 128 * 1024;// V of a head up to which the attend work-groups form its column sums themselves (given sets)
 constexpr int kSegMax = 8;                 // segments per head of the segment-select kernel (lists the attend stage merges)
 constexpr int kSegKeys = 2048;             // most queries of one segment
 constexpr int kSegCandMax = 256;           // longest list a segment hands on
@@ -66,6 +67,7 @@ struct Plan {
     int separate_merge;   // 1: too many splits for the last work-group of a head; a merge kernel follows
     int given_indices;    // 1: I_sparse comes from the caller (no measure, no selection)
     int given_inline;     // 1: the attend work-groups check the caller's sets and form the mean of V themselves (no prep kernel)
+    int own_sums;         // 1: (given_inline, mean fill) each attend work-group forms the V column sums of its head, no launch for them
     int rows_mode;        // 1: many selected queries: a wave owns its queries and walks all keys (no key split);
                           // 2: the same with the keys cut in two inside the work-group
     // workspace carving (byte offsets, each 256-aligned)
@@ -129,7 +131,7 @@ hipError_t launch_measure(const Plan& p, const Args& a, const Scratch& w);
 hipError_t launch_select(const Plan& p, const Args& a, const Scratch& w);
 hipError_t launch_select_segments(const Plan& p, const Args& a, const Scratch& w);     // long heads: lists for the attend stage
 hipError_t launch_attend(const Plan& p, const Args& a, const Scratch& w);
-hipError_t launch_vsum(const Plan& p, const Args& a, const Scratch& w);             // V column sums alone
+hipError_t launch_vsum(const Plan& p, const Args& a, const Scratch& w);             // V column sums (mean fill only), and the tickets at zero
 hipError_t launch_prep_indices(const Plan& p, const Args& a, const Scratch& w);     // mean of V, caller's index sets
 
 // Gradients of stages a3 and a4 for a fixed index set (psa_backward.hip): groups of 64 kept queries, key

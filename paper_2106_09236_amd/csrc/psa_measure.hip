@@ -1596,8 +1596,19 @@ void vsum_kernel(const T* __restrict__ V, const int* __restrict__ lengths, doubl
                            vpart + ((size_t)head * chunks_per_head + chunk) * kD, s_red);
 }
 
+__global__ __launch_bounds__(256)
+void reset_tickets_kernel(int* ticket, int heads)
+{
+    const int head = blockIdx.x * 256 + threadIdx.x;
+    if (head < heads) ticket[head] = 0;
+}
+
 hipError_t launch_vsum(const Plan& p, const Args& a, const Scratch& w)
 {
+    if (a.fill == PSA_FILL_VALUE || p.own_sums) {
+        hipLaunchKernelGGL(reset_tickets_kernel, dim3((p.BH + 255) / 256), dim3(256), 0, a.stream, w.ticket, p.BH);
+        return hipGetLastError();
+    }
     const dim3 grid(p.n_chunk, p.BH);
     if (p.dtype == PSA_F32)
         hipLaunchKernelGGL(vsum_kernel<float>, grid, dim3(256), 0, a.stream, static_cast<const float*>(a.V), a.lengths,

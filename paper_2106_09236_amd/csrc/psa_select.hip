@@ -171,7 +171,7 @@ void prep_indices_kernel(const int* __restrict__ lengths, const double* __restri
 hipError_t launch_prep_indices(const Plan& p, const Args& a, const Scratch& w)
 {
     hipLaunchKernelGGL(prep_indices_kernel, dim3(p.BH), dim3(256), 0, a.stream, a.lengths, w.vpart, w.mu,
-                       a.given_sel, a.given_u, w.sel, w.u, p.H, p.L, p.u_max, p.n_chunk);
+                       a.given_sel, a.given_u, w.sel, w.u, p.H, p.L, p.u_max, a.fill == PSA_FILL_MEAN ? p.n_chunk : 0);
     return hipGetLastError();
 }
 
