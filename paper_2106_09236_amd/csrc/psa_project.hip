@@ -48,6 +48,30 @@ struct ProjLayout {
     static_assert(kEpiRows * kEpiStride <= kOperandElems, "the staging tile fits in the operand tiles");
 };
 
+// Few rows (64 x 64 tiles, all work-groups there at once): a tile's chunks come one after the other, each waiting for rows that were
+// asked for one chunk ahead, which is less than their way takes.  PF > 1: they are asked for PF chunks ahead, past barriers that leave loads in
+// flight.  Whole module, 1 -> 2: B=1 H=4 L=333 25.1 -> 24.8 us, B=1 H=8 L=333 29.0 -> 28.2, B=4 H=8 L=400 34.1 -> 33.2, B=1 H=4 L=40
+// 18.5 | 18.5; 3 ahead (124 registers) the same with d_model = 512 and 0.2 more with 256.  For float32 tensors, whose chunks are bound by
+// the splitting, 37.2 (2) and 38.0 (3) against 36.8 us at B=1 H=4 L=333.
+constexpr int kProjAhead = 2;
+template <bool LDS_ONLY> __device__ __forceinline__ void group_barrier() { if constexpr (LDS_ONLY) lds_barrier(); else __syncthreads(); }
+// One chunk of a thread's rows of A and of the tile's rows of W by way of buffers, which are empty for a chunk past the end: such
+// loads go nowhere, and the number of loads in flight does not depend on the chunk.  (A tensor with few rows has less than 2^31 bytes: the
+// launch has at most 1024 tiles of 64 x 64, and W's buffer is the tile's 64 rows.)
+template <int NA, int NW, typename Vec, typename T>
+__device__ __forceinline__ void fetch_rows(Vec (&ra)[NA], Vec (&rw)[NW], const T* A, const T* Wt, const T* const (&a_ptr)[NA], const T* const (&w_ptr)[NW],
+                                           int ka, int k0, bool there, int M, int Kd)
+{
+    const __amdgpu_buffer_rsrc_t ar = __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(A), 0, there ? M * Kd * (int)sizeof(T) : 0, 0x00020000);
+    const __amdgpu_buffer_rsrc_t wr = __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(Wt), 0, there ? 64 * Kd * (int)sizeof(T) : 0, 0x00020000);
+#pragma unroll
+    for (int j = 0; j < NA; ++j)
+        ra[j] = __builtin_bit_cast(Vec, __builtin_amdgcn_raw_buffer_load_b128(ar, (int)((a_ptr[j] - A) + ka) * (int)sizeof(T), 0, 0));
+#pragma unroll
+    for (int j = 0; j < NW; ++j)
+        rw[j] = __builtin_bit_cast(Vec, __builtin_amdgcn_raw_buffer_load_b128(wr, (int)((w_ptr[j] - Wt) + k0) * (int)sizeof(T), 0, 0));
+}
+
 // (Calls with many rows go to project_stream_kernel below.)
 // What bounds it (in-kernel time stamps and probes at B*L = 16384, d_model = 512, bfloat16): not
 // the contraction loop.  A loop with this mix of LDS reads, LDS writes, loads and one barrier per
@@ -60,8 +84,8 @@ struct ProjLayout {
 // epilogue were slower (the registers those loads hold cost the third work-group per compute
 // unit).  So the simple form is kept, with up to three work-groups per compute unit to overlap
 // the phases.
-template <int WM, int WN>
-__global__ __launch_bounds__(256, 2)
+template <int WM, int WN, int PF>
+__global__ __launch_bounds__(256, PF > 1 ? 4 : 2)
 void project_kernel(const ProjectParams P)
 {
     using T = bf16_t;
@@ -121,7 +145,7 @@ void project_kernel(const ProjectParams P)
     // contraction element k0 (a multiple of the chunk, so inside one head) of a row of A
     const size_t head_stride = (size_t)P.L * kD;
 
-    Vec ra[NA], rw[NW];
+    Vec ra[PF][NA], rw[PF][NW];
     floatx16 acc[WM][WN];
 #pragma unroll
     for (int i = 0; i < WM; ++i)
@@ -130,13 +154,17 @@ void project_kernel(const ProjectParams P)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
-    auto fetch = [&](int kc) {
+    auto fetch = [&](int set, int kc) {
         const int k0 = kc * CH;
         const size_t ka = P.a_heads ? (size_t)(k0 >> 6) * head_stride + (k0 & 63) : (size_t)k0;
+        if constexpr (PF == 1) {
 #pragma unroll
-        for (int j = 0; j < NA; ++j) ra[j] = *reinterpret_cast<const Vec*>(a_ptr[j] + ka);
+            for (int j = 0; j < NA; ++j) ra[set][j] = *reinterpret_cast<const Vec*>(a_ptr[j] + ka);
 #pragma unroll
-        for (int j = 0; j < NW; ++j) rw[j] = *reinterpret_cast<const Vec*>(w_ptr[j] + k0);
+            for (int j = 0; j < NW; ++j) rw[set][j] = *reinterpret_cast<const Vec*>(w_ptr[j] + k0);
+        } else {
+            fetch_rows<NA, NW>(ra[set], rw[set], A, W + (size_t)n0 * P.Kd, a_ptr, w_ptr, (int)ka, k0, kc < n_kc, P.M, P.Kd);
+        }
     };
 
     // the tile's bias values go to LDS once (an unconditional, clamped load; W stands in for a missing bias)
@@ -145,23 +173,29 @@ void project_kernel(const ProjectParams P)
         const int nb = n0 + (tid & (TN - 1));
         bias_raw = (bias ? bias : W)[nb < P.N ? nb : P.N - 1];
     }
-    fetch(0);
+    __builtin_amdgcn_sched_barrier(0);                    // (the bias first: it is waited for alone)
+#pragma unroll
+    for (int p = 0; p < PF; ++p) fetch(p, p);
     if (tid < TN) {
         sBias[tid] = (bias && n0 + tid < P.N) ? bf16_lo((uint32_t)bias_raw.x) : 0.f;
     }
-    for (int kc = 0; kc < n_kc; ++kc) {
+    for (int first = 0; first < n_kc; first += PF) {
+#pragma unroll
+    for (int p = 0; p < PF; ++p) {
+        const int kc = first + p;
+        if (PF > 1 && kc >= n_kc) goto products_done;     // (out of both loops, so that the waits for loads stay exact)
         if (kc < 2) PSA_TS(1 + kc);
-        __syncthreads();                                  // the previous chunk's reads of LDS are done
+        group_barrier<(PF > 1)>();                        // the previous chunk's reads of LDS are done
         {
             T* sa = sA + row0 * S + col * 8;
             T* sw = sW + row0 * S + col * 8;
 #pragma unroll
-            for (int j = 0; j < NA; ++j) *reinterpret_cast<Vec*>(sa + 32 * j * S) = ra[j];
+            for (int j = 0; j < NA; ++j) *reinterpret_cast<Vec*>(sa + 32 * j * S) = ra[p][j];
 #pragma unroll
-            for (int j = 0; j < NW; ++j) *reinterpret_cast<Vec*>(sw + 32 * j * S) = rw[j];
+            for (int j = 0; j < NW; ++j) *reinterpret_cast<Vec*>(sw + 32 * j * S) = rw[p][j];
         }
-        __syncthreads();
-        if (kc + 1 < n_kc) fetch(kc + 1);                 // travels during the products
+        group_barrier<(PF > 1)>();
+        if (PF > 1 || kc + 1 < n_kc) fetch(p, kc + PF);   // travels during the products
         __builtin_amdgcn_sched_barrier(0);                // (keeps the loads above them)
         const T* ar = sA + (wm * 32 * WM + c) * S;
         const T* wr = sW + (wn * 32 * WN + c) * S;
@@ -181,6 +215,8 @@ void project_kernel(const ProjectParams P)
                     acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b[j], a[i], acc[i][j], 0, 0, 0);
         }
     }
+    }
+products_done:
     PSA_TS(3);
 
     // ---- epilogue.  The products were taken as C^T = W A^T (W rows on the MFMA row axis), so a
@@ -736,12 +772,12 @@ static hipError_t launch_project_split(const ProjectParams& P, hipStream_t strea
     return hipGetLastError();
 }
 
-template <int WM, int WN>
+template <int WM, int WN, int PF = 1>
 static hipError_t launch_project_as(const ProjectParams& P, hipStream_t stream)
 {
     using LY = ProjLayout<WM, WN>;
     const int n_nt = (P.N + LY::kTN - 1) / LY::kTN, n_mt = (P.M + LY::kTM - 1) / LY::kTM;
-    hipLaunchKernelGGL((project_kernel<WM, WN>), dim3(8 * ((n_mt + 7) / 8) * n_nt * P.n_mat), dim3(256), 0, stream, P);
+    hipLaunchKernelGGL((project_kernel<WM, WN, PF>), dim3(8 * ((n_mt + 7) / 8) * n_nt * P.n_mat), dim3(256), 0, stream, P);
     return hipGetLastError();
 }
 
@@ -825,7 +861,7 @@ static hipError_t launch_project(const ProjectParams& P, int dtype, hipStream_t 
         case kStream:  return P.a_heads ? launch_project_stream<true, false>(P, stream) : launch_project_stream<false, true>(P, stream);
         case kTiles22: return launch_project_as<2, 2>(P, stream);
         case kTiles21: return launch_project_as<2, 1>(P, stream);
-        case kTiles11: return launch_project_as<1, 1>(P, stream);
+        case kTiles11: return launch_project_as<1, 1, kProjAhead>(P, stream);
         case kSplit22: return launch_project_split<2, 2>(P, stream);
         case kSplit21: return launch_project_split<2, 1>(P, stream);
         case kSplit11: return launch_project_split<1, 1>(P, stream);

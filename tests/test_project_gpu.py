@@ -66,3 +66,27 @@ def test_few_rows_of_float32(B, L, H):
         x, w, b = rows[k].double(), Ws[k].double(), bs[k].double()
         size = x.abs() @ w.abs().T + b.abs()
         assert bool(((have - (x @ w.T + b)).abs() <= 2 * (1.5 + 6 * dm + 2) * 2.0 ** -24 * size).all()), name
+
+
+@pytest.mark.parametrize("B,L,H", [(1, 1, 1), (1, 65, 2), (2, 33, 3), (1, 63, 4), (3, 50, 5), (1, 333, 8), (1, 130, 15)])
+def test_few_rows_of_bfloat16(B, L, H):
+    # as many chunks as heads, asked for two ahead.  Against float64: products are exact, each of at most dm + 1 additions is off by
+    # at most 2^-24 of the sum of the products' sizes (first order; twice that is allowed), and the result is rounded once (2^-8 between neighbours)
+    p = plan(B, H, L, 4, "bf16")
+    assert p["qkv_project"] == p["out_project"] == "tiles_64x64"
+    dm = H * 64
+    g = torch.Generator(device="cuda")
+    g.manual_seed(L)
+
+    def normal(*shape):
+        return torch.randn(shape, generator=g, device="cuda").to(torch.bfloat16)
+    X, A = normal(B, L, dm), normal(B, H, L, 64)
+    Ws, bs = [normal(dm, dm) for _ in range(4)], [normal(dm) for _ in range(4)]
+    weights = psa.make_weights(*Ws, *bs)
+    got = psa.probsparse_qkv_project(X, weights) + (psa.probsparse_out_project(A, weights),)
+    rows = [X, X, X, A.transpose(1, 2).reshape(B, L, dm)]
+    for k, name in enumerate("QKVY"):
+        have = got[k].double() if k == 3 else got[k].double().transpose(1, 2).reshape(B, L, dm)
+        x, w, b = rows[k].double(), Ws[k].double(), bs[k].double()
+        want, size = x @ w.T + b, x.abs() @ w.abs().T + b.abs()
+        assert bool(((have - want).abs() <= 2 * (dm + 1) * 2.0 ** -24 * size + 2.0 ** -8 * want.abs()).all()), name
