@@ -1386,23 +1386,24 @@ __device__ __forceinline__ void measure_quad_body(const T* __restrict__ Q, const
         // wait for it would also wait for the next chunk's loads, which are in flight on purpose).
         const int n_pre = n_r < KPRE ? n_r : KPRE;
         auto sample = [&](int k, int raw) { return active && sample_of(k) < U ? raw : -1; };
-        if constexpr (HALVES == 2) {
+        // A round's rows are requested while the round before is reduced, and every round has its indices at a place the compiler knows
+        // (picked at run time they took ten selections of some 75 instructions a round).  Two bfloat16 work-groups on a CU have 128
+        // registers and enough other waves to fill the waits: there each round is requested and reduced in turn.
+        // Whole call against a loop over rounds one at a time: B=16 H=4 L=512 float32 28.4 -> 28.2 us, B=64 H=4 L=200 ragged 35.3 -> 34.6; bfloat16
+        // B=32 H=4 L=512 ragged 23.7 -> 22.1, B=16 H=8 L=1000 52.3 -> 49.4, B=64 H=8 L=256 43.9 -> 40.0.
+        if constexpr (!(sizeof(T) == 2 && KCOPY == 8 && NQ == kLdsQueries)) {
             Round r[2];
             request(sample(0, jraw[0]), r[0], std::true_type{});
 #pragma unroll
             for (int k = 0; k < KPRE; ++k)
-                if (k < n_pre) {                          // wave-uniform
+                if (k < n_pre) {                              // wave-uniform
                     if (k + 1 < KPRE) request(sample(k + 1, jraw[k + 1 < KPRE ? k + 1 : 0]), r[(k + 1) & 1], std::true_type{});
                     reduce(r[k & 1], all_usable(r[k & 1].jv));
                 }
         } else {
-#pragma unroll 1
-            for (int k = 0; k < n_pre; ++k) {
-                int raw = jraw[KPRE - 1];
 #pragma unroll
-                for (int kk = 0; kk < KPRE - 1; ++kk) raw = (k == kk) ? jraw[kk] : raw;
-                gather_round(sample(k, raw));
-            }
+            for (int k = 0; k < KPRE; ++k)
+                if (k < n_pre) gather_round(sample(k, jraw[k]));      // wave-uniform
         }
         // only for U > 40: the remaining rounds, their indices fetched here
 #pragma unroll 1
