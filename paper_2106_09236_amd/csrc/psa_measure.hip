@@ -1126,8 +1126,8 @@ void measure_parts_kernel(const T* __restrict__ Q, const T* __restrict__ K, cons
 // in f32, L <= 1024 in bf16).  A work-group of 8 waves copies the head's valid K
 // rows into LDS once (coalesced) and gathers from there, FOUR lanes per query (16
 // queries per wave): the sample index reaches the quad's lanes by a DPP quad
-// broadcast, the lane sums take two exchange stages, and every instruction serves
-// 16 (query, sample) pairs.  Lane s of a quad reads bytes 16s .. 16s+15 of each
+// broadcast, the lane sums of four samples take two exchange stages, and every
+// instruction serves 16 (query, sample) pairs.  Lane s of a quad reads bytes 16s .. 16s+15 of each
 // 64-byte piece of the row, and quad number g of the wave takes the pieces in
 // the order g, g+1, ... (mod the pieces of a row): the LDS has 64 banks, a
 // float32 row spans all of them once, so the four quads of any 16 adjacent lanes
@@ -1141,8 +1141,7 @@ void measure_parts_kernel(const T* __restrict__ Q, const T* __restrict__ K, cons
 // -----------------------------------------------------------------------------
 // NQ: queries per chunk (the plan's measure_queries).  128: one per 4 lanes, 8 waves.  64 or 32, where the heads are
 // few and short, leaves a SIMD with one wave, and a wave's own instruction stream is what takes the time: then a query
-// has EIGHT lanes, two quads that take the sample rounds in turn and hand each other the scores, which are still added
-// in the order of the samples; and the rows are requested one round before they are multiplied.
+// has EIGHT lanes, two quads that take the sample rounds in turn.
 // KCOPY: 16-byte pieces of K per thread.  128 queries and 8 pieces (64 KB): two work-groups fit a CU; for bfloat16
 // rows the registers are capped to let them (4 waves per SIMD), so that one work-group copies its K while the other
 // gathers.
@@ -1324,11 +1323,11 @@ __device__ __forceinline__ void measure_quad_body(const T* __restrict__ Q, const
             }
             return d;
         };
-        // One round of 4 samples per quad; jv: this lane's sample, -1 if none.  CLAMP: jv may lie outside [0, n).
+        // One round of 4 samples per quad; jv: this lane's sample, -1 if none.
         struct Round { int jv; Vec kr[4][NP]; };
-        auto request = [&](int jv, Round& r, auto clamp) {
+        auto request = [&](int jv, Round& r) {
             r.jv = jv;
-            const int jc = !clamp.value || (unsigned)jv < (unsigned)n ? jv : 0;
+            const int jc = (unsigned)jv < (unsigned)n ? jv : 0;
             const int j[4] = {quad_bcast<0>(jc), quad_bcast<1>(jc), quad_bcast<2>(jc), quad_bcast<3>(jc)};
 #pragma unroll
             for (int t = 0; t < 4; ++t)
@@ -1336,52 +1335,25 @@ __device__ __forceinline__ void measure_quad_body(const T* __restrict__ Q, const
                 for (int v = 0; v < NP; ++v)
                     r.kr[t][v] = *reinterpret_cast<const Vec*>(sK + (uint32_t)j[t] * RT::kRowBytes + piece_ofs(v));
         };
-        // the quad's four scores of a round.  With two quads per query their rounds follow one another: the first quad
-        // adds its own four and then the other's (what the second quad's sums hold is not used)
-        auto reduce = [&](const Round& r, bool whole) {
+        // A transposing exchange leaves lane s of the quad with the score of its own sample, so that a round adds one value to
+        // each lane's maximum and sum and takes one test (padded queries, the tail of U, indices outside [0, n)), where every lane
+        // took all four, with masks or, behind a ballot, without.  The 1/sqrt(64) is applied once at the end (exact: a power
+        // of 2).  Whole call: B=1 H=4 L=128 float32 13.1 -> 12.8 us, B=9 H=8 L=118 ragged 15.4 -> 14.9; bfloat16 B=32 H=4 L=512 ragged 22.2 -> 21.7,
+        // B=41 H=4 L=200 ragged 19.0 -> 18.1, B=24 H=4 L=1000 ragged 45.6 -> 44.3.
+        auto reduce = [&](const Round& r) {
             float d[4];
 #pragma unroll
             for (int t = 0; t < 4; ++t) d[t] = row_dot(r.kr[t]);
-            // sums over the quad, one exchange stage at a time for all rows; the 1/sqrt(64) is
-            // applied once at the end (exact: a power of 2)
-#pragma unroll
-            for (int t = 0; t < 4; ++t) d[t] += dpp_mov<0xB1>(d[t]);
-#pragma unroll
-            for (int t = 0; t < 4; ++t) d[t] += dpp_mov<0x4E>(d[t]);
-            float e[4];
-            if constexpr (HALVES == 2)
-#pragma unroll
-                for (int t = 0; t < 4; ++t) e[t] = dpp_mov<0x141>(d[t]);                 // the other quad's
-            if (whole) {
-                // every sample of this round is usable in every query of the wave
-#pragma unroll
-                for (int t = 0; t < 4; ++t) { mx = fmaxf(mx, d[t]); sm += d[t]; }
-                if constexpr (HALVES == 2)
-#pragma unroll
-                    for (int t = 0; t < 4; ++t) { mx = fmaxf(mx, e[t]); sm += e[t]; }
-                cnt += LPQ;
-            } else {
-                // padded queries, the tail of U, or indices outside [0, n): drop those samples
-                const int raw[4] = {quad_bcast<0>(r.jv), quad_bcast<1>(r.jv), quad_bcast<2>(r.jv), quad_bcast<3>(r.jv)};
-                auto take = [&](int j, float sc) {
-                    const bool ok = (unsigned)j < (unsigned)n;
-                    mx = ok ? fmaxf(mx, sc) : mx;
-                    sm += ok ? sc : 0.f;
-                    cnt += ok ? 1 : 0;
-                };
-#pragma unroll
-                for (int t = 0; t < 4; ++t) take(raw[t], d[t]);
-                if constexpr (HALVES == 2)
-#pragma unroll
-                    for (int t = 0; t < 4; ++t) take(__builtin_amdgcn_update_dpp(0, raw[t], 0x141, 0xF, 0xF, false), e[t]);
-            }
+            const bool b0 = s & 1, b1 = s & 2;
+            const float r01 = (b0 ? d[1] : d[0]) + dpp_mov<0xB1>(b0 ? d[0] : d[1]);
+            const float r23 = (b0 ? d[3] : d[2]) + dpp_mov<0xB1>(b0 ? d[2] : d[3]);
+            const float x = (b1 ? r23 : r01) + dpp_mov<0x4E>(b1 ? r01 : r23);
+            const bool ok = (unsigned)r.jv < (unsigned)n;
+            mx = ok ? fmaxf(mx, x) : mx;
+            sm += ok ? x : 0.f;
+            cnt += ok ? 1 : 0;
         };
-        auto all_usable = [&](int jv) { return __ballot((unsigned)jv >= (unsigned)n) == 0ull; };      // wave-uniform
-        auto gather_round = [&](int jv) {
-            Round r;
-            if (all_usable(jv)) { request(jv, r, std::false_type{}); reduce(r, true); }
-            else                { request(jv, r, std::true_type{});  reduce(r, false); }
-        };
+        auto gather_round = [&](int jv) { Round r; request(jv, r); reduce(r); };
         // Rounds whose indices came with the chunk's other loads (no global load here: the
         // wait for it would also wait for the next chunk's loads, which are in flight on purpose).
         const int n_pre = n_r < KPRE ? n_r : KPRE;
@@ -1393,12 +1365,12 @@ __device__ __forceinline__ void measure_quad_body(const T* __restrict__ Q, const
         // B=32 H=4 L=512 ragged 23.7 -> 22.1, B=16 H=8 L=1000 52.3 -> 49.4, B=64 H=8 L=256 43.9 -> 40.0.
         if constexpr (!(sizeof(T) == 2 && KCOPY == 8 && NQ == kLdsQueries)) {
             Round r[2];
-            request(sample(0, jraw[0]), r[0], std::true_type{});
+            request(sample(0, jraw[0]), r[0]);
 #pragma unroll
             for (int k = 0; k < KPRE; ++k)
                 if (k < n_pre) {                              // wave-uniform
-                    if (k + 1 < KPRE) request(sample(k + 1, jraw[k + 1 < KPRE ? k + 1 : 0]), r[(k + 1) & 1], std::true_type{});
-                    reduce(r[k & 1], all_usable(r[k & 1].jv));
+                    if (k + 1 < KPRE) request(sample(k + 1, jraw[k + 1 < KPRE ? k + 1 : 0]), r[(k + 1) & 1]);
+                    reduce(r[k & 1]);
                 }
         } else {
 #pragma unroll
@@ -1412,6 +1384,12 @@ __device__ __forceinline__ void measure_quad_body(const T* __restrict__ Q, const
             gather_round(sample(k, irow[t < U ? t : U - 1]));
         }
         PSA_TS(4);
+        // over the query's lanes
+        mx = fmaxf(mx, dpp_mov<0xB1>(mx)); sm += dpp_mov<0xB1>(sm); cnt += __builtin_amdgcn_update_dpp(0, cnt, 0xB1, 0xF, 0xF, false);
+        mx = fmaxf(mx, dpp_mov<0x4E>(mx)); sm += dpp_mov<0x4E>(sm); cnt += __builtin_amdgcn_update_dpp(0, cnt, 0x4E, 0xF, 0xF, false);
+        if constexpr (HALVES == 2) {
+            mx = fmaxf(mx, dpp_mov<0x141>(mx)); sm += dpp_mov<0x141>(sm); cnt += __builtin_amdgcn_update_dpp(0, cnt, 0x141, 0xF, 0xF, false);
+        }
         float m = 0.f;
         if (active && cnt > 0) m = (mx - sm / (float)cnt) * 0.125f;         // 1/sqrt(64), exact
         if (in_tensor && first) M[(size_t)head * L + i] = m;
