@@ -414,10 +414,11 @@ void measure_stream_kernel(const T* __restrict__ Q, const T* __restrict__ K, con
 // -----------------------------------------------------------------------------
 // A buffer load that writes LDS directly, no registers: lane l's 16 bytes land at lds + 16 l.
 // (The body exists in the device pass only: the host pass does not know the instruction's sizes.)
-__device__ __forceinline__ void buffer_load_to_lds_b128(__amdgpu_buffer_rsrc_t rsrc, void* lds, int voffset, int soffset) {
+// The whole offset is the lane's: a buffer's range check is promised for that one only, not for a scalar offset beside it.
+__device__ __forceinline__ void buffer_load_to_lds_b128(__amdgpu_buffer_rsrc_t rsrc, void* lds, int voffset) {
 #if defined(__HIP_DEVICE_COMPILE__)
     typedef __attribute__((address_space(3))) void lds_void;
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_void*)lds, 16, voffset, soffset, 0, 2 /* non-temporal */);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_void*)lds, 16, voffset, 0, 0, 2 /* non-temporal */);
 #endif
 }
 
@@ -521,7 +522,7 @@ void measure_pipe_kernel(const T* __restrict__ Q, const T* __restrict__ K, const
 #pragma unroll
         for (int k = 0; k < NV; ++k)
             if (1024 * k < bytes)                                    // wave-uniform
-                iv[k] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(irsrc, 16 * lane, 1024 * k, kStreamOnce));
+                iv[k] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(irsrc, 1024 * k + 16 * lane, 0, kStreamOnce));
         bool bad = false;                                            // some index of the chunk outside [0, n)
 #pragma unroll
         for (int k = 0; k < NV; ++k)
@@ -542,7 +543,7 @@ void measure_pipe_kernel(const T* __restrict__ Q, const T* __restrict__ K, const
 #pragma unroll
             for (int k = 0; k < NQL; ++k)                            // 16 bytes at position 1024 k + 16 lane of the chunk's 64 rows
                 x[k] = __builtin_bit_cast(Vec, __builtin_amdgcn_raw_buffer_load_b128(
-                           rs, chunk * kMeasureQueries * RT::kRowBytes + 16 * lane, 1024 * k, kStreamOnce));
+                           rs, chunk * kMeasureQueries * RT::kRowBytes + 1024 * k + 16 * lane, 0, kStreamOnce));
         };
         // the query rows go straight to LDS (16 bytes of position 1024 k + 16 lane of the chunk's rows land at
         // the same position of the stage: no staging registers, which would count against the gather waves'
@@ -552,7 +553,7 @@ void measure_pipe_kernel(const T* __restrict__ Q, const T* __restrict__ K, const
                 const_cast<T*>(Q + (size_t)head * L * kD), 0, n * RT::kRowBytes, 0x00020000);
 #pragma unroll
             for (int k = 0; k < NQL; ++k)
-                buffer_load_to_lds_b128(rs, s_q + 1024 * k, q_chunk * kMeasureQueries * RT::kRowBytes + 16 * lane, 1024 * k);
+                buffer_load_to_lds_b128(rs, s_q + 1024 * k, q_chunk * kMeasureQueries * RT::kRowBytes + 1024 * k + 16 * lane);
         }
         if (v_chunk < 0) { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); return; }
         Vec vv[NQL];
@@ -883,10 +884,10 @@ void measure_parts_kernel(const T* __restrict__ Q, const T* __restrict__ K, cons
 #pragma unroll
             for (int k = 0; k < kPartStage / 1024; ++k)              // (reads past the head's indices give 0)
                 in[k] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(
-                            irsrc, (q0 + a * kPartQueries + 16 * wave) * U * 4 + 16 * lane, 1024 * k, kStreamOnce));
+                            irsrc, (q0 + a * kPartQueries + 16 * wave) * U * 4 + 1024 * k + 16 * lane, 0, kStreamOnce));
 #pragma unroll
         for (int v = 0; v < NP; ++v)
-            qn[v] = __builtin_bit_cast(Vec, __builtin_amdgcn_raw_buffer_load_b128(qrsrc, i * RT::kRowBytes + piece_ofs(v), part * PB, kStreamOnce));
+            qn[v] = __builtin_bit_cast(Vec, __builtin_amdgcn_raw_buffer_load_b128(qrsrc, i * RT::kRowBytes + part * PB + piece_ofs(v), 0, kStreamOnce));
     };
     load_query(0, 0, true);
     const int krow = tid / LPR, kcol = tid % LPR;
@@ -896,7 +897,7 @@ void measure_parts_kernel(const T* __restrict__ Q, const T* __restrict__ K, cons
         const int even = krow * RT::kRowBytes + 16 * kcol, odd = (krow ^ 1) * RT::kRowBytes + 16 * (kcol ^ (LPR / 2));
 #pragma unroll
         for (int k = 0; k < KT; ++k)
-            kv[k] = __builtin_bit_cast(Vec, __builtin_amdgcn_raw_buffer_load_b128(krsrc, k & 1 ? odd : even, k * RPL * RT::kRowBytes, 0));
+            kv[k] = __builtin_bit_cast(Vec, __builtin_amdgcn_raw_buffer_load_b128(krsrc, (k & 1 ? odd : even) + k * RPL * RT::kRowBytes, 0, 0));
     }
     PSA_TS(0);
     // lane s of a quad: the samples 4 k + s, as byte offsets into a part; bit k of `usable`: that of round k counts
