@@ -139,20 +139,45 @@ static int stream_cut_f32(const Plan& p)
 
 // Streamed heads whose K fits LDS in two parts: passes of 128 queries that a work-group of the measure kernel which gathers from
 // there takes, or 0 where the heads stay with the gather out of L2.  Its time hardly depends on the samples (8.4 us to start
-// with K and the first indices, 4 for each pass, 2.3 for the ranking; a gather out of L2 gives way with fewer samples: B=8 H=8
-// L=2048 bfloat16, whole call, with 39 samples 55.4 -> 48.4 us, with 28 48.1 | 48.1, with 12 40.4 | 47.8; B=16 H=4 L=750 float32 with 34
-// 49.5 -> 44.0, with 24 45.3 -> 43.8, with 16 42.5 | 43.9), so it takes calls with more than 28.  A CU holds one of its work-groups,
-// which K has to be copied for, so they have to fill more than half of the chip: float32 B=8 H=4 L=640 (96 work-groups) 36.1 | 36.6,
-// B=12 H=4 L=750 (144) 47.9 -> 43.7; bfloat16 B=2 H=8 L=2048 (128) 33.6 | 35.1, B=3 (192) 41.3 -> 35.6 us.
-// Four passes instead of two, bfloat16, where the whole ones of two take more than a round of an XCD's 32 CUs: B=8 H=8 L=2048 (64 of
-// them) 54.9 -> 48.4 us, B=12 H=8 L=1040 61.5 -> 56.8; but B=8 H=8 L=1040 (32, and 8 with 16 queries) 43.7 | 44.4, and 35.4 | 44.3
-// where lengths leave those empty.
+// with K and the first indices, 4 for each pass, 2.3 for the ranking), that of a gather out of L2 does, so it takes calls with more
+// than 28.  A CU holds one of its work-groups, which K has to be copied for, so they have to fill more than half of the chip.
+// float32, two passes (whole call, L2 -> parts): B=16 H=4 L=750 with 34 samples 49.5 -> 44.0 us, with 24 45.3 -> 43.8, with 16 42.5 | 43.9; B=8
+// H=4 L=640 (96 work-groups) 36.1 | 36.6, B=12 H=4 L=750 (144) 47.9 -> 43.7.  Of 168 calls of 44 to 192 heads of 513 to 1024 frames,
+// full and ragged, it loses 2 to 3 % in three.
+// bfloat16: the gather out of L2 works at one rate whatever the shape, but these work-groups come in rounds of an XCD's 32
+// CUs, and a round that is not full costs what a full one does.
+//   * Two passes where all work-groups run in one round, with at least 160 of them (192 for fewer than 28 heads, whose items are few: lengths
+//     may leave little of them): B=10 H=4 L=1500 (35 samples) 40.1 -> 33.8 us, with lengths from an eighth up 38.2 -> 34.6; B=7 H=4 L=1281 (168) 37.9
+//     -> 34.5 and 36.5 -> 34.0, but L=1100 (140) 36.7 -> 33.2 and 32.1 | 33.0; B=3 H=8 L=1600 (168) 38.3 -> 35.3 and 34.1 | 36.0.
+//   * Else four passes, where the rounds (parts_rounds, a start counted like a pass) give enough samples of enough queries in their
+//     time: 21 samples per lane of queries there, 24 beyond 1536 frames, where lengths leave whole work-groups out of
+//     the last round.  Measured for 28 to 192 heads and 27 to 39 samples, full | ragged: B=24 H=4 L=1040 (21.3) 61.9 -> 55.5 | 59.6 -> 53.2,
+//     B=48 H=4 L=1300 (22.8) 118.8 -> 107.6 | 101.4 -> 91.8, L=2048 B=16 H=4 (31.2) 54.8 -> 48.5 | 55.7 -> 47.9; and not: B=24 H=4 L=1300 (18.6)
+//     66.0 | 70.2 and 64.0 -> 55.6, B=16 H=4 L=1300 with 31 (15.7) 42.0 | 45.4 and 43.6 | 45.5, L=2048 B=24 H=4 (23.4) 87.6 | 90.0 and 79.5 | 83.6.
+//     Two passes in more than one round lose on most of these (L=2048 B=16 H=4 54.8 | 54.9 and 55.7 -> 53.7).
+// Four passes wherever two made more than 32 whole work-groups of an XCD, for all calls with 129 work-groups or more, took B=9 H=8 L=2048 with 31
+// samples from 70.1 to 83.0 us, B=14 H=8 L=1400 with 29 from 69.9 to 78.8.  168 calls of 24 to 256 heads of 1150 to 2048 frames, full and
+// ragged, none of those above: 5 % gained in the mean, two lose 2 to 2.5 %.
+// Lengths are known on the device only, so calls with and without them take the same form.
+static int parts_rounds(const Plan& p, int passes)
+{
+    const int heads = (p.BH + 7) / 8, span = passes * 2 * kMeasureQueries, whole = heads * (p.L / span), rest = p.L % span;
+    const int full = 1 + passes, part = 1 + (rest + 2 * kMeasureQueries - 1) / (2 * kMeasureQueries);
+    // the whole work-groups of an XCD first, then the shorter ones of its heads, on the CUs as they come free
+    const int rounds = whole / 32, more = whole % 32;
+    int time = (rounds + (more > 0)) * full;
+    if (rest == 0) return time;
+    while (more * (time / full > rounds ? (time - (rounds + 1) * full) / part : 0) + (32 - more) * ((time - rounds * full) / part) < heads) ++time;
+    return time;
+}
 static int part_passes(const Plan& p, size_t k_bytes)
 {
     const int heads = (p.BH + 7) / 8, span = kPartChunks * kMeasureQueries, groups = (p.L + span - 1) / span;
-    if (k_bytes > 2 * (size_t)kLdsMaxBytes || p.U <= kPartMinSamples || p.U > kPartMaxSamples || (int64_t)p.BH * groups <= 128) return 0;
-    const int whole = heads * (p.L / span + (p.L % span > span / 2 ? 1 : 0));
-    return p.dtype == PSA_F32 || whole <= 32 ? 2 : 4;
+    if (k_bytes > 2 * (size_t)kLdsMaxBytes || p.U <= kPartMinSamples || p.U > kPartMaxSamples) return 0;
+    if (p.dtype == PSA_F32) return (int64_t)p.BH * groups > 128 ? 2 : 0;
+    if (heads * groups <= 32) return p.BH * groups >= (p.BH < 28 ? 192 : 160) ? 2 : 0;
+    const int64_t least = p.L <= 1536 ? 21 : 24;
+    return (int64_t)p.U * p.BH * p.L >= least * 32 * 8 * 2 * kMeasureQueries * parts_rounds(p, 4) ? 4 : 0;
 }
 
 // How much of a plan is cut anew (see make_plan).

@@ -11,7 +11,10 @@ from tests.test_plan import plan
 
 @pytest.mark.parametrize("dtype,B,H,L,U,passes", [
     ("f32", 16, 4, 750, 34, 2), ("f32", 16, 4, 1024, 35, 2), ("f32", 22, 4, 513, 32, 2), ("bf16", 8, 8, 2048, 39, 4),
-    ("bf16", 3, 8, 2048, 39, 2), ("bf16", 8, 8, 1040, 35, 2), ("bf16", 12, 8, 1040, 35, 4),
+    ("bf16", 3, 8, 2048, 39, 2), ("bf16", 5, 8, 1040, 35, 2), ("bf16", 12, 8, 1040, 35, 4), ("bf16", 7, 4, 1281, 29, 2), ("bf16", 20, 8, 1200, 36, 4),
+    # bfloat16: a round that is not full, with few samples; one round of few work-groups, of few heads
+    ("bf16", 8, 8, 1300, 36, 0), ("bf16", 9, 8, 2048, 39, 0), ("bf16", 12, 8, 2048, 39, 0), ("bf16", 14, 8, 1400, 37, 0), ("bf16", 8, 8, 2048, 29, 0),
+    ("bf16", 16, 4, 2000, 31, 4), ("bf16", 7, 4, 1100, 36, 0), ("bf16", 3, 8, 1600, 37, 0),
     # heads that fit LDS whole, or not in two parts; few and many samples; few work-groups
     ("f32", 22, 4, 512, 32, 0), ("f32", 16, 4, 1025, 35, 0), ("bf16", 32, 8, 1024, 35, 0), ("bf16", 8, 8, 2049, 39, 0),
     ("f32", 16, 4, 750, 28, 0), ("f32", 16, 4, 750, 29, 2), ("f32", 16, 4, 750, 40, 2), ("f32", 16, 4, 750, 41, 0),
@@ -44,8 +47,8 @@ def _workload(dtype, B, H, L, U, ragged):
 @pytest.mark.parametrize("ragged", [False, True])
 @pytest.mark.parametrize("dtype,B,H,L,U", [
     ("f32", 15, 3, 513, 29), ("f32", 43, 1, 768, 36), ("f32", 9, 4, 769, 37), ("f32", 33, 1, 1023, 40), ("f32", 11, 3, 1024, 33),
-    ("bf16", 26, 1, 1025, 40), ("bf16", 11, 2, 1536, 36), ("bf16", 19, 1, 1537, 29), ("bf16", 17, 1, 2047, 37), ("bf16", 4, 5, 2048, 33),
-    ("bf16", 17, 2, 2048, 39), ("bf16", 13, 4, 1281, 30),                                  # four passes
+    ("bf16", 33, 1, 1025, 40), ("bf16", 14, 2, 1536, 36), ("bf16", 29, 1, 1537, 29), ("bf16", 25, 1, 2047, 37), ("bf16", 5, 5, 2048, 33),
+    ("bf16", 25, 2, 2048, 39), ("bf16", 126, 1, 1281, 40), ("bf16", 61, 2, 1040, 39),      # four passes
 ])
 def test_edges(dtype, B, H, L, U, ragged):
     assert int(plan(B, H, L, U, dtype)["measure_parts"]) in (2, 4)
@@ -53,9 +56,10 @@ def test_edges(dtype, B, H, L, U, ragged):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("dtype,B,H,L,U", [("f32", 12, 4, 700, 35), ("bf16", 4, 8, 1300, 39), ("bf16", 11, 4, 2048, 38)])
+@pytest.mark.parametrize("dtype,B,H,L,U", [("f32", 12, 4, 700, 35), ("bf16", 4, 8, 1300, 39), ("bf16", 12, 4, 2048, 40)])
 def test_ties_samples_out_of_range_and_padding(dtype, B, H, L, U):
     """Equal measures across the chunks of a list and across lists, a head of equal measures, unusable samples, NaN behind the lengths."""
+    assert int(plan(B, H, L, U, dtype)["measure_parts"]) in (2, 4)
     w = _workload(dtype, B, H, L, U, True)
     w.lengths[2] = L
     w.sample_idx[2] = np.random.default_rng(5).integers(0, L, size=w.sample_idx[2].shape)
@@ -76,7 +80,9 @@ def test_ties_samples_out_of_range_and_padding(dtype, B, H, L, U):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("dtype,B,H,L,U", [("f32", 15, 3, 515, 34), ("bf16", 3, 9, 1100, 35), ("bf16", 13, 4, 1281, 39)])
+@pytest.mark.parametrize("dtype,B,H,L,U", [("f32", 15, 3, 515, 34), ("bf16", 4, 9, 1100, 35), ("bf16", 32, 4, 1281, 39)])
 def test_without_lists(dtype, B, H, L, U):
     # half of the queries kept: column sums per chunk and the measures themselves go to the select kernel
+    p = plan(B, H, L, U, dtype, r_sparse=0.5)
+    assert int(p["measure_parts"]) in (2, 4) and p["select"] == "kernel"
     check_against_oracle(_workload(dtype, B, H, L, U, True), r_sparse=0.5, fill="mean", label=f"parts select {dtype} L{L}")
