@@ -967,7 +967,10 @@ void measure_parts_kernel(const T* __restrict__ Q, const T* __restrict__ K, cons
                 for (int v = 0; v < NP; ++v) {
                     const Vec r = kr[k & 1][t][v];
                     if constexpr (sizeof(T) == 4) {
-                        x = fmaf(q[v].x, r.x, x); x = fmaf(q[v].y, r.y, x); x = fmaf(q[v].z, r.z, x); x = fmaf(q[v].w, r.w, x);
+                        // a sum for each piece: quads take the pieces in different orders, and equal queries get the same bits
+                        float y = q[v].x * r.x;
+                        y = fmaf(q[v].y, r.y, y); y = fmaf(q[v].z, r.z, y); y = fmaf(q[v].w, r.w, y);
+                        x = v == 0 ? y : x + y;
                     } else {
                         x = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, q[v].x), __builtin_bit_cast(bf16x2, r.x), x, false);
                         x = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, q[v].y), __builtin_bit_cast(bf16x2, r.y), x, false);
