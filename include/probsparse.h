@@ -279,10 +279,13 @@ int dense_attn_fwd(const void* Q, const void* K, const void* V, const int32_t* l
 
 /* Host only, no GPU needed: which kernels a call with this shape would launch, as
  * one line of `key=value` words in `buf` (NUL-terminated), e.g. which measure kernel
- * (`measure=lds|lds_half|stream|none`), how I_sparse is found (`select=lists|kernel|
- * segments|given_inline|given_prep`), which attend kernel (`attend=key_split|rows|
- * rows_half_keys`) and how partial results are merged.  Where the buffer has room (512
- * bytes are enough) the kernels of the projections of probsparse_mhsa_fwd at this shape
+ * (`measure=lds|lds_half|stream|none`; `measure_parts` > 0: the keys of streamed heads go
+ * through LDS in two parts, in work-groups of so many passes of 128 queries), how I_sparse
+ * is found (`select=lists|kernel|segments|given_inline|given_prep`; `own_sums=1`: given
+ * sets, whose mean fill needs no launch for the column sums of V), which attend kernel
+ * (`attend=key_split|rows|rows_half_keys`) and how partial results are merged.  Where the
+ * buffer has room (512 bytes are enough) the kernels of the projections of
+ * probsparse_mhsa_fwd at this shape
  * follow and, with u_stride > 0, those of probsparse_attn_bwd.  For tests and for reading
  * profiles; the words are not a stable interface.  A call with `lengths` launches the
  * same kernels as one without.  `opt` gives the selection rule

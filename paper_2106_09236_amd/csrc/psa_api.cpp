@@ -290,6 +290,7 @@ static void build_plan(const psa_shape_t* s, URule urule, int u_stride, Cuts cut
         p->chunks_per_wg = cpw < p->n_chunk ? cpw : p->n_chunk;
     }
     p->part_passes = cuts >= kPartCut && !p->measure_lds && !p->given_indices ? part_passes(*p, k_bytes) : 0;
+    if (p->part_passes > 0) p->chunks_per_wg = p->part_passes * kPartPassChunks;
     // sorted per-chunk candidate lists: only with the LDS measure kernel (few chunks per head)
     p->cand_len = 0;
     if (p->measure_lds) {

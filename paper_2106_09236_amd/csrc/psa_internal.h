@@ -28,6 +28,7 @@ constexpr int kSegKeys = 2048;             // most queries of one segment
 constexpr int kSegCandMax = 256;           // longest list a segment hands on
 constexpr int kPipeMaxSamples = 64;        // samples per query up to which the streaming measure kernel stages a chunk's indices in LDS
 constexpr int kPartChunks = 4;             // chunks of a candidate list of the measure kernel that takes K in two parts
+constexpr int kPartPassChunks = 2;         // ... and of one of its passes
 constexpr int kPartMinSamples = 28;        // it is taken beyond so many samples per query ...
 constexpr int kPartMaxSamples = 40;        // ... and up to so many: a pass's scores stay in registers
 constexpr int kListMax = 256;              // most queries a work-group of the streaming measure kernel ranks among themselves ...
@@ -51,7 +52,7 @@ struct Plan {
     int measure_lds;      // 1: a head's K fits in LDS for the measure stage; 2: in half of it (two work-groups per CU)
     int measure_queries;  // queries per measure chunk: 128, 64 or 32 (LDS kernel), 64 (streaming)
     int n_chunk;          // measure chunks (= V column-sum chunks) per head
-    int chunks_per_wg;    // consecutive chunks of a head one work-group takes (LDS kernel, and the gather out of L2 up to kPipeMaxSamples)
+    int chunks_per_wg;    // consecutive chunks of a head one work-group takes (beyond kPipeMaxSamples the gather out of L2 takes one)
     int part_passes;      // > 0: K goes through LDS in two parts; passes of 128 queries per work-group (2 or 4), a candidate list for two
     int fused_select;     // 1: top-u selection runs inside the attend work-groups
     int cand_len;         // > 0: sorted candidate lists of this length are handed to the attend stage

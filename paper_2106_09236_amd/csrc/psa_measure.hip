@@ -798,6 +798,7 @@ __device__ __forceinline__ int quad_bcast(int x) {
 // -----------------------------------------------------------------------------
 constexpr int kPartThreads = 512;
 constexpr int kPartQueries = kPartThreads / 4;                       // of a pass
+static_assert(kPartQueries == kPartPassChunks * kMeasureQueries, "a pass is two chunks");
 constexpr int kPartStage = (16 * kPartMaxSamples * 4 + 1023) / 1024 * 1024;      // bytes of the sample indices of a wave's 16 queries
 
 // KT: 16-byte pieces of K per thread (24 or 32: 192 or 256 KB, half of which is in LDS)
@@ -1528,7 +1529,7 @@ static hipError_t launch_measure_t(const Plan& p, const Args& a, const Scratch& 
     if (p.part_passes > 0) {
         const hipError_t e = raise_parts_limit<T>();
         if (e != hipSuccess) return e;
-        const int span = p.part_passes * (kPartQueries / kMeasureQueries), groups = (chunks + span - 1) / span;
+        const int groups = (chunks + p.chunks_per_wg - 1) / p.chunks_per_wg;
 #define PSA_PARTS(KT, NPASS, NR)                                                                                           \
         hipLaunchKernelGGL((measure_parts_kernel<T, KT, NPASS, NR>), dim3((unsigned)(head_rounds * groups * 8)), dim3(kPartThreads), \
                            KT * 8 * kPartThreads, a.stream, (const T*)a.Q, (const T*)a.K, (const T*)a.V, a.lengths, a.idx, \

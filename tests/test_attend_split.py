@@ -73,7 +73,8 @@ def test_running_maximum_that_lags(B, H, L, growth):
     (16, 4, 1000, 4), (9, 8, 710, 4), (4, 4, 2048, 2), (2, 4, 1024, 1), (1, 4, 16384, 4),
 ])
 def test_float32_measure_cuts(B, H, L, chunks_per_wg):
-    assert plan(B, H, L, 35, "f32")["chunks_per_wg"] == str(chunks_per_wg)
+    p = plan(B, H, L, 28, "f32")
+    assert (p["measure_parts"], p["chunks_per_wg"]) == ("0", str(chunks_per_wg))
 
 
 def test_static_scratch_admits_what_it_did():
@@ -87,10 +88,11 @@ def test_static_scratch_admits_what_it_did():
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("B,H,L,U", [(16, 4, 1000, 35), (9, 8, 710, 33), (24, 4, 750, 34), (20, 4, 600, 12), (5, 4, 2100, 9),
+@pytest.mark.parametrize("B,H,L,U", [(16, 4, 1000, 28), (9, 8, 710, 27), (24, 4, 750, 25), (20, 4, 600, 12), (5, 4, 2100, 9),
                                      (3, 3, 577, 64), (33, 8, 560, 7)])
 def test_measure_cuts_against_oracle(B, H, L, U):
     # ragged and whole batches of streamed float32 heads: one to nine chunks per work-group, heads in eights and not
+    assert plan(B, H, L, U, "f32")["measure_parts"] == "0"
     for ragged in (False, True):
         cfg = W.small_config("cuts", B, H, L, U, 5.0, "f32", "mixture", ragged, max(1, L // 8), L)
         check_against_oracle(W.make_workload(cfg, seed=700 + L), label=f"B{B} H{H} L{L} ragged={ragged}")
@@ -112,7 +114,9 @@ def _busiest_cu(B, H, L, cpw):
 def test_float32_measure_cut_loses_nothing_on_full_batches(B, H, L):
     # against two work-groups per CU in equal shares; calls with and without lengths take the same cut
     two = min(16, (B * H * ((L + 63) // 64) + 511) // 512)
-    assert _busiest_cu(B, H, L, int(plan(B, H, L, 35, "f32")["chunks_per_wg"])) <= _busiest_cu(B, H, L, two)
+    p = plan(B, H, L, 28, "f32")
+    assert p["measure_parts"] == "0"
+    assert _busiest_cu(B, H, L, int(p["chunks_per_wg"])) <= _busiest_cu(B, H, L, two)
 
 
 @pytest.mark.gpu

@@ -25,6 +25,7 @@ def test_calls_that_take_it(dtype, B, H, L, U, passes):
     assert int(p["measure_parts"]) == passes
     if passes:
         assert (p["measure"], p["select"], int(p["lists"])) == ("stream", "lists", -(-L // 256))
+        assert int(p["chunks_per_wg"]) == 2 * passes                 # of the kernel that is launched
         # half of the queries kept: the same measure, and the select kernel
         r = plan(B, H, L, U, dtype, r_sparse=0.5)
         assert (int(r["measure_parts"]), r["select"]) == (passes, "kernel")
