@@ -43,6 +43,23 @@ static bool good_rule(URule r)
 // them) 14.3 -> 13.3 us, B=1 H=4 L=333 24.1 -> 21.7, B=4 H=4 L=300 23.0 -> 20.3, B=8 H=4 L=200 (64 -> 256) 20.3 -> 18.6 us.
 static int elem_split(int64_t wgs) { return 4 * wgs <= 256 ? 4 : 2 * wgs <= 256 ? 2 : 1; }
 
+// Given sets, mean fill, short heads: each attend work-group (n_wg of a head) reads all of its head's V for the column sums it needs (out of
+// its L2, where the head's other work-groups and its own products find V then) instead of a launch that does.  In microseconds: a
+// CU takes in 105 KB, the launch costs 3.5 and reads V at 5 TB/s.  Whole call, launch -> own: B=16 H=4 L=512 float32, 32 kept
+// 21.2 -> 17.7 us, B=1 H=4 L=128 10.5 -> 8.1, B=32 H=8 L=512 with 100 kept (4 work-groups a head) 118 -> 114, but B=64 H=8 L=400 with
+// 200 kept (7) 349 | 354; bfloat16 B=32 H=4 L=512 15.8 -> 11.1, B=128 H=8 L=1024 135 -> 104, B=8 H=8 L=1024 with 512 kept 27.0 -> 22.7.
+static bool sums_in_attend(const Plan& p, int n_wg)
+{
+    const size_t v_bytes = (size_t)p.L * (p.dtype == PSA_F32 ? 256 : 128);
+    if (!p.given_indices || p.u_max > kSelLdsMax || v_bytes > kOwnSumBytes) return false;
+    const float heads = (float)p.BH * (float)v_bytes;
+    return heads * (float)n_wg / (256.f * 105e3f) + 0.5f <= 3.5f + heads / 5e6f;
+}
+// ... and what the launch that clears the tickets then costs, which a cut without hand-over does not need (B=16 H=4 L=512, 32 kept: one
+// split 17.7 us, four splits 20.2).  Elsewhere the launch for the column sums clears them.  (With value fill nothing needs those
+// sums, but a plan holds for both fills: a call whose heads are split still takes the launch for its tickets.)
+constexpr float kTicketLaunch = 2.f;
+
 // float32 tensors: queries per group and key splits of the key-split attend kernel, by the time of its rounds of
 // work-groups (one per CU).  In microseconds, fitted to sweeps of both over 15 shapes: 5.5 to start a work-group and
 // pick the selection, 2.3 for each tile step of a SIMD (64 float64 MFMAs), and for a split the hand-over of records:
@@ -52,12 +69,8 @@ static int elem_split(int64_t wgs) { return 4 * wgs <= 256 ? 4 : 2 * wgs <= 256 
 // of work-groups that is not full counts half: heads are often shorter than L.
 // Against groups of 32 and 512 work-groups for every shape: B=24 H=4 L=750 ragged 87 -> 75 us, B=16 H=4 L=1000
 // 83 -> 63, B=64 H=4 L=200 52 -> 36, B=1 H=4 L=333 26.0 -> 23.8 us.
-// Given sets whose work-groups form the column sums themselves (own_sums): what the launch that clears the tickets costs, which
-// a cut without hand-over does not need (B=16 H=4 L=512, 32 kept: one split 17.7 us, four splits 20.2).
-constexpr float kTicketLaunch = 2.f;
 static void split_f32(Plan* p, int n_tiles)
 {
-    const float ticket = p->given_indices && (size_t)p->L * 256 <= kOwnSumBytes ? kTicketLaunch : 0.f;
     float best = INFINITY;
     for (int ncg = 2; ncg >= 1; --ncg) {                      // (of equals the larger groups: they read K and V less often)
         const int nq = 16 * ncg, tiles_wg = 8 / ncg;
@@ -76,6 +89,7 @@ static void split_f32(Plan* p, int n_tiles)
             const int steps = (tiles * ncg + 3) / 4;
             const float fills = (float)(per_split * split) / 256.f;
             const float part = split == 1 && elem_split(per_split) == 4 ? 0.75f : 1.f;      // of a tile step
+            const float ticket = sums_in_attend(*p, n_qgroup * split) ? kTicketLaunch : 0.f;
             const float cost = (fills <= 1.f ? 1.f : 0.5f * (fills + ceilf(fills))) * (5.5f + 2.3f * part * (float)steps) +
                 (split == 1 ? 0.f : split > kTicketMaxSplit ? 6.f : ticket + 3.f + 1.5f * (float)((p->u_max + 31) / 32 * ((split + 3) / 4)));
             if (cost < best) {
@@ -334,16 +348,7 @@ static void build_plan(const psa_shape_t* s, URule urule, int u_stride, Cuts cut
     // for one wave to add up: no prep kernel (one launch less: conformer_s 27.8 -> 25 us)
     p->given_inline = p->given_indices && p->u_max <= kSelLdsMax && p->n_chunk <= 64;
     p->separate_merge = p->n_split > kTicketMaxSplit;
-    // Given sets, mean fill, short heads: each attend work-group reads all of its head's V for the column sums it needs (out of its L2,
-    // where the head's other work-groups and its own products find V then) instead of a launch that does.  In microseconds: a
-    // CU takes in 105 KB, the launch costs 3.5 and reads V at 5 TB/s.  Whole call, launch -> own: B=16 H=4 L=512 float32, 32 kept
-    // 21.2 -> 17.7 us, B=1 H=4 L=128 10.5 -> 8.1, B=32 H=8 L=512 with 100 kept (4 work-groups a head) 118 -> 114, but B=64 H=8 L=400 with
-    // 200 kept (7) 349 | 354; bfloat16 B=32 H=4 L=512 15.8 -> 11.1, B=128 H=8 L=1024 135 -> 104, B=8 H=8 L=1024 with 512 kept 27.0 -> 22.7.
-    p->own_sums = 0;
-    if (p->given_inline && p->rows_mode != 1 && (size_t)p->L * row_bytes <= kOwnSumBytes) {
-        const float heads = (float)p->BH * (float)p->L * (float)row_bytes;
-        p->own_sums = heads * (float)p->n_wg_head / (256.f * 105e3f) + 0.5f <= 3.5f + heads / 5e6f;
-    }
+    p->own_sums = p->given_inline && p->rows_mode != 1 && sums_in_attend(*p, p->n_wg_head);
 
     // float32 tensors: m, l as float64 and 64 float32 values per query (34 doubles); bfloat16: 66 floats
     p->part_stride = (size_t)p->nq_group * (p->dtype == PSA_F32 ? 2 + kD / 2 : kD + 2);
