@@ -772,7 +772,7 @@ void measure_pipe_kernel(const T* __restrict__ Q, const T* __restrict__ K, const
 
 template <int T4>                                          // value of lane T4 of the quad, in all four lanes
 __device__ __forceinline__ int quad_bcast(int x) {
-    return __builtin_amdgcn_update_dpp(0, x, T4 * 0x55, 0xF, 0xF, false);
+    return __builtin_amdgcn_update_dpp(0, x, T4 * 0x55, 0xF, 0xF, true);      // (true: no zero to be put there first)
 }
 
 // -----------------------------------------------------------------------------
@@ -1206,6 +1206,16 @@ __device__ __forceinline__ void measure_quad_body(const T* __restrict__ Q, const
     const T* Vh = V + (size_t)head * L * kD;
     // byte offset of this lane's v-th piece inside a row: piece (v + quad index) mod NP, bytes 16 s .. 16 s + 15 of it
     auto piece_ofs = [&](int v) -> uint32_t { return 64u * (uint32_t)((v + qrot) & (NP - 1)) + 16u * (uint32_t)s; };
+    // ... and where that is in row 0 of the head's K in LDS: a piece of a row is one addition away (the compiler takes sums apart
+    // that it can see through, and adds twice)
+    typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
+    typedef const __attribute__((address_space(3))) uintx4* LdsPiece;
+    uint32_t piece0[NP];
+#pragma unroll
+    for (int v = 0; v < NP; ++v) {
+        piece0[v] = (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) unsigned char*)sK + piece_ofs(v);
+        asm volatile("" : "+v"(piece0[v]));
+    }
 
     // ---- All loads of a chunk are issued back to back, unconditionally and on
     // clamped addresses, before anything uses them: a load inside a branch (or
@@ -1312,33 +1322,38 @@ __device__ __forceinline__ void measure_quad_body(const T* __restrict__ Q, const
 
         float mx = -INFINITY, sm = 0.f;
         int cnt = 0;
-        auto row_dot = [&](const Vec (&kr)[NP]) -> float {           // this lane's share of q . k
-            float d = 0.f;
+        // This lane's share of q . k, a sum for each piece: quads take the pieces in rotated orders, and piece v with piece v + 2 first gives
+        // equal queries the same bits whatever the rotation.  (One chain over the pieces takes 3 additions a row less, float32, or one; with
+        // the addresses formed as below whole calls take as long as with the chain: B=16 H=4 L=512 float32 27.2 | 27.2 us, B=1 H=4
+        // L=128 12.8 | 12.9; bfloat16 B=32 H=4 L=512 22.5 | 22.5, B=64 H=8 L=256 37.5 | 37.8, B=24 H=4 L=1000 ragged 44.2 | 44.0.)
+        auto row_dot = [&](const Vec (&kr)[NP]) -> float {
+            float d[NP];
 #pragma unroll
             for (int v = 0; v < NP; ++v) {
                 if constexpr (sizeof(T) == 4) {
-                    d = fmaf(q[v].x, kr[v].x, d); d = fmaf(q[v].y, kr[v].y, d);
-                    d = fmaf(q[v].z, kr[v].z, d); d = fmaf(q[v].w, kr[v].w, d);
+                    d[v] = q[v].x * kr[v].x;
+                    d[v] = fmaf(q[v].y, kr[v].y, d[v]); d[v] = fmaf(q[v].z, kr[v].z, d[v]); d[v] = fmaf(q[v].w, kr[v].w, d[v]);
                 } else {
-                    d = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, q[v].x), __builtin_bit_cast(bf16x2, kr[v].x), d, false);
-                    d = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, q[v].y), __builtin_bit_cast(bf16x2, kr[v].y), d, false);
-                    d = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, q[v].z), __builtin_bit_cast(bf16x2, kr[v].z), d, false);
-                    d = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, q[v].w), __builtin_bit_cast(bf16x2, kr[v].w), d, false);
+                    d[v] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, q[v].x), __builtin_bit_cast(bf16x2, kr[v].x), 0.f, false);
+                    d[v] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, q[v].y), __builtin_bit_cast(bf16x2, kr[v].y), d[v], false);
+                    d[v] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, q[v].z), __builtin_bit_cast(bf16x2, kr[v].z), d[v], false);
+                    d[v] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, q[v].w), __builtin_bit_cast(bf16x2, kr[v].w), d[v], false);
                 }
             }
-            return d;
+            if constexpr (NP == 4) return (d[0] + d[2]) + (d[1] + d[3]);
+            else return d[0] + d[1];
         };
-        // One round of 4 samples per quad; jv: this lane's sample, -1 if none.
+        // One round of 4 samples per quad; jv: this lane's sample, -1 if none.  The offset of a sample's row is formed in its own lane, and
+        // the addition that makes it an address in the others takes it across lanes as it reads it.
         struct Round { int jv; Vec kr[4][NP]; };
         auto request = [&](int jv, Round& r) {
             r.jv = jv;
-            const int jc = (unsigned)jv < (unsigned)n ? jv : 0;
+            const int jc = (unsigned)jv < (unsigned)n ? jv * RT::kRowBytes : 0;
             const int j[4] = {quad_bcast<0>(jc), quad_bcast<1>(jc), quad_bcast<2>(jc), quad_bcast<3>(jc)};
 #pragma unroll
             for (int t = 0; t < 4; ++t)
 #pragma unroll
-                for (int v = 0; v < NP; ++v)
-                    r.kr[t][v] = *reinterpret_cast<const Vec*>(sK + (uint32_t)j[t] * RT::kRowBytes + piece_ofs(v));
+                for (int v = 0; v < NP; ++v) r.kr[t][v] = __builtin_bit_cast(Vec, *(LdsPiece)(uintptr_t)((uint32_t)j[t] + piece0[v]));
         };
         // A transposing exchange leaves lane s of the quad with the score of its own sample, so that a round adds one value to
         // each lane's maximum and sum and takes one test (padded queries, the tail of U, indices outside [0, n)), where every lane
@@ -1358,7 +1373,12 @@ __device__ __forceinline__ void measure_quad_body(const T* __restrict__ Q, const
             sm += ok ? x : 0.f;
             cnt += ok ? 1 : 0;
         };
-        auto gather_round = [&](int jv) { Round r; request(jv, r); reduce(r); };
+        auto gather_round = [&](int jv) {
+            Round r;
+            request(jv, r);
+            __builtin_amdgcn_sched_barrier(0);            // (all rows are asked for before the first is waited for)
+            reduce(r);
+        };
         // Rounds whose indices came with the chunk's other loads (no global load here: the
         // wait for it would also wait for the next chunk's loads, which are in flight on purpose).
         const int n_pre = n_r < KPRE ? n_r : KPRE;

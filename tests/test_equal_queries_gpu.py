@@ -1,4 +1,4 @@
-"""Streamed heads: queries with the same row and the same samples have the same measure to the last bit wherever they lie, on every route
+"""Queries with the same row and the same samples have the same measure to the last bit wherever they lie, on every route
 of the measure stage.  Ties go to the lower index, so rounding must not tell such queries apart."""
 import numpy as np
 import pytest
@@ -14,6 +14,10 @@ pytestmark = pytest.mark.gpu
     ("f32", 16, 4, 750, 34, "stream", 2), ("f32", 16, 4, 1000, 38, "stream", 2),
     ("bf16", 5, 8, 1200, 35, "stream", 2), ("bf16", 8, 8, 2048, 39, "stream", 4),
     ("f32", 2, 4, 800, 24, "stream", 0), ("bf16", 2, 4, 1500, 24, "stream", 0), ("f32", 2, 4, 600, 70, "stream", 0), ("bf16", 2, 4, 1200, 70, "stream", 0),
+    # heads in LDS: chunks of 32, 64 and 128 queries, of two quads and of one to a query
+    ("f32", 2, 4, 128, 25, "lds", 0), ("f32", 2, 4, 333, 30, "lds", 0), ("f32", 20, 8, 250, 28, "lds", 0), ("f32", 16, 4, 512, 32, "lds", 0),
+    ("bf16", 2, 4, 128, 25, "lds_half", 0), ("bf16", 2, 4, 333, 30, "lds_half", 0), ("bf16", 32, 4, 512, 32, "lds_half", 0), ("bf16", 16, 8, 1000, 35, "lds", 0),
+    ("f32", 16, 4, 500, 56, "lds", 0), ("bf16", 32, 4, 512, 56, "lds_half", 0),
 ])
 def test_same_bits(dtype, B, H, L, U, measure, parts):
     p = plan(B, H, L, U, dtype)
