@@ -42,6 +42,9 @@ def _calls():
 @pytest.mark.gpu
 @pytest.mark.parametrize("name", ["fwd", "opt", "indices", "mhsa", "bwd"])
 def test_other_threads_run_during_calls(name):
+    # The other thread waits for the interpreter and has a few microseconds of each call in which it can be had: how soon it wakes is up
+    # to the machine (threads of a library that still spin after an earlier test keep the CPUs busy), so calls go on until it has run.
+    # An entry point that keeps the interpreter lets it run in none of them, however many.
     call = _calls()[name]
     call()
     torch.cuda.synchronize()
@@ -54,19 +57,22 @@ def test_other_threads_run_during_calls(name):
     interval = sys.getswitchinterval()
     thread = threading.Thread(target=other)
     sys.setswitchinterval(1000.0)                # a thread that does not let go of the interpreter keeps it
+    during, end = 0, time.monotonic() + 60.0
     try:
         thread.start()
         while ticks[0] == 0:
             time.sleep(0.001)
-        before = ticks[0]
-        results = [call() for _ in range(500)]   # (kept: freeing a tensor lets other threads run as well)
-        during = ticks[0] - before
+        while during == 0 and time.monotonic() < end:
+            before = ticks[0]
+            results = [call() for _ in range(200)]   # (kept: freeing a tensor lets other threads run as well)
+            during = ticks[0] - before
+            results.clear()
+            torch.cuda.synchronize()
     finally:
         stop.set()
         thread.join()
         sys.setswitchinterval(interval)
-    torch.cuda.synchronize()
-    assert len(results) == 500 and during > 0
+    assert during > 0
 
 
 @pytest.mark.parametrize("module", [None, "not a shared object"])
