@@ -50,6 +50,8 @@ FP64_MFMA_PEAK_TFLOPS = 78.6     # dense float64 matrix
 BF16_MFMA_PEAK_TFLOPS = 2500.0   # dense bfloat16 matrix
 # what a CU's vector-memory path returns: 64 B per clock and CU, 256 CUs, 2.4 GHz
 L1_RETURN_PEAK_GBS = 64 * 256 * 2.4
+# what its LDS is read at: 128 B per clock
+LDS_READ_PEAK_GBS = 128 * 256 * 2.4
 HEADLINE = "longform"
 ORDER = ["tiny", "conformer_s", "ragged", "conformer_l", "longform"]
 METRIC = "prob-sparse MHSA fwd latency (us) & queries/s; % HBM/MFMA roofline"
@@ -218,7 +220,7 @@ def plan_words(shape, opt=None, u_stride=0):
     """Which kernels the call launches (the host's choice), as a short string for the JSON line."""
     from paper_2106_09236_amd import binding as psa
     d = psa.probsparse_describe_plan(shape, opt, u_stride)
-    return " ".join(f"{k}={d[k]}" for k in ("measure", "select", "attend", "key_splits", "merge"))
+    return " ".join(f"{k}={d[k]}" for k in ("measure", "measure_parts", "select", "attend", "key_splits", "merge"))
 
 
 class Timer:
@@ -335,13 +337,17 @@ def gpu_block(cfg, w, args, timer):
     kernels["attend"]["TFLOPs"] = round(fl / (ta * 1e-6) / 1e12, 3)
     kernels["attend"]["mfma_frac"] = round(fl / (ta * 1e-6) / 1e12 / mfma_peak, 4)
     kernels["attend"]["mfma_dtype"] = "f64" if cfg.dtype == "f32" else "bf16"
-    # the measure stage is a gather: its second bound is what the CUs' vector-memory path can return
-    # (every sampled key row crosses it once), beside the HBM bound of the compulsory bytes
+    # the measure stage is a gather: its second bound, beside the HBM bound of the compulsory bytes, is the path that every
+    # sampled key row of a valid query crosses once: what a CU's vector memory can return (heads that are gathered out of
+    # L2) or what its LDS can be read at (heads that fit there, whole or in two parts)
+    gb = int(w.lengths_or_full().sum()) * cfg.H * cfg.U * 64 * (4 if cfg.dtype == "f32" else 2)
+    tm = stage_us["measure"]["median"]
     if plan["measure"] == "stream" and plan["measure_parts"] == "0":
-        gb = queries * cfg.U * 64 * (4 if cfg.dtype == "f32" else 2)
-        tm = stage_us["measure"]["median"]
         kernels["measure"]["gather_bytes"] = gb
         kernels["measure"]["l1_return_frac"] = round(gb / (tm * 1e-6) / 1e9 / L1_RETURN_PEAK_GBS, 4)
+    else:
+        kernels["measure"]["lds_gather_bytes"] = gb
+        kernels["measure"]["lds_read_frac"] = round(gb / (tm * 1e-6) / 1e9 / LDS_READ_PEAK_GBS, 4)
 
     dom = max(stage_us, key=lambda k: stage_us[k]["median"])
     if dom == "attend" and kernels["attend"]["mfma_frac"] > kernels["attend"]["hbm_frac"]:
@@ -362,7 +368,7 @@ def gpu_block(cfg, w, args, timer):
         "frames_per_s": round(float(w.lengths_or_full().sum()) / (us * 1e-6), 1),
         "queries_per_step": queries, "input_copies_rotated": n_sets,
         "tensor_dtype": cfg.dtype, "accumulate_dtype": "f64" if cfg.dtype == "f32" else "f32",
-        "kernel_plan": " ".join(f"{k}={plan[k]}" for k in ("measure", "select", "attend", "key_splits", "merge")),
+        "kernel_plan": " ".join(f"{k}={plan[k]}" for k in ("measure", "measure_parts", "select", "attend", "key_splits", "merge")),
         "whole_call_hbm_frac": round(ib / (us * 1e-6) / 1e9 / HBM_PEAK_GBS, 4), "ideal_bytes": ib,
         "roofline": roofline, "kernels": kernels,
         "dense_baseline": {"us": round(dense["median"], 3), "us_min": round(dense["min"], 3),
